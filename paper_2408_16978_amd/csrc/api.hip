@@ -615,7 +615,7 @@ int bwd_bf16_fused(const Problem& p, const void* Q, const void* K, const void* V
                    hipStream_t st)
 {
     launch_delta(O, dO, p.S, p.Hq, p.D, 1, f.Delta, p.S, st);
-    launch_delta_head(Q, dO, K, V, LSE, p.S, DELTA_HEAD_ROWS, p.Hq, p.Hkv, p.D, p.scale, f.Delta, st);
+    launch_delta_head(Q, dO, K, V, LSE, p.S, p.Hq, p.Hkv, p.D, p.scale, f.Delta, st);
     launch_stat_pack(LSE, f.Delta, p.S, p.S, p.Hq, p.S / 32, f.stat2, st);
     launch_pack(Q, p.S, p.Hq, p.D, f.Qnat, nullptr, p.S / 32, st);
     launch_pack(dO, p.S, p.Hq, p.D, f.dOnat, nullptr, p.S / 32, st);
@@ -765,8 +765,8 @@ int bwd_bf16_pairs(const Problem& p, const char* Q, const char* K, const char* V
         // sequence (pair (0, 0)) and, with a chunk mask, the head of every query chunk that keeps
         // no earlier key chunk (its diagonal pair is then the first pair that reads its Delta).
         if (i == j && p.first_key_chunk(i) == i)
-            launch_delta_head(Qi, dOi, Kj, Vj, LSEi, stat_stride, DELTA_HEAD_ROWS, p.Hq, p.Hkv, p.D,
-                              p.scale, const_cast<float*>(Deltai), st);
+            launch_delta_head(Qi, dOi, Kj, Vj, LSEi, stat_stride, p.Hq, p.Hkv, p.D, p.scale,
+                              const_cast<float*>(Deltai), st);
         if (stat_stale) {  // after the head rows have their final Delta
             launch_stat_pack(LSEi, Deltai, stat_stride, p.C, p.Hq, p.C / 32, f.stat2, st);
             stat_stale = false;

@@ -921,37 +921,48 @@ __global__ __launch_bounds__(256) void delta_kernel(const T* __restrict__ O, con
 // rowsum(dO * O) inherits the bf16 rounding of the stored O; for a row with only a few keys
 // the softmax is often peaked, dS = p (dP - Delta) then cancels almost completely and that
 // rounding dominates dQ.  Its weight decays like 1/sqrt(row), so only the head of the
-// sequence is recomputed (plain FMA, one wave per (row, head); the cost is negligible).
-__global__ __launch_bounds__(256) void delta_head_kernel(const uint16_t* __restrict__ Q,
+// sequence is recomputed.
+// One workgroup per (32-row block, head); wave w takes key block w (of at most 8) through the same
+// MFMAs as the dQ kernel, straight from the row-major tensors, and the eight partial row sums meet in
+// LDS.  Latency-bound: 10 us in place of the 176 us of one wave per row with a scalar dot product
+// per lane and key (D = 128, 8 heads).
+template <int D>
+__global__ __launch_bounds__(512) void delta_head_kernel(const uint16_t* __restrict__ Q,
                                                          const uint16_t* __restrict__ dO,
                                                          const uint16_t* __restrict__ K,
                                                          const uint16_t* __restrict__ V,
                                                          const float* __restrict__ LSE, int64_t stat_stride,
-                                                         int rows, int Hq, int Hkv, int D, float scale,
-                                                         float* __restrict__ Delta)
+                                                         int Hq, int Hkv, float c, float* __restrict__ Delta)
 {
-    const int lane = threadIdx.x & 63;
-    const int pair = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (pair >= rows * Hq) return;  // wave-uniform
-    const int row = pair / Hq, head = pair % Hq;
-    const int kvh = head / (Hq / Hkv);
-    const uint16_t* q = Q + ((size_t)row * Hq + head) * D;
-    const uint16_t* go = dO + ((size_t)row * Hq + head) * D;
-    const float lse = LSE[(size_t)head * stat_stride + row];
-    float acc = 0.f;
-    for (int j = lane; j <= row; j += 64) {
-        const uint16_t* k = K + ((size_t)j * Hkv + kvh) * D;
-        const uint16_t* v = V + ((size_t)j * Hkv + kvh) * D;
-        float s = 0.f, dp = 0.f;
-        for (int d = 0; d < D; ++d) {
-            s = fmaf(ld<uint16_t>(q + d), ld<uint16_t>(k + d), s);
-            dp = fmaf(ld<uint16_t>(go + d), ld<uint16_t>(v + d), dp);
-        }
-        acc = fmaf(expf(scale * s - lse), dp, acc);
-    }
+    constexpr int DT = D / 16;
+    static_assert(DELTA_HEAD_ROWS == 256, "one wave per 32-key block");
+    __shared__ float part[8][32];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, half = lane >> 5, col = lane & 31;
+    const int rb = blockIdx.x / (unsigned)Hq, head = blockIdx.x % (unsigned)Hq, kvh = head / (Hq / Hkv);
+    const int row = 32 * rb + col;
+    float sum = 0.f;
+    if (w <= rb) {
+        const size_t qo = ((size_t)row * Hq + head) * D + 8 * half, ko = ((size_t)(32 * w + col) * Hkv + kvh) * D + 8 * half;
+        floatx16 s = {}, dp = {};
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, 64);
-    if (lane == 0) Delta[(size_t)head * stat_stride + row] = acc;
+        for (int t = 0; t < DT; ++t) {
+            s = mfma32(as_bf16x8(*reinterpret_cast<const u32x4*>(K + ko + 16 * t)), as_bf16x8(*reinterpret_cast<const u32x4*>(Q + qo + 16 * t)), s);
+            dp = mfma32(as_bf16x8(*reinterpret_cast<const u32x4*>(V + ko + 16 * t)), as_bf16x8(*reinterpret_cast<const u32x4*>(dO + qo + 16 * t)), dp);
+        }
+        const float lse2 = LSE[(size_t)head * stat_stride + row] * LOG2E;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (32 * w + acc_row(r, lane) <= row) sum = fmaf(__builtin_amdgcn_exp2f(fmaf(s[r], c, -lse2)), dp[r], sum);
+        sum += xor32(sum);
+    }
+    if (half == 0) part[w][col] = sum;
+    __syncthreads();
+    if (threadIdx.x < 32) {
+        float total = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) total += part[i][threadIdx.x];
+        Delta[(size_t)head * stat_stride + 32 * rb + threadIdx.x] = total;
+    }
 }
 
 }  // namespace
@@ -1039,13 +1050,14 @@ void launch_delta(const void* O, const void* dO, int64_t rows, int Hq, int D, in
 }
 
 void launch_delta_head(const void* Q, const void* dO, const void* K, const void* V, const float* LSE,
-                       int64_t stat_stride, int rows, int Hq, int Hkv, int D, float scale, float* Delta,
-                       hipStream_t st)
+                       int64_t stat_stride, int Hq, int Hkv, int D, float scale, float* Delta, hipStream_t st)
 {
-    dim3 grid((unsigned)((rows * Hq + 3) / 4));
-    delta_head_kernel<<<grid, 256, 0, st>>>((const uint16_t*)Q, (const uint16_t*)dO, (const uint16_t*)K,
-                                            (const uint16_t*)V, LSE, stat_stride, rows, Hq, Hkv, D, scale,
-                                            Delta);
+    const dim3 grid((unsigned)(DELTA_HEAD_ROWS / 32 * Hq));
+    const float c = scale * LOG2E;
+    const uint16_t *q = (const uint16_t*)Q, *g = (const uint16_t*)dO, *k = (const uint16_t*)K, *v = (const uint16_t*)V;
+    if (D == 128) delta_head_kernel<128><<<grid, 512, 0, st>>>(q, g, k, v, LSE, stat_stride, Hq, Hkv, c, Delta);
+    else if (D == 80) delta_head_kernel<80><<<grid, 512, 0, st>>>(q, g, k, v, LSE, stat_stride, Hq, Hkv, c, Delta);
+    else delta_head_kernel<64><<<grid, 512, 0, st>>>(q, g, k, v, LSE, stat_stride, Hq, Hkv, c, Delta);
 }
 
 }  // namespace fpdt

@@ -68,11 +68,10 @@ void launch_delta(const void* O, const void* dO, int64_t rows, int Hq, int D, in
                   float* Delta, int64_t delta_stride, hipStream_t st);
 
 // Overwrite Delta for rows [0, rows) of the sequence with sum_j p_ij (dO_i . v_j), which does
-// not depend on the rounded O.  All pointers are at row 0; rows <= DELTA_HEAD_ROWS.
+// not depend on the rounded O, rows = DELTA_HEAD_ROWS.  All pointers are at row 0.
 enum { DELTA_HEAD_ROWS = 256 };
 void launch_delta_head(const void* Q, const void* dO, const void* K, const void* V, const float* LSE,
-                       int64_t stat_stride, int rows, int Hq, int Hkv, int D, float scale, float* Delta,
-                       hipStream_t st);
+                       int64_t stat_stride, int Hq, int Hkv, int D, float scale, float* Delta, hipStream_t st);
 
 // out[head][block][64] = 32 x LSE * log2(e), 32 x -Delta for `rows` query rows (multiple of 32)
 void launch_stat_pack(const float* LSE, const float* Delta, int64_t stride, int64_t rows, int Hq,
