@@ -172,6 +172,8 @@ struct BwdPlan {
     float* lse_buf[2] = {nullptr, nullptr};
     char* dq_out[2] = {nullptr, nullptr};
     void* ds_frag = nullptr;  // stored-dS backward: the dS tiles of one chunk pair
+    int dkdv_splits = 1;      // workgroups that share a key tile's query walk
+    float* dkdv_part = nullptr;  // their partial dK, dV
     float* stat2 = nullptr;   // row statistics of the packed query rows, as the dK/dV kernel reads them
     size_t total = 0;
 };
@@ -192,7 +194,14 @@ BwdPlan plan_bwd(const Problem& p, void* ws)
         f.Vnat = b.take((size_t)(rows / 32) * p.Hkv * nat_block_bytes(p.D));
         if (!p.act_host()) f.Delta = b.take<float>((size_t)p.Hq * p.S * 4);
         f.stat2 = b.take<float>((size_t)(rows / 32) * p.Hq * 64 * 4);
-        if (!p.fused()) {
+        f.dkdv_splits = bwd_dkdv_splits(rows, rows, p.Hq, p.Hkv, p.D, p.fused());
+        if (f.dkdv_splits > 1) f.dkdv_part = b.take<float>(bwd_part_dkdv_bytes(rows, p.Hkv, p.D, f.dkdv_splits));
+        if (p.fused()) {
+            if (f.dkdv_splits > 1) {  // split 0's share
+                f.acc_dk = b.take<float>(bwd_acc_dkv_bytes(p.S, p.Hkv, p.D));
+                f.acc_dv = b.take<float>(bwd_acc_dkv_bytes(p.S, p.Hkv, p.D));
+            }
+        } else {
             // accumulators: the side that the outer loop holds fixed needs one chunk, the
             // other side one slot per chunk of the sequence
             const bool qo = p.q_outer();
@@ -629,7 +638,8 @@ int bwd_bf16_fused(const Problem& p, const void* Q, const void* K, const void* V
     a.stat2 = f.stat2;
     a.q_pos0 = 0; a.k_pos0 = 0; a.n_q = p.S; a.n_k = p.S;
     a.Hq = p.Hq; a.Hkv = p.Hkv; a.D = p.D; a.scale = p.scale;
-    a.acc_dq = nullptr; a.acc_dk = nullptr; a.acc_dv = nullptr;
+    a.acc_dq = nullptr; a.acc_dk = f.acc_dk; a.acc_dv = f.acc_dv;
+    a.dkdv_splits = f.dkdv_splits; a.dkdv_part = f.dkdv_part;
     a.dQ = dQ; a.dK = dK; a.dV = dV;
     a.flags = ACC_FINAL;
     { PROF(FPDT_PROF_DKDV, st); launch_bwd_dkdv(a, st); }
@@ -783,6 +793,7 @@ int bwd_bf16_pairs(const Problem& p, const char* Q, const char* K, const char* V
         a.acc_dq = f.acc_dq + (qo ? 0 : (size_t)i * acc_q_chunk);
         a.acc_dk = f.acc_dk + (qo ? (size_t)j * acc_kv_chunk : 0);
         a.acc_dv = f.acc_dv + (qo ? (size_t)j * acc_kv_chunk : 0);
+        a.dkdv_splits = f.dkdv_splits; a.dkdv_part = f.dkdv_part;
         const int ob_kv = (int)(j & 1), ob_q = (int)(i & 1);
         a.dK = kvh ? f.dkv_out[ob_kv] : dK + (size_t)j * kvb;
         a.dV = kvh ? f.dkv_out[ob_kv] + kvb : dV + (size_t)j * kvb;

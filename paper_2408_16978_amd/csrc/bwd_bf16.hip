@@ -7,7 +7,8 @@
 //
 // Two MFMA kernels, each keeping its accumulators in registers and recomputing p:
 //   bwd_dkdv_kernel_w4 : a workgroup (4 waves, one per SIMD) owns 256 keys of one KV head and
-//       walks the query rows (all query heads of the group).  Scores are computed as S = Q K^T
+//       walks the query rows (all query heads of the group; where the key tiles are too few to fill
+//       the chip, several workgroups share the walk and dkdv_sum_kernel adds their results).  Scores are computed as S = Q K^T
 //       (queries are MFMA rows, keys are columns): a lane owns one key, and the
 //       register-resident p and dS tiles are the B operands of dV^T += dO^T p and
 //       dK^T += Q^T dS.
@@ -18,6 +19,8 @@
 // Both stream their operands global -> LDS directly through a small ring, as NAT fragments
 // (fpdt_internal.h) only: an operand whose contraction runs over rows (Q^T, dO^T, K^T) is read
 // out of the same LDS block with transposing loads.
+#include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "fpdt_internal.h"
@@ -43,7 +46,9 @@ struct BwdKernelArgs {
     int n_q, n_k;
     int Hq, Hkv, g, flags;
     float scale, c;
+    int splits, head_splits;  // dK/dV kernel: see launch_bwd_dkdv
     float* acc_dq; float* acc_dk; float* acc_dv;
+    float* part;              // partial dK | dV of splits 1, 2, .. (splits > 1)
     uint16_t* dQ; uint16_t* dK; uint16_t* dV;
     u32x4* dS;  // dS fragments of the launch (stored-dS backward), or null
 };
@@ -121,16 +126,23 @@ __global__ __launch_bounds__(256) void bwd_dkdv_kernel_w4(BwdKernelArgs p)
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int wu = __builtin_amdgcn_readfirstlane(w);
     const int half = lane >> 5, col = lane & 31;
+    // Split sp of a key tile takes every rsplit-th 32-row query block (rsub is the first) and g of the
+    // group's heads, starting at head0.  All key tiles of one split walk the same blocks in the same
+    // order, whatever the diagonal cuts off, so the splits keep the L2 sharing of the unsplit walk.
     const int kvh = blockIdx.x % p.Hkv;
-    const int kt = blockIdx.x / p.Hkv;
+    const int sp = (int)(blockIdx.x / p.Hkv) % p.splits;
+    const int kt = (int)(blockIdx.x / p.Hkv) / p.splits;
+    const int g = p.g / p.head_splits, rsplit = p.splits / p.head_splits, rsub = sp / p.head_splits;
+    const int head0 = kvh * p.g + (sp % p.head_splits) * g;
     const int k0 = kt * BKT, kw0 = k0 + 32 * NK * wu;
     const int64_t kpos_w0 = p.k_pos0 + kw0;
 
     floatx16 dk[NK][DB], dv[NK][DB];
-    const size_t wg = blockIdx.x;
-    float* adk = p.acc_dk + ((wg * NW + w) * NK) * (size_t)(DB * 16 * 64);
-    float* adv = p.acc_dv + ((wg * NW + w) * NK) * (size_t)(DB * 16 * 64);
-    if (p.flags & ACC_LOAD) {
+    const size_t wg = (size_t)kt * p.Hkv + kvh, n_wg = gridDim.x / (unsigned)p.splits;
+    constexpr size_t WG_ACC = (size_t)(NW * NK * DB * 16 * 64);
+    float* adk = (sp == 0 ? p.acc_dk : p.part + (size_t)(2 * (sp - 1)) * n_wg * WG_ACC) + wg * WG_ACC + (size_t)(w * NK) * (DB * 16 * 64);
+    float* adv = (sp == 0 ? p.acc_dv : p.part + (size_t)(2 * sp - 1) * n_wg * WG_ACC) + wg * WG_ACC + (size_t)(w * NK) * (DB * 16 * 64);
+    if ((p.flags & ACC_LOAD) && sp == 0) {
 #pragma unroll
         for (int kb = 0; kb < NK; ++kb)
 #pragma unroll
@@ -174,14 +186,15 @@ __global__ __launch_bounds__(256) void bwd_dkdv_kernel_w4(BwdKernelArgs p)
     const int64_t qmin = p.k_pos0 + k0 - p.q_pos0;
     const int qb_start = qmin > 0 ? (int)(qmin / 32) : 0;
     const int n_qb_all = p.n_q / 32;
-    const int n_qb = n_qb_all > qb_start ? n_qb_all - qb_start : 0;
-    const int n_iter = n_qb * p.g;
+    const int qb_top = n_qb_all - 1 - rsub;  // the split's first block of the descending walk
+    const int n_qb = qb_top >= qb_start ? (qb_top - qb_start) / rsplit + 1 : 0;
+    const int n_iter = n_qb * g;
     // blocks whose first query precedes the workgroup's last key need the mask (for some wave)
     const int64_t kpos_last = p.k_pos0 + k0 + BKT - 1;
     int64_t dend = (kpos_last - p.q_pos0 + 31) / 32;
     if (dend < qb_start) dend = qb_start;
     if (dend > n_qb_all) dend = n_qb_all;
-    const int n_hot_iter = (n_qb_all - (int)dend) * p.g;  // walked first (descending order)
+    const int n_hot_iter = qb_top >= (int)dend ? ((qb_top - (int)dend) / rsplit + 1) * g : 0;  // walked first (descending order)
 
     // Operand layout.  A step needs the 32 x D Q and dO blocks twice: as A operands contracted
     // over d (S = Q K^T, dP = dO V^T; lane = query row, 8 consecutive d) and contracted over the
@@ -225,31 +238,31 @@ __global__ __launch_bounds__(256) void bwd_dkdv_kernel_w4(BwdKernelArgs p)
             trb[I] = 1024 * dblk + 512 * hq + 16 * (e + 4 * (h ^ hq) + 8 * (I ^ dblk)) + 8 * (x & 1);
     }
     // issue_begin(it) sets the scalar source addresses of step `it`: block (head, qb) with
-    // hh = it % g, qb = n_qb_all - 1 - it / g, head = kvh g + hh.  It is called for it = 0, 1, 2, ..
+    // hh = it % g, qb = qb_top - rsplit (it / g), head = head0 + hh.  It is called for it = 0, 1, 2, ..
     // in order (and once more for the last step), so the addresses are advanced by one of two
     // precomputed strides instead of being rebuilt: no division, no vector instruction, a dozen
     // scalar instructions at the head of a step, where nothing hides them.
     const int w64 = DT == 8 ? wu * 64 : 0;  // D = 128: the wave's first fragment of each operand
     const int64_t blk_next_head = p.q_head_stride_blocks;                          // hh + 1, same qb
-    const int64_t blk_next_qb = -(int64_t)(p.g - 1) * p.q_head_stride_blocks - 1;  // hh wraps to 0, qb - 1
+    const int64_t blk_next_qb = -(int64_t)(g - 1) * p.q_head_stride_blocks - rsplit;  // hh wraps to 0, qb - rsplit
     const int64_t pair_next_head = (int64_t)n_qb_all * (p.n_k / 32);
-    const int64_t pair_next_qb = -(int64_t)(p.g - 1) * pair_next_head - (p.n_k / 32);
+    const int64_t pair_next_qb = -(int64_t)(g - 1) * pair_next_head - (int64_t)rsplit * (p.n_k / 32);
     int st_it = 0, st_hh = 0;  // the step the addresses below belong to, and its head within the group
     {
-        const int64_t blk0 = (int64_t)(kvh * p.g) * p.q_head_stride_blocks + (n_qb_all - 1);
+        const int64_t blk0 = (int64_t)head0 * p.q_head_stride_blocks + qb_top;
         cp_src[0] = (uint64_t)(uintptr_t)(p.Qnat + blk0 * NAT_U4 + w64);
         cp_src[1] = (uint64_t)(uintptr_t)(p.dOnat + blk0 * NAT_U4 + w64);
         stat_src = (uint64_t)(uintptr_t)(p.stat2 + blk0 * 64);
         if constexpr (STORE_DS) {
             // fragment pairs (head, query block, key block) of a launch are fewer than 2^31 (API layer)
-            const int64_t pair0 = ((int64_t)(kvh * p.g) * n_qb_all + (n_qb_all - 1)) * (p.n_k / 32) + kw0 / 32;
+            const int64_t pair0 = ((int64_t)head0 * n_qb_all + qb_top) * (p.n_k / 32) + kw0 / 32;
             ds_next = (uint64_t)(uintptr_t)p.dS + ((uint64_t)pair0 << 11);
         }
     }
     auto issue_begin = [&](int it) {
         if (it == st_it) return;  // the first step, and the last step's second request
         st_it = it;
-        const bool wrap = ++st_hh == p.g;
+        const bool wrap = ++st_hh == g;
         if (wrap) st_hh = 0;
         const int64_t db = wrap ? blk_next_qb : blk_next_head;
         cp_src[0] += (uint64_t)(db * (int64_t)(NAT_U4 * 16));
@@ -299,7 +312,7 @@ __global__ __launch_bounds__(256) void bwd_dkdv_kernel_w4(BwdKernelArgs p)
 #pragma unroll
             for (int k = 0; k < NCOPY; ++k) issue_one(k, nslot == slot1);
         }
-        const int qb = n_qb_all - 1 - it / p.g;
+        const int qb = qb_top - rsplit * (it / g);
         const int64_t qpos_b0 = p.q_pos0 + (int64_t)qb * 32;
 
         if (!MASKED || qpos_b0 + 31 >= kpos_w0) {  // wave-uniform
@@ -494,7 +507,7 @@ __global__ __launch_bounds__(256) void bwd_dkdv_kernel_w4(BwdKernelArgs p)
 
     // the accumulators are read by ordinary instructions from here on
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-    if (p.flags & ACC_FINAL) {
+    if ((p.flags & ACC_FINAL) && p.splits == 1) {
 #pragma unroll
         for (int kb = 0; kb < NK; ++kb) {
             const size_t off = ((size_t)(kw0 + 32 * kb + col) * p.Hkv + kvh) * D;
@@ -511,6 +524,49 @@ __global__ __launch_bounds__(256) void bwd_dkdv_kernel_w4(BwdKernelArgs p)
                     adk[((kb * DB + db) * 16 + r) * 64 + lane] = dk[kb][db][r];
                     adv[((kb * DB + db) * 16 + r) * 64 + lane] = dv[kb][db][r];
                 }
+    }
+}
+
+// Sum of the splits of a dK/dV launch: acc += partials, or, with ACC_FINAL, the rounded outputs.  One
+// wave per 32-key x 32-channel accumulator tile; blockIdx.y = 0: dK, 1: dV.  Memory-bound: (splits + 1)
+// passes over n_k * Hkv * D fp32 values each of dK and dV.
+template <int D>
+__global__ __launch_bounds__(256) void dkdv_sum_kernel(BwdKernelArgs p, unsigned n_wg)
+{
+    constexpr int NW = 4, NK = 2, DB = (D + 31) / 32;
+    constexpr int TILE = 16 * 64;
+    const unsigned lane = threadIdx.x & 63;
+    const size_t tile = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6);  // (workgroup, wave, key block, channel block)
+    const bool is_v = blockIdx.y != 0;
+    const size_t all = (size_t)n_wg * (NW * NK * DB) * TILE;  // floats per operand
+    float* acc = (is_v ? p.acc_dv : p.acc_dk) + tile * TILE + lane;
+    const float* part = p.part + (is_v ? all : 0) + tile * TILE + lane;
+    floatx16 v;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[r] = acc[r * 64];
+    for (int sp = 1; sp < p.splits; ++sp, part += 2 * all) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[r] += part[r * 64];
+    }
+    if (!(p.flags & ACC_FINAL)) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r * 64] = v[r];
+        return;
+    }
+    const int half = (int)lane >> 5, col = (int)lane & 31;
+    const unsigned db = (unsigned)(tile % DB), blk = (unsigned)(tile / DB) % (NW * NK), wg = (unsigned)(tile / (DB * NW * NK));
+    const size_t key = (size_t)(wg / (unsigned)p.Hkv) * (NW * NK * 32) + 32 * blk + col;
+    uint16_t* row = (is_v ? p.dV : p.dK) + (key * p.Hkv + wg % (unsigned)p.Hkv) * D;
+    const float mul = is_v ? 1.f : p.scale;
+#pragma unroll
+    for (int a4 = 0; a4 < 4; ++a4) {
+        const int d = 32 * (int)db + 8 * a4 + 4 * half;
+        if (d < D) {
+            floatx4 o;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) o[b] = v[4 * a4 + b] * mul;
+            *reinterpret_cast<bf16x4*>(row + d) = __builtin_convertvector(o, bf16x4);
+        }
     }
 }
 
@@ -989,25 +1045,66 @@ static BwdKernelArgs to_kernel_args(const BwdArgs& a)
     k.Hq = a.Hq; k.Hkv = a.Hkv; k.g = a.Hq / a.Hkv; k.flags = a.flags;
     k.scale = a.scale; k.c = a.scale * LOG2E;
     k.acc_dq = a.acc_dq; k.acc_dk = a.acc_dk; k.acc_dv = a.acc_dv;
+    k.splits = a.dkdv_splits; k.part = a.dkdv_part;
+    k.head_splits = 1;  // the largest common divisor of the splits and the group's heads
+    for (int h = 2; h <= a.dkdv_splits && h <= k.g; ++h)
+        if (a.dkdv_splits % h == 0 && k.g % h == 0) k.head_splits = h;
     k.dQ = (uint16_t*)a.dQ; k.dK = (uint16_t*)a.dK; k.dV = (uint16_t*)a.dV;
     k.dS = (u32x4*)a.dS_frag;
     return k;
 }
 
+size_t bwd_part_dkdv_bytes(int64_t n_k, int Hkv, int D, int splits) { return 2 * (size_t)(splits - 1) * bwd_acc_dkv_bytes(n_k, Hkv, D); }
+
+// Into how many splits a dK/dV launch divides the query walk of its key tiles.  Unsplit it has n_k / 256
+// * Hkv workgroups of four waves, one per compute unit: 64 at 8K tokens and two KV heads, so that three
+// quarters of the chip idle, and below the diagonal's last rows the longest workgroup decides.  Each
+// split adds a partial dK, dV (written once, read once by dkdv_sum_kernel).  The count is the cheapest
+// of 1, 2, 4, .. 16 in units of steps (one 32-query block of one head; 1.7 us per workgroup, measured):
+//   whole pair    rounds of 256 workgroups x (steps of a workgroup + its fixed cost)
+//   causal pair   list scheduling of lengths that fall linearly to zero: the longest, or the average load
+//   partials      (splits + 1) passes at 4.5 bytes per ns, one more launch
+// Measured (dK/dV with its sum, before -> after): 8K tokens, 8 query / 2 KV heads, D = 128: 1357 -> 274 us
+// (8 splits); pairs of 32K chunks, 8 / 1 heads: 12.77 -> 7.33 ms (4 splits), 8 / 2 heads: 7.66 -> 7.15 ms (2:
+// only the diagonal pairs gain); pairs of 16K chunks, 8 / 2 heads: 3.07 -> 1.76 ms (4).
+int bwd_dkdv_splits(int64_t n_q, int64_t n_k, int Hq, int Hkv, int D, bool causal_launch)
+{
+    const double cus = 256.0, fixed = 12.0, us_per_step = 1.7;
+    const double wgs = (double)(n_k / bwd_k_tile(D)) * Hkv, steps = (double)(n_q / 32) * (Hq / Hkv);
+    int best = 1;
+    double best_cost = 0.0;
+    for (int s = 1; s <= 16; s *= 2) {
+        if (s > 1 && steps / s < 8.0) break;
+        const double w = wgs * s, len = steps / s;
+        const double full = std::ceil(w / cus) * (len + fixed);
+        const double causal = std::max(len + fixed, w / cus * (len / 2 + fixed) + len / 4);
+        const double sum = s == 1 ? 0.0 : ((double)(s + 1) * 2 * (double)bwd_acc_dkv_bytes(n_k, Hkv, D) / 4.5e6 + 6.0) / us_per_step;
+        const double cost = sum + (causal_launch ? causal : (full + causal) / 2);
+        if (s == 1 || cost < 0.97 * best_cost) { best = s; best_cost = cost; }
+    }
+    return best;
+}
+
 void launch_bwd_dkdv(const BwdArgs& a, hipStream_t st)
 {
     const BwdKernelArgs k = to_kernel_args(a);
-    dim3 grid((unsigned)((a.n_k / bwd_k_tile(a.D)) * a.Hkv));
+    const unsigned n_wg = (unsigned)((a.n_k / bwd_k_tile(a.D)) * a.Hkv);
+    dim3 grid(n_wg * (unsigned)k.splits);
     // (dS fragment pairs are indexed in 32 bits inside the kernels; the API layer sizes the buffer)
     if (a.dS_frag) {
         if (a.D == 128) bwd_dkdv_kernel_w4<128, true><<<grid, 256, 0, st>>>(k);
         else if (a.D == 80) bwd_dkdv_kernel_w4<80, true><<<grid, 256, 0, st>>>(k);
         else bwd_dkdv_kernel_w4<64, true><<<grid, 256, 0, st>>>(k);
-        return;
+    } else {
+        if (a.D == 128) bwd_dkdv_kernel_w4<128, false><<<grid, 256, 0, st>>>(k);
+        else if (a.D == 80) bwd_dkdv_kernel_w4<80, false><<<grid, 256, 0, st>>>(k);
+        else bwd_dkdv_kernel_w4<64, false><<<grid, 256, 0, st>>>(k);
     }
-    if (a.D == 128) bwd_dkdv_kernel_w4<128, false><<<grid, 256, 0, st>>>(k);
-    else if (a.D == 80) bwd_dkdv_kernel_w4<80, false><<<grid, 256, 0, st>>>(k);
-    else bwd_dkdv_kernel_w4<64, false><<<grid, 256, 0, st>>>(k);
+    if (k.splits == 1) return;
+    const dim3 sum_grid(n_wg * 2 * (unsigned)(dpad(a.D) / 32), 2);  // 8 DB accumulator tiles per workgroup, four per block
+    if (a.D == 128) dkdv_sum_kernel<128><<<sum_grid, 256, 0, st>>>(k, n_wg);
+    else if (a.D == 80) dkdv_sum_kernel<80><<<sum_grid, 256, 0, st>>>(k, n_wg);
+    else dkdv_sum_kernel<64><<<sum_grid, 256, 0, st>>>(k, n_wg);
 }
 
 // dQ of the launch from the dS fragments that launch_bwd_dkdv wrote for the same ranges

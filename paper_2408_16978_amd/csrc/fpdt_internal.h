@@ -110,9 +110,16 @@ struct BwdArgs {
     // stored-dS backward: n_q * n_k * Hq bf16 of dS tiles, written by the dK/dV kernel of the
     // launch and read by launch_bwd_dq_from_ds; null = dQ recomputes S and dP (launch_bwd_dq)
     void* dS_frag = nullptr;
+    // dK/dV launch: the query walk of every key tile is divided among dkdv_splits workgroups
+    // (bwd_dkdv_splits); split 0 uses acc_dk / acc_dv, the others bwd_part_dkdv_bytes of partials
+    int dkdv_splits = 1;
+    float* dkdv_part = nullptr;
 };
 size_t bwd_acc_dq_bytes(int64_t n_q, int Hq, int D);
 size_t bwd_acc_dkv_bytes(int64_t n_k, int Hkv, int D);  // each of dK, dV
+// causal_launch: one launch over the whole sequence; otherwise chunk pairs, most of them below the diagonal
+int bwd_dkdv_splits(int64_t n_q, int64_t n_k, int Hq, int Hkv, int D, bool causal_launch);
+size_t bwd_part_dkdv_bytes(int64_t n_k, int Hkv, int D, int splits);
 int bwd_k_tile(int D);
 int bwd_q_tile(int D);
 void launch_bwd_dkdv(const BwdArgs& a, hipStream_t st);

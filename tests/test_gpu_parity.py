@@ -282,3 +282,18 @@ def test_results_are_reproducible_bit_for_bit(flags):
     for n in ("O", "LSE", "dQ", "dK", "dV"):
         assert torch.equal(first[n].cpu(), second[n].cpu()), n
     del pad
+
+
+@pytest.mark.parametrize("S,chunk,Hq,Hkv,D,flags", [
+    (256, 256, 8, 1, 128, 0), (512, 512, 8, 2, 128, 0), (4096, 4096, 1, 1, 64, 0), (2304, 768, 6, 2, 80, 0),
+    (1024, 256, 8, 1, 128, B.FPDT_PAIRWISE | B.FPDT_BWD_Q_OUTER), (3072, 1536, 1, 1, 128, B.FPDT_BWD_STORE_DS)])
+def test_bf16_dkdv_walk_divided_among_workgroups(S, chunk, Hq, Hkv, D, flags):
+    """Few key tiles: the dK/dV launch divides each tile's query walk by heads, by query blocks or by
+    both; splits with no block left below the diagonal, a single key tile, group sizes that the split
+    count does not divide, carried accumulators in both loop orders, stored dS."""
+    announce("bf16 dK/dV splits", S, chunk, Hq, Hkv, D, flags)
+    Q, K, V, dO = inputs.make_qkvdo(S, Hq, Hkv, D, "bf16", seed=21)
+    scale = D ** -0.5
+    ref = parity.oracle_full(Q, K, V, dO, scale)
+    out = run(Q, K, V, dO, chunk, scale, flags)
+    print(parity.check_all(out, ref, True))
