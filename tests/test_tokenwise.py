@@ -405,3 +405,39 @@ def test_gpu_tokenwise_calls_replay_from_a_graph():
         torch.cuda.synchronize()
         for n, t in outs.items():
             assert torch.equal(t.view(torch.uint8), want[n].view(torch.uint8)), (n, rep)
+
+
+# ------------------------------------------------------------------ edges of the dense products
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,n_in,n_out,n_chunks,offset", [
+    (1, 8, 8, 1, 0),         # one element row, less than one k stage
+    (63, 40, 72, 2, 0),      # ragged k (not a multiple of 32), less than a tile in every direction
+    (257, 264, 248, 1, 0),   # one row / column past and short of the large tile
+    (300, 4096, 64, 1, 0),   # long k, few tiles: the k range is split
+    (129, 1000, 1001, 3, 0),  # odd widths: no row is 16-byte aligned
+    (200, 96, 520, 1, 1),    # operands that start 2 bytes behind a 16-byte boundary
+    (1030, 2048, 1160, 4, 0)])
+def test_gpu_linear_tile_edges(rows, n_in, n_out, n_chunks, offset):
+    """Forward, dX and dW of the projection against fp64 at the edges of the product's tiles, k stages and
+    splits.  Exact bf16 products summed in fp32: rel 1e-4 of a row's rms (k <= 4096 terms, error of about
+    sqrt(k) 2^-24 of the rms, under 1e-5) plus half a bf16 ulp of the stored value."""
+    print("[case] linear edges", rows, n_in, n_out, n_chunks, offset, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(rows + n_in)
+
+    def bf(r, c, std=1.0):
+        flat = torch.empty(r * c + offset, dtype=torch.bfloat16, device="cuda")
+        t = flat[offset:].view(r, c)
+        t.copy_(torch.randn(r, c, device="cuda", generator=g) * std)
+        return t
+
+    X, W, dY = bf(rows, n_in), bf(n_out, n_in, n_in ** -0.5), bf(rows, n_out)
+    Y, dX = torch.full_like(dY, float("nan")), torch.full_like(X, float("nan"))
+    dW = torch.ones(n_out, n_in, device="cuda")
+    TW.fpdt_tw_linear_fwd(X, W, Y, n_chunks)
+    TW.fpdt_tw_linear_bwd(X, W, dY, dX, dW, n_chunks)
+    torch.cuda.synchronize()
+    f64 = lambda t: t.double().cpu().numpy()
+    ref = otw.linear(f64(X), f64(W), f64(dY))
+    _rowwise_ok("Y", f64(Y), ref["Y"], rel=1e-4)
+    _rowwise_ok("dX", f64(dX), ref["dX"], rel=1e-4)
+    np.testing.assert_allclose(f64(dW), 1 + ref["dW"], atol=1e-4 * max(1.0, float(np.abs(ref["dW"]).max())))
