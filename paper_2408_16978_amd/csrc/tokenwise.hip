@@ -95,10 +95,10 @@ __device__ __forceinline__ uint16_t to_bf16(float f)
 }
 
 // One workgroup per row of logits [n, vocab] fp32: lse, loss and (G != nullptr) the bf16
-// gradient grad_scale * (softmax - onehot).  Two passes over the row: HBM-bound.
+// gradient grad_scale * (softmax - onehot), rows ldg apart.  Two passes over the row: HBM-bound.
 __global__ __launch_bounds__(256) void loss_rows_kernel(const float* __restrict__ logits, const int32_t* __restrict__ target,
                                                         int vocab, float grad_scale, float* __restrict__ loss,
-                                                        float* __restrict__ lse_out, uint16_t* __restrict__ G)
+                                                        float* __restrict__ lse_out, uint16_t* __restrict__ G, int64_t ldg)
 {
     __shared__ float red[2][4];
     const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -142,7 +142,8 @@ __global__ __launch_bounds__(256) void loss_rows_kernel(const float* __restrict_
         loss[row] = lse - ((t >= 0 && t < vocab) ? x[t] : 0.f);
     }
     if (!G) return;
-    uint16_t* g = G + (size_t)row * vocab;
+    uint16_t* g = G + (size_t)row * ldg;
+    if (vocab + tid < ldg) g[vocab + tid] = 0;  // at most 7: the products read whole 16-byte pieces
     if (vec) {
         const float4* x4 = reinterpret_cast<const float4*>(x);
         uint2* g2 = reinterpret_cast<uint2*>(g);
@@ -241,11 +242,13 @@ unsigned ew_blocks(size_t n)
 }
 size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+constexpr int64_t MAX_ROWS = (int64_t)1 << 24;  // of one product
+
 int check_chunking(int64_t rows, int n_chunks)
 {
     if (rows <= 0) return fail(TW_INVALID, "rows must be positive");
     if (n_chunks <= 0 || n_chunks > rows) return fail(TW_INVALID, "n_chunks=%d must be in [1, rows]", n_chunks);
-    if ((rows + n_chunks - 1) / n_chunks > (int64_t)1 << 24) return fail(TW_UNSUPPORTED, "chunk beyond the 32-bit GEMM limits");
+    if ((rows + n_chunks - 1) / n_chunks > MAX_ROWS) return fail(TW_UNSUPPORTED, "chunk beyond the 32-bit GEMM limits");
     return TW_OK;
 }
 
@@ -261,13 +264,15 @@ int fpdt_tw_linear_fwd(const void* X, const void* W, void* Y, int64_t rows, int 
     if (n_in <= 0 || n_out <= 0) return fail(TW_INVALID, "n_in and n_out must be positive");
     int rc = check_chunking(rows, n_chunks);
     if (rc != TW_OK) return rc;
-    const int64_t c = (rows + n_chunks - 1) / n_chunks;
     hipStream_t st = static_cast<hipStream_t>(stream);
     std::lock_guard<std::mutex> lock(g_mu);
     gemm_handle h;
     if ((rc = get_handle(&h, st)) != TW_OK) return rc;
-    for (int64_t r0 = 0; r0 < rows; r0 += c) {
-        const int n = (int)(rows - r0 < c ? rows - r0 : c);
+    // A row of Y is its own dot products and nothing lives between the chunks: one product over all rows
+    // fills the chip better than one per chunk (16384 x 4096 x 6144 in four chunks, with dX
+    // in the backward: 2506 -> 2251 us for forward and backward).
+    for (int64_t r0 = 0; r0 < rows; r0 += MAX_ROWS) {
+        const int n = (int)(rows - r0 < MAX_ROWS ? rows - r0 : MAX_ROWS);
         rc = gemm_nt(h, n, n_out, n_in, static_cast<const char*>(X) + (size_t)r0 * n_in * 2, W,
                      static_cast<char*>(Y) + (size_t)r0 * n_out * 2, TW_C_BF16, 0.f);
         if (rc != TW_OK) return rc;
@@ -288,17 +293,17 @@ int fpdt_tw_linear_bwd(const void* X, const void* W, const void* dY, void* dX, f
     std::lock_guard<std::mutex> lock(g_mu);
     gemm_handle h;
     if ((rc = get_handle(&h, st)) != TW_OK) return rc;
-    for (int64_t r0 = 0; r0 < rows; r0 += c) {
+    for (int64_t r0 = 0; dX && r0 < rows; r0 += MAX_ROWS) {  // dX[n, n_in] = dY[n, n_out] W[n_out, n_in], as in the forward
+        const int n = (int)(rows - r0 < MAX_ROWS ? rows - r0 : MAX_ROWS);
+        rc = gemm_nn(h, n, n_in, n_out, static_cast<const char*>(dY) + (size_t)r0 * n_out * 2, W,
+                     static_cast<char*>(dX) + (size_t)r0 * n_in * 2, TW_C_BF16, 0.f);
+        if (rc != TW_OK) return rc;
+    }
+    for (int64_t r0 = 0; dW && r0 < rows; r0 += c) {  // dW[n_out, n_in] += dY_c^T X_c: the chunks are the order of its sums
         const int n = (int)(rows - r0 < c ? rows - r0 : c);
-        const char* dYc = static_cast<const char*>(dY) + (size_t)r0 * n_out * 2;
-        if (dX) {  // dX_c[n, n_in] = dY_c[n, n_out] W[n_out, n_in]
-            rc = gemm_nn(h, n, n_in, n_out, dYc, W, static_cast<char*>(dX) + (size_t)r0 * n_in * 2, TW_C_BF16, 0.f);
-            if (rc != TW_OK) return rc;
-        }
-        if (dW) {  // dW[n_out, n_in] += dY_c^T X_c
-            rc = gemm_tn(h, n_out, n_in, n, dYc, static_cast<const char*>(X) + (size_t)r0 * n_in * 2, dW, TW_C_F32, 1.f);
-            if (rc != TW_OK) return rc;
-        }
+        rc = gemm_tn(h, n_out, n_in, n, static_cast<const char*>(dY) + (size_t)r0 * n_out * 2,
+                     static_cast<const char*>(X) + (size_t)r0 * n_in * 2, dW, TW_C_F32, 1.f);
+        if (rc != TW_OK) return rc;
     }
     return TW_OK;
 }
@@ -439,21 +444,41 @@ int fpdt_tw_loss_fwd_bwd(const void* H, const void* W, const int32_t* target, fl
     gemm_handle h;
     int rc = get_handle(&h, st);
     if (rc != TW_OK) return rc;
-    for (int64_t r0 = 0; r0 < rows; r0 += c) {
-        const int n = (int)(rows - r0 < c ? rows - r0 : c);
-        const char* Hc = static_cast<const char*>(H) + (size_t)r0 * hidden * 2;
-        // logits[n, vocab] = H_c W^T
-        rc = gemm_nt(h, n, vocab, hidden, Hc, W, logits, TW_C_F32, 0.f);
-        if (rc != TW_OK) return rc;
-        loss_rows_kernel<<<dim3((unsigned)n), 256, 0, st>>>(logits, target + r0, vocab, grad_scale, loss + r0, lse + r0,
-                                                             bwd ? G : nullptr);
-        if (dH) {  // dH_c[n, hidden] = G[n, vocab] W[vocab, hidden]
-            rc = gemm_nn(h, n, hidden, vocab, G, W, static_cast<char*>(dH) + (size_t)r0 * hidden * 2,
-                         TW_C_BF16, 0.f);
+    // The logit gradients of several chunks are gathered before they are multiplied: dW += G^T H reads and
+    // writes the whole fp32 dW (2.1 GB at 128256 x 4096), which at 1058 rows per chunk took as long as its
+    // MFMAs, and dH = G W has too few tiles at that height.  As many chunks as make `hidden` rows: their G
+    // then takes the memory of one bf16 copy of W, in the library's scratch.  Rows of G are padded to 16
+    // bytes there, so an odd vocabulary takes this way with a single chunk too.
+    // Measured (65536 tokens, hidden 4096, 62 chunks): 310 -> 235 ms, of which the memory-bound part of dW fell to a third.
+    int64_t per_group = hidden / c > 1 ? hidden / c : 1, ldg = vocab;
+    if (bwd && (per_group > 1 || vocab % 8)) {
+        const int64_t group_rows = per_group * c < rows ? per_group * c : rows, ld = ((int64_t)vocab + 7) / 8 * 8;
+        if (void* mem = fpdt_tw::scratch((size_t)group_rows * ld * 2)) {
+            G = static_cast<uint16_t*>(mem);
+            ldg = ld;
+        } else {
+            per_group = 1;
+        }
+    }
+    for (int64_t g0 = 0; g0 < rows; g0 += per_group * c) {
+        const int64_t g1 = rows - g0 < per_group * c ? rows : g0 + per_group * c;
+        for (int64_t r0 = g0; r0 < g1; r0 += c) {
+            const int n = (int)(g1 - r0 < c ? g1 - r0 : c);
+            // logits[n, vocab] = H_c W^T
+            rc = gemm_nt(h, n, vocab, hidden, static_cast<const char*>(H) + (size_t)r0 * hidden * 2, W, logits, TW_C_F32, 0.f);
+            if (rc != TW_OK) return rc;
+            loss_rows_kernel<<<dim3((unsigned)n), 256, 0, st>>>(logits, target + r0, vocab, grad_scale, loss + r0, lse + r0,
+                                                                 bwd ? G + (size_t)(r0 - g0) * ldg : nullptr, ldg);
+        }
+        const int n = (int)(g1 - g0);
+        if (dH) {  // dH[n, hidden] = G[n, vocab] W[vocab, hidden]
+            rc = gemm_status(fpdt_tw::gemm(0, 1, n, hidden, vocab, G, ldg, W, hidden, static_cast<char*>(dH) + (size_t)g0 * hidden * 2,
+                                           hidden, false, false, true, h->st));
             if (rc != TW_OK) return rc;
         }
-        if (dW) {  // dW[vocab, hidden] += G^T[vocab, n] H_c[n, hidden]
-            rc = gemm_tn(h, vocab, hidden, n, G, Hc, dW, TW_C_F32, 1.f);
+        if (dW) {  // dW[vocab, hidden] += G^T[vocab, n] H[n, hidden]
+            rc = gemm_status(fpdt_tw::gemm(1, 1, vocab, hidden, n, G, ldg, static_cast<const char*>(H) + (size_t)g0 * hidden * 2, hidden,
+                                           dW, hidden, true, true, false, h->st));
             if (rc != TW_OK) return rc;
         }
     }

@@ -5,13 +5,17 @@
 
 namespace fpdt_tw {
 
-// Start of a library call: forget the packed weights of the previous call and reuse its scratch.
+// Start of a library call: forget the realigned weights of the previous call and reuse its scratch.
 void begin_call();
+
+// Device scratch that lives until the next begin_call; null if there is not enough memory.
+void* scratch(size_t bytes);
 
 // C[M,N] (+)= sum_k Aop[m,k] * Bop[n,k], bf16 operands, fp32 accumulation.
 //   a_transposed = 0: A is stored [M,K] (leading dimension lda); 1: A is stored [K,M]
 //   b_transposed = 0: B is stored [N,K] (ldb);                   1: B is stored [K,N]
 //   C row-major [M,N], leading dimension ldc, bf16 or fp32 (c_f32); accumulate: C += instead of C =
+//   lda wider than A's rows: they are followed by zeros up to a multiple of 8
 //   cache_b: B is a weight that further products of this library call will use again
 // Only enqueues on `st`.  Returns 0, 1 (HIP failure) or 2 (sizes beyond the launch limits).
 int gemm(int a_transposed, int b_transposed, int M, int N, int K, const void* A, int64_t lda, const void* B,

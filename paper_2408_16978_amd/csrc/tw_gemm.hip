@@ -1,16 +1,15 @@
 // Dense bf16 products of the token-wise chunked operations (Sec. 4.1, 5.4: the per-chunk QKV
 // projection, the feed-forward block and the output projection of the loss are plain GEMMs over
-// one chunk of tokens at a time) on v_mfma_f32_32x32x16_bf16, with the operand machinery of the
-// attention kernels: operands re-laid once into 1 KiB MFMA fragments, a four-slot LDS ring
-// filled by direct global -> LDS copies three stages ahead, four waves (one per SIMD) per
-// output tile of up to 256 x 256.
+// one chunk of tokens at a time) on v_mfma_f32_32x32x16_bf16: a four-slot LDS ring filled by direct
+// global -> LDS copies three stages ahead, four waves (one per SIMD) per output tile of up to
+// 256 x 256.
 //
 //   C[M,N] (+)= sum_k Aop[m,k] * Bop[n,k]          fp32 accumulation, C bf16 or fp32
 //
 // Every product of the library is of this form once each operand is read either as stored
-// (row = row, k = column) or transposed (row = column, k = row); the pack kernel does both, pads
-// rows to a multiple of 256 and k to a multiple of the stage depth with zeros, so the product kernel has no
-// edge cases on its reads; its stores are bounds-checked.
+// (row = row, k = column) or transposed (row = column, k = row).  Both are read in place: the copy
+// engine fetches 16-byte pieces of the stored rows, a plain LDS read delivers the fragments of the
+// first form and a transposing LDS read those of the second.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -30,66 +29,28 @@ using fpdt::u32x4;
 
 namespace {
 
-// ---- pack -------------------------------------------------------------------------------
-// X [R, C] bf16 row-major, leading dimension ld.  transposed = 0: fragment rows are rows of X,
-// the contraction runs over its columns; 1: fragment rows are columns of X, the contraction
-// runs over its rows.  out[rb][kt][lane][8]: lane (r = lane % 32, h = lane / 32) of fragment
-// (rb, kt) holds element (row 32 rb + r, k = 16 kt + 8 h + e), e = 0..7; zero outside X.
-// One workgroup: 32 fragment rows x 64 contraction indices (four fragments).
-__global__ __launch_bounds__(256) void tw_pack_kernel(const uint16_t* __restrict__ X, int64_t R, int64_t C, int64_t ld,
-                                                      int transposed, u32x4* __restrict__ out, int KT, int KC)
+// ---- realign ----------------------------------------------------------------------------
+// The product kernel copies 16-byte pieces of its operands' rows and needs at least one whole stage of
+// k.  An operand that does not offer that (a width that is not a multiple of 8, a base that is not
+// 16-byte aligned, k < 32) is copied once into out [R2, C2], zero behind X [R, C].
+__global__ __launch_bounds__(256) void tw_realign_kernel(const uint16_t* __restrict__ X, int64_t R, int64_t C, int64_t ld,
+                                                         u32x4* __restrict__ out, int64_t R2, int64_t C2)
 {
-    __shared__ uint16_t tile[32][64 + 2];
-    const int tid = threadIdx.x;
-    const unsigned rb = blockIdx.x / (unsigned)KC, kc = blockIdx.x % (unsigned)KC;  // KC = chunks of 64 along k
-    const int64_t row0 = (int64_t)rb * 32, k0 = (int64_t)kc * 64;
-    // 256 threads x 8 consecutive elements of X = the 32 x 64 tile; 16-byte loads where the row
-    // allows it (8 elements inside the matrix, 16-byte aligned), element by element at the edges
-    auto load8 = [&](int64_t gr, int64_t gc0, uint16_t (&e)[8]) {
-        const uint16_t* src = X + gr * ld + gc0;
-        if (gr < R && gc0 + 8 <= C && (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
-            const uint4 v = *reinterpret_cast<const uint4*>(src);
-            e[0] = (uint16_t)v.x; e[1] = (uint16_t)(v.x >> 16); e[2] = (uint16_t)v.y; e[3] = (uint16_t)(v.y >> 16);
-            e[4] = (uint16_t)v.z; e[5] = (uint16_t)(v.z >> 16); e[6] = (uint16_t)v.w; e[7] = (uint16_t)(v.w >> 16);
-        } else {
+    const int64_t pieces = C2 / 8, n = R2 * pieces;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        const int64_t r = i / pieces, c = i % pieces * 8;
+        unsigned e[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) e[j] = (gr < R && gc0 + j < C) ? src[j] : (uint16_t)0;
-        }
-    };
-    uint16_t e8[8];
-    if (!transposed) {
-        const int r = tid >> 3, k = (tid & 7) * 8;  // row r of the tile, contraction indices k .. k + 7
-        load8(row0 + r, k0 + k, e8);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) tile[r][k + j] = e8[j];
-    } else {
-        const int k = tid >> 2, r = (tid & 3) * 8;  // row k0 + k of X, its columns row0 + r .. + 7
-        load8(k0 + k, row0 + r, e8);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) tile[r + j][k] = e8[j];
-    }
-    __syncthreads();
-    const int t = tid >> 6, lane = tid & 63;
-    const int kt = (int)kc * 4 + t;
-    if (kt < KT) {
-        const int r = lane & 31, h = lane >> 5;
-        uint16_t e[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) e[j] = tile[r][16 * t + 8 * h + j];
-        u32x4 v;
-        v[0] = e[0] | ((unsigned)e[1] << 16);
-        v[1] = e[2] | ((unsigned)e[3] << 16);
-        v[2] = e[4] | ((unsigned)e[5] << 16);
-        v[3] = e[6] | ((unsigned)e[7] << 16);
-        out[((size_t)rb * KT + kt) * 64 + lane] = v;
+        for (int j = 0; j < 8; ++j) e[j] = r < R && c + j < C ? X[r * ld + c + j] : 0u;
+        out[i] = u32x4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
     }
 }
 
 // ---- product ----------------------------------------------------------------------------
 constexpr int NWAVE = 4, NTHREAD = NWAVE * 64;
-constexpr int TILE = 256;  // packed operands are padded to this many rows
-constexpr int SKT = 2;     // k-steps of 16 per LDS stage
-constexpr int RING = 4;    // LDS slots of one stage each
+constexpr int SK = 32;        // k per LDS stage: two MFMA k-steps
+constexpr int RING = 4;       // LDS slots of one stage each; one more holds a last stage of less than SK
+constexpr unsigned PANEL = 4096;  // bytes of a panel: 64 rows of one operand x SK
 
 __device__ __forceinline__ uint16_t to_bf16(float f)
 {
@@ -99,9 +60,98 @@ __device__ __forceinline__ uint16_t to_bf16(float f)
 }
 __device__ __forceinline__ float from_bf16(uint16_t b) { return __uint_as_float((unsigned)b << 16); }
 
-// Af, Bf: packed operands (row blocks padded to the tile, KT a multiple of SKT).  C [M, N] row-major,
-// leading dimension ldc elements.  A workgroup of four waves, one per SIMD, computes a (64 WMT) x
-// (64 WNT) tile over the k-steps of its split; wave (w / 2, w % 2) owns WMT x WNT accumulator tiles.
+// One operand as stored: row r at p + r * ld, 16-byte aligned, ld a multiple of 8.  Form N: rows are the
+// product's rows, columns its k.  Form T: rows are k, columns the product's rows.  `rows` counts the
+// product's rows (form T: rounded up to 8, in bounds).
+struct Operand {
+    const uint16_t* p;
+    int64_t ld;
+    int rows;
+};
+
+// Per-lane source of one operand's copies and fragment reads.  A stage of an operand is PANEL bytes per 64
+// rows; wave w copies quarter w of every panel.
+//   Form N: panel row r (64 bytes) holds its four 16-byte pieces q at position q ^ f(r),
+//           f(r) = (r / 2) % 4 ^ (r / 8) % 2: any 8 rows aligned to 8, read at one piece, lie in different
+//           16-byte columns of 128 bytes, and any 16 rows in different columns of 256 bytes.
+//   Form T: panel row k (128 bytes, 64 columns) holds its two 64-byte halves at half ^ (k / 2) % 2: the four
+//           k x 32 columns that half a wave's transposing read covers lie in different 64-byte columns of
+//           256 bytes.
+template <bool T, int NP>
+struct Side {
+    uint64_t pos;        // scalar: the current stage
+    uint64_t step;       // bytes from a stage to the next
+    uint64_t rel[NP];    // scalar: panel j's quarter
+    unsigned off[NP];    // this lane's piece of it
+    unsigned rd[2];      // LDS bytes within a stage: form N k-step 0 / 1, form T even / odd fragments
+
+    __device__ __forceinline__ void init(const Operand& x, int row0, int stage0, int w, int wave_frag0, int lane, unsigned lds0)
+    {
+        const uint64_t pitch = (uint64_t)x.ld * 2;
+        const int limit = x.rows - row0;  // >= 1
+        if (T) {
+            step = SK * pitch;
+            pos = (uint64_t)(uintptr_t)(x.p + row0) + (uint64_t)stage0 * step + (uint64_t)(8 * w) * pitch;
+            const int k = lane >> 3, half = ((lane >> 2) & 1) ^ ((k >> 1) & 1);
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                const int c = 64 * j + 32 * half + 8 * (lane & 3);
+                rel[j] = 0;
+                off[j] = (unsigned)k * (unsigned)pitch + 2u * (unsigned)(c < limit - 8 ? c : limit - 8);
+            }
+            const int grp = lane >> 4, e = (lane & 15) >> 2, x4 = lane & 3;
+            const unsigned lane_part = 128u * (unsigned)(8 * (grp >> 1) + e) + 32u * (unsigned)(grp & 1) + 8u * (unsigned)x4;
+#pragma unroll
+            for (int par = 0; par < 2; ++par) {
+                const int f = wave_frag0 + par;
+                rd[par] = lds0 + PANEL * (unsigned)(f >> 1) + 64u * (unsigned)((f & 1) ^ (e >> 1)) + lane_part;
+            }
+        } else {
+            step = SK * 2;
+            pos = (uint64_t)(uintptr_t)x.p + (uint64_t)row0 * pitch + (uint64_t)stage0 * step;
+            const int r = lane >> 2, q = (lane & 3) ^ ((r >> 1) & 3) ^ ((r >> 3) & 1);
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                // rows behind the operand are read as its last row: their products are not stored
+                const int first = 64 * j + 16 * w < limit ? 64 * j + 16 * w : limit - 1;
+                const int mine = 64 * j + 16 * w + r < limit ? 64 * j + 16 * w + r : limit - 1;
+                rel[j] = (uint64_t)first * pitch;
+                off[j] = (unsigned)(mine - first) * (unsigned)pitch + 16u * (unsigned)q;
+            }
+            const int fr = lane & 15, swz = ((fr >> 1) & 3) ^ ((fr >> 3) & 1);
+            rd[0] = lds0 + 64u * (unsigned)(32 * wave_frag0 + (lane & 31)) + 16u * (unsigned)((lane >> 5) ^ swz);
+            rd[1] = rd[0] ^ 32u;
+        }
+        pos = fpdt::uniform(pos);
+    }
+    // does this lane's piece of stage `s` hold k < K (form N: K rounded up to 8)?
+    __device__ __forceinline__ bool has(int s, int K, int w, int lane) const
+    {
+        if (T) return s * SK + 8 * w + (lane >> 3) < K;
+        const int r = lane >> 2, q = (lane & 3) ^ ((r >> 1) & 3) ^ ((r >> 3) & 1);
+        return s * SK + 8 * q < K;
+    }
+    // fragment i of the wave, k-step t, of the stage at LDS byte `slot`
+    __device__ __forceinline__ bf16x8 frag(int i, int t, unsigned slot) const
+    {
+        if (T) {
+            typedef short short4v __attribute__((ext_vector_type(4)));
+            typedef short short8v __attribute__((ext_vector_type(8)));
+            typedef __attribute__((address_space(3))) short4v* lds_short4_ptr;
+            const unsigned at = rd[i & 1] + slot + PANEL * (unsigned)(i >> 1) + 2048u * (unsigned)t;
+            const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(uintptr_t)at);
+            const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(uintptr_t)(at + 512u));
+            const short8v both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+            return __builtin_bit_cast(bf16x8, both);
+        }
+        typedef __attribute__((address_space(3))) u32x4* lds_u32x4_ptr;
+        return fpdt::as_bf16x8(*(lds_u32x4_ptr)(uintptr_t)(rd[t] + slot + 2048u * (unsigned)i));
+    }
+};
+
+// C [M, N] row-major, leading dimension ldc elements.  A workgroup of four waves, one per SIMD, computes a
+// (64 WMT) x (64 WNT) tile over the stages of its split; wave (w / 2, w % 2) owns WMT x WNT accumulator
+// tiles of 32 x 32.
 //
 // What bounds it: LDS traffic next to the MFMAs.  A wave reads WMT + WNT fragments (1 KiB) per
 // WMT * WNT MFMAs, so the 128 x 128 elements of a wave at WMT = WNT = 4 need 0.5 fragments per MFMA;
@@ -111,23 +161,26 @@ __device__ __forceinline__ float from_bf16(uint16_t b) { return __uint_as_float(
 // set, one read behind every MFMA, and the copies go out one at a time between the MFMAs.
 // Stages of 32 k keep four slots in LDS, so a copy has two to three stages to land.  One barrier per
 // stage, in its middle: there stage s + 1 has landed and every wave has read all of stage s, whose
-// slot is free for stage s + RING.  Eight waves and 64-deep stages before, here (4096 rows): 14336 -> 4096
-// 409 -> 386 us, 1060 x 4096 x 128256 2128 -> 968 us (there the k splits), with fp32 accumulation into
-// 14336 x 4096 580 -> 478 us (there the epilogue below).
+// slot is free for stage s + RING.
+//
+// Measured: 1030-1270 TFLOP/s (8192^3 in the three forms: 1240, 1267, 1136).  The same loop without its
+// copies reaches 1300-1500, with every copy a hit in L2 1060-1220, with three or five slots the same as
+// with four: the copies' throughput into LDS next to the fragment reads is what is left, not their
+// latency.  Operands packed into MFMA fragments first (contiguous KiB per copy) gave the loop 5-10% and
+// cost 8-15% of an operation in packing.
+//
 // The MFMAs are issued through inline assembly so that the accumulators stay in accumulation registers
 // for the whole loop (with the builtin the allocator moved tiles between the two register files).
 #define TW_MFMA(d, x, y) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(x), "v"(y))
-template <bool OUT_F32, bool ACCUM, int WMT, int WNT>
-__global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(const u32x4* __restrict__ Af, const u32x4* __restrict__ Bf,
-                                                              int KT, void* __restrict__ Cout, int64_t ldc, int M, int N,
-                                                              int tiles_n, int tiles_total, int splits, int split_stages)
+template <bool TA, bool TB, bool OUT_F32, bool ACCUM, int WMT, int WNT>
+__global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand B, int K, void* __restrict__ Cout, int64_t ldc,
+                                                              int M, int N, int tiles_n, int tiles_total, int splits, int split_stages)
 {
-    constexpr int NA = 2 * WMT, NB = 2 * WNT;            // row blocks of a stage
-    constexpr int STAGE_U4 = (NA + NB) * SKT * 64;
+    constexpr unsigned STAGE = (WMT + WNT) * PANEL;      // bytes of a slot: A's panels, then B's
     constexpr int NC = WMT + WNT;                        // copies of a wave per stage
     constexpr int NC0 = (NC + 1) / 2;                    // .. of which in the first of the two k-steps that issue them
-    static_assert(SKT == 2 && NWAVE == 4, "a wave copies one k-step of every second block");
-    __shared__ u32x4 ring[RING * STAGE_U4];
+    static_assert(NWAVE == 4, "a wave copies a quarter of every panel");
+    __shared__ __attribute__((aligned(256))) u32x4 ring[(RING + 1) * STAGE / 16];
     // Consecutive workgroup ids land on different XCDs (each with its own L2): give every XCD a
     // contiguous run of tiles, so that the tiles that share an operand row share an L2.
     const unsigned work_total = (unsigned)tiles_total * (unsigned)splits;
@@ -147,21 +200,39 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(const u32x4* __rest
     const int lane = threadIdx.x & 63;
     const int wu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wu >> 1, wn = wu & 1;
+    const int stages = K / SK;  // whole ones, >= 1 in every split (host)
     const int stage0 = (int)split * split_stages;
-    const int n_stages = KT / SKT - stage0 < split_stages ? KT / SKT - stage0 : split_stages;  // >= 1 (host)
+    const int n_full = stages - stage0 < split_stages ? stages - stage0 : split_stages;
+    const bool tail = K % SK != 0 && stage0 + n_full == stages;  // the last split's stage of less than SK
 
-    // This wave copies k-step wu % 2 of the blocks wu / 2, wu / 2 + 2, .. of each operand.
-    const uint64_t blk_bytes = (uint64_t)KT * 1024;
-    const uint64_t first = (uint64_t)(wu >> 1) * blk_bytes + (uint64_t)(wu & 1) * 1024 + (uint64_t)stage0 * (SKT * 1024);
-    uint64_t a_src = fpdt::uniform((uint64_t)(uintptr_t)Af + (uint64_t)tile_m * NA * blk_bytes + first);
-    uint64_t b_src = fpdt::uniform((uint64_t)(uintptr_t)Bf + (uint64_t)tile_n * NB * blk_bytes + first);
-    const unsigned ring_lds = fpdt::lds_address(ring) + 1024u * (unsigned)wu;  // block wu / 2, k-step wu % 2
-    const int lane16 = 16 * lane;
-    auto copy = [&](int j, uint64_t ahead, unsigned slot) {  // copy j of the stage `ahead` bytes behind a_src / b_src
-        const uint64_t src = (j < WMT ? a_src : b_src) + (uint64_t)(2 * (j < WMT ? j : j - WMT)) * blk_bytes + ahead;
-        const unsigned blk = (unsigned)(j < WMT ? 2 * j : NA + 2 * (j - WMT));
-        fpdt::frag_to_lds_at(src, ring_lds + slot * (STAGE_U4 * 16u) + blk * (SKT * 1024u), lane16);
+    const unsigned ring0 = fpdt::lds_address(ring);
+    Side<TA, WMT> a_side;
+    Side<TB, WNT> b_side;
+    a_side.init(A, tile_m * (64 * WMT), stage0, wu, wm * WMT, lane, ring0);
+    b_side.init(B, tile_n * (64 * WNT), stage0, wu, wn * WNT, lane, ring0 + WMT * PANEL);
+    const unsigned copy_lds = ring0 + 1024u * (unsigned)wu;
+    // copy j of the stage `t` stages behind the current one
+    auto copy = [&](int j, int t, unsigned slot) {
+        const unsigned dst = copy_lds + slot * STAGE + PANEL * (unsigned)j;
+        if (j < WMT) fpdt::frag_to_lds_at(a_side.pos + a_side.rel[j % WMT] + (uint64_t)((int64_t)t * (int64_t)a_side.step), dst, (int)a_side.off[j % WMT]);
+        else fpdt::frag_to_lds_at(b_side.pos + b_side.rel[(j - WMT) % WNT] + (uint64_t)((int64_t)t * (int64_t)b_side.step), dst, (int)b_side.off[(j - WMT) % WNT]);
     };
+    if (tail) {  // its pieces pass through registers, zero behind K, into the slot behind the ring
+        u32x4 v[NC];
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {
+            v[j] = u32x4{0, 0, 0, 0};
+            if (j < WMT) {
+                const uint64_t src = a_side.pos + a_side.rel[j % WMT] + (uint64_t)n_full * a_side.step + a_side.off[j % WMT];
+                if (a_side.has(stages, K, wu, lane)) v[j] = *reinterpret_cast<const u32x4*>((uintptr_t)src);
+            } else {
+                const uint64_t src = b_side.pos + b_side.rel[(j - WMT) % WNT] + (uint64_t)n_full * b_side.step + b_side.off[(j - WMT) % WNT];
+                if (b_side.has(stages, K, wu, lane)) v[j] = *reinterpret_cast<const u32x4*>((uintptr_t)src);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < NC; ++j) ring[(RING * STAGE + PANEL * j + 1024u * wu) / 16 + lane] = v[j];
+    }
 
     floatx16 acc[WMT][WNT];
 #pragma unroll
@@ -175,41 +246,39 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(const u32x4* __rest
 #pragma unroll
         for (int j = 0; j < WNT; ++j) asm volatile("" : "+a"(acc[i][j]));
 
-    // stages 0 .. RING - 2 whole and the first copies of stage RING - 1.  A copy behind the last stage
-    // fetches that stage again, into a slot that nobody reads any more: the loop then needs no branch
-    // (with one, the allocator spilled the accumulators) and its wait counts are constants.
-    auto ahead = [&](int t, int left) { return (uint64_t)(unsigned)(t < left ? t : left - 1) * (SKT * 1024); };
+    // Stages 0 .. RING - 2 whole and the first copies of stage RING - 1.  A copy behind the last whole
+    // stage fetches that stage again, into a slot that nobody reads any more: the loop then needs no
+    // branch (with one, the allocator spilled the accumulators) and its wait counts are constants.
+    auto ahead = [&](int t, int full) { return t < full ? t : full - 1; };
 #pragma unroll
     for (int t = 0; t < RING; ++t)
 #pragma unroll
-        for (int j = 0; j < (t < RING - 1 ? NC : NC0); ++j) copy(j, ahead(t, n_stages), (unsigned)t);
+        for (int j = 0; j < (t < RING - 1 ? NC : NC0); ++j) copy(j, ahead(t, n_full), (unsigned)t);
     fpdt::wait_vmem_at_most<(RING - 2) * NC + NC0>();
     fpdt::barrier_no_fence();
 
     bf16x8 a[2][WMT], b[2][WNT];
-    const u32x4* mine = ring + lane;
-    auto read = [&](int set, int i, const u32x4* slot) {  // fragment i of the set, b first: the order of use
-        if (i < WNT) b[set][i] = fpdt::as_bf16x8(slot[((NA + wn * WNT + i) * SKT + set) * 64]);
-        else a[set][i - WNT] = fpdt::as_bf16x8(slot[((wm * WMT + i - WNT) * SKT + set) * 64]);
+    auto read = [&](int set, int i, unsigned slot) {  // fragment i of the set, b first: the order of use
+        if (i < WNT) b[set][i % WNT] = b_side.frag(i, set, slot);
+        else a[set][(i - WNT) % WMT] = a_side.frag(i - WNT, set, slot);
     };
 #pragma unroll
-    for (int i = 0; i < NC; ++i) read(0, i, mine);
+    for (int i = 0; i < NC; ++i) read(0, i, 0u);
 
-    // a_src / b_src point at the current stage, which is in slot `cur`
+    // the sides' pos is at the current stage, which is in slot `cur`
     unsigned cur = 0;
-    int left = n_stages;
+    int left = n_full + (tail ? 1 : 0);
     do {
-        const unsigned nxt = (cur + 1) % RING, prv = (cur + RING - 1) % RING;
-        const u32x4* sl = mine + cur * STAGE_U4;
-        const u32x4* nsl = mine + nxt * STAGE_U4;
-        const uint64_t ahead_prv = ahead(RING - 1, left), ahead_cur = ahead(RING, left);
+        const int full = tail ? left - 1 : left;  // (0 in the tail stage: its copies fetch the stage before it)
+        const unsigned nxt = tail && left == 2 ? RING : (cur + 1) % RING, prv = (cur + RING - 1) % RING;
+        const int ahead_prv = ahead(RING - 1, full), ahead_cur = ahead(RING, full);
         // reads in the first half of a k-step (they are waited for at its end), copies all over it
         constexpr int NM = WMT * WNT, NH = NM / 2;
 #pragma unroll
         for (int m = 0; m < NM; ++m) {
             TW_MFMA(acc[m / WNT][m % WNT], a[0][m / WNT], b[0][m % WNT]);
 #pragma unroll
-            for (int q = m * NC / NH; q < (m + 1) * NC / NH && q < NC; ++q) read(1, q, sl);
+            for (int q = m * NC / NH; q < (m + 1) * NC / NH && q < NC; ++q) read(1, q, cur * STAGE);
 #pragma unroll
             for (int q = m * (NC - NC0) / NM; q < (m + 1) * (NC - NC0) / NM; ++q) copy(NC0 + q, ahead_prv, prv);  // the rest of stage s + RING - 1
             __builtin_amdgcn_sched_barrier(0);
@@ -221,13 +290,13 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(const u32x4* __rest
         for (int m = 0; m < NM; ++m) {
             TW_MFMA(acc[m / WNT][m % WNT], a[1][m / WNT], b[1][m % WNT]);
 #pragma unroll
-            for (int q = m * NC / NH; q < (m + 1) * NC / NH && q < NC; ++q) read(0, q, nsl);
+            for (int q = m * NC / NH; q < (m + 1) * NC / NH && q < NC; ++q) read(0, q, nxt * STAGE);
 #pragma unroll
             for (int q = m * NC0 / NM; q < (m + 1) * NC0 / NM; ++q) copy(q, ahead_cur, cur);  // stage s + RING
             __builtin_amdgcn_sched_barrier(0);
         }
-        a_src += SKT * 1024;
-        b_src += SKT * 1024;
+        a_side.pos += a_side.step;
+        b_side.pos += b_side.step;
         cur = nxt;
     } while (--left > 0);
     fpdt::wait_vmem_at_most<0>();  // nothing may still be on its way into LDS when the workgroup ends
@@ -307,29 +376,20 @@ __global__ __launch_bounds__(256) void tw_split_sum_kernel(const float* __restri
     }
 }
 
-// ---- host side: packed-operand scratch and the per-call cache of packed weights --------------
+// ---- host side: scratch and the per-call cache of realigned weights --------------
 struct Pool {
     char* base = nullptr;
     size_t cap = 0, off = 0;
     std::vector<void*> retired;  // outgrown buffers: work already enqueued may still read them
 };
-struct Packed {
+struct Realigned {
     const void* src;
-    int64_t R, C, ld;
-    int transposed;
-    const u32x4* frags;
-    int RB, KT;
+    int64_t R, C, ld, R2, C2;
+    const uint16_t* copy;
 };
 Pool g_pool[64];
-std::vector<Packed> g_cache;  // weights packed during the current library call
+std::vector<Realigned> g_cache;  // weights realigned during the current library call
 std::mutex g_mu;
-
-size_t packed_bytes(int64_t rows, int64_t k, int tile, int* RB, int* KT)
-{
-    *RB = (int)((rows + tile - 1) / tile * (tile / 32));
-    *KT = (int)((k + 16 * SKT - 1) / (16 * SKT) * SKT);
-    return (size_t)*RB * *KT * 1024;
-}
 
 // Output tile (64 wmt x 64 wnt) and number of k splits of a product: the cheapest in units of the
 // core clock, from
@@ -387,28 +447,34 @@ int pool_take(Pool& p, size_t bytes, char** out)
     return 0;
 }
 
-int pack_operand(Pool& pool, const void* X, int64_t R, int64_t C, int64_t ld, int transposed, int tile,
-                 bool cache, hipStream_t st, Packed* res)
+// X [R, C], leading dimension ld, as the product kernel can read it: in place, or copied.  `k_rows`: the
+// contraction runs over the rows of X.  `padded`: rows are followed by zeros up to a multiple of 8.
+int take_operand(Pool& pool, const void* X, int64_t R, int64_t C, int64_t ld, bool k_rows, bool padded, bool cache, hipStream_t st, Operand* res)
 {
-    if (cache)
-        for (const Packed& c : g_cache)
-            if (c.src == X && c.R == R && c.C == C && c.ld == ld && c.transposed == transposed) {
-                *res = c;
-                return 0;
-            }
-    Packed p{X, R, C, ld, transposed, nullptr, 0, 0};
-    const int64_t rows = transposed ? C : R, k = transposed ? R : C;
-    const size_t bytes = packed_bytes(rows, k, tile, &p.RB, &p.KT);
-    char* mem = nullptr;
-    if (pool_take(pool, bytes, &mem)) return 1;
-    p.frags = reinterpret_cast<const u32x4*>(mem);
-    const int KC = (p.KT + 3) / 4;
-    if ((long long)p.RB * KC > (1ll << 30)) return 2;
-    tw_pack_kernel<<<dim3((unsigned)(p.RB * KC)), 256, 0, st>>>(static_cast<const uint16_t*>(X), R, C, ld, transposed,
-                                                               reinterpret_cast<u32x4*>(mem), p.KT, KC);
-    if (cache) g_cache.push_back(p);
-    *res = p;
-    return 0;
+    const int64_t K = k_rows ? R : C;
+    res->rows = (int)(k_rows ? (C + 7) / 8 * 8 : R);
+    if (K >= SK && (C % 8 == 0 || padded) && ld % 8 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0) {
+        res->p = static_cast<const uint16_t*>(X);
+        res->ld = ld;
+    } else {
+        const int64_t R2 = k_rows && R < SK ? SK : R, C2 = !k_rows && C < SK ? SK : (C + 7) / 8 * 8;
+        res->ld = C2;
+        res->p = nullptr;
+        if (cache)
+            for (const Realigned& c : g_cache)
+                if (c.src == X && c.R == R && c.C == C && c.ld == ld && c.R2 == R2 && c.C2 == C2) res->p = c.copy;
+        if (!res->p) {
+            char* mem = nullptr;
+            if (pool_take(pool, (size_t)R2 * C2 * 2, &mem)) return 1;
+            const int64_t blocks = (R2 * (C2 / 8) + 255) / 256;
+            tw_realign_kernel<<<dim3((unsigned)(blocks < 65536 ? blocks : 65536)), 256, 0, st>>>(
+                static_cast<const uint16_t*>(X), R, C, ld, reinterpret_cast<u32x4*>(mem), R2, C2);
+            res->p = reinterpret_cast<const uint16_t*>(mem);
+            if (cache) g_cache.push_back({X, R, C, ld, R2, C2, res->p});
+        }
+    }
+    // a lane's offset from its quarter panel (15 rows of form N, 7 of form T) is kept in 32 bits
+    return res->ld >= (int64_t)1 << 27 ? 2 : 0;
 }
 
 }  // namespace
@@ -422,6 +488,15 @@ void begin_call()
     g_pool[dev].off = 0;  // everything enqueued earlier on the stream is ordered before what follows
 }
 
+void* scratch(size_t bytes)
+{
+    std::lock_guard<std::mutex> lk(g_mu);
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
+    char* mem = nullptr;
+    return pool_take(g_pool[dev], bytes, &mem) ? nullptr : mem;
+}
+
 int gemm(int a_transposed, int b_transposed, int M, int N, int K, const void* A, int64_t lda, const void* B,
          int64_t ldb, void* C, int64_t ldc, bool c_f32, bool accumulate, bool cache_b, hipStream_t st)
 {
@@ -432,17 +507,18 @@ int gemm(int a_transposed, int b_transposed, int M, int N, int K, const void* A,
     if (M <= 0 || N <= 0 || K <= 0) return 2;
     const char* base0 = pool.base;
     const size_t off0 = pool.off;
-    const Plan plan = plan_product(M, N, (int)(((int64_t)K + 16 * SKT - 1) / (16 * SKT)));
+    const int Kp = K < SK ? SK : K;  // (realigned operands of less are padded to one stage)
+    const Plan plan = plan_product(M, N, Kp / SK);
     const int tile_rows = 64 * plan.wmt, tile_cols = 64 * plan.wnt;
     const int tiles_n = (N + tile_cols - 1) / tile_cols, tiles_m = (M + tile_rows - 1) / tile_rows;
     const long long total = (long long)tiles_m * tiles_n;
     if (total * plan.splits > (1ll << 30)) return 2;
     // Aop[m,k]: A stored [M,K] (as is) or [K,M] (transposed); Bop[n,k]: B stored [N,K] or [K,N]
-    Packed pa, pb;
-    int rc = pack_operand(pool, B, b_transposed ? K : N, b_transposed ? N : K, ldb, b_transposed, TILE, cache_b, st, &pb);
+    Operand pa, pb;
+    int rc = take_operand(pool, B, b_transposed ? K : N, b_transposed ? N : K, ldb, b_transposed, false, cache_b, st, &pb);
     if (rc) return rc;
     const size_t mark = pool.off;  // what follows is scratch of this product only
-    rc = pack_operand(pool, A, a_transposed ? K : M, a_transposed ? M : K, lda, a_transposed, tile_rows, false, st, &pa);
+    rc = take_operand(pool, A, a_transposed ? K : M, a_transposed ? M : K, lda, a_transposed, lda > (a_transposed ? M : K), false, st, &pa);
     if (rc) return rc;
     void* out = C;
     int64_t out_ld = ldc;
@@ -453,22 +529,32 @@ int gemm(int a_transposed, int b_transposed, int M, int N, int K, const void* A,
         out_ld = N;
     }
     const unsigned grid = (unsigned)((total * plan.splits + 7) / 8 * 8);
-    const int KT = pa.KT;  // = pb.KT: both contract over K
-#define TW_LAUNCH_TILE(F32, ACC, WM, WN)                                                                            \
-    tw_gemm_kernel<F32, ACC, WM, WN><<<grid, NTHREAD, 0, st>>>(pa.frags, pb.frags, KT, out, out_ld, M, N, tiles_n,   \
-                                                               (int)total, plan.splits, plan.split_stages)
-#define TW_LAUNCH(F32, ACC)                                             \
-    do {                                                                \
-        if (plan.wnt == 2) TW_LAUNCH_TILE(F32, ACC, 2, 2);              \
-        else if (plan.wmt == 4) TW_LAUNCH_TILE(F32, ACC, 4, 4);         \
-        else if (plan.wmt == 3) TW_LAUNCH_TILE(F32, ACC, 3, 4);         \
-        else if (plan.wmt == 2) TW_LAUNCH_TILE(F32, ACC, 2, 4);         \
-        else TW_LAUNCH_TILE(F32, ACC, 1, 4);                            \
+#define TW_LAUNCH_TILE(TA, TB, F32, ACC, WM, WN)                                                                     \
+    tw_gemm_kernel<TA, TB, F32, ACC, WM, WN><<<grid, NTHREAD, 0, st>>>(pa, pb, Kp, out, out_ld, M, N, tiles_n,        \
+                                                                       (int)total, plan.splits, plan.split_stages)
+#define TW_LAUNCH(TA, TB, F32, ACC)                                             \
+    do {                                                                        \
+        if (plan.wnt == 2) TW_LAUNCH_TILE(TA, TB, F32, ACC, 2, 2);              \
+        else if (plan.wmt == 4) TW_LAUNCH_TILE(TA, TB, F32, ACC, 4, 4);         \
+        else if (plan.wmt == 3) TW_LAUNCH_TILE(TA, TB, F32, ACC, 3, 4);         \
+        else if (plan.wmt == 2) TW_LAUNCH_TILE(TA, TB, F32, ACC, 2, 4);         \
+        else TW_LAUNCH_TILE(TA, TB, F32, ACC, 1, 4);                            \
     } while (0)
-    if (plan.splits > 1 || (c_f32 && !accumulate)) TW_LAUNCH(true, false);
-    else if (c_f32) TW_LAUNCH(true, true);
-    else if (accumulate) TW_LAUNCH(false, true);
-    else TW_LAUNCH(false, false);
+    const bool f32 = c_f32 || plan.splits > 1, add = accumulate && plan.splits == 1;
+    // the forms and outputs that the library's operations use
+    if (!a_transposed && !b_transposed && !add) {
+        if (f32) TW_LAUNCH(false, false, true, false);
+        else TW_LAUNCH(false, false, false, false);
+    } else if (!a_transposed && b_transposed && !(f32 && add)) {
+        if (f32) TW_LAUNCH(false, true, true, false);
+        else if (add) TW_LAUNCH(false, true, false, true);
+        else TW_LAUNCH(false, true, false, false);
+    } else if (a_transposed && b_transposed && f32) {
+        if (add) TW_LAUNCH(true, true, true, true);
+        else TW_LAUNCH(true, true, true, false);
+    } else {
+        return 2;
+    }
 #undef TW_LAUNCH
 #undef TW_LAUNCH_TILE
     if (plan.splits > 1) {
@@ -487,7 +573,7 @@ int gemm(int a_transposed, int b_transposed, int M, int N, int K, const void* A,
         else TW_SUM(false, false);
 #undef TW_SUM
     }
-    // The next product's packs run after this launch on the same stream, so this product's scratch
+    // The next product's copies run after this launch on the same stream, so this product's scratch
     // is free again: everything it took, or everything behind a weight that stays cached.  (Not if
     // the pool was replaced by a larger one on the way: then nothing is given back until the next
     // library call.)
