@@ -444,24 +444,26 @@ int copy_d2h(void* dst, const void* src, size_t bytes, hipStream_t st)
 // =========================================================================================
 // forward
 // =========================================================================================
+// Pair by pair only under a chunk mask; a dense call is one launch over the whole sequence.
 int fwd_f32(const Problem& p, const float* Q, const float* K, const float* V, float* O, float* LSE,
             const FwdPlan& f, hipStream_t st)
 {
-    for (int64_t m = 0; m < p.u; ++m)
+    const int64_t C = p.mask.empty() ? p.S : p.C, u = p.S / C;
+    for (int64_t m = 0; m < u; ++m)
         for (int64_t i = 0; i <= m; ++i) {
             if (!p.on(m, i)) continue;
             F32FwdArgs a;
-            a.Q = Q + (size_t)m * p.C * p.Hq * p.D;
-            a.K = K + (size_t)i * p.C * p.Hkv * p.D;
-            a.V = V + (size_t)i * p.C * p.Hkv * p.D;
-            a.O = O + (size_t)m * p.C * p.Hq * p.D;
-            a.LSE = LSE + m * p.C;
+            a.Q = Q + (size_t)m * C * p.Hq * p.D;
+            a.K = K + (size_t)i * C * p.Hkv * p.D;
+            a.V = V + (size_t)i * C * p.Hkv * p.D;
+            a.O = O + (size_t)m * C * p.Hq * p.D;
+            a.LSE = LSE + m * C;
             a.lse_stride = p.S;
             a.st_acc = f.st_acc; a.st_ml = f.st_ml;
-            a.q_pos0 = m * p.C; a.k_pos0 = i * p.C; a.n_q = p.C; a.n_k = p.C;
+            a.q_pos0 = m * C; a.k_pos0 = i * C; a.n_q = C; a.n_k = C;
             a.Hq = p.Hq; a.Hkv = p.Hkv; a.D = p.D; a.scale = p.scale;
             a.flags = (i == p.first_key_chunk(m) ? SWEEP_INIT : 0) | (i == m ? SWEEP_FINAL : 0);
-            launch_f32_fwd_pair(a, st);
+            launch_f32_fwd(a, st);
         }
     return launch_status("fp32 forward");
 }
@@ -589,25 +591,32 @@ int bwd_f32(const Problem& p, const float* Q, const float* K, const float* V, co
             const float* LSE, const float* dO, float* dQ, float* dK, float* dV, const BwdPlan& f,
             hipStream_t st)
 {
-    launch_zero(dQ, (size_t)p.S * p.Hq * p.D * 4, st);
-    launch_zero(dK, (size_t)p.S * p.Hkv * p.D * 4, st);
-    launch_zero(dV, (size_t)p.S * p.Hkv * p.D * 4, st);
+    const bool dense = p.mask.empty();  // one launch over the whole sequence, which overwrites
+    if (!dense) {
+        launch_zero(dQ, (size_t)p.S * p.Hq * p.D * 4, st);
+        launch_zero(dK, (size_t)p.S * p.Hkv * p.D * 4, st);
+        launch_zero(dV, (size_t)p.S * p.Hkv * p.D * 4, st);
+    }
     launch_delta(O, dO, p.S, p.Hq, p.D, 0, f.Delta, p.S, st);
+    const int64_t C = dense ? p.S : p.C;
     auto pair = [&](int64_t i, int64_t j) {
         F32BwdArgs a;
-        a.Q = Q + (size_t)i * p.C * p.Hq * p.D;
-        a.dO = dO + (size_t)i * p.C * p.Hq * p.D;
-        a.K = K + (size_t)j * p.C * p.Hkv * p.D;
-        a.V = V + (size_t)j * p.C * p.Hkv * p.D;
-        a.LSE = LSE + i * p.C; a.Delta = f.Delta + i * p.C; a.row_stat_stride = p.S;
-        a.dQ = dQ + (size_t)i * p.C * p.Hq * p.D;
-        a.dK = dK + (size_t)j * p.C * p.Hkv * p.D;
-        a.dV = dV + (size_t)j * p.C * p.Hkv * p.D;
-        a.q_pos0 = i * p.C; a.k_pos0 = j * p.C; a.n_q = p.C; a.n_k = p.C;
+        a.Q = Q + (size_t)i * C * p.Hq * p.D;
+        a.dO = dO + (size_t)i * C * p.Hq * p.D;
+        a.K = K + (size_t)j * C * p.Hkv * p.D;
+        a.V = V + (size_t)j * C * p.Hkv * p.D;
+        a.LSE = LSE + i * C; a.Delta = f.Delta + i * C; a.row_stat_stride = p.S;
+        a.dQ = dQ + (size_t)i * C * p.Hq * p.D;
+        a.dK = dK + (size_t)j * C * p.Hkv * p.D;
+        a.dV = dV + (size_t)j * C * p.Hkv * p.D;
+        a.accumulate = !dense;
+        a.q_pos0 = i * C; a.k_pos0 = j * C; a.n_q = C; a.n_k = C;
         a.Hq = p.Hq; a.Hkv = p.Hkv; a.D = p.D; a.scale = p.scale;
-        launch_f32_bwd_pair(a, st);
+        launch_f32_bwd(a, st);
     };
-    if (p.q_outer()) {
+    if (dense) {
+        pair(0, 0);
+    } else if (p.q_outer()) {
         for (int64_t i = 0; i < p.u; ++i)
             for (int64_t j = 0; j <= i; ++j)
                 if (p.on(i, j)) pair(i, j);

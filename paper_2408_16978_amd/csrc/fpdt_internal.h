@@ -128,7 +128,7 @@ void launch_bwd_dq_from_ds(const BwdArgs& a, hipStream_t st);
 static inline size_t bwd_ds_bytes(int64_t n_q, int64_t n_k, int Hq) { return (size_t)n_q * (size_t)n_k * Hq * 2; }
 
 // ---------------------------------------------------------------------------
-// fp32 path (accuracy path; plain FMA, one wave per row)
+// fp32 path (accuracy path; fp32 MFMA)
 // ---------------------------------------------------------------------------
 struct F32FwdArgs {
     const float* Q; const float* K; const float* V;  // at first row of the ranges
@@ -139,17 +139,18 @@ struct F32FwdArgs {
     float scale;
     int flags;  // SWEEP_INIT / SWEEP_FINAL
 };
-void launch_f32_fwd_pair(const F32FwdArgs& a, hipStream_t st);
+void launch_f32_fwd(const F32FwdArgs& a, hipStream_t st);
 
 struct F32BwdArgs {
     const float* Q; const float* dO; const float* K; const float* V;
     const float* LSE; const float* Delta; int64_t row_stat_stride;
-    float* dQ; float* dK; float* dV;  // accumulated in place (caller zero-fills first)
+    float* dQ; float* dK; float* dV;
+    bool accumulate;  // add to dQ, dK, dV instead of overwriting them
     int64_t q_pos0, k_pos0, n_q, n_k;
     int Hq, Hkv, D;
     float scale;
 };
-void launch_f32_bwd_pair(const F32BwdArgs& a, hipStream_t st);
+void launch_f32_bwd(const F32BwdArgs& a, hipStream_t st);
 
 // merge of two partial results (both dtypes)
 void launch_merge(const void* Oa, const float* La, const void* Ob, const float* Lb, void* Oo,

@@ -297,3 +297,38 @@ def test_bf16_dkdv_walk_divided_among_workgroups(S, chunk, Hq, Hkv, D, flags):
     ref = parity.oracle_full(Q, K, V, dO, scale)
     out = run(Q, K, V, dO, chunk, scale, flags)
     print(parity.check_all(out, ref, True))
+
+
+@pytest.mark.parametrize("S,chunk,Hq,Hkv,D", [(1, 1, 1, 1, 64), (31, 31, 4, 1, 128), (33, 11, 2, 2, 80), (289, 289, 3, 1, 64)])
+def test_fp32_tile_edges(S, chunk, Hq, Hkv, D):
+    """One row, one short of and one past a 32-row tile, one past the first block of every wave."""
+    announce("fp32 edges", S, chunk, Hq, Hkv, D)
+    Q, K, V, dO = inputs.make_qkvdo(S, Hq, Hkv, D, "f32", seed=18)
+    scale = D ** -0.5
+    ref = parity.oracle_full(Q, K, V, dO, scale)
+    print(parity.check_all(run(Q, K, V, dO, chunk, scale), ref, False))
+
+
+@pytest.mark.parametrize("D", [64, 80, 128])
+def test_fp32_masked_rows_may_hold_anything(D):
+    """Infinities and NaN in rows that the causal mask excludes leave the other rows alone, bit for bit:
+    later keys and values for O, LSE and dQ, earlier queries and output gradients for dK and dV."""
+    S, Hq, Hkv, cut = 150, 2, 1, 70
+    announce("fp32 non-finite", S, Hq, Hkv, D)
+    Q, K, V, dO = inputs.make_qkvdo(S, Hq, Hkv, D, "f32", seed=19)
+    scale = D ** -0.5
+    want = run(Q, K, V, dO, S, scale)
+    odd = torch.tensor([float("inf"), float("nan"), float("-inf")])
+
+    def spoil(t, rows):
+        t = t.clone()
+        t[rows] = odd.to(t.device).repeat(t[rows].numel() // 3 + 1)[:t[rows].numel()].view_as(t[rows])
+        return t
+
+    late = run(Q, spoil(K, slice(cut, S)), spoil(V, slice(cut, S)), dO, S, scale)
+    for n in ("O", "dQ"):
+        assert torch.equal(late[n][:cut], want[n][:cut]), n
+    assert torch.equal(late["LSE"][:, :cut], want["LSE"][:, :cut])
+    early = run(spoil(Q, slice(0, cut)), K, V, spoil(dO, slice(0, cut)), S, scale)
+    for n in ("dK", "dV"):
+        assert torch.equal(early[n][cut:], want[n][cut:]), n
