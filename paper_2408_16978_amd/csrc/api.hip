@@ -50,6 +50,7 @@ struct Problem {
     int Hq, Hkv, D, dtype;
     unsigned flags;
     float scale;
+    int fwd_kg;  // key groups of the bf16 forward: by the whole sequence, so that every schedule sums alike
     bool bf16() const { return dtype == FPDT_DTYPE_BF16; }
     size_t esize() const { return bf16() ? 2 : 4; }
     bool kv_host() const { return flags & FPDT_KV_ON_HOST; }
@@ -104,6 +105,7 @@ int validate_scalars(Problem& p, int64_t S, int64_t chunk, int Hq, int Hkv, int 
     if (S > (int64_t)1 << 30 || (int64_t)Hq * (S / 32 + 1) > (int64_t)1 << 30) return fail(FPDT_ERR_UNSUPPORTED, "S=%lld beyond launch limits", (long long)S);
     p.S = S; p.C = chunk; p.u = S / chunk; p.Hq = Hq; p.Hkv = Hkv; p.D = D; p.dtype = dtype;
     p.flags = flags; p.scale = scale;
+    p.fwd_kg = sweep_key_groups(S, S, Hq, true);
     return FPDT_OK;
 }
 
@@ -145,8 +147,8 @@ FwdPlan plan_fwd(const Problem& p, void* ws)
     } else {
         f.Knat = b.take((size_t)(p.C / 32) * p.Hkv * nat_block_bytes(p.D));
         f.Vtr = b.take((size_t)(p.C / 32) * p.Hkv * tr_block_bytes(p.D));
-        f.st_acc = b.take<float>(fwd_state_acc_bytes(p.C, p.Hq, p.D));
-        f.st_ml = b.take<float>(fwd_state_ml_bytes(p.C, p.Hq, p.D));
+        f.st_acc = b.take<float>(fwd_state_acc_bytes(p.C, p.Hq, p.D, p.fwd_kg));
+        f.st_ml = b.take<float>(fwd_state_ml_bytes(p.C, p.Hq, p.D, p.fwd_kg));
         if (p.kv_host())
             for (int i = 0; i < 2; ++i) f.kv_raw[i] = b.take<char>(2 * p.kv_chunk_bytes());
         if (p.act_host())
@@ -478,6 +480,7 @@ int fwd_bf16_fused(const Problem& p, const void* Q, const void* K, const void* V
     a.O = O; a.LSE = LSE; a.lse_stride = p.S; a.st_acc = nullptr; a.st_ml = nullptr;
     a.q_pos0 = 0; a.k_pos0 = 0; a.n_q = p.S; a.n_keys = p.S;
     a.Hq = p.Hq; a.Hkv = p.Hkv; a.D = p.D; a.scale = p.scale;
+    a.key_groups = p.fwd_kg;
     a.flags = SWEEP_INIT | SWEEP_FINAL;
     { PROF(FPDT_PROF_FWD, st); launch_fwd_sweep(a, st); }
     return launch_status("bf16 forward");
@@ -560,6 +563,7 @@ int fwd_bf16_pairs(const Problem& p, const char* Q, const char* K, const char* V
             a.st_acc = f.st_acc; a.st_ml = f.st_ml;
             a.q_pos0 = m * p.C; a.k_pos0 = i * p.C; a.n_q = p.C; a.n_keys = p.C;
             a.Hq = p.Hq; a.Hkv = p.Hkv; a.D = p.D; a.scale = p.scale;
+            a.key_groups = p.fwd_kg;
             a.flags = (i == p.first_key_chunk(m) ? SWEEP_INIT : 0) | (i == m ? SWEEP_FINAL : 0);
             { PROF(FPDT_PROF_FWD, st); launch_fwd_sweep(a, st); }
             ++t;
@@ -898,7 +902,11 @@ static int attn_fwd_impl(const void* Q, const void* K, const void* V, void* O, f
     Problem p;
     TRY(validate_scalars(p, S, chunk, Hq, Hkv, D, scale, dtype, flags));
     if (sparse) TRY(take_mask(p, chunk_mask));
-    const size_t need = plan_fwd(p, nullptr).total;
+    size_t need = plan_fwd(p, nullptr).total;
+    if (static_workspace && need > workspace_bytes && p.fwd_kg > 1) {  // one state per row takes less
+        p.fwd_kg = 1;
+        need = plan_fwd(p, nullptr).total;
+    }
     if (static_workspace) {
         if (need > workspace_bytes)
             return fail(FPDT_ERR_WORKSPACE, "these sizes need %zu bytes of workspace; the built-in scratch array of fpdt_attn_fwd_noalloc holds %zu (use fpdt_attn_fwd with a workspace of your own)", need, workspace_bytes);

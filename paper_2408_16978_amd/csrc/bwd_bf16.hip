@@ -574,31 +574,39 @@ __global__ __launch_bounds__(256) void dkdv_sum_kernel(BwdKernelArgs p, unsigned
 // dQ.  Wave w owns query rows [q0 + 32 w, +32) of one head (Q and dO fragments, LSE and Delta
 // stationary in registers).  Every step stages a 64-key tile (K-NAT, V-NAT, K-TR) in a 3-slot
 // LDS ring, loaded two tiles ahead.
-template <int D>
+//
+// KG = 2, 4 (as in the forward): 128 or 64 query rows per workgroup, the waves of one row block take every
+// KG-th 32-key block and add their results through LDS at the end (sweep_key_groups).
+template <int D, int KG>
 __global__ __launch_bounds__(NTHREAD) void bwd_dq_kernel(BwdKernelArgs p)
 {
     constexpr int DT = D / 16, DP = (D + 31) / 32 * 32, DB = DP / 32;
-    constexpr int BK = 64, KB = BK / 32;
-    constexpr int BQ = NWAVE * 32;
-    constexpr int NAT_U4 = KB * DT * 64;  // per tile of BK keys
+    constexpr int KB = KG == 1 ? 2 : 1;                // 32-key blocks of a wave per tile
+    constexpr int NB = KG * KB, BK = NB * 32;          // blocks and keys per tile
+    constexpr int NQ = NWAVE / KG, BQ = NQ * 32;
+    constexpr int NAT_U4 = NB * DT * 64;  // per tile of BK keys
     // The K tile is staged once; the key-contracted operand of dQ^T += K^T dS^T is read from the
     // same block with transposing LDS loads (layout and swizzle as in the dK/dV kernel above,
     // keys in the place of queries).  With DP > D the loads of the padded channels reach into the
     // next fragments of the slot; they only feed accumulator columns that are never stored.
     constexpr int SLOT_U4 = 2 * NAT_U4;
-    constexpr int NATF = KB * DT, NFRAG = 2 * NATF;
-    constexpr int RING = 3;
-    static_assert(RING == 3, "the tile loop below is unrolled over three slots");
-    __shared__ u32x4 ring0[SLOT_U4], ring1[SLOT_U4], ring2[SLOT_U4];
+    constexpr int NATF = NB * DT, NFRAG = 2 * NATF;
+    constexpr int RING = KG == 4 ? 2 : 3, PF = RING - 1;
+    // (DP > D: the transposing loads of the last block's padded channels stay within its slot: V follows K)
+    __shared__ u32x4 ring_a[KG == 1 ? SLOT_U4 : RING * SLOT_U4], ring_b[KG == 1 ? SLOT_U4 : 1], ring_c[KG == 1 ? SLOT_U4 : 1];
+    u32x4* const ring0 = ring_a;
+    u32x4* const ring1 = KG == 1 ? ring_b : ring_a + SLOT_U4;
+    u32x4* const ring2 = KG == 1 ? ring_c : ring_a + (RING - 1) * SLOT_U4;
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int wu = __builtin_amdgcn_readfirstlane(w);
     const int half = lane >> 5, col = lane & 31;
+    const int qb = KG == 1 ? w : wu % NQ, kg = KG == 1 ? 0 : wu / NQ;  // this wave's row block and its share of the key blocks
     const int head = blockIdx.x % p.Hq;
     const int n_qt = p.n_q / BQ;
     const int qt = n_qt - 1 - (int)(blockIdx.x / p.Hq);
     const int kvh = head / p.g;
-    const int q0 = qt * BQ, qw0 = q0 + w * 32;
+    const int q0 = qt * BQ, qw0 = q0 + qb * 32;
 
     const int64_t last_q_pos = p.q_pos0 + q0 + BQ - 1;
     int64_t need = last_q_pos - p.k_pos0 + 1;
@@ -661,9 +669,9 @@ __global__ __launch_bounds__(NTHREAD) void bwd_dq_kernel(BwdKernelArgs p)
     }
 
     floatx16 acc[DB];
-    const size_t wg = blockIdx.x;
-    float* aq = p.acc_dq + (wg * NWAVE + w) * (size_t)(DB * 16 * 64);
-    if (p.flags & ACC_LOAD) {
+    // accumulator slot of the row block: the same whatever KG a launch of the call has
+    float* aq = p.acc_dq + ((size_t)(qw0 / 32) * p.Hq + head) * (size_t)(DB * 16 * 64);
+    if ((p.flags & ACC_LOAD) && kg == 0) {
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -676,19 +684,20 @@ __global__ __launch_bounds__(NTHREAD) void bwd_dq_kernel(BwdKernelArgs p)
     }
 
     if (n_tiles > 0) issue(0, ring0);
-    if (n_tiles > 1) issue(1, ring1);
+    if (PF > 1 && n_tiles > 1) issue(1, ring1);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
     const int64_t qpos_first = p.q_pos0 + qw0, qpos_last = qpos_first + 31, qpos = qpos_first + col;
     const floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    // One tile: compute on slot `kn`, prefetch tile it+2 into slot `pf_slot`.
+    // One tile: compute on slot `kn`, prefetch tile it+PF into slot `pf_slot`.
     auto tile = [&](int it, const u32x4* kn, u32x4* pf_slot) {
-        if (it + 2 < n_tiles) issue(it + 2, pf_slot);
+        if (it + PF < n_tiles) issue(it + PF, pf_slot);
         const u32x4* vn = kn + NAT_U4;
         const unsigned kn_addr = lds_address(kn);
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
+        for (int kb_i = 0; kb_i < KB; ++kb_i) {
+            const int kb = kg * KB + kb_i;
             const int64_t key0 = p.k_pos0 + (int64_t)it * BK + 32 * kb;
             if (key0 <= qpos_last) {  // wave-uniform
                 // K fragments first; the V fragments are requested one per score MFMA (each has
@@ -741,15 +750,46 @@ __global__ __launch_bounds__(NTHREAD) void bwd_dq_kernel(BwdKernelArgs p)
                 }
             }
         }
-        // tile it+1 must have landed; the loads of tile it+2 issued above may stay in flight
-        if (it + 2 < n_tiles) wait_vmem_at_most<NFRAG / NWAVE>();
+        // tile it+1 must have landed; the loads of tile it+PF issued above may stay in flight (PF = 2)
+        if (it + PF < n_tiles) wait_vmem_at_most<(PF - 1) * (NFRAG / NWAVE)>();
         else wait_vmem_at_most<0>();
         barrier_no_fence();
     };
-    for (int it = 0; it < n_tiles; it += 3) {
-        tile(it, ring0, ring2);
-        if (it + 1 < n_tiles) tile(it + 1, ring1, ring0);
-        if (it + 2 < n_tiles) tile(it + 2, ring2, ring1);
+    if (RING == 3) {
+        for (int it = 0; it < n_tiles; it += 3) {
+            tile(it, ring0, ring2);
+            if (it + 1 < n_tiles) tile(it + 1, ring1, ring0);
+            if (it + 2 < n_tiles) tile(it + 2, ring2, ring1);
+        }
+    } else {
+        for (int it = 0; it < n_tiles; it += 2) {
+            tile(it, ring0, ring1);
+            if (it + 1 < n_tiles) tile(it + 1, ring1, ring0);
+        }
+    }
+
+    if constexpr (KG > 1) {  // (the loop ended with a barrier behind the last reads of the ring)
+        constexpr int PART = DB * 16 * 64;
+        static_assert((NWAVE - NQ) * PART * 4 <= RING * SLOT_U4 * 16, "the ring holds the parts");
+        __syncthreads();
+        float* part = reinterpret_cast<float*>(ring_a);
+        if (kg > 0) {
+            float* mine = part + (size_t)((kg - 1) * NQ + qb) * PART + lane;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) mine[(db * 16 + r) * 64] = acc[db][r];
+        }
+        __syncthreads();
+        if (kg > 0) return;
+#pragma unroll
+        for (int i = 1; i < KG; ++i) {
+            const float* other = part + (size_t)((i - 1) * NQ + qb) * PART + lane;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[db][r] += other[(db * 16 + r) * 64];
+        }
     }
 
     if (p.flags & ACC_FINAL) {
@@ -1117,13 +1157,24 @@ void launch_bwd_dq_from_ds(const BwdArgs& a, hipStream_t st)
     else bwd_dq_ds_kernel<64><<<grid, NTHREAD, 0, st>>>(k);
 }
 
+
+
+
 void launch_bwd_dq(const BwdArgs& a, hipStream_t st)
 {
     const BwdKernelArgs k = to_kernel_args(a);
-    dim3 grid((unsigned)((a.n_q / bwd_q_tile(a.D)) * a.Hq));
-    if (a.D == 128) bwd_dq_kernel<128><<<grid, NTHREAD, 0, st>>>(k);
-    else if (a.D == 80) bwd_dq_kernel<80><<<grid, NTHREAD, 0, st>>>(k);
-    else bwd_dq_kernel<64><<<grid, NTHREAD, 0, st>>>(k);
+    const int kg = sweep_key_groups(a.n_q, a.n_k, a.Hq, a.q_pos0 == a.k_pos0);
+    const dim3 grid((unsigned)((a.n_q / (bwd_q_tile(a.D) / kg)) * a.Hq));
+#define DQ_LAUNCH(D_)                                                        \
+    do {                                                                     \
+        if (kg == 4) bwd_dq_kernel<D_, 4><<<grid, NTHREAD, 0, st>>>(k);      \
+        else if (kg == 2) bwd_dq_kernel<D_, 2><<<grid, NTHREAD, 0, st>>>(k); \
+        else bwd_dq_kernel<D_, 1><<<grid, NTHREAD, 0, st>>>(k);              \
+    } while (0)
+    if (a.D == 128) DQ_LAUNCH(128);
+    else if (a.D == 80) DQ_LAUNCH(80);
+    else DQ_LAUNCH(64);
+#undef DQ_LAUNCH
 }
 
 void launch_stat_pack(const float* LSE, const float* Delta, int64_t stride, int64_t rows, int Hq,

@@ -37,6 +37,29 @@ void launch_pack(const void* X, int64_t rows, int H, int D, void* nat, void* tr,
 // bf16 forward sweep: query rows [q_pos0, q_pos0 + n_q) against keys
 // [k_pos0, k_pos0 + n_keys) (causal: key position <= query position).
 // ---------------------------------------------------------------------------
+// Key groups of a forward or dQ launch (a workgroup of eight waves = 8 / KG row blocks of 32 queries x KG
+// waves that share the keys): the cheapest of 1, 2, 4 in units of a 64-key tile of eight row blocks.  A
+// launch on the diagonal lasts as long as its longest row tile or as the average load of the 256 compute
+// units; KG > 1 divides the first, and costs a little more per tile (copies and barriers per MFMA).
+// Measured (us for KG = 1, 2, 4; forward | dQ): 2K tokens, 8 heads, D = 128: 57, 38, 29 | 77, 50, 35;
+// 8K: 216, 169, 207 | 303, 230, 270; 16K: 535, 592, 684 | 753, 812, 903; 32K, 2 heads, D = 64: 517, 388,
+// 354 | 670, 461, 477.
+static inline int sweep_key_groups(int64_t n_q, int64_t n_keys, int Hq, bool causal)
+{
+    const double tiles = (double)n_keys / 64.0, cus = 256.0;
+    int best = 1;
+    double best_cost = 0.0;
+    for (int kg = 1; kg <= 4; kg *= 2) {
+        const double work = kg == 1 ? 1.0 : kg == 2 ? 1.08 : 1.15, wgs = (double)n_q / 256.0 * kg * Hq;
+        const double longest = tiles / kg * work + 2.0;
+        const double load = (double)(int64_t)((wgs + cus - 1.0) / cus) * longest;       // below the diagonal
+        const double mean = wgs / cus * (tiles / kg / 2 * work + 2.0) + longest / 4.0;  // on it
+        const double cost = causal ? (mean > longest ? mean : longest) : load;
+        if (kg == 1 || cost < 0.97 * best_cost) { best = kg; best_cost = cost; }
+    }
+    return best;
+}
+
 enum { SWEEP_INIT = 1, SWEEP_FINAL = 2 };
 
 struct FwdArgs {
@@ -53,11 +76,11 @@ struct FwdArgs {
     int64_t n_q, n_keys;
     int Hq, Hkv, D;
     float scale;
+    int key_groups;     // sweep_key_groups of the whole sequence: every launch of a call has the same
     int flags;          // SWEEP_INIT: start from empty state; SWEEP_FINAL: normalise + write O, LSE
 };
-int fwd_q_tile(int D);                                    // query rows per workgroup
-size_t fwd_state_acc_bytes(int64_t n_q, int Hq, int D);   // carried state for n_q rows
-size_t fwd_state_ml_bytes(int64_t n_q, int Hq, int D);
+size_t fwd_state_acc_bytes(int64_t n_q, int Hq, int D, int key_groups);   // carried state for n_q rows
+size_t fwd_state_ml_bytes(int64_t n_q, int Hq, int D, int key_groups);
 void launch_fwd_sweep(const FwdArgs& a, hipStream_t st);
 
 // ---------------------------------------------------------------------------

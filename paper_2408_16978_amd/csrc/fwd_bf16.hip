@@ -10,9 +10,11 @@
 // stays in registers.
 //
 // Workgroup = 8 waves (two per SIMD, so one wave's softmax arithmetic runs under the other's
-// MFMAs), each wave owns 32 query rows of one head and at most 256 registers; all waves
-// share the 64-key K/V tiles, which travel global -> LDS directly (no register staging)
-// through a 3-slot ring filled two tiles ahead.
+// MFMAs), each wave owns 32 query rows of one head and at most 256 registers.  The K/V tiles travel
+// global -> LDS directly (no register staging) through a ring filled ahead.  KG = 1: the waves own 256
+// query rows and share 64-key tiles.  KG = 2, 4: 128 or 64 query rows, the waves of one row block take
+// every KG-th 32-key block and merge their (max, sum, output) through LDS at the end, for launches whose
+// row tiles are too few to fill the chip or whose longest row tile decides (sweep_key_groups).
 #include "fpdt_internal.h"
 #include "mfma_tiles.h"
 
@@ -20,13 +22,8 @@ namespace fpdt {
 
 namespace {
 
-constexpr int BK = 64;       // keys per LDS tile
-constexpr int KB = BK / 32;  // 32-key blocks per tile
 constexpr int NWAVE = 8;
 constexpr int NTHREAD = NWAVE * 64;
-constexpr int BQ = NWAVE * 32;  // query rows per workgroup
-constexpr int RING = 3;
-constexpr int PF = RING - 1;  // tiles in flight ahead of the one being computed
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
@@ -46,27 +43,35 @@ struct FwdKernelArgs {
     float c;  // scale * log2(e)
 };
 
-template <int D>
+template <int D, int KG>
 __global__ __launch_bounds__(NTHREAD) void fwd_sweep_kernel(FwdKernelArgs p)
 {
     constexpr int DT = D / 16, DP = (D + 31) / 32 * 32, DB = DP / 32;
-    constexpr int K_U4 = KB * DT * 64;      // u32x4 per K tile
-    constexpr int V_U4 = KB * 2 * DB * 64;  // u32x4 per V tile
+    constexpr int KB = KG == 1 ? 2 : 1;     // 32-key blocks of a wave per tile
+    constexpr int NB = KG * KB, BK = NB * 32;  // blocks and keys per LDS tile
+    constexpr int NQ = NWAVE / KG, BQ = NQ * 32;  // row blocks and query rows per workgroup
+    constexpr int RING = KG == 4 ? 2 : 3;   // (a tile of 128 keys: 64 KiB at D = 128)
+    constexpr int PF = RING - 1;            // tiles in flight ahead of the one being computed
+    constexpr int K_U4 = NB * DT * 64;      // u32x4 per K tile
+    constexpr int V_U4 = NB * 2 * DB * 64;  // u32x4 per V tile
     constexpr int T_U4 = K_U4 + V_U4;
-    constexpr int KFRAG = KB * DT, NFRAG = KFRAG + KB * 2 * DB;  // 1 KiB fragments per tile
-    // one LDS array per ring slot
-    static_assert(RING == 3, "the tile loop below is unrolled over three slots");
-    __shared__ u32x4 ring0[T_U4], ring1[T_U4], ring2[T_U4];
+    constexpr int KFRAG = NB * DT, NFRAG = KFRAG + NB * 2 * DB;  // 1 KiB fragments per tile
+    // KG = 1: one LDS array per ring slot; otherwise one for all, which the final merge uses again
+    __shared__ u32x4 ring_a[KG == 1 ? T_U4 : RING * T_U4], ring_b[KG == 1 ? T_U4 : 1], ring_c[KG == 1 ? T_U4 : 1];
+    u32x4* const ring0 = ring_a;
+    u32x4* const ring1 = KG == 1 ? ring_b : ring_a + T_U4;
+    u32x4* const ring2 = KG == 1 ? ring_c : ring_a + (RING - 1) * T_U4;
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int wu = __builtin_amdgcn_readfirstlane(w);
     const int half = lane >> 5, col = lane & 31;
+    const int qb = KG == 1 ? w : wu % NQ, kg = KG == 1 ? 0 : wu / NQ;  // this wave's row block and its share of the key blocks
     const int head = blockIdx.x % p.Hq;
     const int n_qt = p.n_q / BQ;
     const int qt = n_qt - 1 - (int)(blockIdx.x / p.Hq);  // heaviest (latest) tiles first
     const int kvh = head / p.g;
     const int q0 = qt * BQ;       // first row of the workgroup within the launch
-    const int qw0 = q0 + w * 32;  // first row of this wave
+    const int qw0 = q0 + qb * 32;  // first row of this wave
 
     // keys this workgroup needs: positions <= last query position
     const int64_t last_q_pos = p.q_pos0 + q0 + BQ - 1;
@@ -101,9 +106,9 @@ __global__ __launch_bounds__(NTHREAD) void fwd_sweep_kernel(FwdKernelArgs p)
 
     floatx16 acc[DB];
     float m_run, l_run;  // l_run is this lane's partial sum (its 16 keys per block)
-    const size_t wg = blockIdx.x;
-    float* sa = p.st_acc + (wg * NWAVE + w) * (size_t)(DB * 16 * 64);
-    float* sm = p.st_ml + (wg * NWAVE + w) * (size_t)(2 * 64);
+    const size_t slot = ((size_t)(qw0 / 32) * p.Hq + head) * KG + kg;  // every key group carries its own state
+    float* sa = p.st_acc + slot * (size_t)(DB * 16 * 64);
+    float* sm = p.st_ml + slot * (size_t)(2 * 64);
     if (p.flags & SWEEP_INIT) {
         m_run = -INFINITY;
         l_run = 0.f;
@@ -121,7 +126,7 @@ __global__ __launch_bounds__(NTHREAD) void fwd_sweep_kernel(FwdKernelArgs p)
     }
 
     if (n_tiles > 0) issue(0, ring0);
-    if (n_tiles > 1) issue(1, ring1);
+    if (PF > 1 && n_tiles > 1) issue(1, ring1);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
@@ -134,7 +139,8 @@ __global__ __launch_bounds__(NTHREAD) void fwd_sweep_kernel(FwdKernelArgs p)
     auto tile = [&](int it, const u32x4* ks, u32x4* pf_slot) {
         if (it + PF < n_tiles) issue(it + PF, pf_slot);
         const u32x4* vs = ks + K_U4;
-        const int64_t key0 = p.k_pos0 + (int64_t)it * BK;  // position of the tile's first key
+        const int kb0 = kg * KB;  // this wave's first block within the tile
+        const int64_t key0 = p.k_pos0 + (int64_t)it * BK + 32 * kb0;  // position of its first key
 
         if (key0 <= qpos_last) {  // wave-uniform: tile not entirely above this wave's diagonal
             // ---- S^T = K Q^T for the whole tile: all K fragments are requested up front so
@@ -143,7 +149,7 @@ __global__ __launch_bounds__(NTHREAD) void fwd_sweep_kernel(FwdKernelArgs p)
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-                for (int t = 0; t < DT; ++t) kfr[kb][t] = as_bf16x8(ks[(kb * DT + t) * 64 + lane]);
+                for (int t = 0; t < DT; ++t) kfr[kb][t] = as_bf16x8(ks[((kb0 + kb) * DT + t) * 64 + lane]);
             floatx16 s[KB];
 #pragma unroll
             for (int t = 0; t < DT; ++t)
@@ -158,14 +164,14 @@ __global__ __launch_bounds__(NTHREAD) void fwd_sweep_kernel(FwdKernelArgs p)
 #pragma unroll
                 for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
-                    for (int db = 0; db < DB; ++db) vfr[kb][s2][db] = as_bf16x8(vs[((kb * 2 + s2) * DB + db) * 64 + lane]);
+                    for (int db = 0; db < DB; ++db) vfr[kb][s2][db] = as_bf16x8(vs[(((kb0 + kb) * 2 + s2) * DB + db) * 64 + lane]);
             __builtin_amdgcn_sched_group_barrier(0x100, KB * 2 * DB, 0);
             // ---- online softmax, one query per lane ----
-            if (key0 + BK - 1 > qpos_first) {  // wave-uniform: the tile straddles the diagonal
+            if (key0 + 32 * KB - 1 > qpos_first) {  // wave-uniform: the tile straddles the diagonal
                 // key index within the tile vs this lane's query, in 32 bits: a key is masked
                 // when 32 kb + 8 (r / 4) + r % 4 + 4 half > qpos - key0
                 int64_t d = qpos - key0;
-                d = d < -1 ? -1 : d > BK ? BK : d;
+                d = d < -1 ? -1 : d > 32 * KB ? 32 * KB : d;
                 const int rel = (int)d - 4 * half;
 #pragma unroll
                 for (int kb = 0; kb < KB; ++kb)
@@ -205,7 +211,10 @@ __global__ __launch_bounds__(NTHREAD) void fwd_sweep_kernel(FwdKernelArgs p)
                 mx = fmaxf(mx, xor32(mx));
                 const float mc = mx * p.c;
                 const float m_new = mc > m_run ? mc : m_run;  // (a lane whose keys are all masked keeps its reference)
-                const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 on a row's first tile, 1 where nothing moved
+                // (KG > 1: a row may have had no key in this wave's blocks yet; its reference stays at -inf,
+                // and 0 takes its place in the exponents)
+                const float m_exp = KG > 1 && m_new == -INFINITY ? 0.f : m_new;
+                const float alpha = __builtin_amdgcn_exp2f(m_run - m_exp);  // 0 on a row's first tile, 1 where nothing moved
                 l_run *= alpha;
 #pragma unroll
                 for (int db = 0; db < DB; ++db)
@@ -218,7 +227,7 @@ __global__ __launch_bounds__(NTHREAD) void fwd_sweep_kernel(FwdKernelArgs p)
                     floatx16 e;
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
-                        e[r] = __builtin_amdgcn_exp2f(fmaf(s[kb][r], p.c, -m_new));
+                        e[r] = __builtin_amdgcn_exp2f(fmaf(s[kb][r], p.c, -m_exp));
                         lsum += e[r];
                     }
                     pf[kb][0] = pack_half<0>(e);
@@ -236,14 +245,53 @@ __global__ __launch_bounds__(NTHREAD) void fwd_sweep_kernel(FwdKernelArgs p)
                         acc[db] = mfma32(vfr[kb][s2][db], pf[kb][s2], acc[db]);
         }
         // tile it+1 must have landed; the loads of tile it+PF issued above may stay in flight
-        if (it + PF < n_tiles) wait_vmem_at_most<NFRAG / NWAVE>();
+        if (it + PF < n_tiles) wait_vmem_at_most<(PF - 1) * (NFRAG / NWAVE)>();
         else wait_vmem_at_most<0>();
         barrier_no_fence();
     };
-    for (int it = 0; it < n_tiles; it += 3) {
-        tile(it, ring0, ring2);
-        if (it + 1 < n_tiles) tile(it + 1, ring1, ring0);
-        if (it + 2 < n_tiles) tile(it + 2, ring2, ring1);
+    if (RING == 3) {
+        for (int it = 0; it < n_tiles; it += 3) {
+            tile(it, ring0, ring2);
+            if (it + 1 < n_tiles) tile(it + 1, ring1, ring0);
+            if (it + 2 < n_tiles) tile(it + 2, ring2, ring1);
+        }
+    } else {
+        for (int it = 0; it < n_tiles; it += 2) {
+            tile(it, ring0, ring1);
+            if (it + 1 < n_tiles) tile(it + 1, ring1, ring0);
+        }
+    }
+
+    if (KG > 1 && (p.flags & SWEEP_FINAL)) {
+        // Merge into the waves of kg = 0.  (Every copy has landed and every wave is past the last barrier:
+        // nobody reads the ring any more.)
+        constexpr int PART = (DB * 16 + 2) * 64;  // floats of a wave
+        static_assert(KG == 1 || (NWAVE - NQ) * PART * 4 <= RING * T_U4 * 16, "the ring holds the parts");
+        float* part = reinterpret_cast<float*>(ring_a);
+        if (kg > 0) {
+            float* mine = part + (size_t)((kg - 1) * NQ + qb) * PART + lane;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) mine[(db * 16 + r) * 64] = acc[db][r];
+            mine[DB * 16 * 64] = m_run;
+            mine[(DB * 16 + 1) * 64] = l_run;
+        }
+        __syncthreads();
+        if (kg > 0) return;
+#pragma unroll
+        for (int i = 1; i < KG; ++i) {
+            const float* other = part + (size_t)((i - 1) * NQ + qb) * PART + lane;
+            const float m_o = other[DB * 16 * 64], l_o = other[(DB * 16 + 1) * 64];
+            const float m_new = m_o > m_run ? m_o : m_run;  // finite: this wave saw the first key of every row
+            const float mine = __builtin_amdgcn_exp2f(m_run - m_new), theirs = __builtin_amdgcn_exp2f(m_o - m_new);
+            l_run = l_run * mine + l_o * theirs;
+            m_run = m_new;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[db][r] = acc[db][r] * mine + other[(db * 16 + r) * 64] * theirs;
+        }
     }
 
     // ---- epilogue ----
@@ -277,16 +325,14 @@ __global__ __launch_bounds__(NTHREAD) void fwd_sweep_kernel(FwdKernelArgs p)
 
 }  // namespace
 
-int fwd_q_tile(int D) { (void)D; return BQ; }
-
-size_t fwd_state_acc_bytes(int64_t n_q, int Hq, int D)
+size_t fwd_state_acc_bytes(int64_t n_q, int Hq, int D, int key_groups)
 {
-    return (size_t)n_q * Hq * dpad(D) * sizeof(float);
+    return (size_t)n_q * Hq * dpad(D) * sizeof(float) * key_groups;
 }
-size_t fwd_state_ml_bytes(int64_t n_q, int Hq, int D)
+size_t fwd_state_ml_bytes(int64_t n_q, int Hq, int D, int key_groups)
 {
     (void)D;
-    return (size_t)n_q * Hq * 2 * 2 * sizeof(float);  // (m, l) for both half-lanes of a row
+    return (size_t)n_q * Hq * 2 * 2 * sizeof(float) * key_groups;  // (m, l) for both half-lanes of a row
 }
 
 void launch_fwd_sweep(const FwdArgs& a, hipStream_t st)
@@ -309,10 +355,18 @@ void launch_fwd_sweep(const FwdArgs& a, hipStream_t st)
     k.g = a.Hq / a.Hkv;
     k.flags = a.flags;
     k.c = a.scale * LOG2E;
-    dim3 grid((unsigned)((a.n_q / BQ) * a.Hq));
-    if (a.D == 128) fwd_sweep_kernel<128><<<grid, NTHREAD, 0, st>>>(k);
-    else if (a.D == 80) fwd_sweep_kernel<80><<<grid, NTHREAD, 0, st>>>(k);
-    else fwd_sweep_kernel<64><<<grid, NTHREAD, 0, st>>>(k);
+    const int kg = a.key_groups;
+#define FWD_LAUNCH(D_)                                                                              \
+    do {                                                                                            \
+        const dim3 grid((unsigned)((a.n_q / (NWAVE * 32 / kg)) * a.Hq));                            \
+        if (kg == 4) fwd_sweep_kernel<D_, 4><<<grid, NTHREAD, 0, st>>>(k);                          \
+        else if (kg == 2) fwd_sweep_kernel<D_, 2><<<grid, NTHREAD, 0, st>>>(k);                     \
+        else fwd_sweep_kernel<D_, 1><<<grid, NTHREAD, 0, st>>>(k);                                  \
+    } while (0)
+    if (a.D == 128) FWD_LAUNCH(128);
+    else if (a.D == 80) FWD_LAUNCH(80);
+    else FWD_LAUNCH(64);
+#undef FWD_LAUNCH
 }
 
 }  // namespace fpdt

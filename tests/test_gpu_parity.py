@@ -299,6 +299,20 @@ def test_bf16_dkdv_walk_divided_among_workgroups(S, chunk, Hq, Hkv, D, flags):
     print(parity.check_all(out, ref, True))
 
 
+@pytest.mark.parametrize("S,chunk,Hq,Hkv,D,flags", [
+    (256, 256, 1, 1, 64, 0), (256, 256, 8, 8, 128, 0), (512, 512, 2, 1, 80, 0), (1280, 1280, 8, 1, 128, 0),
+    (4096, 4096, 8, 2, 128, 0), (2304, 768, 8, 2, 128, B.FPDT_PAIRWISE), (1536, 512, 4, 4, 80, B.FPDT_PAIRWISE),
+    (4096, 2048, 4, 2, 64, B.FPDT_PAIRWISE | B.FPDT_BWD_Q_OUTER)])
+def test_bf16_key_groups(S, chunk, Hq, Hkv, D, flags):
+    """Launches whose row tiles are too few for the chip, or whose longest row tile decides: the waves of a
+    row block share its keys and merge at the end (forward and dQ), alone and with carried state."""
+    announce("bf16 key groups", S, chunk, Hq, Hkv, D, flags)
+    Q, K, V, dO = inputs.make_qkvdo(S, Hq, Hkv, D, "bf16", seed=17)
+    scale = D ** -0.5
+    ref = parity.oracle_full(Q, K, V, dO, scale)
+    print(parity.check_all(run(Q, K, V, dO, chunk, scale, flags), ref, True))
+
+
 @pytest.mark.parametrize("S,chunk,Hq,Hkv,D", [(1, 1, 1, 1, 64), (31, 31, 4, 1, 128), (33, 11, 2, 2, 80), (289, 289, 3, 1, 64)])
 def test_fp32_tile_edges(S, chunk, Hq, Hkv, D):
     """One row, one short of and one past a 32-row tile, one past the first block of every wave."""
