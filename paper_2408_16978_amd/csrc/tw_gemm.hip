@@ -24,7 +24,7 @@
 namespace fpdt_tw {
 
 using fpdt::bf16x8;
-using fpdt::floatx16;
+using fpdt::floatx4;
 using fpdt::u32x4;
 
 namespace {
@@ -74,16 +74,15 @@ struct Operand {
 //   Form N: panel row r (64 bytes) holds its four 16-byte pieces q at position q ^ f(r),
 //           f(r) = (r / 2) % 4 ^ (r / 8) % 2: any 8 rows aligned to 8, read at one piece, lie in different
 //           16-byte columns of 128 bytes, and any 16 rows in different columns of 256 bytes.
-//   Form T: panel row k (128 bytes, 64 columns) holds its two 64-byte halves at half ^ (k / 2) % 2: the four
-//           k x 32 columns that half a wave's transposing read covers lie in different 64-byte columns of
-//           256 bytes.
+//   Form T: panel row k (128 bytes, 64 columns) holds its 32-byte quarter u at u ^ (2 ((k / 2) % 2) + (k / 8) % 2):
+//           the eight k x 16 columns that half a wave's transposing read covers lie in different 32-byte
+//           columns of 256 bytes.
 template <bool T, int NP>
 struct Side {
     uint64_t pos;        // scalar: the current stage
     uint64_t step;       // bytes from a stage to the next
-    uint64_t rel[NP];    // scalar: panel j's quarter
-    unsigned off[NP];    // this lane's piece of it
-    unsigned rd[2];      // LDS bytes within a stage: form N k-step 0 / 1, form T even / odd fragments
+    unsigned off[NP];    // this lane's piece of panel j
+    unsigned rd[4];      // LDS bytes within a stage: of fragments 0, 4, .., of 1, 5, .., (form N: rd[0] only)
 
     __device__ __forceinline__ void init(const Operand& x, int row0, int stage0, int w, int wave_frag0, int lane, unsigned lds0)
     {
@@ -92,19 +91,20 @@ struct Side {
         if (T) {
             step = SK * pitch;
             pos = (uint64_t)(uintptr_t)(x.p + row0) + (uint64_t)stage0 * step + (uint64_t)(8 * w) * pitch;
-            const int k = lane >> 3, half = ((lane >> 2) & 1) ^ ((k >> 1) & 1);
+            const int k = lane >> 3, u = ((lane >> 1) & 3) ^ (2 * ((k >> 1) & 1) + (w & 1));
 #pragma unroll
             for (int j = 0; j < NP; ++j) {
-                const int c = 64 * j + 32 * half + 8 * (lane & 3);
-                rel[j] = 0;
+                const int c = 64 * j + 16 * u + 8 * (lane & 1);
                 off[j] = (unsigned)k * (unsigned)pitch + 2u * (unsigned)(c < limit - 8 ? c : limit - 8);
             }
-            const int grp = lane >> 4, e = (lane & 15) >> 2, x4 = lane & 3;
-            const unsigned lane_part = 128u * (unsigned)(8 * (grp >> 1) + e) + 32u * (unsigned)(grp & 1) + 8u * (unsigned)x4;
+            // 16-lane group g supplies k rows 8 g + 0..3 (and + 4..7 with the second read), lane i of it row
+            // i / 4, columns 4 (i % 4) .. + 3
+            const int g = lane >> 4, e = (lane & 15) >> 2;
+            const unsigned lane_part = 128u * (unsigned)(8 * g + e) + 8u * (unsigned)(lane & 3);
 #pragma unroll
-            for (int par = 0; par < 2; ++par) {
-                const int f = wave_frag0 + par;
-                rd[par] = lds0 + PANEL * (unsigned)(f >> 1) + 64u * (unsigned)((f & 1) ^ (e >> 1)) + lane_part;
+            for (int q = 0; q < 4; ++q) {
+                const int f = wave_frag0 + q;
+                rd[q] = lds0 + PANEL * (unsigned)(f >> 2) + 32u * (unsigned)((f & 3) ^ (2 * (e >> 1) + (g & 1))) + lane_part;
             }
         } else {
             step = SK * 2;
@@ -113,14 +113,11 @@ struct Side {
 #pragma unroll
             for (int j = 0; j < NP; ++j) {
                 // rows behind the operand are read as its last row: their products are not stored
-                const int first = 64 * j + 16 * w < limit ? 64 * j + 16 * w : limit - 1;
                 const int mine = 64 * j + 16 * w + r < limit ? 64 * j + 16 * w + r : limit - 1;
-                rel[j] = (uint64_t)first * pitch;
-                off[j] = (unsigned)(mine - first) * (unsigned)pitch + 16u * (unsigned)q;
+                off[j] = (unsigned)mine * (unsigned)pitch + 16u * (unsigned)q;
             }
             const int fr = lane & 15, swz = ((fr >> 1) & 3) ^ ((fr >> 3) & 1);
-            rd[0] = lds0 + 64u * (unsigned)(32 * wave_frag0 + (lane & 31)) + 16u * (unsigned)((lane >> 5) ^ swz);
-            rd[1] = rd[0] ^ 32u;
+            rd[0] = lds0 + 64u * (unsigned)(16 * wave_frag0 + fr) + 16u * (unsigned)((lane >> 4) ^ swz);
         }
         pos = fpdt::uniform(pos);
     }
@@ -131,52 +128,60 @@ struct Side {
         const int r = lane >> 2, q = (lane & 3) ^ ((r >> 1) & 3) ^ ((r >> 3) & 1);
         return s * SK + 8 * q < K;
     }
-    // fragment i of the wave, k-step t, of the stage at LDS byte `slot`
-    __device__ __forceinline__ bf16x8 frag(int i, int t, unsigned slot) const
+    // fragment i of the wave (16 rows x 32 k: lane l holds row l % 16, k = 8 (l / 16) .. + 7) of the stage at
+    // LDS byte `slot`
+    __device__ __forceinline__ bf16x8 frag(int i, unsigned slot) const
     {
         if (T) {
             typedef short short4v __attribute__((ext_vector_type(4)));
             typedef short short8v __attribute__((ext_vector_type(8)));
             typedef __attribute__((address_space(3))) short4v* lds_short4_ptr;
-            const unsigned at = rd[i & 1] + slot + PANEL * (unsigned)(i >> 1) + 2048u * (unsigned)t;
+            const unsigned at = rd[i & 3] + slot + PANEL * (unsigned)(i >> 2);
             const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(uintptr_t)at);
             const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(uintptr_t)(at + 512u));
             const short8v both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
             return __builtin_bit_cast(bf16x8, both);
         }
         typedef __attribute__((address_space(3))) u32x4* lds_u32x4_ptr;
-        return fpdt::as_bf16x8(*(lds_u32x4_ptr)(uintptr_t)(rd[t] + slot + 2048u * (unsigned)i));
+        return fpdt::as_bf16x8(*(lds_u32x4_ptr)(uintptr_t)(rd[0] + slot + 1024u * (unsigned)i));
     }
 };
 
 // C [M, N] row-major, leading dimension ldc elements.  A workgroup of four waves, one per SIMD, computes a
-// (64 WMT) x (64 WNT) tile over the stages of its split; wave (w / 2, w % 2) owns WMT x WNT accumulator
-// tiles of 32 x 32.
+// (64 WMT) x (64 WNT) tile over the stages of its split; wave (w / 2, w % 2) owns 2 WMT x 2 WNT accumulator
+// tiles of 16 x 16.
 //
-// What bounds it: LDS traffic next to the MFMAs.  A wave reads WMT + WNT fragments (1 KiB) per
-// WMT * WNT MFMAs, so the 128 x 128 elements of a wave at WMT = WNT = 4 need 0.5 fragments per MFMA;
-// eight waves of 128 x 64 need 0.75, and with the copies' writes LDS was then as busy as the MFMA
-// pipes.  The 256 accumulator registers leave room for one wave per SIMD, so nothing but this wave's
-// own instruction order hides a latency: fragments are read one k-step ahead into a second register
-// set, one read behind every MFMA, and the copies go out one at a time between the MFMAs.
-// Stages of 32 k keep four slots in LDS, so a copy has two to three stages to land.  One barrier per
-// stage, in its middle: there stage s + 1 has landed and every wave has read all of stage s, whose
-// slot is free for stage s + RING.
+// What bounds it: LDS traffic next to the MFMAs.  The 128 x 128 elements of a wave at WMT = WNT = 4 need
+// 16 KiB of fragments per 32 k; eight waves of 128 x 64 need 24 KiB each pair, and with the copies' writes
+// LDS was then as busy as the MFMA pipes.  The 256 accumulator registers leave room for one wave per SIMD,
+// so nothing but this wave's own instruction order hides a latency.  A stage runs in two phases, the left
+// and the right half of the wave's columns.  Each fragment register is read again as soon as its last MFMA
+// of the stage is issued, at least 28 MFMAs (of 64) ahead of its next use: B's right half in the first
+// phase, A and B's left half (of the next stage) in the second.  The copies go out one at a time between
+// the MFMAs.  Stages of 32 k keep four slots in LDS, so a copy has two to three stages to land.  One barrier
+// per stage, between the phases: there stage s + 1 has landed and every wave has read all of stage s,
+// whose slot is free for stage s + RING.
 //
-// Measured: 1030-1270 TFLOP/s (8192^3 in the three forms: 1240, 1267, 1136).  The same loop without its
-// copies reaches 1300-1500, with every copy a hit in L2 1060-1220, with three or five slots the same as
-// with four: the copies' throughput into LDS next to the fragment reads is what is left, not their
-// latency.  Operands packed into MFMA fragments first (contiguous KiB per copy) gave the loop 5-10% and
-// cost 8-15% of an operation in packing.
+// The 16 x 16 x 32 MFMA moves half as many accumulator registers per product as the 32 x 32 x 16 one and
+// leaves the fragments in the registers they were read into for a whole stage (64 instead of 128
+// registers): 8192^3, X W^T 889 -> 832 us, dY W 872 -> 818, dY^T X 961 -> 867.
+//
+// Measured: 1030-1340 TFLOP/s.  With the 32 x 32 x 16 MFMA 8192^3 ran at 1237 TFLOP/s, the same loop without
+// its copies at 1497, with every copy a hit in L2 at 1217, with three or five slots as with four: the
+// copies' throughput into LDS next to the fragment reads is what is left, not their latency.  Operands
+// packed into MFMA fragments first (contiguous KiB per copy) gave the loop 5-10% and cost 8-15% of an
+// operation in packing.
 //
 // The MFMAs are issued through inline assembly so that the accumulators stay in accumulation registers
 // for the whole loop (with the builtin the allocator moved tiles between the two register files).
-#define TW_MFMA(d, x, y) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(x), "v"(y))
+// (B's fragment is the first operand: a lane then holds four consecutive columns of one row of C.)
+#define TW_MFMA(d, x, y) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(y), "v"(x))
 template <bool TA, bool TB, bool OUT_F32, bool ACCUM, int WMT, int WNT>
 __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand B, int K, void* __restrict__ Cout, int64_t ldc,
                                                               int M, int N, int tiles_n, int tiles_total, int splits, int split_stages)
 {
     constexpr unsigned STAGE = (WMT + WNT) * PANEL;      // bytes of a slot: A's panels, then B's
+    constexpr int MI = 2 * WMT, NI = 2 * WNT, NH = NI / 2;  // accumulator tiles of a wave; NH: columns of a phase
     constexpr int NC = WMT + WNT;                        // copies of a wave per stage
     constexpr int NC0 = (NC + 1) / 2;                    // .. of which in the first of the two k-steps that issue them
     static_assert(NWAVE == 4, "a wave copies a quarter of every panel");
@@ -208,25 +213,29 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand 
     const unsigned ring0 = fpdt::lds_address(ring);
     Side<TA, WMT> a_side;
     Side<TB, WNT> b_side;
-    a_side.init(A, tile_m * (64 * WMT), stage0, wu, wm * WMT, lane, ring0);
-    b_side.init(B, tile_n * (64 * WNT), stage0, wu, wn * WNT, lane, ring0 + WMT * PANEL);
+    a_side.init(A, tile_m * (64 * WMT), stage0, wu, wm * MI, lane, ring0);
+    b_side.init(B, tile_n * (64 * WNT), stage0, wu, wn * NI, lane, ring0 + WMT * PANEL);
     const unsigned copy_lds = ring0 + 1024u * (unsigned)wu;
-    // copy j of the stage `t` stages behind the current one
-    auto copy = [&](int j, int t, unsigned slot) {
-        const unsigned dst = copy_lds + slot * STAGE + PANEL * (unsigned)j;
-        if (j < WMT) fpdt::frag_to_lds_at(a_side.pos + a_side.rel[j % WMT] + (uint64_t)((int64_t)t * (int64_t)a_side.step), dst, (int)a_side.off[j % WMT]);
-        else fpdt::frag_to_lds_at(b_side.pos + b_side.rel[(j - WMT) % WNT] + (uint64_t)((int64_t)t * (int64_t)b_side.step), dst, (int)b_side.off[(j - WMT) % WNT]);
+    // Copy j of the stage at a_at / b_at into the slot at LDS byte `slot_lds`: one scalar instruction besides
+    // the copy.  (m0 is written one wait state ahead of the copy that uses it; the address registers come
+    // from scalar arithmetic, see copy_address_rule in mfma_tiles.h.)
+    auto copy = [&](int j, uint64_t a_at, uint64_t b_at, unsigned slot_lds) {
+        asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3"
+                     :
+                     : "s"(slot_lds), "i"(PANEL * j), "v"(j < WMT ? a_side.off[j % WMT] : b_side.off[(j - WMT) % WNT]), "s"(j < WMT ? a_at : b_at)
+                     : "memory", "scc");
     };
+    auto stage_at = [&](uint64_t pos, int t, uint64_t step) { return pos + (uint64_t)((int64_t)t * (int64_t)step); };  // t stages behind pos
     if (tail) {  // its pieces pass through registers, zero behind K, into the slot behind the ring
         u32x4 v[NC];
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
             v[j] = u32x4{0, 0, 0, 0};
             if (j < WMT) {
-                const uint64_t src = a_side.pos + a_side.rel[j % WMT] + (uint64_t)n_full * a_side.step + a_side.off[j % WMT];
+                const uint64_t src = a_side.pos + (uint64_t)n_full * a_side.step + a_side.off[j % WMT];
                 if (a_side.has(stages, K, wu, lane)) v[j] = *reinterpret_cast<const u32x4*>((uintptr_t)src);
             } else {
-                const uint64_t src = b_side.pos + b_side.rel[(j - WMT) % WNT] + (uint64_t)n_full * b_side.step + b_side.off[(j - WMT) % WNT];
+                const uint64_t src = b_side.pos + (uint64_t)n_full * b_side.step + b_side.off[(j - WMT) % WNT];
                 if (b_side.has(stages, K, wu, lane)) v[j] = *reinterpret_cast<const u32x4*>((uintptr_t)src);
             }
         }
@@ -234,17 +243,14 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand 
         for (int j = 0; j < NC; ++j) ring[(RING * STAGE + PANEL * j + 1024u * wu) / 16 + lane] = v[j];
     }
 
-    floatx16 acc[WMT][WNT];
+    floatx4 acc[MI][NI];
 #pragma unroll
-    for (int i = 0; i < WMT; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < WNT; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-#pragma unroll
-    for (int i = 0; i < WMT; ++i)
-#pragma unroll
-        for (int j = 0; j < WNT; ++j) asm volatile("" : "+a"(acc[i][j]));
+        for (int j = 0; j < NI; ++j) {
+            acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+            asm volatile("" : "+a"(acc[i][j]));
+        }
 
     // Stages 0 .. RING - 2 whole and the first copies of stage RING - 1.  A copy behind the last whole
     // stage fetches that stage again, into a slot that nobody reads any more: the loop then needs no
@@ -253,17 +259,18 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand 
 #pragma unroll
     for (int t = 0; t < RING; ++t)
 #pragma unroll
-        for (int j = 0; j < (t < RING - 1 ? NC : NC0); ++j) copy(j, ahead(t, n_full), (unsigned)t);
+        for (int j = 0; j < (t < RING - 1 ? NC : NC0); ++j)
+            fpdt::frag_to_lds_at(j < WMT ? stage_at(a_side.pos, ahead(t, n_full), a_side.step) : stage_at(b_side.pos, ahead(t, n_full), b_side.step),
+                                 copy_lds + (unsigned)t * STAGE + PANEL * (unsigned)j,
+                                 (int)(j < WMT ? a_side.off[j % WMT] : b_side.off[(j - WMT) % WNT]));
     fpdt::wait_vmem_at_most<(RING - 2) * NC + NC0>();
     fpdt::barrier_no_fence();
 
-    bf16x8 a[2][WMT], b[2][WNT];
-    auto read = [&](int set, int i, unsigned slot) {  // fragment i of the set, b first: the order of use
-        if (i < WNT) b[set][i % WNT] = b_side.frag(i, set, slot);
-        else a[set][(i - WNT) % WMT] = a_side.frag(i - WNT, set, slot);
-    };
+    bf16x8 a[MI], b[NI];
 #pragma unroll
-    for (int i = 0; i < NC; ++i) read(0, i, 0u);
+    for (int j = 0; j < NH; ++j) b[j] = b_side.frag(j, 0u);
+#pragma unroll
+    for (int i = 0; i < MI; ++i) a[i] = a_side.frag(i, 0u);
 
     // the sides' pos is at the current stage, which is in slot `cur`
     unsigned cur = 0;
@@ -271,16 +278,17 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand 
     do {
         const int full = tail ? left - 1 : left;  // (0 in the tail stage: its copies fetch the stage before it)
         const unsigned nxt = tail && left == 2 ? RING : (cur + 1) % RING, prv = (cur + RING - 1) % RING;
-        const int ahead_prv = ahead(RING - 1, full), ahead_cur = ahead(RING, full);
-        // reads in the first half of a k-step (they are waited for at its end), copies all over it
-        constexpr int NM = WMT * WNT, NH = NM / 2;
+        const int t_prv = ahead(RING - 1, full), t_cur = ahead(RING, full);
+        const uint64_t a_prv = stage_at(a_side.pos, t_prv, a_side.step), b_prv = stage_at(b_side.pos, t_prv, b_side.step);
+        const uint64_t a_cur = stage_at(a_side.pos, t_cur, a_side.step), b_cur = stage_at(b_side.pos, t_cur, b_side.step);
+        const unsigned lds_prv = copy_lds + prv * STAGE, lds_cur = copy_lds + cur * STAGE;
+        constexpr int NM = MI * NH;  // MFMAs of a phase
 #pragma unroll
         for (int m = 0; m < NM; ++m) {
-            TW_MFMA(acc[m / WNT][m % WNT], a[0][m / WNT], b[0][m % WNT]);
+            TW_MFMA(acc[m / NH][m % NH], a[m / NH], b[m % NH]);
+            if (m < NH) b[NH + m] = b_side.frag(NH + m, cur * STAGE);
 #pragma unroll
-            for (int q = m * NC / NH; q < (m + 1) * NC / NH && q < NC; ++q) read(1, q, cur * STAGE);
-#pragma unroll
-            for (int q = m * (NC - NC0) / NM; q < (m + 1) * (NC - NC0) / NM; ++q) copy(NC0 + q, ahead_prv, prv);  // the rest of stage s + RING - 1
+            for (int q = m * (NC - NC0) / NM; q < (m + 1) * (NC - NC0) / NM; ++q) copy(NC0 + q, a_prv, b_prv, lds_prv);  // the rest of stage s + RING - 1
             __builtin_amdgcn_sched_barrier(0);
         }
         fpdt::wait_vmem_at_most<(RING - 2) * NC>();
@@ -288,66 +296,90 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand 
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int m = 0; m < NM; ++m) {
-            TW_MFMA(acc[m / WNT][m % WNT], a[1][m / WNT], b[1][m % WNT]);
+            TW_MFMA(acc[m / NH][NH + m % NH], a[m / NH], b[NH + m % NH]);
+            if (m < NH) b[m] = b_side.frag(m, nxt * STAGE);
+            if (m % NH == NH - 1) a[m / NH] = a_side.frag(m / NH, nxt * STAGE);
 #pragma unroll
-            for (int q = m * NC / NH; q < (m + 1) * NC / NH && q < NC; ++q) read(0, q, nxt * STAGE);
-#pragma unroll
-            for (int q = m * NC0 / NM; q < (m + 1) * NC0 / NM; ++q) copy(q, ahead_cur, cur);  // stage s + RING
+            for (int q = m * NC0 / NM; q < (m + 1) * NC0 / NM; ++q) copy(q, a_cur, b_cur, lds_cur);  // stage s + RING
             __builtin_amdgcn_sched_barrier(0);
         }
         a_side.pos += a_side.step;
         b_side.pos += b_side.step;
         cur = nxt;
     } while (--left > 0);
-    fpdt::wait_vmem_at_most<0>();  // nothing may still be on its way into LDS when the workgroup ends
+    fpdt::wait_vmem_at_most<0>();  // nothing may still be on its way into LDS when the ring is used again or the workgroup ends
+    fpdt::barrier_no_fence();
 
     // the accumulators are read by ordinary instructions from here on
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-    // accumulator tile (i, j): lane l holds column l % 32, register r row 8 (r / 4) + 4 (l / 32) + r % 4.
-    // With ACCUM the old values of two tiles are all requested, and those of the next two in front
-    // of their stores: one load at a time, each waited for behind the store before it, left the
-    // read-modify-write of a weight gradient at a sixth of the memory rate.
-    const int col = lane & 31, half = lane >> 5;
-    const int m0 = tile_m * (64 * WMT) + wm * (32 * WMT) + 4 * half, n0 = tile_n * (64 * WNT) + wn * (32 * WNT) + col;
+    // accumulator tile (i, j): lane l holds row l % 16, columns 4 (l / 16) .. + 3
+    const int mw = tile_m * (64 * WMT) + wm * (32 * WMT), nw = tile_n * (64 * WNT) + wn * (32 * WNT);  // the wave's first row and column
     typedef typename std::conditional<OUT_F32, float, uint16_t>::type out_t;
+    typedef out_t out4 __attribute__((ext_vector_type(4)));
     // (splits > 1: fp32, this split's sums)
-    out_t* c0 = static_cast<out_t*>(Cout) + (size_t)split * (splits > 1 ? (size_t)M * N : 0) + (size_t)m0 * ldc + n0;
-    auto epilogue = [&](auto inside_tag) {  // INSIDE: no element of the tile lies behind C
-        constexpr bool INSIDE = decltype(inside_tag)::value;
-        auto row = [&](int i, int r) { return 32 * i + 8 * (r >> 2) + (r & 3); };
-        auto in = [&](int i, int j, int r) { return INSIDE || (m0 + row(i, r) < M && n0 + 32 * j < N); };
-        constexpr int NU = WMT * WNT / 2;  // units of two tiles side by side
-        out_t old[2][2][16];
-        auto request = [&](int u) {
+    out_t* out = static_cast<out_t*>(Cout) + (size_t)split * (splits > 1 ? (size_t)M * N : 0);
+    auto sum = [&](float v, out_t old) -> out_t {
+        if constexpr (OUT_F32) return ACCUM ? old + v : v;
+        else return to_bf16(ACCUM ? from_bf16(old) + v : v);
+    };
+    const bool inside = (tile_m + 1) * (64 * WMT) <= M && (tile_n + 1) * (64 * WNT) <= N;
+    if (inside && ldc % 4 == 0 && reinterpret_cast<uintptr_t>(Cout) % sizeof(out4) == 0 && (splits == 1 || (size_t)M * N % 4 == 0)) {
+        // Sixteen rows at a time pass through LDS (each wave its own part of the idle ring), so that a store
+        // covers 128 WNT bytes of a row in fp32.  With ACCUM the old values of sixteen rows are all
+        // requested, and those of the next sixteen in front of their stores: one load at a time, each
+        // waited for behind the store before it, left the read-modify-write of a weight gradient at a sixth
+        // of the memory rate.
+        constexpr int LPR = 8 * WNT, RPI = 64 / LPR, PITCH = 32 * WNT + 4;  // lanes per row, rows per access, floats (4 apart: no bank conflicts)
+        static_assert(4 * 16 * PITCH * 4 <= (RING + 1) * (int)STAGE, "the ring holds sixteen rows of every wave");
+        float* rows = reinterpret_cast<float*>(ring) + wu * (16 * PITCH);
+        float* put = rows + (lane & 15) * PITCH + 4 * (lane >> 4);
+        const float* get = rows + (lane / LPR) * PITCH + 4 * (lane % LPR);
+        out_t* c0 = out + (size_t)(mw + lane / LPR) * ldc + nw + 4 * (lane % LPR);
+        out4 old[2][NI];
+        auto request = [&](int i) {
 #pragma unroll
-            for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int i = 2 * u / WNT, j = 2 * u % WNT + jj;
-                    old[u & 1][jj][r] = 0;
-                    if (in(i, j, r)) old[u & 1][jj][r] = c0[(size_t)row(i, r) * ldc + 32 * j];
-                }
+            for (int k = 0; k < NI; ++k) old[i & 1][k] = *reinterpret_cast<const out4*>(c0 + (size_t)(16 * i + RPI * k) * ldc);
         };
         if (ACCUM) request(0);
 #pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            if (ACCUM && u + 1 < NU) request(u + 1);
+        for (int i = 0; i < MI; ++i) {
+            if (ACCUM && i + 1 < MI) request(i + 1);
             __builtin_amdgcn_sched_barrier(0);  // no further ahead: the registers are spoken for
 #pragma unroll
-            for (int jj = 0; jj < 2; ++jj)
+            for (int j = 0; j < NI; ++j) {
+                asm volatile("" : "+a"(acc[i][j]));  // stays in its accumulation registers until here
+                *reinterpret_cast<floatx4*>(put + 16 * j) = acc[i][j];
+            }
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int i = 2 * u / WNT, j = 2 * u % WNT + jj;
-                    if (in(i, j, r)) {
-                        const float v = acc[i][j][r];
-                        if constexpr (OUT_F32) c0[(size_t)row(i, r) * ldc + 32 * j] = ACCUM ? old[u & 1][jj][r] + v : v;
-                        else c0[(size_t)row(i, r) * ldc + 32 * j] = to_bf16(ACCUM ? from_bf16(old[u & 1][jj][r]) + v : v);
-                    }
-                }
+            for (int k = 0; k < NI; ++k) {
+                const floatx4 x = *reinterpret_cast<const floatx4*>(get + RPI * k * PITCH);
+                out4 v;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = sum(x[r], ACCUM ? old[i & 1][k][r] : out_t(0));
+                *reinterpret_cast<out4*>(c0 + (size_t)(16 * i + RPI * k) * ldc) = v;
+            }
+            __builtin_amdgcn_wave_barrier();
         }
-    };
-    if ((tile_m + 1) * (64 * WMT) <= M && (tile_n + 1) * (64 * WNT) <= N) epilogue(std::true_type{});
-    else epilogue(std::false_type{});
+        return;
+    }
+    const int m0 = mw + (lane & 15), n0 = nw + 4 * (lane >> 4);
+    out_t* c0 = out + (size_t)m0 * ldc + n0;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            asm volatile("" : "+a"(acc[i][j]));
+            if (m0 + 16 * i >= M) continue;
+            out_t* c = c0 + (size_t)(16 * i) * ldc + 16 * j;
+            out_t old[4] = {};
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (ACCUM && n0 + 16 * j + r < N) old[r] = c[r];
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (n0 + 16 * j + r < N) c[r] = sum(acc[i][j][r], old[r]);
+        }
 }
 
 // C (+)= the splits' sums, part [splits][M * N] fp32; V consecutive elements of C per thread (V divides N,
@@ -447,6 +479,8 @@ int pool_take(Pool& p, size_t bytes, char** out)
     return 0;
 }
 
+constexpr int64_t MAX_PITCH = (int64_t)1 << 23;  // of rows along k
+
 // X [R, C], leading dimension ld, as the product kernel can read it: in place, or copied.  `k_rows`: the
 // contraction runs over the rows of X.  `padded`: rows are followed by zeros up to a multiple of 8.
 int take_operand(Pool& pool, const void* X, int64_t R, int64_t C, int64_t ld, bool k_rows, bool padded, bool cache, hipStream_t st, Operand* res)
@@ -473,8 +507,9 @@ int take_operand(Pool& pool, const void* X, int64_t R, int64_t C, int64_t ld, bo
             if (cache) g_cache.push_back({X, R, C, ld, R2, C2, res->p});
         }
     }
-    // a lane's offset from its quarter panel (15 rows of form N, 7 of form T) is kept in 32 bits
-    return res->ld >= (int64_t)1 << 27 ? 2 : 0;
+    // a lane's offset within its tile (255 rows of form N, 7 of form T) is kept in 32 bits; product() sees
+    // to it for form N
+    return res->ld >= (k_rows ? (int64_t)1 << 28 : MAX_PITCH) ? 2 : 0;
 }
 
 }  // namespace
@@ -497,14 +532,26 @@ void* scratch(size_t bytes)
     return pool_take(g_pool[dev], bytes, &mem) ? nullptr : mem;
 }
 
-int gemm(int a_transposed, int b_transposed, int M, int N, int K, const void* A, int64_t lda, const void* B,
-         int64_t ldb, void* C, int64_t ldc, bool c_f32, bool accumulate, bool cache_b, hipStream_t st)
+static void split_sum(const float* part, int splits, int64_t M, int N, void* C, int64_t ldc, bool c_f32, bool accumulate, hipStream_t st)
 {
-    std::lock_guard<std::mutex> lk(g_mu);
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 1;
-    Pool& pool = g_pool[dev];
-    if (M <= 0 || N <= 0 || K <= 0) return 2;
+    const int64_t MN = M * N;
+    const bool v4 = N % 4 == 0 && ldc % 4 == 0 && reinterpret_cast<uintptr_t>(C) % (c_f32 ? 16 : 8) == 0;
+    const unsigned blocks = (unsigned)((MN / (v4 ? 4 : 1) + 255) / 256);
+#define TW_SUM(F32, ACC)                                                                             \
+    do {                                                                                             \
+        if (v4) tw_split_sum_kernel<F32, ACC, 4><<<blocks, 256, 0, st>>>(part, splits, MN, N, C, ldc); \
+        else tw_split_sum_kernel<F32, ACC, 1><<<blocks, 256, 0, st>>>(part, splits, MN, N, C, ldc);    \
+    } while (0)
+    if (c_f32 && accumulate) TW_SUM(true, true);
+    else if (c_f32) TW_SUM(true, false);
+    else if (accumulate) TW_SUM(false, true);
+    else TW_SUM(false, false);
+#undef TW_SUM
+}
+
+static int product(Pool& pool, int a_transposed, int b_transposed, int M, int N, int K, const void* A, int64_t lda, const void* B,
+                   int64_t ldb, void* C, int64_t ldc, bool c_f32, bool accumulate, bool cache_b, hipStream_t st)
+{
     const char* base0 = pool.base;
     const size_t off0 = pool.off;
     const int Kp = K < SK ? SK : K;  // (realigned operands of less are padded to one stage)
@@ -557,27 +604,54 @@ int gemm(int a_transposed, int b_transposed, int M, int N, int K, const void* A,
     }
 #undef TW_LAUNCH
 #undef TW_LAUNCH_TILE
-    if (plan.splits > 1) {
-        const int64_t MN = (int64_t)M * N;
-        const bool v4 = N % 4 == 0 && ldc % 4 == 0 && reinterpret_cast<uintptr_t>(C) % (c_f32 ? 16 : 8) == 0;
-        const unsigned blocks = (unsigned)((MN / (v4 ? 4 : 1) + 255) / 256);
-        const float* part = static_cast<const float*>(out);
-#define TW_SUM(F32, ACC)                                                                                  \
-    do {                                                                                                  \
-        if (v4) tw_split_sum_kernel<F32, ACC, 4><<<blocks, 256, 0, st>>>(part, plan.splits, MN, N, C, ldc); \
-        else tw_split_sum_kernel<F32, ACC, 1><<<blocks, 256, 0, st>>>(part, plan.splits, MN, N, C, ldc);    \
-    } while (0)
-        if (c_f32 && accumulate) TW_SUM(true, true);
-        else if (c_f32) TW_SUM(true, false);
-        else if (accumulate) TW_SUM(false, true);
-        else TW_SUM(false, false);
-#undef TW_SUM
-    }
+    if (plan.splits > 1) split_sum(static_cast<const float*>(out), plan.splits, M, N, C, ldc, c_f32, accumulate, st);
     // The next product's copies run after this launch on the same stream, so this product's scratch
     // is free again: everything it took, or everything behind a weight that stays cached.  (Not if
     // the pool was replaced by a larger one on the way: then nothing is given back until the next
     // library call.)
     if (pool.base == base0) pool.off = cache_b ? mark : off0;
+    return hipGetLastError() == hipSuccess ? 0 : 1;
+}
+
+int gemm(int a_transposed, int b_transposed, int M, int N, int K, const void* A, int64_t lda, const void* B,
+         int64_t ldb, void* C, int64_t ldc, bool c_f32, bool accumulate, bool cache_b, hipStream_t st)
+{
+    std::lock_guard<std::mutex> lk(g_mu);
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 1;
+    Pool& pool = g_pool[dev];
+    if (M <= 0 || N <= 0 || K <= 0) return 2;
+    const bool long_a = !a_transposed && lda >= MAX_PITCH, long_b = !b_transposed && ldb >= MAX_PITCH;
+    if (!long_a && !long_b)
+        return product(pool, a_transposed, b_transposed, M, N, K, A, lda, B, ldb, C, ldc, c_f32, accumulate, cache_b, st);
+    // Rows too long for the kernel's offsets: k in segments, the long operand's copied out one at a time,
+    // the fp32 sums of the segments added at the end as those of splits are.
+    constexpr int64_t SEG = (int64_t)1 << 22;
+    const int segs = (int)((K + SEG - 1) / SEG);
+    char* part = nullptr;
+    if (pool_take(pool, (size_t)segs * M * N * 4, &part)) return 1;
+    for (int i = 0; i < segs; ++i) {
+        const int64_t k0 = i * SEG, k = K - k0 < SEG ? K - k0 : SEG, k8 = (k + 7) / 8 * 8;
+        const char* base0 = pool.base;
+        const size_t off0 = pool.off;
+        const uint16_t *a = static_cast<const uint16_t*>(A) + (a_transposed ? k0 * lda : k0), *b = static_cast<const uint16_t*>(B) + (b_transposed ? k0 * ldb : k0);
+        int64_t la = lda, lb = ldb;
+        for (int side = 0; side < 2; ++side) {
+            if (!(side ? long_b : long_a)) continue;
+            const int64_t rows = side ? N : M;
+            char* mem = nullptr;
+            if (pool_take(pool, (size_t)rows * k8 * 2, &mem)) return 1;
+            const int64_t blocks = (rows * (k8 / 8) + 255) / 256;
+            tw_realign_kernel<<<dim3((unsigned)(blocks < 65536 ? blocks : 65536)), 256, 0, st>>>(side ? b : a, rows, k, side ? ldb : lda,
+                                                                                              reinterpret_cast<u32x4*>(mem), rows, k8);
+            (side ? b : a) = reinterpret_cast<const uint16_t*>(mem);
+            (side ? lb : la) = k8;
+        }
+        const int rc = product(pool, a_transposed, b_transposed, M, N, (int)k, a, la, b, lb, part + (size_t)i * M * N * 4, N, true, false, false, st);
+        if (rc) return rc;
+        if (pool.base == base0) pool.off = off0;
+    }
+    split_sum(reinterpret_cast<const float*>(part), segs, M, N, C, ldc, c_f32, accumulate, st);
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 

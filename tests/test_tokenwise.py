@@ -441,3 +441,19 @@ def test_gpu_linear_tile_edges(rows, n_in, n_out, n_chunks, offset):
     _rowwise_ok("Y", f64(Y), ref["Y"], rel=1e-4)
     _rowwise_ok("dX", f64(dX), ref["dX"], rel=1e-4)
     np.testing.assert_allclose(f64(dW), 1 + ref["dW"], atol=1e-4 * max(1.0, float(np.abs(ref["dW"]).max())))
+
+
+@pytest.mark.gpu
+def test_gpu_linear_rows_of_eight_million():
+    """Rows longer than the product kernel's 32-bit offsets: the contraction runs in segments.  2^23 + 40 terms
+    of exact products, summed in fp32 over segments of 2^22: about sqrt(2^22 / 32) 2^-24 = 2e-5 of the rms."""
+    n_in, n_out, rows = (1 << 23) + 40, 8, 9
+    print("[case] linear long rows", rows, n_in, n_out, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    X = torch.randn(rows, n_in, device="cuda", generator=g).to(torch.bfloat16)
+    W = (torch.randn(n_out, n_in, device="cuda", generator=g) * n_in ** -0.5).to(torch.bfloat16)
+    Y = torch.empty(rows, n_out, dtype=torch.bfloat16, device="cuda")
+    TW.fpdt_tw_linear_fwd(X, W, Y, 1)
+    torch.cuda.synchronize()
+    ref = (X.double() @ W.double().t()).cpu().numpy()
+    _rowwise_ok("Y", Y.double().cpu().numpy(), ref, rel=4e-4)
