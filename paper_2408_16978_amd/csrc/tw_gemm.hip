@@ -60,6 +60,18 @@ __device__ __forceinline__ uint16_t to_bf16(float f)
 }
 __device__ __forceinline__ float from_bf16(uint16_t b) { return __uint_as_float((unsigned)b << 16); }
 
+// Sum in fp32, stored as fp32 or bf16
+template <bool ACC>
+__device__ __forceinline__ float combine(float v, float old) { return ACC ? old + v : v; }
+template <bool ACC>
+__device__ __forceinline__ uint16_t combine(float v, uint16_t old) { return to_bf16(ACC ? from_bf16(old) + v : v); }
+
+// The work of a product: the first `whole` of its tiles over all of k, the others divided into `splits`
+// ranges of `split_stages` stages (the last one may be shorter).
+struct Units {
+    int tiles, tiles_n, whole, splits, split_stages;
+};
+
 // One operand as stored: row r at p + r * ld, 16-byte aligned, ld a multiple of 8.  Form N: rows are the
 // product's rows, columns its k.  Form T: rows are k, columns the product's rows.  `rows` counts the
 // product's rows (form T: rounded up to 8, in bounds).
@@ -178,7 +190,7 @@ struct Side {
 #define TW_MFMA(d, x, y) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(y), "v"(x))
 template <bool TA, bool TB, bool OUT_F32, bool ACCUM, int WMT, int WNT>
 __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand B, int K, void* __restrict__ Cout, int64_t ldc,
-                                                              int M, int N, int tiles_n, int tiles_total, int splits, int split_stages)
+                                                              int M, int N, Units u, float* __restrict__ part)
 {
     constexpr unsigned STAGE = (WMT + WNT) * PANEL;      // bytes of a slot: A's panels, then B's
     constexpr int MI = 2 * WMT, NI = 2 * WNT, NH = NI / 2;  // accumulator tiles of a wave; NH: columns of a phase
@@ -187,18 +199,29 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand 
     static_assert(NWAVE == 4, "a wave copies a quarter of every panel");
     __shared__ __attribute__((aligned(256))) u32x4 ring[(RING + 1) * STAGE / 16];
     // Consecutive workgroup ids land on different XCDs (each with its own L2): give every XCD a
-    // contiguous run of tiles, so that the tiles that share an operand row share an L2.
-    const unsigned work_total = (unsigned)tiles_total * (unsigned)splits;
-    const unsigned per_xcd = (work_total + 7) / 8;
-    const unsigned wid = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-    if (blockIdx.x / 8 >= per_xcd || wid >= work_total) return;  // whole workgroup, before any barrier
-    const unsigned split = wid / (unsigned)tiles_total, id = wid % (unsigned)tiles_total;
+    // contiguous run of tiles, so that the tiles that share an operand row share an L2.  The units of the
+    // divided tiles go half in front of the whole tiles and half behind them: the compute units that
+    // start with one are out of step with the others from then on, and the epilogues of the ones run under
+    // the MFMAs of the others.
+    const unsigned xcd = blockIdx.x % 8, turn = blockIdx.x / 8;
+    const unsigned divided = (unsigned)(u.tiles - u.whole), parts = divided * (unsigned)u.splits;
+    const unsigned whole_run = ((unsigned)u.whole + 7) / 8, part_run = (parts + 7) / 8, lead = part_run / 2;
+    const bool is_part = turn < lead || turn >= lead + whole_run;
+    unsigned id = xcd * whole_run + turn - lead, split = 0;
+    if (is_part) {
+        const unsigned i = turn < lead ? turn : turn - whole_run, unit = xcd * part_run + i;
+        if (i >= part_run || unit >= parts) return;  // whole workgroup, before any barrier
+        id = (unsigned)u.whole + unit % divided;
+        split = unit / divided;
+    } else if (id >= (unsigned)u.whole) {
+        return;
+    }
     // Within a run the tiles go in groups of four tile rows, row index fastest: the 32 workgroups
     // that an XCD runs at a time then cover about 4 x 8 tiles and share 4 + 8 operand slices in its
     // L2 instead of 1 + 32.
     constexpr unsigned GROUP_M = 4;
-    const unsigned tiles_m = (unsigned)tiles_total / (unsigned)tiles_n;
-    const unsigned grp = id / (GROUP_M * (unsigned)tiles_n), in_grp = id % (GROUP_M * (unsigned)tiles_n);
+    const unsigned tiles_n = (unsigned)u.tiles_n, tiles_m = (unsigned)u.tiles / tiles_n;
+    const unsigned grp = id / (GROUP_M * tiles_n), in_grp = id % (GROUP_M * tiles_n);
     const unsigned rows_in_grp = tiles_m - grp * GROUP_M < GROUP_M ? tiles_m - grp * GROUP_M : GROUP_M;
     const int tile_m = (int)(grp * GROUP_M + in_grp % rows_in_grp), tile_n = (int)(in_grp / rows_in_grp);
 
@@ -206,8 +229,8 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand 
     const int wu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wu >> 1, wn = wu & 1;
     const int stages = K / SK;  // whole ones, >= 1 in every split (host)
-    const int stage0 = (int)split * split_stages;
-    const int n_full = stages - stage0 < split_stages ? stages - stage0 : split_stages;
+    const int unit_stages = is_part ? u.split_stages : stages, stage0 = (int)split * unit_stages;
+    const int n_full = stages - stage0 < unit_stages ? stages - stage0 : unit_stages;
     const bool tail = K % SK != 0 && stage0 + n_full == stages;  // the last split's stage of less than SK
 
     const unsigned ring0 = fpdt::lds_address(ring);
@@ -216,12 +239,12 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand 
     a_side.init(A, tile_m * (64 * WMT), stage0, wu, wm * MI, lane, ring0);
     b_side.init(B, tile_n * (64 * WNT), stage0, wu, wn * NI, lane, ring0 + WMT * PANEL);
     const unsigned copy_lds = ring0 + 1024u * (unsigned)wu;
-    // Copy j of the stage at a_at / b_at into the slot at LDS byte `slot_lds`: one scalar instruction besides
-    // the copy.  (m0 is written one wait state ahead of the copy that uses it; the address registers come
-    // from scalar arithmetic, see copy_address_rule in mfma_tiles.h.)
+    // Copy j of the stage at a_at / b_at into the slot at LDS byte `slot_lds`: two scalar instructions besides
+    // the copy, the second one for copy_address_rule (mfma_tiles.h) and as m0's wait state.
     auto copy = [&](int j, uint64_t a_at, uint64_t b_at, unsigned slot_lds) {
-        asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3"
-                     :
+        uint64_t addr;
+        asm volatile("s_add_u32 m0, %1, %2\n\ts_mov_b64 %0, %4\n\tglobal_load_lds_dwordx4 %3, %0"
+                     : "=&s"(addr)
                      : "s"(slot_lds), "i"(PANEL * j), "v"(j < WMT ? a_side.off[j % WMT] : b_side.off[(j - WMT) % WNT]), "s"(j < WMT ? a_at : b_at)
                      : "memory", "scc");
     };
@@ -313,37 +336,30 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand 
     // the accumulators are read by ordinary instructions from here on
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
     // accumulator tile (i, j): lane l holds row l % 16, columns 4 (l / 16) .. + 3
-    const int mw = tile_m * (64 * WMT) + wm * (32 * WMT), nw = tile_n * (64 * WNT) + wn * (32 * WNT);  // the wave's first row and column
-    typedef typename std::conditional<OUT_F32, float, uint16_t>::type out_t;
-    typedef out_t out4 __attribute__((ext_vector_type(4)));
-    // (splits > 1: fp32, this split's sums)
-    out_t* out = static_cast<out_t*>(Cout) + (size_t)split * (splits > 1 ? (size_t)M * N : 0);
-    auto sum = [&](float v, out_t old) -> out_t {
-        if constexpr (OUT_F32) return ACCUM ? old + v : v;
-        else return to_bf16(ACCUM ? from_bf16(old) + v : v);
-    };
-    const bool inside = (tile_m + 1) * (64 * WMT) <= M && (tile_n + 1) * (64 * WNT) <= N;
-    if (inside && ldc % 4 == 0 && reinterpret_cast<uintptr_t>(Cout) % sizeof(out4) == 0 && (splits == 1 || (size_t)M * N % 4 == 0)) {
-        // Sixteen rows at a time pass through LDS (each wave its own part of the idle ring), so that a store
-        // covers 128 WNT bytes of a row in fp32.  With ACCUM the old values of sixteen rows are all
-        // requested, and those of the next sixteen in front of their stores: one load at a time, each
-        // waited for behind the store before it, left the read-modify-write of a weight gradient at a sixth
-        // of the memory rate.
+    const int mw = wm * (32 * WMT), nw = wn * (32 * WNT);  // the wave's first row and column within the tile
+    // Sixteen rows at a time pass through LDS (each wave its own part of the idle ring), so that a store
+    // covers 128 WNT bytes of a row in fp32.  With ACC the old values of sixteen rows are all requested, and
+    // those of the next sixteen in front of their stores: one load at a time, each waited for behind the
+    // store before it, left the read-modify-write of a weight gradient at a sixth of the memory rate.
+    auto store_tile = [&](auto* out, int64_t pitch, auto acc_tag) {
+        constexpr bool ACC = decltype(acc_tag)::value;
+        typedef std::remove_pointer_t<decltype(out)> out_t;
+        typedef out_t out4 __attribute__((ext_vector_type(4)));
         constexpr int LPR = 8 * WNT, RPI = 64 / LPR, PITCH = 32 * WNT + 4;  // lanes per row, rows per access, floats (4 apart: no bank conflicts)
         static_assert(4 * 16 * PITCH * 4 <= (RING + 1) * (int)STAGE, "the ring holds sixteen rows of every wave");
         float* rows = reinterpret_cast<float*>(ring) + wu * (16 * PITCH);
         float* put = rows + (lane & 15) * PITCH + 4 * (lane >> 4);
         const float* get = rows + (lane / LPR) * PITCH + 4 * (lane % LPR);
-        out_t* c0 = out + (size_t)(mw + lane / LPR) * ldc + nw + 4 * (lane % LPR);
+        out_t* c0 = out + (size_t)(mw + lane / LPR) * pitch + nw + 4 * (lane % LPR);
         out4 old[2][NI];
         auto request = [&](int i) {
 #pragma unroll
-            for (int k = 0; k < NI; ++k) old[i & 1][k] = *reinterpret_cast<const out4*>(c0 + (size_t)(16 * i + RPI * k) * ldc);
+            for (int k = 0; k < NI; ++k) old[i & 1][k] = *reinterpret_cast<const out4*>(c0 + (size_t)(16 * i + RPI * k) * pitch);
         };
-        if (ACCUM) request(0);
+        if (ACC) request(0);
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
-            if (ACCUM && i + 1 < MI) request(i + 1);
+            if (ACC && i + 1 < MI) request(i + 1);
             __builtin_amdgcn_sched_barrier(0);  // no further ahead: the registers are spoken for
 #pragma unroll
             for (int j = 0; j < NI; ++j) {
@@ -356,55 +372,71 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand 
                 const floatx4 x = *reinterpret_cast<const floatx4*>(get + RPI * k * PITCH);
                 out4 v;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = sum(x[r], ACCUM ? old[i & 1][k][r] : out_t(0));
-                *reinterpret_cast<out4*>(c0 + (size_t)(16 * i + RPI * k) * ldc) = v;
+                for (int r = 0; r < 4; ++r) v[r] = combine<ACC>(x[r], ACC ? old[i & 1][k][r] : out_t(0));
+                *reinterpret_cast<out4*>(c0 + (size_t)(16 * i + RPI * k) * pitch) = v;
             }
             __builtin_amdgcn_wave_barrier();
         }
+    };
+    if (is_part) {  // this split's sums of the whole tile; tw_split_sum_kernel adds them
+        constexpr size_t TILE_ELEMS = (size_t)(64 * WMT) * (64 * WNT);
+        store_tile(part + ((size_t)split * divided + (id - (unsigned)u.whole)) * TILE_ELEMS, 64 * WNT, std::false_type{});
+        return;
+    }
+    typedef typename std::conditional<OUT_F32, float, uint16_t>::type out_t;
+    const int mt = tile_m * (64 * WMT), nt = tile_n * (64 * WNT);
+    out_t* tile = static_cast<out_t*>(Cout) + (size_t)mt * ldc + nt;
+    if (mt + 64 * WMT <= M && nt + 64 * WNT <= N && ldc % 4 == 0 && reinterpret_cast<uintptr_t>(Cout) % (4 * sizeof(out_t)) == 0) {
+        store_tile(tile, ldc, std::integral_constant<bool, ACCUM>{});
         return;
     }
     const int m0 = mw + (lane & 15), n0 = nw + 4 * (lane >> 4);
-    out_t* c0 = out + (size_t)m0 * ldc + n0;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             asm volatile("" : "+a"(acc[i][j]));
-            if (m0 + 16 * i >= M) continue;
-            out_t* c = c0 + (size_t)(16 * i) * ldc + 16 * j;
+            if (mt + m0 + 16 * i >= M) continue;
+            out_t* c = tile + (size_t)(m0 + 16 * i) * ldc + n0 + 16 * j;
             out_t old[4] = {};
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                if (ACCUM && n0 + 16 * j + r < N) old[r] = c[r];
+                if (ACCUM && nt + n0 + 16 * j + r < N) old[r] = c[r];
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                if (n0 + 16 * j + r < N) c[r] = sum(acc[i][j][r], old[r]);
+                if (nt + n0 + 16 * j + r < N) c[r] = combine<ACCUM>(acc[i][j][r], old[r]);
         }
 }
 
-// C (+)= the splits' sums, part [splits][M * N] fp32; V consecutive elements of C per thread (V divides N,
-// ldc and the alignment).  Memory-bound: (splits + 1) passes over C.
-template <bool OUT_F32, bool ACCUM, int V>
-__global__ __launch_bounds__(256) void tw_split_sum_kernel(const float* __restrict__ part, int splits, int64_t MN, int N,
-                                                            void* __restrict__ Cout, int64_t ldc)
+// The divided tiles of a product: C (+)= the sums of their splits, part [split][tile][TM x TN] fp32.
+// Memory-bound: (splits + 1) passes over those tiles.
+template <bool OUT_F32, bool ACCUM>
+__global__ __launch_bounds__(256) void tw_split_sum_kernel(const float* __restrict__ part, Units u, int first, int tm, int tn, void* __restrict__ Cout,
+                                                            int64_t ldc, int M, int N)
 {
-    typedef float fvec __attribute__((ext_vector_type(V)));
-    typedef uint16_t hvec __attribute__((ext_vector_type(V)));
-    const int64_t at = ((int64_t)blockIdx.x * 256 + threadIdx.x) * V;
-    if (at >= MN) return;
-    fvec v = *reinterpret_cast<const fvec*>(part + at);
-    for (int s = 1; s < splits; ++s) v += *reinterpret_cast<const fvec*>(part + s * MN + at);
-    const int64_t c = at / N * ldc + at % N;
-    if (OUT_F32) {
-        fvec* o = reinterpret_cast<fvec*>(static_cast<float*>(Cout) + c);
-        *o = ACCUM ? *o + v : v;
-    } else {
-        hvec* o = reinterpret_cast<hvec*>(static_cast<uint16_t*>(Cout) + c);
-        hvec h;
-        if (ACCUM) h = *o;
+    typedef typename std::conditional<OUT_F32, float, uint16_t>::type out_t;
+    typedef out_t out4 __attribute__((ext_vector_type(4)));
+    constexpr unsigned GROUP_M = 4;  // the order of the tiles, as in the product
+    const unsigned i = (unsigned)first + blockIdx.y, id = (unsigned)u.whole + i, tiles_n = (unsigned)u.tiles_n, tiles_m = (unsigned)u.tiles / tiles_n;
+    const unsigned grp = id / (GROUP_M * tiles_n), in_grp = id % (GROUP_M * tiles_n);
+    const unsigned rows_in_grp = tiles_m - grp * GROUP_M < GROUP_M ? tiles_m - grp * GROUP_M : GROUP_M;
+    const int tile_m = (int)(grp * GROUP_M + in_grp % rows_in_grp), tile_n = (int)(in_grp / rows_in_grp);
+    const int at = ((int)blockIdx.x * 256 + (int)threadIdx.x) * 4;  // within the tile: tm * tn is a multiple of 1024
+    const int m = tile_m * tm + at / tn, n = tile_n * tn + at % tn;
+    if (m >= M || n >= N) return;
+    const size_t stride = (size_t)(u.tiles - u.whole) * tm * tn;
+    const float* p = part + (size_t)i * tm * tn + at;
+    floatx4 v = *reinterpret_cast<const floatx4*>(p);
+    for (int s = 1; s < u.splits; ++s) v += *reinterpret_cast<const floatx4*>(p + s * stride);
+    out_t* c = static_cast<out_t*>(Cout) + (size_t)m * ldc + n;
+    if (n + 4 <= N && ldc % 4 == 0 && reinterpret_cast<uintptr_t>(Cout) % (4 * sizeof(out_t)) == 0) {
+        out4 o = {};
+        if (ACCUM) o = *reinterpret_cast<const out4*>(c);
 #pragma unroll
-        for (int e = 0; e < V; ++e) h[e] = to_bf16(ACCUM ? from_bf16(h[e]) + v[e] : v[e]);
-        *o = h;
+        for (int r = 0; r < 4; ++r) o[r] = combine<ACCUM>(v[r], o[r]);
+        *reinterpret_cast<out4*>(c) = o;
+    } else {
+        for (int r = 0; r < 4 && n + r < N; ++r) c[r] = combine<ACCUM>(v[r], ACCUM ? c[r] : out_t(0));
     }
 }
 
@@ -423,32 +455,41 @@ Pool g_pool[64];
 std::vector<Realigned> g_cache;  // weights realigned during the current library call
 std::mutex g_mu;
 
-// Output tile (64 wmt x 64 wnt) and number of k splits of a product: the cheapest in units of the
-// core clock, from
-//   stage   the MFMAs of a wave (32 clocks each) or, on the small tiles, the fragments that pass
-//           through LDS (reads and copies, 128 bytes per clock), and about 100 for the barrier
-//   tile    a fixed part (first operands, epilogue), rounds of 256 tiles (512 where two fit a CU)
-//   splits  one more launch and (splits + 1) passes over the fp32 sums at about 4.5 bytes per ns
-struct Plan { int wmt, wnt, splits, split_stages; };
+// Output tile (64 wmt x 64 wnt), and which tiles are divided along k: the cheapest in units of the core
+// clock, from
+//   stage   the MFMAs of a wave (16 clocks each) or the bytes that a stage copies into LDS: 21 per clock and
+//           compute unit, measured for all tile shapes
+//   unit    a fixed part (first operands, epilogue)
+//   rounds  of 256 units (512 where two fit a CU).  Tiles that do not fill the last round are divided, so
+//           that it is full and short; with fewer tiles than slots all of them are
+//   sums    of the divided tiles: one more launch and (splits + 1) passes over them at about 4.5 bytes per ns
+// Measured, all tiles whole -> the rest divided (most of it without a free round at the end, some from the
+// epilogues out of step): SwiGLU block at 16K tokens 21.1 -> 18.9 ms, GELU block on 3001 tokens 1562 -> 1458
+// us, 4096 x 14336 += 4096 rows 586 -> 475 us.
+struct Plan { int wmt, wnt; Units u; };
 Plan plan_product(int64_t M, int64_t N, int stages)
 {
     static const int shapes[][2] = {{4, 4}, {3, 4}, {2, 4}, {1, 4}, {2, 2}};
-    Plan best = {4, 4, 1, stages};
+    Plan best = {4, 4, {}};
     double best_cost = 0.0;
     for (const auto& sh : shapes) {
         const int wm = sh[0], wn = sh[1];
-        const double lds = 96.0 * (wm + wn), mfma = 64.0 * wm * wn;
-        const double stage = (mfma > lds ? mfma : lds) + 100.0;
-        const double slots = wm * wn <= 4 && wn == 2 ? 512.0 : 256.0, share = slots / 256.0;
-        const double tiles = (double)((M + 64 * wm - 1) / (64 * wm)) * (double)((N + 64 * wn - 1) / (64 * wn));
+        const double mfma = 64.0 * wm * wn + 100.0, copies = 192.0 * (wm + wn);
+        const double stage = mfma > copies ? mfma : copies, fixed = 1200.0 + 160.0 * wm * wn;
+        const int slots = wm * wn <= 4 && wn == 2 ? 512 : 256;
+        const double share = slots / 256.0;
+        const int64_t tiles_n = (N + 64 * wn - 1) / (64 * wn), tiles = (M + 64 * wm - 1) / (64 * wm) * tiles_n;
+        if (tiles > (int64_t)1 << 30) continue;
+        const int64_t rest = tiles % slots, whole = tiles - rest;
         for (int sp = 1; sp <= 16; ++sp) {
             const int per = (stages + sp - 1) / sp;
-            if (sp > 1 && (per < 8 || (int64_t)(sp - 1) * per >= stages)) continue;
-            if (sp > 1 && (double)M * (double)N * sp > 1.0e8) break;  // the sums would not stay near the chip
-            double cost = std::ceil(tiles * sp / slots) * share * (per * stage + 1200.0 + 10.0 * wm * wn * 16);
-            if (sp > 1) cost += 9000.0 + (sp + 1) * 4.0 * (double)M * (double)N / 2250.0;
+            if (sp > 1 && (rest == 0 || per < 8 || (int64_t)(sp - 1) * per >= stages)) continue;
+            double cost = (double)(whole / slots) * (stages * stage + fixed);
+            cost += std::ceil((double)(rest * sp) / slots) * (per * stage + fixed);
+            cost *= share;
+            if (sp > 1) cost += 9000.0 + (sp + 1) * 4.0 * (double)rest * (64 * wm) * (64 * wn) / 2250.0;
             if (best_cost == 0.0 || cost < 0.98 * best_cost) {
-                best = {wm, wn, sp, per};
+                best = {wm, wn, {(int)tiles, (int)tiles_n, (int)(sp == 1 ? tiles : whole), sp, per}};
                 best_cost = cost;
             }
         }
@@ -487,7 +528,7 @@ int take_operand(Pool& pool, const void* X, int64_t R, int64_t C, int64_t ld, bo
 {
     const int64_t K = k_rows ? R : C;
     res->rows = (int)(k_rows ? (C + 7) / 8 * 8 : R);
-    if (K >= SK && (C % 8 == 0 || padded) && ld % 8 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0) {
+    if (K >= SK && (C % 8 == 0 || padded) && ld % 8 == 0 && (k_rows || ld < MAX_PITCH) && reinterpret_cast<uintptr_t>(X) % 16 == 0) {
         res->p = static_cast<const uint16_t*>(X);
         res->ld = ld;
     } else {
@@ -507,8 +548,7 @@ int take_operand(Pool& pool, const void* X, int64_t R, int64_t C, int64_t ld, bo
             if (cache) g_cache.push_back({X, R, C, ld, R2, C2, res->p});
         }
     }
-    // a lane's offset within its tile (255 rows of form N, 7 of form T) is kept in 32 bits; product() sees
-    // to it for form N
+    // a lane's offset within its tile (255 rows of form N, 7 of form T) is kept in 32 bits
     return res->ld >= (k_rows ? (int64_t)1 << 28 : MAX_PITCH) ? 2 : 0;
 }
 
@@ -532,21 +572,52 @@ void* scratch(size_t bytes)
     return pool_take(g_pool[dev], bytes, &mem) ? nullptr : mem;
 }
 
-static void split_sum(const float* part, int splits, int64_t M, int N, void* C, int64_t ldc, bool c_f32, bool accumulate, hipStream_t st)
+// The launch of a product (or, with u.whole = 0 and one split at a time, of one k segment of it)
+static int launch_product(const Plan& plan, int a_transposed, int b_transposed, const Operand& a, const Operand& b, int M, int N, int K,
+                          void* C, int64_t ldc, bool c_f32, bool accumulate, float* part, hipStream_t st)
 {
-    const int64_t MN = M * N;
-    const bool v4 = N % 4 == 0 && ldc % 4 == 0 && reinterpret_cast<uintptr_t>(C) % (c_f32 ? 16 : 8) == 0;
-    const unsigned blocks = (unsigned)((MN / (v4 ? 4 : 1) + 255) / 256);
-#define TW_SUM(F32, ACC)                                                                             \
-    do {                                                                                             \
-        if (v4) tw_split_sum_kernel<F32, ACC, 4><<<blocks, 256, 0, st>>>(part, splits, MN, N, C, ldc); \
-        else tw_split_sum_kernel<F32, ACC, 1><<<blocks, 256, 0, st>>>(part, splits, MN, N, C, ldc);    \
+    const Units& u = plan.u;
+    const int64_t parts = (int64_t)(u.tiles - u.whole) * u.splits;
+    const unsigned grid = 8 * ((unsigned)((u.whole + 7) / 8) + (unsigned)((parts + 7) / 8));
+#define TW_LAUNCH_TILE(TA, TB, F32, ACC, WM, WN) tw_gemm_kernel<TA, TB, F32, ACC, WM, WN><<<grid, NTHREAD, 0, st>>>(a, b, K, C, ldc, M, N, u, part)
+#define TW_LAUNCH(TA, TB, F32, ACC)                                             \
+    do {                                                                        \
+        if (plan.wnt == 2) TW_LAUNCH_TILE(TA, TB, F32, ACC, 2, 2);              \
+        else if (plan.wmt == 4) TW_LAUNCH_TILE(TA, TB, F32, ACC, 4, 4);         \
+        else if (plan.wmt == 3) TW_LAUNCH_TILE(TA, TB, F32, ACC, 3, 4);         \
+        else if (plan.wmt == 2) TW_LAUNCH_TILE(TA, TB, F32, ACC, 2, 4);         \
+        else TW_LAUNCH_TILE(TA, TB, F32, ACC, 1, 4);                            \
     } while (0)
-    if (c_f32 && accumulate) TW_SUM(true, true);
-    else if (c_f32) TW_SUM(true, false);
-    else if (accumulate) TW_SUM(false, true);
-    else TW_SUM(false, false);
-#undef TW_SUM
+    // the forms and outputs that the library's operations use
+    if (!a_transposed && !b_transposed && !accumulate) {
+        if (c_f32) TW_LAUNCH(false, false, true, false);
+        else TW_LAUNCH(false, false, false, false);
+    } else if (!a_transposed && b_transposed && !c_f32) {
+        if (accumulate) TW_LAUNCH(false, true, false, true);
+        else TW_LAUNCH(false, true, false, false);
+    } else if (a_transposed && b_transposed && c_f32 && accumulate) {
+        TW_LAUNCH(true, true, true, true);
+    } else {
+        return 2;
+    }
+#undef TW_LAUNCH
+#undef TW_LAUNCH_TILE
+    return 0;
+}
+
+static size_t part_bytes(const Plan& plan) { return (size_t)plan.u.splits * (plan.u.tiles - plan.u.whole) * (64 * plan.wmt) * (64 * plan.wnt) * 4; }
+
+static void launch_split_sum(const Plan& plan, const float* part, int M, int N, void* C, int64_t ldc, bool c_f32, bool accumulate, hipStream_t st)
+{
+    const int tm = 64 * plan.wmt, tn = 64 * plan.wnt, divided = plan.u.tiles - plan.u.whole;
+    for (int t0 = 0; t0 < divided; t0 += 65535) {  // the grid's second dimension
+        const Units& u = plan.u;
+        const dim3 grid((unsigned)(tm * tn / 1024), (unsigned)(divided - t0 < 65535 ? divided - t0 : 65535));
+        if (c_f32 && accumulate) tw_split_sum_kernel<true, true><<<grid, 256, 0, st>>>(part, u, t0, tm, tn, C, ldc, M, N);
+        else if (c_f32) tw_split_sum_kernel<true, false><<<grid, 256, 0, st>>>(part, u, t0, tm, tn, C, ldc, M, N);
+        else if (accumulate) tw_split_sum_kernel<false, true><<<grid, 256, 0, st>>>(part, u, t0, tm, tn, C, ldc, M, N);
+        else tw_split_sum_kernel<false, false><<<grid, 256, 0, st>>>(part, u, t0, tm, tn, C, ldc, M, N);
+    }
 }
 
 static int product(Pool& pool, int a_transposed, int b_transposed, int M, int N, int K, const void* A, int64_t lda, const void* B,
@@ -556,10 +627,7 @@ static int product(Pool& pool, int a_transposed, int b_transposed, int M, int N,
     const size_t off0 = pool.off;
     const int Kp = K < SK ? SK : K;  // (realigned operands of less are padded to one stage)
     const Plan plan = plan_product(M, N, Kp / SK);
-    const int tile_rows = 64 * plan.wmt, tile_cols = 64 * plan.wnt;
-    const int tiles_n = (N + tile_cols - 1) / tile_cols, tiles_m = (M + tile_rows - 1) / tile_rows;
-    const long long total = (long long)tiles_m * tiles_n;
-    if (total * plan.splits > (1ll << 30)) return 2;
+    if (plan.u.tiles == 0) return 2;
     // Aop[m,k]: A stored [M,K] (as is) or [K,M] (transposed); Bop[n,k]: B stored [N,K] or [K,N]
     Operand pa, pb;
     int rc = take_operand(pool, B, b_transposed ? K : N, b_transposed ? N : K, ldb, b_transposed, false, cache_b, st, &pb);
@@ -567,44 +635,15 @@ static int product(Pool& pool, int a_transposed, int b_transposed, int M, int N,
     const size_t mark = pool.off;  // what follows is scratch of this product only
     rc = take_operand(pool, A, a_transposed ? K : M, a_transposed ? M : K, lda, a_transposed, lda > (a_transposed ? M : K), false, st, &pa);
     if (rc) return rc;
-    void* out = C;
-    int64_t out_ld = ldc;
-    if (plan.splits > 1) {
+    float* part = nullptr;
+    if (plan.u.splits > 1) {
         char* mem = nullptr;
-        if (pool_take(pool, (size_t)plan.splits * M * N * 4, &mem)) return 1;
-        out = mem;
-        out_ld = N;
+        if (pool_take(pool, part_bytes(plan), &mem)) return 1;
+        part = reinterpret_cast<float*>(mem);
     }
-    const unsigned grid = (unsigned)((total * plan.splits + 7) / 8 * 8);
-#define TW_LAUNCH_TILE(TA, TB, F32, ACC, WM, WN)                                                                     \
-    tw_gemm_kernel<TA, TB, F32, ACC, WM, WN><<<grid, NTHREAD, 0, st>>>(pa, pb, Kp, out, out_ld, M, N, tiles_n,        \
-                                                                       (int)total, plan.splits, plan.split_stages)
-#define TW_LAUNCH(TA, TB, F32, ACC)                                             \
-    do {                                                                        \
-        if (plan.wnt == 2) TW_LAUNCH_TILE(TA, TB, F32, ACC, 2, 2);              \
-        else if (plan.wmt == 4) TW_LAUNCH_TILE(TA, TB, F32, ACC, 4, 4);         \
-        else if (plan.wmt == 3) TW_LAUNCH_TILE(TA, TB, F32, ACC, 3, 4);         \
-        else if (plan.wmt == 2) TW_LAUNCH_TILE(TA, TB, F32, ACC, 2, 4);         \
-        else TW_LAUNCH_TILE(TA, TB, F32, ACC, 1, 4);                            \
-    } while (0)
-    const bool f32 = c_f32 || plan.splits > 1, add = accumulate && plan.splits == 1;
-    // the forms and outputs that the library's operations use
-    if (!a_transposed && !b_transposed && !add) {
-        if (f32) TW_LAUNCH(false, false, true, false);
-        else TW_LAUNCH(false, false, false, false);
-    } else if (!a_transposed && b_transposed && !(f32 && add)) {
-        if (f32) TW_LAUNCH(false, true, true, false);
-        else if (add) TW_LAUNCH(false, true, false, true);
-        else TW_LAUNCH(false, true, false, false);
-    } else if (a_transposed && b_transposed && f32) {
-        if (add) TW_LAUNCH(true, true, true, true);
-        else TW_LAUNCH(true, true, true, false);
-    } else {
-        return 2;
-    }
-#undef TW_LAUNCH
-#undef TW_LAUNCH_TILE
-    if (plan.splits > 1) split_sum(static_cast<const float*>(out), plan.splits, M, N, C, ldc, c_f32, accumulate, st);
+    rc = launch_product(plan, a_transposed, b_transposed, pa, pb, M, N, Kp, C, ldc, c_f32, accumulate, part, st);
+    if (rc) return rc;
+    if (plan.u.splits > 1) launch_split_sum(plan, part, M, N, C, ldc, c_f32, accumulate, st);
     // The next product's copies run after this launch on the same stream, so this product's scratch
     // is free again: everything it took, or everything behind a weight that stays cached.  (Not if
     // the pool was replaced by a larger one on the way: then nothing is given back until the next
@@ -624,34 +663,34 @@ int gemm(int a_transposed, int b_transposed, int M, int N, int K, const void* A,
     const bool long_a = !a_transposed && lda >= MAX_PITCH, long_b = !b_transposed && ldb >= MAX_PITCH;
     if (!long_a && !long_b)
         return product(pool, a_transposed, b_transposed, M, N, K, A, lda, B, ldb, C, ldc, c_f32, accumulate, cache_b, st);
-    // Rows too long for the kernel's offsets: k in segments, the long operand's copied out one at a time,
-    // the fp32 sums of the segments added at the end as those of splits are.
+    // Rows too long for the kernel's offsets: k in segments, which are the splits of every tile, one launch
+    // each; the long operand's segment is copied out in front of it.
     constexpr int64_t SEG = (int64_t)1 << 22;
-    const int segs = (int)((K + SEG - 1) / SEG);
-    char* part = nullptr;
-    if (pool_take(pool, (size_t)segs * M * N * 4, &part)) return 1;
-    for (int i = 0; i < segs; ++i) {
-        const int64_t k0 = i * SEG, k = K - k0 < SEG ? K - k0 : SEG, k8 = (k + 7) / 8 * 8;
+    Plan plan = {4, 4, {}};
+    const int64_t tiles_n = ((int64_t)N + 255) / 256, tiles = ((int64_t)M + 255) / 256 * tiles_n;
+    if (tiles > (int64_t)1 << 30) return 2;
+    plan.u = {(int)tiles, (int)tiles_n, 0, (int)((K + SEG - 1) / SEG), 0};
+    char* mem = nullptr;
+    if (pool_take(pool, part_bytes(plan), &mem)) return 1;
+    float* part = reinterpret_cast<float*>(mem);
+    for (int i = 0; i < plan.u.splits; ++i) {
+        const int64_t k0 = i * SEG, k = K - k0 < SEG ? K - k0 : SEG;
         const char* base0 = pool.base;
         const size_t off0 = pool.off;
-        const uint16_t *a = static_cast<const uint16_t*>(A) + (a_transposed ? k0 * lda : k0), *b = static_cast<const uint16_t*>(B) + (b_transposed ? k0 * ldb : k0);
-        int64_t la = lda, lb = ldb;
-        for (int side = 0; side < 2; ++side) {
-            if (!(side ? long_b : long_a)) continue;
-            const int64_t rows = side ? N : M;
-            char* mem = nullptr;
-            if (pool_take(pool, (size_t)rows * k8 * 2, &mem)) return 1;
-            const int64_t blocks = (rows * (k8 / 8) + 255) / 256;
-            tw_realign_kernel<<<dim3((unsigned)(blocks < 65536 ? blocks : 65536)), 256, 0, st>>>(side ? b : a, rows, k, side ? ldb : lda,
-                                                                                              reinterpret_cast<u32x4*>(mem), rows, k8);
-            (side ? b : a) = reinterpret_cast<const uint16_t*>(mem);
-            (side ? lb : la) = k8;
-        }
-        const int rc = product(pool, a_transposed, b_transposed, M, N, (int)k, a, la, b, lb, part + (size_t)i * M * N * 4, N, true, false, false, st);
+        Operand a, b;
+        // (a segment of a long row is never read in place: its pitch is the row's)
+        int rc = take_operand(pool, static_cast<const uint16_t*>(B) + (b_transposed ? k0 * ldb : k0), b_transposed ? k : N, b_transposed ? N : k, ldb, b_transposed, false, false, st, &b);
+        if (!rc) rc = take_operand(pool, static_cast<const uint16_t*>(A) + (a_transposed ? k0 * lda : k0), a_transposed ? k : M, a_transposed ? M : k, lda, a_transposed, false, false, st, &a);
+        if (rc) return rc;
+        Plan one = plan;
+        one.u.splits = 1;
+        const int Kp = k < SK ? SK : (int)k;
+        one.u.split_stages = Kp / SK;
+        rc = launch_product(one, a_transposed, b_transposed, a, b, M, N, Kp, C, ldc, c_f32, accumulate, part + (size_t)i * (part_bytes(one) / 4), st);
         if (rc) return rc;
         if (pool.base == base0) pool.off = off0;
     }
-    split_sum(reinterpret_cast<const float*>(part), segs, M, N, C, ldc, c_f32, accumulate, st);
+    launch_split_sum(plan, part, M, N, C, ldc, c_f32, accumulate, st);
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 

@@ -416,7 +416,8 @@ def test_gpu_tokenwise_calls_replay_from_a_graph():
     (300, 4096, 64, 1, 0),   # long k, few tiles: the k range is split
     (129, 1000, 1001, 3, 0),  # odd widths: no row is 16-byte aligned
     (200, 96, 520, 1, 1),    # operands that start 2 bytes behind a 16-byte boundary
-    (1030, 2048, 1160, 4, 0)])
+    (1030, 2048, 1160, 4, 0),
+    (4100, 1032, 4200, 1, 0)])  # one full round of large tiles and a divided rest
 def test_gpu_linear_tile_edges(rows, n_in, n_out, n_chunks, offset):
     """Forward, dX and dW of the projection against fp64 at the edges of the product's tiles, k stages and
     splits.  Exact bf16 products summed in fp32: rel 1e-4 of a row's rms (k <= 4096 terms, error of about
