@@ -473,8 +473,7 @@ int fwd_f32(const Problem& p, const float* Q, const float* K, const float* V, fl
 int fwd_bf16_fused(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* LSE,
                    const FwdPlan& f, hipStream_t st)
 {
-    launch_pack(K, p.S, p.Hkv, p.D, f.Knat, nullptr, p.S / 32, st);
-    launch_pack(V, p.S, p.Hkv, p.D, nullptr, f.Vtr, p.S / 32, st);
+    launch_pack({{K, p.Hkv, f.Knat, nullptr}, {V, p.Hkv, nullptr, f.Vtr}}, p.S, p.D, p.S / 32, st);
     FwdArgs a;
     a.Q = Q; a.Knat = f.Knat; a.Vtr = f.Vtr; a.kv_head_stride_blocks = p.S / 32;
     a.O = O; a.LSE = LSE; a.lse_stride = p.S; a.st_acc = nullptr; a.st_ml = nullptr;
@@ -552,8 +551,7 @@ int fwd_bf16_pairs(const Problem& p, const char* Q, const char* K, const char* V
                 Ki = f.kv_raw[b];
                 Vi = f.kv_raw[b] + kvb;
             }
-            launch_pack(Ki, p.C, p.Hkv, p.D, f.Knat, nullptr, p.C / 32, st);
-            launch_pack(Vi, p.C, p.Hkv, p.D, nullptr, f.Vtr, p.C / 32, st);
+            launch_pack({{Ki, p.Hkv, f.Knat, nullptr}, {Vi, p.Hkv, nullptr, f.Vtr}}, p.C, p.D, p.C / 32, st);
             if (kvh) TRY(ev.record(EV_KV_FREE0 + (int)(t & 1), st));
             if (acth && i == m)  // the finalising sweep overwrites the staging O / LSE chunk
                 TRY(ev.wait(st, EV_OUT_COPIED0 + qbuf));
@@ -639,10 +637,8 @@ int bwd_bf16_fused(const Problem& p, const void* Q, const void* K, const void* V
     launch_delta(O, dO, p.S, p.Hq, p.D, 1, f.Delta, p.S, st);
     launch_delta_head(Q, dO, K, V, LSE, p.S, p.Hq, p.Hkv, p.D, p.scale, f.Delta, st);
     launch_stat_pack(LSE, f.Delta, p.S, p.S, p.Hq, p.S / 32, f.stat2, st);
-    launch_pack(Q, p.S, p.Hq, p.D, f.Qnat, nullptr, p.S / 32, st);
-    launch_pack(dO, p.S, p.Hq, p.D, f.dOnat, nullptr, p.S / 32, st);
-    launch_pack(K, p.S, p.Hkv, p.D, f.Knat, nullptr, p.S / 32, st);
-    launch_pack(V, p.S, p.Hkv, p.D, f.Vnat, nullptr, p.S / 32, st);
+    launch_pack({{Q, p.Hq, f.Qnat, nullptr}, {dO, p.Hq, f.dOnat, nullptr}, {K, p.Hkv, f.Knat, nullptr}, {V, p.Hkv, f.Vnat, nullptr}},
+                p.S, p.D, p.S / 32, st);
     BwdArgs a;
     a.Q = Q; a.dO = dO; a.K = K; a.V = V;
     a.Qnat = f.Qnat; a.dOnat = f.dOnat; a.q_head_stride_blocks = p.S / 32;
@@ -755,8 +751,7 @@ int bwd_bf16_pairs(const Problem& p, const char* Q, const char* K, const char* V
                 Kj = K + (size_t)j * kvb;
                 Vj = V + (size_t)j * kvb;
             }
-            launch_pack(Kj, p.C, p.Hkv, p.D, f.Knat, nullptr, p.C / 32, st);
-            launch_pack(Vj, p.C, p.Hkv, p.D, f.Vnat, nullptr, p.C / 32, st);
+            launch_pack({{Kj, p.Hkv, f.Knat, nullptr}, {Vj, p.Hkv, f.Vnat, nullptr}}, p.C, p.D, p.C / 32, st);
             cur_j = j;
         }
         // ---- query side ----
@@ -779,8 +774,7 @@ int bwd_bf16_pairs(const Problem& p, const char* Q, const char* K, const char* V
                 Deltai = f.Delta + i * p.C;
                 stat_stride = p.S;
             }
-            launch_pack(Qi, p.C, p.Hq, p.D, f.Qnat, nullptr, p.C / 32, st);
-            launch_pack(dOi, p.C, p.Hq, p.D, f.dOnat, nullptr, p.C / 32, st);
+            launch_pack({{Qi, p.Hq, f.Qnat, nullptr}, {dOi, p.Hq, f.dOnat, nullptr}}, p.C, p.D, p.C / 32, st);
             cur_i = i;
             stat_stale = true;
         }

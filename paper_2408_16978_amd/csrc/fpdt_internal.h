@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <initializer_list>
+
 namespace fpdt {
 
 typedef uint16_t bf16_bits;  // storage type of a bfloat16 element on the host side
@@ -27,11 +29,17 @@ static inline int dpad(int D) { return (D + 31) / 32 * 32; }
 static inline size_t nat_block_bytes(int D) { return (size_t)(D / 16) * 1024; }
 static inline size_t tr_block_bytes(int D) { return (size_t)(2 * (dpad(D) / 32)) * 1024; }
 
-// Pack `rows` rows (multiple of 32) of X [rows, H, D] into NAT and/or TR form.
-// Output head stride is given in 32-row blocks (>= rows/32) so that a chunk
-// can be packed into its slot of a whole-sequence buffer.
-void launch_pack(const void* X, int64_t rows, int H, int D, void* nat, void* tr,
-                 int64_t head_stride_blocks, hipStream_t st);
+// Pack `rows` rows (multiple of 32) of up to PACK_MAX_JOBS tensors X [rows, H, D] into NAT and/or TR
+// form (null: not wanted), in one launch.  Output head stride is given in 32-row blocks (>= rows/32) so
+// that a chunk can be packed into its slot of a whole-sequence buffer.
+enum { PACK_MAX_JOBS = 4 };
+struct PackJob {
+    const void* X;
+    int H;
+    void* nat;
+    void* tr;
+};
+void launch_pack(std::initializer_list<PackJob> tensors, int64_t rows, int D, int64_t head_stride_blocks, hipStream_t st);
 
 // ---------------------------------------------------------------------------
 // bf16 forward sweep: query rows [q_pos0, q_pos0 + n_q) against keys
