@@ -1157,9 +1157,6 @@ void launch_bwd_dq_from_ds(const BwdArgs& a, hipStream_t st)
     else bwd_dq_ds_kernel<64><<<grid, NTHREAD, 0, st>>>(k);
 }
 
-
-
-
 void launch_bwd_dq(const BwdArgs& a, hipStream_t st)
 {
     const BwdKernelArgs k = to_kernel_args(a);
