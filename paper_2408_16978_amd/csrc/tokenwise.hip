@@ -446,11 +446,11 @@ int fpdt_tw_loss_fwd_bwd(const void* H, const void* W, const int32_t* target, fl
     if (rc != TW_OK) return rc;
     // The logit gradients of several chunks are gathered before they are multiplied: dW += G^T H reads and
     // writes the whole fp32 dW (2.1 GB at 128256 x 4096), which at 1058 rows per chunk took as long as its
-    // MFMAs, and dH = G W has too few tiles at that height.  As many chunks as make `hidden` rows: their G
-    // then takes the memory of one bf16 copy of W, in the library's scratch.  Rows of G are padded to 16
+    // MFMAs, and dH = G W has too few tiles at that height.  As many chunks as make 2 `hidden` rows: their
+    // G then takes the memory of two bf16 copies of W, in the library's scratch.  Rows of G are padded to 16
     // bytes there, so an odd vocabulary takes this way with a single chunk too.
-    // Measured (65536 tokens, hidden 4096, 62 chunks): 310 -> 235 ms, of which the memory-bound part of dW fell to a third.
-    int64_t per_group = hidden / c > 1 ? hidden / c : 1, ldg = vocab;
+    // Measured (65536 tokens, hidden 4096, 62 chunks): 310 -> 235 ms with `hidden` rows, 210 -> 204 ms from there to twice as many.
+    int64_t per_group = 2 * (int64_t)hidden / c > 1 ? 2 * (int64_t)hidden / c : 1, ldg = vocab;
     if (bwd && (per_group > 1 || vocab % 8)) {
         const int64_t group_rows = per_group * c < rows ? per_group * c : rows, ld = ((int64_t)vocab + 7) / 8 * 8;
         if (void* mem = fpdt_tw::scratch((size_t)group_rows * ld * 2)) {
