@@ -160,7 +160,9 @@ int fpdt_attn_fwd(const void *Q, const void *K, const void *V, void *O, float *L
  *   - Tensors are resident: FPDT_KV_ON_HOST / FPDT_ACT_ON_HOST give FPDT_ERR_UNSUPPORTED.
  *   - Sizes whose fpdt_attn_workspace_bytes(..., 0) exceeds FPDT_NOALLOC_SCRATCH_BYTES give
  *     FPDT_ERR_WORKSPACE and enqueue nothing.  bf16 without FPDT_PAIRWISE needs
- *     S / 32 * Hkv * (D / 16 + 2 * ceil(D / 32)) KiB: S * Hkv <= 65,536 at D = 128.
+ *     S / 32 * Hkv * (D / 16 + 2 * ceil(D / 32)) KiB: S * Hkv <= 65,536 at D = 128.  (A short
+ *     sequence with FPDT_PAIRWISE, whose workspace holds several carried states per row, also runs
+ *     if it fits with one state per row; its results then differ from fpdt_attn_fwd's in rounding.)
  *   - Every call on a GPU uses that GPU's one array and finds the previous call's contents in
  *     it.  Nothing has to start at zero (a call writes every byte it later reads), but two
  *     calls that overlap in time on one GPU (different streams, or different threads) race on

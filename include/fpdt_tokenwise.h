@@ -15,7 +15,7 @@
  *                          count, forward and (recomputing) backward.
  *
  * The dense products run on this library's own bf16 MFMA kernels (csrc/tw_gemm.hip: operands
- * re-laid into MFMA fragments, 256 x 256 output tiles, fp32 accumulation); the row-wise softmax /
+ * read in place, output tiles of up to 256 x 256, fp32 accumulation); the row-wise softmax /
  * loss / gradient and the activations are HIP kernels of this library as well.  Built as a
  * separate shared library (libfpdt_tokenwise.so).
  *
@@ -23,8 +23,10 @@
  * buffers, `stream` is a hipStream_t passed as void*, calls only enqueue, every function returns
  * an fpdt status code (0 = OK, 1 = invalid argument, 2 = unsupported, 3 = workspace, 4 = HIP
  * failure; text from fpdt_tw_last_error).  Besides the caller's workspace the library keeps one
- * device scratch pool per GPU for the re-laid operands of the running call (weights once per
- * call, activations per product); it grows on demand with hipMalloc -- so the first call of a
+ * device scratch pool per GPU for the running call: logit gradients of up to 2 hidden rows, fp32
+ * sums of output tiles that several workgroups share, copies of operands whose rows are not
+ * 16-byte aligned.  It grows
+ * on demand with hipMalloc -- so the first call of a
  * given size must not run under stream capture -- and is kept until the process ends.  Calls
  * that overlap in time on one GPU (different streams or threads) would share that pool: keep
  * the library's calls on one stream.
@@ -68,8 +70,10 @@ int fpdt_tw_loss_fwd_bwd(const void *H, const void *W, const int32_t *target, fl
  * Chunked linear projection (Sec. 4.1: every sequence chunk T_i is projected to q_i, k_i, v_i on
  * its own, so that chunk i's attention can start while chunk i+1 is still being projected).
  *     Y = X W^T          X [rows, n_in] bf16, W [n_out, n_in] bf16  ->  Y [rows, n_out] bf16
- * computed ceil(rows / n_chunks) rows at a time; needs no workspace.  Backward:
+ * needs no workspace.  Backward:
  *     dX = dY W  (written, bf16; NULL to skip),   dW += dY^T X  (accumulated, fp32; NULL to skip)
+ * dW is summed ceil(rows / n_chunks) rows at a time; Y and dX, whose rows are independent and which
+ * have no intermediates, are computed over all rows at once.
  */
 int fpdt_tw_linear_fwd(const void *X, const void *W, void *Y, int64_t rows, int n_in, int n_out,
                        int n_chunks, void *stream);
