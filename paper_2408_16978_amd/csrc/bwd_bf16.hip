@@ -980,13 +980,25 @@ __global__ __launch_bounds__(256) void stat_pack_kernel(const float* __restrict_
 }
 
 // ---------------------------------------------------------------------------------------
-// Delta[h][row] = sum_d dO * O.  One wave per (row, head) pair group: lanes split channels.
-template <typename T>
-__device__ __forceinline__ float ld(const T* p);
-template <> __device__ __forceinline__ float ld<float>(const float* p) { return *p; }
-template <> __device__ __forceinline__ float ld<uint16_t>(const uint16_t* p)
+// Delta[h][row] = sum_d dO * O.  16 lanes per (row, head), 16 bytes of each tensor per lane and access
+// (all head dimensions are multiples of 16, the tensors 16-byte aligned).  HBM-bound: 131072 rows x 8
+// heads, D = 128, bf16 97 us (5.5 TB/s; with 2-byte loads 156).
+typedef float float4v __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ float dot16(const float* a, const float* b)
 {
-    return __uint_as_float(((unsigned)*p) << 16);
+    const float4v x = *reinterpret_cast<const float4v*>(a), y = *reinterpret_cast<const float4v*>(b);
+    return fmaf(x[0], y[0], fmaf(x[1], y[1], fmaf(x[2], y[2], x[3] * y[3])));
+}
+__device__ __forceinline__ float dot16(const uint16_t* a, const uint16_t* b)
+{
+    const u32x4 x = *reinterpret_cast<const u32x4*>(a), y = *reinterpret_cast<const u32x4*>(b);
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        s = fmaf(__uint_as_float(x[i] << 16), __uint_as_float(y[i] << 16), s);
+        s = fmaf(__uint_as_float(x[i] & 0xffff0000u), __uint_as_float(y[i] & 0xffff0000u), s);
+    }
+    return s;
 }
 
 template <typename T>
@@ -994,6 +1006,7 @@ __global__ __launch_bounds__(256) void delta_kernel(const T* __restrict__ O, con
                                                     int64_t rows, int Hq, int D, float* __restrict__ Delta,
                                                     int64_t stride)
 {
+    constexpr int V = 16 / (int)sizeof(T);
     // 16 lanes per (row, head): 4 pairs per wave, 16 pairs per workgroup
     const int tid = threadIdx.x;
     const int64_t pair = (int64_t)blockIdx.x * 16 + (tid >> 4);
@@ -1002,7 +1015,7 @@ __global__ __launch_bounds__(256) void delta_kernel(const T* __restrict__ O, con
     const T* o = O + (size_t)pair * D;
     const T* g = dO + (size_t)pair * D;
     float acc = 0.f;
-    for (int d = sub; d < D; d += 16) acc += ld<T>(o + d) * ld<T>(g + d);
+    for (int d = V * sub; d < D; d += 16 * V) acc += dot16(o + d, g + d);
 #pragma unroll
     for (int m = 8; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, 64);
     if (sub == 0) {
