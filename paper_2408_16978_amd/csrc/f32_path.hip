@@ -187,13 +187,16 @@ __global__ __launch_bounds__(64 * NW) void f32_fwd_kernel(F32FwdArgs a)
             }
         }
         const float m_new = fmaxf(m, max_over_rows(mx));
-        const float alpha = m_new > -INFINITY ? expf(m - m_new) : 1.f;  // (no key of this row yet: nothing to rescale)
+        // (every score of this wave so far may be -infinity, masked or overflowed: then 0 takes the maximum's
+        // place, whatever was added is 0, and so stays what the next finite score rescales)
+        const float m_ref = m_new > -INFINITY ? m_new : 0.f;
+        const float alpha = expf(m - m_ref);
         l *= alpha;
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                s[b][r] = (keep[b] >> r) & 1 ? expf(s[b][r] - m_new) : 0.f;
+                s[b][r] = (keep[b] >> r) & 1 ? expf(s[b][r] - m_ref) : 0.f;
                 l += s[b][r];
             }
 #pragma unroll

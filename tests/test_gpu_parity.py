@@ -346,3 +346,23 @@ def test_fp32_masked_rows_may_hold_anything(D):
     early = run(spoil(Q, slice(0, cut)), K, V, spoil(dO, slice(0, cut)), S, scale)
     for n in ("dK", "dV"):
         assert torch.equal(early[n][cut:], want[n][cut:]), n
+
+
+@pytest.mark.parametrize("chunk", [150, 50])
+@pytest.mark.parametrize("D", [64, 80, 128])
+def test_fp32_scores_that_overflow_to_minus_infinity(D, chunk):
+    """Finite inputs whose scores with a run of keys overflow to -infinity: those keys get no weight and leave
+    the other keys' results alone, also where a whole 32-key block (all that one wave sees of a row) is of
+    that kind.  The other keys' scores do not involve the large channel, so all outputs meet the fp32
+    tolerance (but for that channel of dK, which multiplies the large queries)."""
+    S, Hq, Hkv = 150, 2, 1
+    announce("fp32 overflowing scores", S, chunk, D)
+    Q, K, V, dO = inputs.make_qkvdo(S, Hq, Hkv, D, "f32", seed=20)
+    Q[:, :, 0], K[:, :, 0] = 1e20, 0.0
+    K[32:64, :, 0] = -1e20
+    K[100:142, :, 0] = -1e20
+    scale = D ** -0.5
+    ref = parity.oracle_full(Q, K, V, dO, scale)
+    out = run(Q, K, V, dO, chunk, scale, B.FPDT_PAIRWISE)
+    print(parity.check_all(out, ref, False, names=("O", "LSE", "dQ", "dV")))
+    print(parity.check("dK", out["dK"][:, :, 1:], ref["dK"][:, :, 1:], False))
