@@ -77,11 +77,10 @@ enum {
     FPDT_BWD_Q_OUTER = 1u << 3,
     /* Run the chunk-pair schedule launch by launch (carried fp32 state between pairs)
      * even when every tensor is resident.  Without this bit and without offload flags
-     * the bf16 path ignores `chunk` (beyond validating it) and runs ONE causal sweep over
-     * the whole sequence per kernel: the same set of (query, key) tiles, no carried state
-     * between launches.  The offload pipeline always runs pair by pair, with the same
-     * kernels in the same order as this mode: the two agree bit for bit.  fp32 always
-     * runs pair by pair.                                                               */
+     * `chunk` is ignored (beyond validating it) and every kernel runs ONE causal sweep over
+     * the whole sequence: the same set of (query, key) tiles, no carried state between
+     * launches.  The offload pipeline always runs pair by pair, with the same kernels in
+     * the same order as this mode: the two agree bit for bit.                          */
     FPDT_PAIRWISE = 1u << 4,
     /* Backward only (bf16; the forward ignores it): the stored-dS backward.  The paper's
      * backward, like any FlashAttention backward, recomputes the probabilities per chunk

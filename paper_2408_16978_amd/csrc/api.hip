@@ -57,6 +57,7 @@ struct Problem {
     bool act_host() const { return flags & FPDT_ACT_ON_HOST; }
     bool store_ds() const { return flags & FPDT_BWD_STORE_DS; }
     bool fused() const { return bf16() && !(flags & (FPDT_KV_ON_HOST | FPDT_ACT_ON_HOST | FPDT_PAIRWISE | FPDT_BWD_STORE_DS)); }
+    bool f32_pairs() const { return flags & FPDT_PAIRWISE; }
     bool q_outer() const
     {
         if (flags & FPDT_BWD_Q_OUTER) return true;
@@ -446,11 +447,11 @@ int copy_d2h(void* dst, const void* src, size_t bytes, hipStream_t st)
 // =========================================================================================
 // forward
 // =========================================================================================
-// Pair by pair only under a chunk mask; a dense call is one launch over the whole sequence.
+// One launch over the whole sequence, or (FPDT_PAIRWISE, which a chunk mask implies) one per chunk pair.
 int fwd_f32(const Problem& p, const float* Q, const float* K, const float* V, float* O, float* LSE,
             const FwdPlan& f, hipStream_t st)
 {
-    const int64_t C = p.mask.empty() ? p.S : p.C, u = p.S / C;
+    const int64_t C = p.f32_pairs() ? p.C : p.S, u = p.S / C;
     for (int64_t m = 0; m < u; ++m)
         for (int64_t i = 0; i <= m; ++i) {
             if (!p.on(m, i)) continue;
@@ -593,14 +594,14 @@ int bwd_f32(const Problem& p, const float* Q, const float* K, const float* V, co
             const float* LSE, const float* dO, float* dQ, float* dK, float* dV, const BwdPlan& f,
             hipStream_t st)
 {
-    const bool dense = p.mask.empty();  // one launch over the whole sequence, which overwrites
-    if (!dense) {
+    const bool pairs = p.f32_pairs();  // they accumulate; one launch over the whole sequence overwrites
+    if (pairs) {
         launch_zero(dQ, (size_t)p.S * p.Hq * p.D * 4, st);
         launch_zero(dK, (size_t)p.S * p.Hkv * p.D * 4, st);
         launch_zero(dV, (size_t)p.S * p.Hkv * p.D * 4, st);
     }
     launch_delta(O, dO, p.S, p.Hq, p.D, 0, f.Delta, p.S, st);
-    const int64_t C = dense ? p.S : p.C;
+    const int64_t C = pairs ? p.C : p.S;
     auto pair = [&](int64_t i, int64_t j) {
         F32BwdArgs a;
         a.Q = Q + (size_t)i * C * p.Hq * p.D;
@@ -611,12 +612,12 @@ int bwd_f32(const Problem& p, const float* Q, const float* K, const float* V, co
         a.dQ = dQ + (size_t)i * C * p.Hq * p.D;
         a.dK = dK + (size_t)j * C * p.Hkv * p.D;
         a.dV = dV + (size_t)j * C * p.Hkv * p.D;
-        a.accumulate = !dense;
+        a.accumulate = pairs;
         a.q_pos0 = i * C; a.k_pos0 = j * C; a.n_q = C; a.n_k = C;
         a.Hq = p.Hq; a.Hkv = p.Hkv; a.D = p.D; a.scale = p.scale;
         launch_f32_bwd(a, st);
     };
-    if (dense) {
+    if (!pairs) {
         pair(0, 0);
     } else if (p.q_outer()) {
         for (int64_t i = 0; i < p.u; ++i)

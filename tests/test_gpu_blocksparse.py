@@ -90,6 +90,22 @@ def test_all_ones_mask_is_bitwise_the_pairwise_dense_path():
         assert torch.equal(sp[name], t), name
 
 
+@pytest.mark.parametrize("S,chunk,Hq,Hkv,D", [(1024, 128, 2, 2, 64), (300, 100, 4, 2, 80), (99, 11, 4, 1, 128), (70, 35, 2, 1, 64)])
+@pytest.mark.parametrize("order", [0, B.FPDT_BWD_Q_OUTER])
+def test_fp32_all_ones_mask_is_bitwise_the_pairwise_dense_path(S, chunk, Hq, Hkv, D, order):
+    print("[case] fp32 all-ones mask vs pairwise dense", S, chunk, Hq, Hkv, D, order, flush=True)
+    Q, K, V, dO = inputs.make_qkvdo(S, Hq, Hkv, D, "f32", seed=29)
+    u = S // chunk
+    sp = run(Q, K, V, dO, chunk, D ** -0.5, np.ones((u, u)), order)
+    b = runner.make_buffers(Q, K, V, dO, chunk, D ** -0.5, B.FPDT_PAIRWISE | order)
+    runner.forward(b)
+    runner.backward(b)
+    torch.cuda.synchronize()
+    for name, t in (("O", b.O), ("LSE", b.LSE), ("dQ", b.dQ), ("dK", b.dK), ("dV", b.dV)):
+        assert torch.equal(sp[name], t), name
+    print(parity.check_all(sp, parity.oracle_full(Q, K, V, dO, D ** -0.5), False))
+
+
 def test_offloaded_blocksparse_fetches_only_kept_chunks():
     """K/V on the host: the link carries exactly the kept pairs' chunks, and the result equals
     the resident block-sparse run bit for bit."""
