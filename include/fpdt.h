@@ -161,7 +161,7 @@ int fpdt_attn_fwd(const void *Q, const void *K, const void *V, void *O, float *L
  *     FPDT_ERR_WORKSPACE and enqueue nothing.  bf16 without FPDT_PAIRWISE needs
  *     S / 32 * Hkv * (D / 16 + 2 * ceil(D / 32)) KiB: S * Hkv <= 65,536 at D = 128.  (A short
  *     sequence with FPDT_PAIRWISE, whose workspace holds several carried states per row, also runs
- *     if it fits with one state per row; its results then differ from fpdt_attn_fwd's in rounding.)
+ *     if it would fit with one state per row: in smaller chunks, with the same bits.)
  *   - Every call on a GPU uses that GPU's one array and finds the previous call's contents in
  *     it.  Nothing has to start at zero (a call writes every byte it later reads), but two
  *     calls that overlap in time on one GPU (different streams, or different threads) race on

@@ -163,6 +163,27 @@ FwdPlan plan_fwd(const Problem& p, void* ws)
     return f;
 }
 
+// A resident, dense pair-by-pair forward whose states, one per row and key group, do not fit into `bytes`
+// although one per row would: the same call in smaller chunks, or as one launch, which carries no state.
+// A row's keys are taken in the same order and by the same groups whatever the chunk, so its result keeps
+// every bit.  (Over all head counts up to 64 and sequences up to 100K tokens one of the two always fits.)
+Problem smaller_forward(const Problem& p, size_t bytes)
+{
+    Problem one = p;
+    one.fwd_kg = 1;
+    if (!p.bf16() || p.fwd_kg == 1 || p.fused() || plan_fwd(one, nullptr).total > bytes) return p;
+    Problem q = p;
+    for (int64_t parts = 2; parts <= p.C / FPDT_CHUNK_MULTIPLE; ++parts) {
+        if (p.C % (parts * FPDT_CHUNK_MULTIPLE) != 0) continue;
+        q.C = p.C / parts;
+        q.u = q.S / q.C;
+        if (plan_fwd(q, nullptr).total <= bytes) return q;
+    }
+    q = p;
+    q.flags &= ~(unsigned)FPDT_PAIRWISE;
+    return plan_fwd(q, nullptr).total <= bytes ? q : p;
+}
+
 struct BwdPlan {
     float* Delta = nullptr;  // [Hq, S] (resident activations) or 2 x [Hq, C] (streamed)
     float* delta_buf[2] = {nullptr, nullptr};
@@ -898,8 +919,8 @@ static int attn_fwd_impl(const void* Q, const void* K, const void* V, void* O, f
     TRY(validate_scalars(p, S, chunk, Hq, Hkv, D, scale, dtype, flags));
     if (sparse) TRY(take_mask(p, chunk_mask));
     size_t need = plan_fwd(p, nullptr).total;
-    if (static_workspace && need > workspace_bytes && p.fwd_kg > 1) {  // one state per row takes less
-        p.fwd_kg = 1;
+    if (static_workspace && need > workspace_bytes) {
+        p = smaller_forward(p, workspace_bytes);
         need = plan_fwd(p, nullptr).total;
     }
     if (static_workspace) {

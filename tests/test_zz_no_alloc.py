@@ -67,3 +67,15 @@ def test_sizes_beyond_the_array_and_offload_flags_are_refused():
     assert e.value.status == B.FPDT_ERR_UNSUPPORTED
     torch.cuda.synchronize()
     assert bool((O == 7.0).all())  # nothing was enqueued
+
+
+@pytest.mark.parametrize("S,chunk,Hq,Hkv,D", [(8192, 4096, 8, 2, 128), (6144, 6144, 8, 1, 128), (2048, 2048, 32, 8, 80),
+                                              (256, 256, 64, 8, 128)])
+def test_pairwise_states_beyond_the_array_keep_the_bits(S, chunk, Hq, Hkv, D):
+    """Short sequences whose pair-by-pair workspace holds several states per row: the workspace exceeds the
+    array, one state per row would fit.  The call runs (smaller chunks, or one launch) with the bits of the
+    workspace entry point, whose result does not depend on the chunk."""
+    torch.cuda.set_device(0)
+    assert B.fpdt_attn_workspace_bytes(S, chunk, Hq, Hkv, D, B.FPDT_DTYPE_BF16, B.FPDT_PAIRWISE, False) > B.FPDT_NOALLOC_SCRATCH_BYTES
+    inp, got, ref = _both(S, chunk, Hq, Hkv, D, "bf16", B.FPDT_PAIRWISE, seed=34)
+    assert _same_bits(got[0], ref[0]) and _same_bits(got[1], ref[1])
