@@ -109,6 +109,13 @@ enum {
  *   Q-outer: dK and dV accumulators 2 * S * Hkv * dpad(D) * 4 bytes (2 GiB at S = 2M,
  *       Hkv = 2), plus Delta S * Hq * 4 unless FPDT_ACT_ON_HOST streams it per chunk;
  * dpad(D) = D rounded up to a multiple of 32.
+ * Both hold, where a launch would leave most of the GPU idle, what lets several workgroups share a
+ * tile: the forward 2 or 4 carried states per row of a chunk (short sequences, pair by pair), the
+ * backward partial dK and dV of the s - 1 (s = 2 .. 16) further workgroups of a key tile, rows * Hkv *
+ * dpad(D) * 8 bytes each (rows = chunk; S in one launch, which then also holds the first's).  The
+ * entry points take a workspace without them too: the forward then runs in smaller chunks (which
+ * offloaded K/V cross the link more often for) with the same bits, or with one state per row where
+ * these do not fit either, the backward with fewer workgroups per key tile and sums in another order.
  */
 size_t fpdt_attn_workspace_bytes(int64_t S, int64_t chunk, int Hq, int Hkv, int D, int dtype,
                                  unsigned flags, int is_bwd);

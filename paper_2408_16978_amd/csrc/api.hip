@@ -4,6 +4,7 @@
 // chunk pair runs when, where its operands live, and which copies overlap which kernels.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdarg>
@@ -163,25 +164,32 @@ FwdPlan plan_fwd(const Problem& p, void* ws)
     return f;
 }
 
-// A resident, dense pair-by-pair forward whose states, one per row and key group, do not fit into `bytes`
-// although one per row would: the same call in smaller chunks, or as one launch, which carries no state.
+// A pair-by-pair forward whose states, one per row and key group, do not fit into `bytes` although one per
+// row would: the same call in smaller chunks, or (resident and dense) as one launch, which carries no state.
 // A row's keys are taken in the same order and by the same groups whatever the chunk, so its result keeps
-// every bit.  (Over all head counts up to 64 and sequences up to 100K tokens one of the two always fits.)
+// every bit.  (Of the resident dense calls with up to 64 heads and 100K tokens one of the two always fits.)
+// Where neither does, one key group.
 Problem smaller_forward(const Problem& p, size_t bytes)
 {
     Problem one = p;
     one.fwd_kg = 1;
     if (!p.bf16() || p.fwd_kg == 1 || p.fused() || plan_fwd(one, nullptr).total > bytes) return p;
-    Problem q = p;
     for (int64_t parts = 2; parts <= p.C / FPDT_CHUNK_MULTIPLE; ++parts) {
         if (p.C % (parts * FPDT_CHUNK_MULTIPLE) != 0) continue;
+        Problem q = p;
         q.C = p.C / parts;
         q.u = q.S / q.C;
-        if (plan_fwd(q, nullptr).total <= bytes) return q;
+        if (plan_fwd(q, nullptr).total > bytes) continue;
+        if (!p.mask.empty())
+            q.mask.resize((size_t)(q.u * q.u));
+        for (int64_t m = 0; m < q.u && !p.mask.empty(); ++m)
+            for (int64_t i = 0; i < q.u; ++i) q.mask[(size_t)(m * q.u + i)] = p.mask[(size_t)(m / parts * p.u + i / parts)];
+        return q;
     }
-    q = p;
-    q.flags &= ~(unsigned)FPDT_PAIRWISE;
-    return plan_fwd(q, nullptr).total <= bytes ? q : p;
+    Problem launch = p;
+    launch.flags &= ~(unsigned)FPDT_PAIRWISE;
+    if (p.mask.empty() && launch.fused() && plan_fwd(launch, nullptr).total <= bytes) return launch;
+    return one;
 }
 
 struct BwdPlan {
@@ -202,7 +210,8 @@ struct BwdPlan {
     size_t total = 0;
 };
 
-BwdPlan plan_bwd(const Problem& p, void* ws)
+// `have`: bytes of the workspace; the splits of the dK/dV launches are halved until their partial sums fit
+BwdPlan plan_bwd(const Problem& p, void* ws, size_t have = SIZE_MAX, int most_splits = 16)
 {
     BwdPlan f;
     Bump b(ws);
@@ -218,7 +227,7 @@ BwdPlan plan_bwd(const Problem& p, void* ws)
         f.Vnat = b.take((size_t)(rows / 32) * p.Hkv * nat_block_bytes(p.D));
         if (!p.act_host()) f.Delta = b.take<float>((size_t)p.Hq * p.S * 4);
         f.stat2 = b.take<float>((size_t)(rows / 32) * p.Hq * 64 * 4);
-        f.dkdv_splits = bwd_dkdv_splits(rows, rows, p.Hq, p.Hkv, p.D, p.fused());
+        f.dkdv_splits = std::min(most_splits, bwd_dkdv_splits(rows, rows, p.Hq, p.Hkv, p.D, p.fused()));
         if (f.dkdv_splits > 1) f.dkdv_part = b.take<float>(bwd_part_dkdv_bytes(rows, p.Hkv, p.D, f.dkdv_splits));
         if (p.fused()) {
             if (f.dkdv_splits > 1) {  // split 0's share
@@ -248,6 +257,7 @@ BwdPlan plan_bwd(const Problem& p, void* ws)
         }
     }
     f.total = (b.off + 255) & ~(size_t)255;
+    if (f.total > have && f.dkdv_splits > 1) return plan_bwd(p, ws, have, f.dkdv_splits / 2);
     return f;
 }
 
@@ -919,7 +929,7 @@ static int attn_fwd_impl(const void* Q, const void* K, const void* V, void* O, f
     TRY(validate_scalars(p, S, chunk, Hq, Hkv, D, scale, dtype, flags));
     if (sparse) TRY(take_mask(p, chunk_mask));
     size_t need = plan_fwd(p, nullptr).total;
-    if (static_workspace && need > workspace_bytes) {
+    if (need > workspace_bytes) {
         p = smaller_forward(p, workspace_bytes);
         need = plan_fwd(p, nullptr).total;
     }
@@ -992,7 +1002,11 @@ static int attn_bwd_impl(const void* Q, const void* K, const void* V, const void
     Problem p;
     TRY(validate_scalars(p, S, chunk, Hq, Hkv, D, scale, dtype, flags));
     if (sparse) TRY(take_mask(p, chunk_mask));
-    const size_t need = plan_bwd(p, nullptr).total;
+    size_t need = plan_bwd(p, nullptr).total;
+    if (need > workspace_bytes) {
+        const size_t least = plan_bwd(p, nullptr, workspace_bytes).total;
+        if (least <= workspace_bytes) need = least;  // (otherwise the error names what the call wants)
+    }
     if (need && (!workspace || workspace_bytes < need || reinterpret_cast<uintptr_t>(workspace) % 256))
         TRY(check_workspace(workspace, workspace_bytes, need));
     const size_t qbytes = (size_t)S * Hq * D * p.esize(), kbytes = (size_t)S * Hkv * D * p.esize();
@@ -1006,7 +1020,7 @@ static int attn_bwd_impl(const void* Q, const void* K, const void* V, const void
     TRY(check_ptr(dK, kbytes, p.kv_host(), "dK"));
     TRY(check_ptr(dV, kbytes, p.kv_host(), "dV"));
     TRY(check_workspace(workspace, workspace_bytes, need));
-    const BwdPlan f = plan_bwd(p, workspace);
+    const BwdPlan f = plan_bwd(p, workspace, workspace_bytes);
     hipStream_t st = static_cast<hipStream_t>(stream);
     std::lock_guard<std::mutex> lock(g_mu);
     if (!p.bf16())

@@ -136,6 +136,35 @@ def test_workspace_sizes():
         == (1 << 21) * 8 * 128 * 4 - 2 * (1 << 21) * 2 * 128 * 4 - (65536 * 8 * 128 * 4 - 2 * 65536 * 2 * 128 * 4)
 
 
+def shared_tile_shares(S, chunk, Hq, Hkv, D, flags):
+    """(forward, backward) workspace without the states and partial sums that let workgroups and waves share
+    a tile: packed operands, one carried state per row, Delta, row statistics, accumulators (KV-outer)."""
+    dp, nat, tr = (D + 31) // 32 * 32, D // 16 * 1024, (D + 31) // 32 * 2048
+    pairs = flags & B.FPDT_PAIRWISE
+    rows = chunk if pairs else S
+    fwd = rows // 32 * Hkv * (nat + tr) + (rows * Hq * (dp * 4 + 16) if pairs else 0)
+    bwd = rows // 32 * 2 * (Hq + Hkv) * nat + Hq * S * 4 + rows // 32 * Hq * 256
+    if pairs:
+        bwd += S * Hq * dp * 4 + 2 * chunk * Hkv * dp * 4
+    return fwd, bwd
+
+
+SHARED_TILE_CALLS = [(8192, 8192, 8, 2, 128, 0), (65536, 65536, 8, 1, 128, 0), (4096, 2048, 8, 2, 128, B.FPDT_PAIRWISE),
+                     (512, 256, 16, 4, 80, B.FPDT_PAIRWISE)]
+
+
+@pytest.mark.parametrize("S,chunk,Hq,Hkv,D,flags", SHARED_TILE_CALLS)
+def test_workspace_of_an_unshared_tile_is_enough(lib, S, chunk, Hq, Hkv, D, flags):
+    """What lets workgroups share a tile is asked for, not insisted on: the calls get past the workspace check
+    (to the pointers, which are no memory) with a workspace that holds none of it, but not with less."""
+    fwd, bwd = shared_tile_shares(S, chunk, Hq, Hkv, D, flags)
+    assert B.fpdt_attn_workspace_bytes(S, chunk, Hq, Hkv, D, B.FPDT_DTYPE_BF16, flags, True) > bwd
+    call_b = lambda n: lib.fpdt_attn_bwd(*([0x1000] * 9), S, chunk, Hq, Hkv, D, 0.125, B.FPDT_DTYPE_BF16, flags, 0x100000, n, None)
+    assert call_b(bwd) != B.FPDT_ERR_WORKSPACE and call_b(bwd - 256) == B.FPDT_ERR_WORKSPACE
+    call_f = lambda n: _fwd(lib, S=S, chunk=chunk, Hq=Hq, Hkv=Hkv, D=D, flags=flags, ws_bytes=n)
+    assert call_f(fwd) != B.FPDT_ERR_WORKSPACE and call_f(fwd - 256) == B.FPDT_ERR_WORKSPACE
+
+
 def test_pick_chunk_host_logic(lib):
     BF, F32 = B.FPDT_DTYPE_BF16, B.FPDT_DTYPE_F32
     # largest divisor of S up to the 64K knee of the measured curve

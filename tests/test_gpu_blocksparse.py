@@ -9,6 +9,7 @@ from paper_2408_16978_amd import inputs, runner
 from oracle import definition
 
 import parity
+from test_abi import shared_tile_shares
 
 pytestmark = pytest.mark.gpu
 
@@ -139,3 +140,23 @@ def test_bad_masks_are_rejected():
                                             b.LSE.data_ptr(), S, chunk, Hq, Hkv, D, D ** -0.5, 1, 0, None,
                                             b.ws_fwd.data_ptr(), b.ws_fwd.numel(), None)
     assert st == B.FPDT_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("kv_host", [0, B.FPDT_KV_ON_HOST])
+def test_forward_in_the_smallest_workspace_keeps_the_bits(kv_host):
+    """One carried state per row: the call runs in smaller chunks under the same mask, resident and offloaded."""
+    S, chunk, Hq, Hkv, D = 4096, 1024, 8, 2, 128
+    print("[case] block-sparse, smallest workspace", kv_host, flush=True)
+    Q, K, V, dO = inputs.make_qkvdo(S, Hq, Hkv, D, "bf16", seed=30)
+    mask = chunk_mask(S // chunk, 31)
+    mask[3] = [True, False, True, True]
+    want = run(Q, K, V, dO, chunk, D ** -0.5, mask)
+    b = runner.make_buffers(Q, K, V, dO, chunk, D ** -0.5, kv_host, bwd=False, chunk_mask=mask)
+    n = shared_tile_shares(S, chunk, Hq, Hkv, D, B.FPDT_PAIRWISE)[0] + (4 * chunk * Hkv * D * 2 if kv_host else 0)
+    assert n < b.ws_fwd.numel()
+    t = torch.full((n + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    b.ws_fwd = t[:n]
+    runner.forward(b)
+    torch.cuda.synchronize()
+    assert torch.equal(b.O, want["O"]) and torch.equal(b.LSE, want["LSE"])
+    assert bool((t[n:] == 0x5A).all())

@@ -9,6 +9,7 @@ from paper_2408_16978_amd import inputs, runner
 from oracle import chunked
 
 import parity
+from test_abi import SHARED_TILE_CALLS, shared_tile_shares
 
 pytestmark = pytest.mark.gpu
 
@@ -366,3 +367,27 @@ def test_fp32_scores_that_overflow_to_minus_infinity(D, chunk):
     out = run(Q, K, V, dO, chunk, scale, B.FPDT_PAIRWISE)
     print(parity.check_all(out, ref, False, names=("O", "LSE", "dQ", "dV")))
     print(parity.check("dK", out["dK"][:, :, 1:], ref["dK"][:, :, 1:], False))
+
+
+@pytest.mark.parametrize("S,chunk,Hq,Hkv,D,flags", SHARED_TILE_CALLS[2:] + [(2048, 2048, 8, 2, 128, 0), (3072, 1536, 8, 1, 64, B.FPDT_PAIRWISE)])
+def test_bf16_in_the_smallest_workspace(S, chunk, Hq, Hkv, D, flags):
+    """A workspace without the states and partial sums of shared tiles: the forward keeps its bits, the backward
+    meets the oracle, and neither writes behind its end."""
+    announce("bf16 smallest workspace", S, chunk, Hq, Hkv, D, flags)
+    Q, K, V, dO = inputs.make_qkvdo(S, Hq, Hkv, D, "bf16", seed=22)
+    scale = D ** -0.5
+    want = run(Q, K, V, dO, chunk, scale, flags)
+    b = runner.make_buffers(Q, K, V, dO, chunk, scale, flags)
+    ends = []
+    for name, n in zip(("ws_fwd", "ws_bwd"), shared_tile_shares(S, chunk, Hq, Hkv, D, flags)):
+        t = torch.full((n + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+        setattr(b, name, t[:n])
+        ends.append(t[n:])
+    runner.forward(b)
+    runner.backward(b)
+    torch.cuda.synchronize()
+    assert torch.equal(b.O, want["O"]) and torch.equal(b.LSE, want["LSE"])
+    ref = parity.oracle_full(Q, K, V, dO, scale)
+    print(parity.check_all({"dQ": b.dQ, "dK": b.dK, "dV": b.dV}, ref, True, names=("dQ", "dK", "dV")))
+    for t in ends:
+        assert bool((t == 0x5A).all())
