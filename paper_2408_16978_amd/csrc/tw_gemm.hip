@@ -522,13 +522,29 @@ int pool_take(Pool& p, size_t bytes, char** out)
 
 constexpr int64_t MAX_PITCH = (int64_t)1 << 23;  // of rows along k
 
+// The bytes that a product writes
+struct Written {
+    const void* C;
+    int64_t rows, cols, ld;
+    int size;
+    bool overlaps(const void* X, int64_t R, int64_t cols_x, int64_t ld_x) const
+    {
+        const uintptr_t c = reinterpret_cast<uintptr_t>(C), x = reinterpret_cast<uintptr_t>(X);
+        return x < c + (uintptr_t)((rows - 1) * ld + cols) * size && c < x + (uintptr_t)((R - 1) * ld_x + cols_x) * 2;
+    }
+};
+
 // X [R, C], leading dimension ld, as the product kernel can read it: in place, or copied.  `k_rows`: the
 // contraction runs over the rows of X.  `padded`: rows are followed by zeros up to a multiple of 8.
-int take_operand(Pool& pool, const void* X, int64_t R, int64_t C, int64_t ld, bool k_rows, bool padded, bool cache, hipStream_t st, Operand* res)
+// An operand that the product itself overwrites (Y in the place of X) is copied: tiles are stored while
+// others still read their rows.
+int take_operand(Pool& pool, const void* X, int64_t R, int64_t C, int64_t ld, bool k_rows, bool padded, bool cache, const Written& out,
+                 hipStream_t st, Operand* res)
 {
     const int64_t K = k_rows ? R : C;
     res->rows = (int)(k_rows ? (C + 7) / 8 * 8 : R);
-    if (K >= SK && (C % 8 == 0 || padded) && ld % 8 == 0 && (k_rows || ld < MAX_PITCH) && reinterpret_cast<uintptr_t>(X) % 16 == 0) {
+    if (K >= SK && (C % 8 == 0 || padded) && ld % 8 == 0 && (k_rows || ld < MAX_PITCH) && reinterpret_cast<uintptr_t>(X) % 16 == 0 &&
+        !out.overlaps(X, R, C, ld)) {
         res->p = static_cast<const uint16_t*>(X);
         res->ld = ld;
     } else {
@@ -629,11 +645,12 @@ static int product(Pool& pool, int a_transposed, int b_transposed, int M, int N,
     const Plan plan = plan_product(M, N, Kp / SK);
     if (plan.u.tiles == 0) return 2;
     // Aop[m,k]: A stored [M,K] (as is) or [K,M] (transposed); Bop[n,k]: B stored [N,K] or [K,N]
+    const Written out = {C, M, N, ldc, c_f32 ? 4 : 2};
     Operand pa, pb;
-    int rc = take_operand(pool, B, b_transposed ? K : N, b_transposed ? N : K, ldb, b_transposed, false, cache_b, st, &pb);
+    int rc = take_operand(pool, B, b_transposed ? K : N, b_transposed ? N : K, ldb, b_transposed, false, cache_b, out, st, &pb);
     if (rc) return rc;
     const size_t mark = pool.off;  // what follows is scratch of this product only
-    rc = take_operand(pool, A, a_transposed ? K : M, a_transposed ? M : K, lda, a_transposed, lda > (a_transposed ? M : K), false, st, &pa);
+    rc = take_operand(pool, A, a_transposed ? K : M, a_transposed ? M : K, lda, a_transposed, lda > (a_transposed ? M : K), false, out, st, &pa);
     if (rc) return rc;
     float* part = nullptr;
     if (plan.u.splits > 1) {
@@ -678,9 +695,10 @@ int gemm(int a_transposed, int b_transposed, int M, int N, int K, const void* A,
         const char* base0 = pool.base;
         const size_t off0 = pool.off;
         Operand a, b;
-        // (a segment of a long row is never read in place: its pitch is the row's)
-        int rc = take_operand(pool, static_cast<const uint16_t*>(B) + (b_transposed ? k0 * ldb : k0), b_transposed ? k : N, b_transposed ? N : k, ldb, b_transposed, false, false, st, &b);
-        if (!rc) rc = take_operand(pool, static_cast<const uint16_t*>(A) + (a_transposed ? k0 * lda : k0), a_transposed ? k : M, a_transposed ? M : k, lda, a_transposed, false, false, st, &a);
+        // (a segment of a long row is never read in place: its pitch is the row's; C is written behind all of them)
+        const Written out = {part, 1, 1, 1, 4};
+        int rc = take_operand(pool, static_cast<const uint16_t*>(B) + (b_transposed ? k0 * ldb : k0), b_transposed ? k : N, b_transposed ? N : k, ldb, b_transposed, false, false, out, st, &b);
+        if (!rc) rc = take_operand(pool, static_cast<const uint16_t*>(A) + (a_transposed ? k0 * lda : k0), a_transposed ? k : M, a_transposed ? M : k, lda, a_transposed, false, false, out, st, &a);
         if (rc) return rc;
         Plan one = plan;
         one.u.splits = 1;

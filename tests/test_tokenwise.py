@@ -458,3 +458,22 @@ def test_gpu_linear_rows_of_eight_million():
     torch.cuda.synchronize()
     ref = (X.double() @ W.double().t()).cpu().numpy()
     _rowwise_ok("Y", Y.double().cpu().numpy(), ref, rel=4e-4)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,n,n_chunks", [(4100, 1024, 1), (700, 264, 3), (33, 40, 1), (300, 8192, 2)])
+def test_gpu_linear_in_place(rows, n, n_chunks):
+    """Y in the place of X and dX in that of dY: against the same calls on tensors of their own (another
+    chunking of the same sums at most: half a bf16 ulp of the stored value plus fp32 rounding)."""
+    print("[case] linear in place", rows, n, n_chunks, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    X = torch.randn(rows, n, device="cuda", generator=g).to(torch.bfloat16)
+    W = (torch.randn(n, n, device="cuda", generator=g) * n ** -0.5).to(torch.bfloat16)
+    f64 = lambda t: t.double().cpu().numpy()
+    ref = otw.linear(f64(X), f64(W), f64(X))
+    Y, dX = X.clone(), X.clone()
+    TW.fpdt_tw_linear_fwd(Y, W, Y, n_chunks)
+    TW.fpdt_tw_linear_bwd(X, W, dX, dX, None, n_chunks)
+    torch.cuda.synchronize()
+    _rowwise_ok("Y", f64(Y), ref["Y"], rel=1e-4)
+    _rowwise_ok("dX", f64(dX), ref["dX"], rel=1e-4)
