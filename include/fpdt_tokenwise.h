@@ -73,7 +73,8 @@ int fpdt_tw_loss_fwd_bwd(const void *H, const void *W, const int32_t *target, fl
  * needs no workspace.  Backward:
  *     dX = dY W  (written, bf16; NULL to skip),   dW += dY^T X  (accumulated, fp32; NULL to skip)
  * dW is summed ceil(rows / n_chunks) rows at a time; Y and dX, whose rows are independent and which
- * have no intermediates, are computed over all rows at once.
+ * have no intermediates, are computed over all rows at once, or chunk by chunk where X or dY has to be
+ * copied first (rows that are not 16-byte aligned, or Y in the place of X, dX in that of dY: allowed).
  */
 int fpdt_tw_linear_fwd(const void *X, const void *W, void *Y, int64_t rows, int n_in, int n_out,
                        int n_chunks, void *stream);

@@ -252,6 +252,15 @@ int check_chunking(int64_t rows, int n_chunks)
     return TW_OK;
 }
 
+// Rows of a projection's product out [rows, cols] = A [rows, k] * ..  A row is its own dot products and nothing
+// lives between the chunks: one product over all rows fills the chip better than one per chunk (16384 x 4096
+// x 6144 in four chunks, Y and dX: 2506 -> 2251 us for forward and backward).  Where A has to be copied (its rows
+// are not 16-byte aligned, or `out` is in its place) the chunks bound the copy: one chunk at a time.
+int64_t product_rows(const void* A, int64_t rows, int k, const void* out, int cols, int n_chunks)
+{
+    return fpdt_tw::reads_in_place(A, rows, k, out, cols) ? MAX_ROWS : (rows + n_chunks - 1) / n_chunks;
+}
+
 }  // namespace
 
 extern "C" {
@@ -268,11 +277,9 @@ int fpdt_tw_linear_fwd(const void* X, const void* W, void* Y, int64_t rows, int 
     std::lock_guard<std::mutex> lock(g_mu);
     gemm_handle h;
     if ((rc = get_handle(&h, st)) != TW_OK) return rc;
-    // A row of Y is its own dot products and nothing lives between the chunks: one product over all rows
-    // fills the chip better than one per chunk (16384 x 4096 x 6144 in four chunks, with dX
-    // in the backward: 2506 -> 2251 us for forward and backward).
-    for (int64_t r0 = 0; r0 < rows; r0 += MAX_ROWS) {
-        const int n = (int)(rows - r0 < MAX_ROWS ? rows - r0 : MAX_ROWS);
+    const int64_t step = product_rows(X, rows, n_in, Y, n_out, n_chunks);
+    for (int64_t r0 = 0; r0 < rows; r0 += step) {
+        const int n = (int)(rows - r0 < step ? rows - r0 : step);
         rc = gemm_nt(h, n, n_out, n_in, static_cast<const char*>(X) + (size_t)r0 * n_in * 2, W,
                      static_cast<char*>(Y) + (size_t)r0 * n_out * 2, TW_C_BF16, 0.f);
         if (rc != TW_OK) return rc;
@@ -293,8 +300,9 @@ int fpdt_tw_linear_bwd(const void* X, const void* W, const void* dY, void* dX, f
     std::lock_guard<std::mutex> lock(g_mu);
     gemm_handle h;
     if ((rc = get_handle(&h, st)) != TW_OK) return rc;
-    for (int64_t r0 = 0; dX && r0 < rows; r0 += MAX_ROWS) {  // dX[n, n_in] = dY[n, n_out] W[n_out, n_in], as in the forward
-        const int n = (int)(rows - r0 < MAX_ROWS ? rows - r0 : MAX_ROWS);
+    const int64_t step = dX ? product_rows(dY, rows, n_out, dX, n_in, n_chunks) : 0;
+    for (int64_t r0 = 0; dX && r0 < rows; r0 += step) {  // dX[n, n_in] = dY[n, n_out] W[n_out, n_in], as in the forward
+        const int n = (int)(rows - r0 < step ? rows - r0 : step);
         rc = gemm_nn(h, n, n_in, n_out, static_cast<const char*>(dY) + (size_t)r0 * n_out * 2, W,
                      static_cast<char*>(dX) + (size_t)r0 * n_in * 2, TW_C_BF16, 0.f);
         if (rc != TW_OK) return rc;

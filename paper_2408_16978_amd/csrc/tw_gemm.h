@@ -11,6 +11,9 @@ void begin_call();
 // Device scratch that lives until the next begin_call; null if there is not enough memory.
 void* scratch(size_t bytes);
 
+// Does the product C [rows, cols] bf16 = A [rows, k] * .. read A where it is (and not a copy in scratch)?
+bool reads_in_place(const void* A, int64_t rows, int64_t k, const void* C, int64_t cols);
+
 // C[M,N] (+)= sum_k Aop[m,k] * Bop[n,k], bf16 operands, fp32 accumulation.
 //   a_transposed = 0: A is stored [M,K] (leading dimension lda); 1: A is stored [K,M]
 //   b_transposed = 0: B is stored [N,K] (ldb);                   1: B is stored [K,N]

@@ -534,6 +534,13 @@ struct Written {
     }
 };
 
+// Can the product kernel read X [R, C] where it is?
+bool readable(const void* X, int64_t R, int64_t C, int64_t ld, bool k_rows, bool padded, const Written& out)
+{
+    return (k_rows ? R : C) >= SK && (C % 8 == 0 || padded) && ld % 8 == 0 && (k_rows || ld < MAX_PITCH) && reinterpret_cast<uintptr_t>(X) % 16 == 0 &&
+           !out.overlaps(X, R, C, ld);
+}
+
 // X [R, C], leading dimension ld, as the product kernel can read it: in place, or copied.  `k_rows`: the
 // contraction runs over the rows of X.  `padded`: rows are followed by zeros up to a multiple of 8.
 // An operand that the product itself overwrites (Y in the place of X) is copied: tiles are stored while
@@ -541,10 +548,8 @@ struct Written {
 int take_operand(Pool& pool, const void* X, int64_t R, int64_t C, int64_t ld, bool k_rows, bool padded, bool cache, const Written& out,
                  hipStream_t st, Operand* res)
 {
-    const int64_t K = k_rows ? R : C;
     res->rows = (int)(k_rows ? (C + 7) / 8 * 8 : R);
-    if (K >= SK && (C % 8 == 0 || padded) && ld % 8 == 0 && (k_rows || ld < MAX_PITCH) && reinterpret_cast<uintptr_t>(X) % 16 == 0 &&
-        !out.overlaps(X, R, C, ld)) {
+    if (readable(X, R, C, ld, k_rows, padded, out)) {
         res->p = static_cast<const uint16_t*>(X);
         res->ld = ld;
     } else {
@@ -577,6 +582,11 @@ void begin_call()
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return;
     g_cache.clear();
     g_pool[dev].off = 0;  // everything enqueued earlier on the stream is ordered before what follows
+}
+
+bool reads_in_place(const void* A, int64_t rows, int64_t k, const void* C, int64_t cols)
+{
+    return readable(A, rows, k, k, false, false, Written{C, rows, cols, cols, 2});
 }
 
 void* scratch(size_t bytes)

@@ -477,3 +477,22 @@ def test_gpu_linear_in_place(rows, n, n_chunks):
     torch.cuda.synchronize()
     _rowwise_ok("Y", f64(Y), ref["Y"], rel=1e-4)
     _rowwise_ok("dX", f64(dX), ref["dX"], rel=1e-4)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_in,in_place", [(2049, False), (264, True)])
+def test_gpu_linear_copies_one_chunk_at_a_time(n_in, in_place):
+    """A projection whose X cannot be read where it is copies a chunk, not all of X, to scratch: with X of
+    4.3 GB (2.2 GB in place) in 64 chunks the pool, which is kept, takes under 512 MiB."""
+    n_out, n_chunks = (n_in if in_place else 8), 64
+    rows = (1 << 20) if not in_place else (1 << 22)
+    print("[case] linear chunk copies", rows, n_in, in_place, flush=True)
+    X = torch.zeros(rows, n_in, dtype=torch.bfloat16, device="cuda")
+    W = torch.zeros(n_out, n_in, dtype=torch.bfloat16, device="cuda")
+    Y = X if in_place else torch.empty(rows, n_out, dtype=torch.bfloat16, device="cuda")
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    TW.fpdt_tw_linear_fwd(X, W, Y, n_chunks)
+    torch.cuda.synchronize()
+    assert before - torch.cuda.mem_get_info()[0] <= 512 << 20
+    assert not bool(Y.any())
