@@ -520,7 +520,9 @@ int pool_take(Pool& p, size_t bytes, char** out)
     return 0;
 }
 
-constexpr int64_t MAX_PITCH = (int64_t)1 << 23;  // of rows along k
+// A lane's offset within its tile (255 rows of form N, 7 of form T) is kept in 32 bits
+constexpr int64_t MAX_PITCH = (int64_t)1 << 23;    // elements between rows along k
+constexpr int64_t MAX_PITCH_T = (int64_t)1 << 28;  // and between the rows of k, form T
 
 // The bytes that a product writes
 struct Written {
@@ -537,8 +539,8 @@ struct Written {
 // Can the product kernel read X [R, C] where it is?
 bool readable(const void* X, int64_t R, int64_t C, int64_t ld, bool k_rows, bool padded, const Written& out)
 {
-    return (k_rows ? R : C) >= SK && (C % 8 == 0 || padded) && ld % 8 == 0 && (k_rows || ld < MAX_PITCH) && reinterpret_cast<uintptr_t>(X) % 16 == 0 &&
-           !out.overlaps(X, R, C, ld);
+    return (k_rows ? R : C) >= SK && (C % 8 == 0 || padded) && ld % 8 == 0 && ld < (k_rows ? MAX_PITCH_T : MAX_PITCH) &&
+           reinterpret_cast<uintptr_t>(X) % 16 == 0 && !out.overlaps(X, R, C, ld);
 }
 
 // X [R, C], leading dimension ld, as the product kernel can read it: in place, or copied.  `k_rows`: the
@@ -569,8 +571,7 @@ int take_operand(Pool& pool, const void* X, int64_t R, int64_t C, int64_t ld, bo
             if (cache) g_cache.push_back({X, R, C, ld, R2, C2, res->p});
         }
     }
-    // a lane's offset within its tile (255 rows of form N, 7 of form T) is kept in 32 bits
-    return res->ld >= (k_rows ? (int64_t)1 << 28 : MAX_PITCH) ? 2 : 0;
+    return res->ld >= (k_rows ? MAX_PITCH_T : MAX_PITCH) ? 2 : 0;
 }
 
 }  // namespace
@@ -679,14 +680,28 @@ static int product(Pool& pool, int a_transposed, int b_transposed, int M, int N,
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
-int gemm(int a_transposed, int b_transposed, int M, int N, int K, const void* A, int64_t lda, const void* B,
-         int64_t ldb, void* C, int64_t ldc, bool c_f32, bool accumulate, bool cache_b, hipStream_t st)
+static int any_product(Pool& pool, int a_transposed, int b_transposed, int M, int N, int K, const void* A, int64_t lda, const void* B,
+                       int64_t ldb, void* C, int64_t ldc, bool c_f32, bool accumulate, bool cache_b, hipStream_t st)
 {
-    std::lock_guard<std::mutex> lk(g_mu);
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 1;
-    Pool& pool = g_pool[dev];
-    if (M <= 0 || N <= 0 || K <= 0) return 2;
+    // Rows of k too far apart (form T, an operand of more than 2^28 columns): the columns, which are rows or
+    // columns of C, in segments, whose copies have a shorter pitch.
+    constexpr int SEG_T = 1 << 24;
+    if (b_transposed && ldb >= MAX_PITCH_T && N > SEG_T) {
+        for (int64_t n0 = 0; n0 < N; n0 += SEG_T) {
+            const int rc = any_product(pool, a_transposed, b_transposed, M, (int)(N - n0 < SEG_T ? N - n0 : SEG_T), K, A, lda, static_cast<const uint16_t*>(B) + n0, ldb,
+                                       static_cast<char*>(C) + n0 * (c_f32 ? 4 : 2), ldc, c_f32, accumulate, false, st);
+            if (rc) return rc;
+        }
+        return 0;
+    }
+    if (a_transposed && lda >= MAX_PITCH_T && M > SEG_T) {
+        for (int64_t m0 = 0; m0 < M; m0 += SEG_T) {
+            const int rc = any_product(pool, a_transposed, b_transposed, (int)(M - m0 < SEG_T ? M - m0 : SEG_T), N, K, static_cast<const uint16_t*>(A) + m0, lda, B, ldb,
+                                       static_cast<char*>(C) + (size_t)m0 * ldc * (c_f32 ? 4 : 2), ldc, c_f32, accumulate, cache_b, st);
+            if (rc) return rc;
+        }
+        return 0;
+    }
     const bool long_a = !a_transposed && lda >= MAX_PITCH, long_b = !b_transposed && ldb >= MAX_PITCH;
     if (!long_a && !long_b)
         return product(pool, a_transposed, b_transposed, M, N, K, A, lda, B, ldb, C, ldc, c_f32, accumulate, cache_b, st);
@@ -720,6 +735,16 @@ int gemm(int a_transposed, int b_transposed, int M, int N, int K, const void* A,
     }
     launch_split_sum(plan, part, M, N, C, ldc, c_f32, accumulate, st);
     return hipGetLastError() == hipSuccess ? 0 : 1;
+}
+
+int gemm(int a_transposed, int b_transposed, int M, int N, int K, const void* A, int64_t lda, const void* B,
+         int64_t ldb, void* C, int64_t ldc, bool c_f32, bool accumulate, bool cache_b, hipStream_t st)
+{
+    std::lock_guard<std::mutex> lk(g_mu);
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 1;
+    if (M <= 0 || N <= 0 || K <= 0) return 2;
+    return any_product(g_pool[dev], a_transposed, b_transposed, M, N, K, A, lda, B, ldb, C, ldc, c_f32, accumulate, cache_b, st);
 }
 
 }  // namespace fpdt_tw

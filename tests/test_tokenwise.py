@@ -496,3 +496,30 @@ def test_gpu_linear_copies_one_chunk_at_a_time(n_in, in_place):
     torch.cuda.synchronize()
     assert before - torch.cuda.mem_get_info()[0] <= 512 << 20
     assert not bool(Y.any())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,n_in,n_out", [(2, (1 << 28) + 8, 3), (3, 8, (1 << 28) + 24), (33, (1 << 28) + 1, 1)])
+def test_gpu_linear_rows_of_two_hundred_million(rows, n_in, n_out):
+    """Gradients where consecutive rows of k lie further apart than the product kernel's 32-bit offsets reach:
+    the columns run in segments.  Every element against sums of exact products in fp32 (up to 33 terms; where
+    the long width is contracted, against sums in fp64 with the bound of long rows above)."""
+    print("[case] linear very long rows", rows, n_in, n_out, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(4)
+
+    def bf(r, c):  # (randn takes its time at this size)
+        return torch.randint(-127, 128, (r, c), device="cuda", generator=g, dtype=torch.int8).to(torch.bfloat16) / 64
+
+    X, W, dY = bf(rows, n_in), bf(n_out, n_in), bf(rows, n_out)
+    dX, dW = torch.full_like(X, float("nan")), torch.ones(n_out, n_in, device="cuda")
+    TW.fpdt_tw_linear_bwd(X, W, dY, dX, dW, 1)
+    torch.cuda.synchronize()
+    if n_out < 1000:
+        for r in range(rows):
+            want = sum(dY[r, k].float() * W[k].float() for k in range(n_out))
+            assert bool(((dX[r].float() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5).all()), r
+    else:
+        _rowwise_ok("dX", dX.double().cpu().numpy(), (dY.double() @ W.double()).cpu().numpy(), rel=4e-4)
+    for o in range(0, n_out, max(1, n_out // 3)):
+        want = 1 + sum(dY[r, o:o + max(1, n_out // 3), None].float() * X[r].float() for r in range(rows))
+        assert bool(((dW[o:o + max(1, n_out // 3)] - want).abs() <= 1e-5 * want.abs() + 1e-5).all()), o
