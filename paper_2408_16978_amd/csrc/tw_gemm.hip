@@ -501,9 +501,11 @@ int pool_take(Pool& p, size_t bytes, char** out)
 {
     bytes = (bytes + 255) & ~(size_t)255;
     if (p.off + bytes > p.cap) {
-        // grow: a new buffer; the old one stays alive (kernels in flight may read it) until exit
+        // Grow: a new buffer; the old one stays alive (kernels in flight, and the rest of this call, read
+        // it) until exit.  The call's offsets go on as if all of it were in the new buffer, so that it
+        // holds all of the next call of these sizes, which may be captured.
         size_t want = p.cap ? p.cap * 2 : (size_t)256 << 20;
-        while (want < bytes) want *= 2;
+        while (want < p.off + bytes) want *= 2;
         void* nb = nullptr;
         if (hipMalloc(&nb, want) != hipSuccess) {
             (void)hipGetLastError();
@@ -512,8 +514,6 @@ int pool_take(Pool& p, size_t bytes, char** out)
         if (p.base) p.retired.push_back(p.base);
         p.base = static_cast<char*>(nb);
         p.cap = want;
-        p.off = 0;
-        g_cache.clear();  // cached fragments lived in the old buffer
     }
     *out = p.base + p.off;
     p.off += bytes;
@@ -650,7 +650,6 @@ static void launch_split_sum(const Plan& plan, const float* part, int M, int N, 
 static int product(Pool& pool, int a_transposed, int b_transposed, int M, int N, int K, const void* A, int64_t lda, const void* B,
                    int64_t ldb, void* C, int64_t ldc, bool c_f32, bool accumulate, bool cache_b, hipStream_t st)
 {
-    const char* base0 = pool.base;
     const size_t off0 = pool.off;
     const int Kp = K < SK ? SK : K;  // (realigned operands of less are padded to one stage)
     const Plan plan = plan_product(M, N, Kp / SK);
@@ -673,10 +672,8 @@ static int product(Pool& pool, int a_transposed, int b_transposed, int M, int N,
     if (rc) return rc;
     if (plan.u.splits > 1) launch_split_sum(plan, part, M, N, C, ldc, c_f32, accumulate, st);
     // The next product's copies run after this launch on the same stream, so this product's scratch
-    // is free again: everything it took, or everything behind a weight that stays cached.  (Not if
-    // the pool was replaced by a larger one on the way: then nothing is given back until the next
-    // library call.)
-    if (pool.base == base0) pool.off = cache_b ? mark : off0;
+    // is free again: everything it took, or everything behind a weight that stays cached.
+    pool.off = cache_b ? mark : off0;
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
@@ -712,13 +709,13 @@ static int any_product(Pool& pool, int a_transposed, int b_transposed, int M, in
     const int64_t tiles_n = ((int64_t)N + 255) / 256, tiles = ((int64_t)M + 255) / 256 * tiles_n;
     if (tiles > (int64_t)1 << 30) return 2;
     plan.u = {(int)tiles, (int)tiles_n, 0, (int)((K + SEG - 1) / SEG), 0};
+    const size_t off0 = pool.off;
     char* mem = nullptr;
     if (pool_take(pool, part_bytes(plan), &mem)) return 1;
     float* part = reinterpret_cast<float*>(mem);
     for (int i = 0; i < plan.u.splits; ++i) {
         const int64_t k0 = i * SEG, k = K - k0 < SEG ? K - k0 : SEG;
-        const char* base0 = pool.base;
-        const size_t off0 = pool.off;
+        const size_t off1 = pool.off;
         Operand a, b;
         // (a segment of a long row is never read in place: its pitch is the row's; C is written behind all of them)
         const Written out = {part, 1, 1, 1, 4};
@@ -731,9 +728,10 @@ static int any_product(Pool& pool, int a_transposed, int b_transposed, int M, in
         one.u.split_stages = Kp / SK;
         rc = launch_product(one, a_transposed, b_transposed, a, b, M, N, Kp, C, ldc, c_f32, accumulate, part + (size_t)i * (part_bytes(one) / 4), st);
         if (rc) return rc;
-        if (pool.base == base0) pool.off = off0;
+        pool.off = off1;
     }
     launch_split_sum(plan, part, M, N, C, ldc, c_f32, accumulate, st);
+    pool.off = off0;
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 

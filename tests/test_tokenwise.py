@@ -3,6 +3,8 @@ parity of libfpdt_tokenwise.so against the oracle."""
 import math
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -523,3 +525,35 @@ def test_gpu_linear_rows_of_two_hundred_million(rows, n_in, n_out):
     for o in range(0, n_out, max(1, n_out // 3)):
         want = 1 + sum(dY[r, o:o + max(1, n_out // 3), None].float() * X[r].float() for r in range(rows))
         assert bool(((dW[o:o + max(1, n_out // 3)] - want).abs() <= 1e-5 * want.abs() + 1e-5).all()), o
+
+
+@pytest.mark.gpu
+def test_gpu_second_call_of_a_size_finds_its_scratch():
+    """The first call of a size grows the scratch pool, twice here (200 MB of logit gradients, then a 400 MB copy
+    of a weight whose rows are not 16-byte aligned); the second one must not, as it may be captured.  In a
+    process of its own, whose pool is empty."""
+    code = """
+import torch
+from paper_2408_16978_amd import tokenwise as TW
+rows, hidden, vocab = 500, 1001, 200000
+bf = lambda *s: (torch.randn(*s, device="cuda") * hidden ** -0.25).to(torch.bfloat16)
+H, W = bf(rows, hidden), bf(vocab, hidden)
+target = torch.randint(0, vocab, (rows,), device="cuda", dtype=torch.int32)
+loss, lse, dH = torch.empty(rows, device="cuda"), torch.empty(rows, device="cuda"), torch.empty_like(H)
+ws = torch.empty(TW.fpdt_tw_loss_workspace_bytes(rows, hidden, vocab, 2), dtype=torch.uint8, device="cuda")
+call = lambda: TW.fpdt_tw_loss_fwd_bwd(H, W, target, 1.0 / rows, loss, lse, dH, None, 2, ws)
+call()
+torch.cuda.synchronize()
+want = dH.clone()
+graph = torch.cuda.CUDAGraph()
+with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+    call()
+for rep in range(3):
+    dH.fill_(float("nan"))
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(dH, want), rep
+print("replayed")
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "replayed" in r.stdout, r.stderr[-2000:]
