@@ -58,6 +58,10 @@ size_t fpdt_tw_loss_workspace_bytes(int64_t rows, int hidden, int vocab, int n_c
  *   loss, lse [rows] fp32                                                             out
  *   dH [rows, hidden] bf16 or NULL, dW [vocab, hidden] fp32 or NULL                   out / in-out
  *   workspace: device memory, 256-byte aligned, >= fpdt_tw_loss_workspace_bytes(...)
+ * dW is summed in fp32 over as many chunks at a time as make 2 hidden rows (one chunk at least); the
+ * logit gradients of these rows are gathered in the library's scratch, [rows, vocab rounded up to 8],
+ * and the workspace's are then not used (they are where a chunk has more than hidden rows and vocab is
+ * a multiple of 8).  Status 4 if there is no memory for them.
  * A target outside [0, vocab) is not detected (its row's loss is lse_r and its gradient the
  * plain softmax).
  */

@@ -458,15 +458,13 @@ int fpdt_tw_loss_fwd_bwd(const void* H, const void* W, const int32_t* target, fl
     // G then takes the memory of two bf16 copies of W, in the library's scratch.  Rows of G are padded to 16
     // bytes there, so an odd vocabulary takes this way with a single chunk too.
     // Measured (65536 tokens, hidden 4096, 62 chunks): 310 -> 235 ms with `hidden` rows, 210 -> 204 ms from there to twice as many.
-    int64_t per_group = 2 * (int64_t)hidden / c > 1 ? 2 * (int64_t)hidden / c : 1, ldg = vocab;
+    const int64_t per_group = 2 * (int64_t)hidden / c > 1 ? 2 * (int64_t)hidden / c : 1;
+    int64_t ldg = vocab;
     if (bwd && (per_group > 1 || vocab % 8)) {
         const int64_t group_rows = per_group * c < rows ? per_group * c : rows, ld = ((int64_t)vocab + 7) / 8 * 8;
-        if (void* mem = fpdt_tw::scratch((size_t)group_rows * ld * 2)) {
-            G = static_cast<uint16_t*>(mem);
-            ldg = ld;
-        } else {
-            per_group = 1;
-        }
+        G = static_cast<uint16_t*>(fpdt_tw::scratch((size_t)group_rows * ld * 2));
+        if (!G) return gemm_status(1);  // (no smaller groups instead: how dW is summed depends on the arguments alone)
+        ldg = ld;
     }
     for (int64_t g0 = 0; g0 < rows; g0 += per_group * c) {
         const int64_t g1 = rows - g0 < per_group * c ? rows : g0 + per_group * c;
