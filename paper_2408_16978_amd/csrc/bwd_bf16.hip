@@ -19,8 +19,6 @@
 // Both stream their operands global -> LDS directly through a small ring, as NAT fragments
 // (fpdt_internal.h) only: an operand whose contraction runs over rows (Q^T, dO^T, K^T) is read
 // out of the same LDS block with transposing loads.
-#include <algorithm>
-#include <cmath>
 #include <type_traits>
 
 #include "fpdt_internal.h"
@@ -1108,35 +1106,6 @@ static BwdKernelArgs to_kernel_args(const BwdArgs& a)
 }
 
 size_t bwd_part_dkdv_bytes(int64_t n_k, int Hkv, int D, int splits) { return 2 * (size_t)(splits - 1) * bwd_acc_dkv_bytes(n_k, Hkv, D); }
-
-// Into how many splits a dK/dV launch divides the query walk of its key tiles.  Unsplit it has n_k / 256
-// * Hkv workgroups of four waves, one per compute unit: 64 at 8K tokens and two KV heads, so that three
-// quarters of the chip idle, and below the diagonal's last rows the longest workgroup decides.  Each
-// split adds a partial dK, dV (written once, read once by dkdv_sum_kernel).  The count is the cheapest
-// of 1, 2, 4, .. 16 in units of steps (one 32-query block of one head; 1.7 us per workgroup, measured):
-//   whole pair    rounds of 256 workgroups x (steps of a workgroup + its fixed cost)
-//   causal pair   list scheduling of lengths that fall linearly to zero: the longest, or the average load
-//   partials      (splits + 1) passes at 4.5 bytes per ns, one more launch
-// Measured (dK/dV with its sum, before -> after): 8K tokens, 8 query / 2 KV heads, D = 128: 1357 -> 274 us
-// (8 splits); pairs of 32K chunks, 8 / 1 heads: 12.77 -> 7.33 ms (4 splits), 8 / 2 heads: 7.66 -> 7.15 ms (2:
-// only the diagonal pairs gain); pairs of 16K chunks, 8 / 2 heads: 3.07 -> 1.76 ms (4).
-int bwd_dkdv_splits(int64_t n_q, int64_t n_k, int Hq, int Hkv, int D, bool causal_launch)
-{
-    const double cus = 256.0, fixed = 12.0, us_per_step = 1.7;
-    const double wgs = (double)(n_k / bwd_k_tile(D)) * Hkv, steps = (double)(n_q / 32) * (Hq / Hkv);
-    int best = 1;
-    double best_cost = 0.0;
-    for (int s = 1; s <= 16; s *= 2) {
-        if (s > 1 && steps / s < 8.0) break;
-        const double w = wgs * s, len = steps / s;
-        const double full = std::ceil(w / cus) * (len + fixed);
-        const double causal = std::max(len + fixed, w / cus * (len / 2 + fixed) + len / 4);
-        const double sum = s == 1 ? 0.0 : ((double)(s + 1) * 2 * (double)bwd_acc_dkv_bytes(n_k, Hkv, D) / 4.5e6 + 6.0) / us_per_step;
-        const double cost = sum + (causal_launch ? causal : (full + causal) / 2);
-        if (s == 1 || cost < 0.97 * best_cost) { best = s; best_cost = cost; }
-    }
-    return best;
-}
 
 void launch_bwd_dkdv(const BwdArgs& a, hipStream_t st)
 {

@@ -8,6 +8,8 @@
 
 #include <initializer_list>
 
+#include "launch_rules.h"
+
 namespace fpdt {
 
 typedef uint16_t bf16_bits;  // storage type of a bfloat16 element on the host side
@@ -45,29 +47,6 @@ void launch_pack(std::initializer_list<PackJob> tensors, int64_t rows, int D, in
 // bf16 forward sweep: query rows [q_pos0, q_pos0 + n_q) against keys
 // [k_pos0, k_pos0 + n_keys) (causal: key position <= query position).
 // ---------------------------------------------------------------------------
-// Key groups of a forward or dQ launch (a workgroup of eight waves = 8 / KG row blocks of 32 queries x KG
-// waves that share the keys): the cheapest of 1, 2, 4 in units of a 64-key tile of eight row blocks.  A
-// launch on the diagonal lasts as long as its longest row tile or as the average load of the 256 compute
-// units; KG > 1 divides the first, and costs a little more per tile (copies and barriers per MFMA).
-// Measured (us for KG = 1, 2, 4; forward | dQ): 2K tokens, 8 heads, D = 128: 57, 38, 29 | 77, 50, 35;
-// 8K: 216, 169, 207 | 303, 230, 270; 16K: 535, 592, 684 | 753, 812, 903; 32K, 2 heads, D = 64: 517, 388,
-// 354 | 670, 461, 477.
-static inline int sweep_key_groups(int64_t n_q, int64_t n_keys, int Hq, bool causal)
-{
-    const double tiles = (double)n_keys / 64.0, cus = 256.0;
-    int best = 1;
-    double best_cost = 0.0;
-    for (int kg = 1; kg <= 4; kg *= 2) {
-        const double work = kg == 1 ? 1.0 : kg == 2 ? 1.08 : 1.15, wgs = (double)n_q / 256.0 * kg * Hq;
-        const double longest = tiles / kg * work + 2.0;
-        const double load = (double)(int64_t)((wgs + cus - 1.0) / cus) * longest;       // below the diagonal
-        const double mean = wgs / cus * (tiles / kg / 2 * work + 2.0) + longest / 4.0;  // on it
-        const double cost = causal ? (mean > longest ? mean : longest) : load;
-        if (kg == 1 || cost < 0.97 * best_cost) { best = kg; best_cost = cost; }
-    }
-    return best;
-}
-
 enum { SWEEP_INIT = 1, SWEEP_FINAL = 2 };
 
 struct FwdArgs {
@@ -148,8 +127,6 @@ struct BwdArgs {
 };
 size_t bwd_acc_dq_bytes(int64_t n_q, int Hq, int D);
 size_t bwd_acc_dkv_bytes(int64_t n_k, int Hkv, int D);  // each of dK, dV
-// causal_launch: one launch over the whole sequence; otherwise chunk pairs, most of them below the diagonal
-int bwd_dkdv_splits(int64_t n_q, int64_t n_k, int Hq, int Hkv, int D, bool causal_launch);
 size_t bwd_part_dkdv_bytes(int64_t n_k, int Hkv, int D, int splits);
 int bwd_k_tile(int D);
 int bwd_q_tile(int D);

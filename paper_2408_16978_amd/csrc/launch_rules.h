@@ -1,0 +1,64 @@
+// How the attention's launches are laid out, by their sizes.  Host code only, without HIP, so that a plain
+// C++ compiler takes it too: the tests ask these rules which kernel a size runs.
+#pragma once
+#include <stdint.h>
+
+#include <algorithm>
+#include <cmath>
+
+namespace fpdt {
+
+// Key groups of a forward or dQ launch (a workgroup of eight waves = 8 / KG row blocks of 32 queries x KG
+// waves that share the keys): the cheapest of 1, 2, 4 in units of a 64-key tile of eight row blocks.  A
+// launch on the diagonal lasts as long as its longest row tile or as the average load of the 256 compute
+// units; KG > 1 divides the first, and costs a little more per tile (copies and barriers per MFMA).
+// Measured (us for KG = 1, 2, 4; forward | dQ): 2K tokens, 8 heads, D = 128: 57, 38, 29 | 77, 50, 35;
+// 8K: 216, 169, 207 | 303, 230, 270; 16K: 535, 592, 684 | 753, 812, 903; 32K, 2 heads, D = 64: 517, 388,
+// 354 | 670, 461, 477.
+static inline int sweep_key_groups(int64_t n_q, int64_t n_keys, int Hq, bool causal)
+{
+    const double tiles = (double)n_keys / 64.0, cus = 256.0;
+    int best = 1;
+    double best_cost = 0.0;
+    for (int kg = 1; kg <= 4; kg *= 2) {
+        const double work = kg == 1 ? 1.0 : kg == 2 ? 1.08 : 1.15, wgs = (double)n_q / 256.0 * kg * Hq;
+        const double longest = tiles / kg * work + 2.0;
+        const double load = (double)(int64_t)((wgs + cus - 1.0) / cus) * longest;       // below the diagonal
+        const double mean = wgs / cus * (tiles / kg / 2 * work + 2.0) + longest / 4.0;  // on it
+        const double cost = causal ? (mean > longest ? mean : longest) : load;
+        if (kg == 1 || cost < 0.97 * best_cost) { best = kg; best_cost = cost; }
+    }
+    return best;
+}
+
+// Into how many splits a dK/dV launch divides the query walk of its key tiles.  Unsplit it has n_k / 256
+// * Hkv workgroups of four waves, one per compute unit: 64 at 8K tokens and two KV heads, so that three
+// quarters of the chip idle, and below the diagonal's last rows the longest workgroup decides.  Each
+// split adds a partial dK, dV (written once, read once by dkdv_sum_kernel).  The count is the cheapest
+// of 1, 2, 4, .. 16 in units of steps (one 32-query block of one head; 1.7 us per workgroup, measured):
+//   whole pair    rounds of 256 workgroups x (steps of a workgroup + its fixed cost)
+//   causal pair   list scheduling of lengths that fall linearly to zero: the longest, or the average load
+//   partials      (splits + 1) passes at 4.5 bytes per ns, one more launch
+// Measured (dK/dV with its sum, before -> after): 8K tokens, 8 query / 2 KV heads, D = 128: 1357 -> 274 us
+// (8 splits); pairs of 32K chunks, 8 / 1 heads: 12.77 -> 7.33 ms (4 splits), 8 / 2 heads: 7.66 -> 7.15 ms (2:
+// only the diagonal pairs gain); pairs of 16K chunks, 8 / 2 heads: 3.07 -> 1.76 ms (4).
+// causal_launch: one launch over the whole sequence; otherwise chunk pairs, most of them below the diagonal.
+static inline int bwd_dkdv_splits(int64_t n_q, int64_t n_k, int Hq, int Hkv, int D, bool causal_launch)
+{
+    const double cus = 256.0, fixed = 12.0, us_per_step = 1.7;
+    const double wgs = (double)(n_k / 256) * Hkv, steps = (double)(n_q / 32) * (Hq / Hkv);
+    int best = 1;
+    double best_cost = 0.0;
+    for (int s = 1; s <= 16; s *= 2) {
+        if (s > 1 && steps / s < 8.0) break;
+        const double w = wgs * s, len = steps / s;
+        const double full = std::ceil(w / cus) * (len + fixed);
+        const double causal = std::max(len + fixed, w / cus * (len / 2 + fixed) + len / 4);
+        const double sum = s == 1 ? 0.0 : ((double)(s + 1) * 2 * ((double)n_k * Hkv * ((D + 31) / 32 * 32) * 4.0) / 4.5e6 + 6.0) / us_per_step;
+        const double cost = sum + (causal_launch ? causal : (full + causal) / 2);
+        if (s == 1 || cost < 0.97 * best_cost) { best = s; best_cost = cost; }
+    }
+    return best;
+}
+
+}  // namespace fpdt

@@ -12,7 +12,6 @@
 // first form and a transposing LDS read those of the second.
 #include <hip/hip_runtime.h>
 
-#include <cmath>
 #include <cstdint>
 #include <mutex>
 #include <type_traits>
@@ -20,6 +19,7 @@
 
 #include "mfma_tiles.h"
 #include "tw_gemm.h"
+#include "tw_plan.h"
 
 namespace fpdt_tw {
 
@@ -48,7 +48,6 @@ __global__ __launch_bounds__(256) void tw_realign_kernel(const uint16_t* __restr
 
 // ---- product ----------------------------------------------------------------------------
 constexpr int NWAVE = 4, NTHREAD = NWAVE * 64;
-constexpr int SK = 32;        // k per LDS stage: two MFMA k-steps
 constexpr int RING = 4;       // LDS slots of one stage each; one more holds a last stage of less than SK
 constexpr unsigned PANEL = 4096;  // bytes of a panel: 64 rows of one operand x SK
 
@@ -65,12 +64,6 @@ template <bool ACC>
 __device__ __forceinline__ float combine(float v, float old) { return ACC ? old + v : v; }
 template <bool ACC>
 __device__ __forceinline__ uint16_t combine(float v, uint16_t old) { return to_bf16(ACC ? from_bf16(old) + v : v); }
-
-// The work of a product: the first `whole` of its tiles over all of k, the others divided into `splits`
-// ranges of `split_stages` stages (the last one may be shorter).
-struct Units {
-    int tiles, tiles_n, whole, splits, split_stages;
-};
 
 // One operand as stored: row r at p + r * ld, 16-byte aligned, ld a multiple of 8.  Form N: rows are the
 // product's rows, columns its k.  Form T: rows are k, columns the product's rows.  `rows` counts the
@@ -454,48 +447,6 @@ struct Realigned {
 Pool g_pool[64];
 std::vector<Realigned> g_cache;  // weights realigned during the current library call
 std::mutex g_mu;
-
-// Output tile (64 wmt x 64 wnt), and which tiles are divided along k: the cheapest in units of the core
-// clock, from
-//   stage   the MFMAs of a wave (16 clocks each) or the bytes that a stage copies into LDS: 21 per clock and
-//           compute unit, measured for all tile shapes
-//   unit    a fixed part (first operands, epilogue)
-//   rounds  of 256 units (512 where two fit a CU).  Tiles that do not fill the last round are divided, so
-//           that it is full and short; with fewer tiles than slots all of them are
-//   sums    of the divided tiles: one more launch and (splits + 1) passes over them at about 4.5 bytes per ns
-// Measured, all tiles whole -> the rest divided (most of it without a free round at the end, some from the
-// epilogues out of step): SwiGLU block at 16K tokens 21.1 -> 18.9 ms, GELU block on 3001 tokens 1562 -> 1458
-// us, 4096 x 14336 += 4096 rows 586 -> 475 us.
-struct Plan { int wmt, wnt; Units u; };
-Plan plan_product(int64_t M, int64_t N, int stages)
-{
-    static const int shapes[][2] = {{4, 4}, {3, 4}, {2, 4}, {1, 4}, {2, 2}};
-    Plan best = {4, 4, {}};
-    double best_cost = 0.0;
-    for (const auto& sh : shapes) {
-        const int wm = sh[0], wn = sh[1];
-        const double mfma = 64.0 * wm * wn + 100.0, copies = 192.0 * (wm + wn);
-        const double stage = mfma > copies ? mfma : copies, fixed = 1200.0 + 160.0 * wm * wn;
-        const int slots = wm * wn <= 4 && wn == 2 ? 512 : 256;
-        const double share = slots / 256.0;
-        const int64_t tiles_n = (N + 64 * wn - 1) / (64 * wn), tiles = (M + 64 * wm - 1) / (64 * wm) * tiles_n;
-        if (tiles > (int64_t)1 << 30) continue;
-        const int64_t rest = tiles % slots, whole = tiles - rest;
-        for (int sp = 1; sp <= 16; ++sp) {
-            const int per = (stages + sp - 1) / sp;
-            if (sp > 1 && (rest == 0 || per < 8 || (int64_t)(sp - 1) * per >= stages)) continue;
-            double cost = (double)(whole / slots) * (stages * stage + fixed);
-            cost += std::ceil((double)(rest * sp) / slots) * (per * stage + fixed);
-            cost *= share;
-            if (sp > 1) cost += 9000.0 + (sp + 1) * 4.0 * (double)rest * (64 * wm) * (64 * wn) / 2250.0;
-            if (best_cost == 0.0 || cost < 0.98 * best_cost) {
-                best = {wm, wn, {(int)tiles, (int)tiles_n, (int)(sp == 1 ? tiles : whole), sp, per}};
-                best_cost = cost;
-            }
-        }
-    }
-    return best;
-}
 
 int pool_take(Pool& p, size_t bytes, char** out)
 {

@@ -8,6 +8,7 @@ from paper_2408_16978_amd import binding as B
 from paper_2408_16978_amd import inputs, runner
 from oracle import chunked
 
+import launch_rules
 import parity
 from test_abi import SHARED_TILE_CALLS, shared_tile_shares
 
@@ -316,7 +317,8 @@ def test_bf16_key_groups(S, chunk, Hq, Hkv, D, flags):
 
 @pytest.mark.parametrize("S,chunk,Hq,Hkv,D", [(1, 1, 1, 1, 64), (31, 31, 4, 1, 128), (33, 11, 2, 2, 80), (289, 289, 3, 1, 64)])
 def test_fp32_tile_edges(S, chunk, Hq, Hkv, D):
-    """One row, one short of and one past a 32-row tile, one past the first block of every wave."""
+    """One row, one short of and one past a 32-row block of the other side (two 16-row tiles), one past the
+    first block of every wave.  (The pair-by-pair schedule at ragged chunks: test_gpu_blocksparse.py.)"""
     announce("fp32 edges", S, chunk, Hq, Hkv, D)
     Q, K, V, dO = inputs.make_qkvdo(S, Hq, Hkv, D, "f32", seed=18)
     scale = D ** -0.5
@@ -391,3 +393,49 @@ def test_bf16_in_the_smallest_workspace(S, chunk, Hq, Hkv, D, flags):
     print(parity.check_all({"dQ": b.dQ, "dK": b.dK, "dV": b.dV}, ref, True, names=("dQ", "dK", "dV")))
     for t in ends:
         assert bool((t == 0x5A).all())
+
+
+# (S, chunk, Hq, Hkv) of a pair-by-pair call: key groups of the forward, of dQ on the diagonal and below it
+KEY_GROUPS = [((512, 256, 8, 2), (4, 4, 4)), ((1024, 512, 48, 6), (2, 4, 2)), ((512, 256, 96, 12), (2, 2, 2)),
+              ((512, 256, 160, 20), (1, 2, 1)), ((512, 256, 256, 32), (1, 1, 1))]
+
+
+@pytest.mark.parametrize("D", [64, 80, 128])
+@pytest.mark.parametrize("sizes,groups", KEY_GROUPS)
+def test_bf16_every_key_group_count(sizes, groups, D):
+    """Each count of waves that share a row block's keys, in the forward and in dQ, one launch and pair by pair
+    with carried state (many heads stand in for long sequences, which have counts of one too).  The two
+    schedules' O and LSE have the same bits."""
+    S, chunk, Hq, Hkv = sizes
+    announce("bf16 key group count", S, chunk, Hq, Hkv, D, groups)
+    assert (launch_rules.forward_key_groups(S, Hq), launch_rules.dq_key_groups(chunk, Hq, True),
+            launch_rules.dq_key_groups(chunk, Hq, False)) == groups
+    Q, K, V, dO = inputs.make_qkvdo(S, Hq, Hkv, D, "bf16", seed=23)
+    scale = D ** -0.5
+    ref = parity.oracle_full(Q, K, V, dO, scale)
+    pairs = run(Q, K, V, dO, chunk, scale, B.FPDT_PAIRWISE)
+    print(parity.check_all(pairs, ref, True))
+    one = run(Q, K, V, dO, chunk, scale)
+    print(parity.check_all(one, ref, True))
+    assert torch.equal(one["O"], pairs["O"]) and torch.equal(one["LSE"], pairs["LSE"])
+
+
+@pytest.mark.parametrize("S,Hq,Hkv,groups", [(512, 4, 2, 4), (768, 48, 6, 2), (512, 256, 32, 1)])
+@pytest.mark.parametrize("D", [64, 80, 128])
+def test_bf16_scores_that_overflow_to_minus_infinity(D, S, Hq, Hkv, groups):
+    """As in fp32: runs of keys whose scores overflow, among them all that one wave of a row block sees at first
+    (the first tile, which holds every row's first keys, keeps some).  Rows behind such a run attend few keys,
+    so that dQ and dK have the rounding noise of peaked rows in their budget (parity.backward_noise)."""
+    announce("bf16 overflowing scores", S, Hq, Hkv, D)
+    assert launch_rules.forward_key_groups(S, Hq) == groups
+    Q, K, V, dO = inputs.make_qkvdo(S, Hq, Hkv, D, "bf16", seed=24)
+    Q[:, :, 0], K[:, :, 0] = 1e20, 0.0
+    K[32:64, :, 0] = -1e20
+    K[100:290, :, 0] = -1e20
+    scale = D ** -0.5
+    ref = parity.oracle_full(Q, K, V, dO, scale)
+    sigma = parity.backward_noise(Q, K, V, dO, ref, scale)
+    out = run(Q, K, V, dO, S, scale)
+    print(parity.check_all(out, ref, True, names=("O", "LSE", "dV")))
+    for n, first in (("dQ", 0), ("dK", 1)):  # (dK's large channel multiplies the large queries)
+        parity.check_with_noise(n, out[n][:, :, first:], ref[n][:, :, first:], sigma[n][:, :, first:])

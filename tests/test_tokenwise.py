@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 import torch
 
+import launch_rules
 from oracle import tokenwise as otw
 from paper_2408_16978_amd import tokenwise as TW
 
@@ -419,7 +420,7 @@ def test_gpu_tokenwise_calls_replay_from_a_graph():
     (129, 1000, 1001, 3, 0),  # odd widths: no row is 16-byte aligned
     (200, 96, 520, 1, 1),    # operands that start 2 bytes behind a 16-byte boundary
     (1030, 2048, 1160, 4, 0),
-    (4100, 1032, 4200, 1, 0)])  # one full round of large tiles and a divided rest
+    (4100, 1032, 4200, 1, 0)])  # more tiles than compute units (Y), few and all divided (dX, dW)
 def test_gpu_linear_tile_edges(rows, n_in, n_out, n_chunks, offset):
     """Forward, dX and dW of the projection against fp64 at the edges of the product's tiles, k stages and
     splits.  Exact bf16 products summed in fp32: rel 1e-4 of a row's rms (k <= 4096 terms, error of about
@@ -557,3 +558,74 @@ print("replayed")
 """
     r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=100)
     assert r.returncode == 0 and "replayed" in r.stdout, r.stderr[-2000:]
+
+
+# ------------------------------------------------------------------ every layout of a product
+# (M, N, K) and what the planning rule makes of them: the output tile in units of 64, and whether its tiles
+# run whole, divided along k, or some each.  Ragged in all three; widths that are read in place, but for the
+# last two.  (The rule does not choose 2 x 2 tiles whole, nor 1 x 4 ones of both kinds for more than 64 rows.)
+PRODUCTS = [((72, 72, 72), (1, 4, "whole")), ((72, 72, 648), (1, 4, "divided")), ((40, 67248, 792), (1, 4, "mixed")),
+            ((4304, 72, 1288), (2, 2, "divided")), ((67872, 72, 752), (2, 2, "mixed")),
+            ((17104, 72, 72), (2, 4, "whole")), ((1488, 72, 5496), (2, 4, "divided")), ((5448, 1384, 4632), (2, 4, "mixed")),
+            ((33368, 72, 72), (3, 4, "whole")), ((136, 7392, 1304), (3, 4, "divided")), ((3544, 6824, 2328), (3, 4, "mixed")),
+            ((49552, 72, 72), (4, 4, "whole")), ((6248, 264, 2448), (4, 4, "divided")), ((6536, 2312, 712), (4, 4, "mixed")),
+            ((6541, 2317, 711), (4, 4, "mixed")), ((1501, 251, 5003), (1, 4, "divided"))]
+
+
+def test_products_cover_the_rule():
+    assert all(launch_rules.product(*size) == plan for size, plan in PRODUCTS)
+    seen = {plan for _, plan in PRODUCTS}
+    r = np.random.default_rng(6)
+    for _ in range(20000):
+        M, N, K = (int(np.exp(r.uniform(np.log(8), np.log(140000)))) for _ in range(3))
+        assert launch_rules.product(M, N, K) in seen, (M, N, K)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("size,plan", PRODUCTS)
+def test_gpu_every_layout_of_a_product(size, plan):
+    """The five forms that the operations multiply in, each at the (M, N, K) of the case: X W^T as bf16 (Y) and
+    fp32 (logits), dY W (dX), dY^T X += (dW) and the bf16 product that adds to another (dX of SwiGLU).
+    Against fp64: exact bf16 products summed in fp32, sqrt(k) 2^-24 of the rms at most (under 3e-5 at k =
+    67248) and half an ulp of a bf16 output.  SwiGLU's reference has the operation's bf16 intermediates; where
+    fp32 and fp64 sums round one of them differently, the result moves by an ulp of it: of the summand that
+    is added to, 2^-8 of at most five times the rms, 2e-2 of it (of one of k terms, far less).  The logits through their log-sum-exp, in which every one of them counts, and the targets'."""
+    M, N, K = size
+    print("[case] product", size, plan, flush=True)
+    assert launch_rules.product(M, N, K) == plan
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    bf = lambda *s, std=1.0: (torch.randn(*s, device="cuda", generator=g) * std).to(torch.bfloat16)
+
+    def rowwise(name, got, ref, rel):
+        budget = rel * ref.pow(2).mean(1, keepdim=True).sqrt() + 2.0 ** -8 * ref.abs() + 1e-9
+        assert bool(((got.double() - ref).abs() <= budget).all()), name
+
+    A, Bn, Bt = bf(M, K), bf(N, K, std=K ** -0.5), bf(K, N, std=K ** -0.5)
+    Y = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    TW.fpdt_tw_linear_fwd(A, Bn, Y, 1)
+    logits = A.double() @ Bn.double().t()
+    rowwise("Y", Y, logits, 1e-4)
+    target = torch.randint(0, N, (M,), device="cuda", generator=g, dtype=torch.int32)
+    loss, lse = torch.empty(M, device="cuda"), torch.empty(M, device="cuda")
+    ws = torch.empty(TW.fpdt_tw_loss_workspace_bytes(M, K, N, 1), dtype=torch.uint8, device="cuda")
+    TW.fpdt_tw_loss_fwd_bwd(A, Bn, target, 1.0, loss, lse, None, None, 1, ws)
+    want = torch.logsumexp(logits, 1)
+    assert float((lse.double() - want).abs().max()) <= 2e-5
+    assert float((loss.double() - (want - logits.gather(1, target.long()[:, None])[:, 0])).abs().max()) <= 1e-4
+    dX = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    TW.fpdt_tw_linear_bwd(dX, Bt, A, dX, None, 1)
+    rowwise("dX", dX, A.double() @ Bt.double(), 1e-4)
+    At, dW = bf(K, M), torch.ones(M, N, device="cuda")
+    TW.fpdt_tw_linear_bwd(Bt, torch.empty(M, N, dtype=torch.bfloat16, device="cuda"), At, None, dW, 1)
+    ref = At.double().t() @ Bt.double()
+    assert float((dW.double() - 1 - ref).abs().max()) <= 1e-4 * max(1.0, float(ref.abs().max()))
+    # rows M, model width N, hidden width K
+    X, dY = bf(M, N), bf(M, N)
+    W1, W3, W2 = bf(K, N, std=N ** -0.5), bf(K, N, std=N ** -0.5), bf(N, K, std=K ** -0.5)
+    ws = torch.empty(TW.fpdt_tw_ffn_workspace_bytes(M, N, K, TW.FPDT_TW_SWIGLU, 1, True), dtype=torch.uint8, device="cuda")
+    TW.fpdt_tw_ffn_bwd(X, W1, W3, W2, dY, dX, None, None, None, TW.FPDT_TW_SWIGLU, 1, ws)
+    bf64 = lambda t: t.to(torch.bfloat16).double()  # the roundings between the products, which are part of the operation
+    a, b, dh = bf64(X.double() @ W1.double().t()), bf64(X.double() @ W3.double().t()), bf64(dY.double() @ W2.double())
+    sg = torch.sigmoid(a)
+    first = bf64(bf64(dh * b * sg * (1 + a * (1 - sg))) @ W1.double())
+    rowwise("SwiGLU dX", dX, first + bf64(dh * a * sg) @ W3.double(), 2e-2)
