@@ -79,8 +79,9 @@ enum {
      * even when every tensor is resident.  Without this bit and without offload flags
      * `chunk` is ignored (beyond validating it) and every kernel runs ONE causal sweep over
      * the whole sequence: the same set of (query, key) tiles, no carried state between
-     * launches.  The offload pipeline always runs pair by pair, with the same kernels in
-     * the same order as this mode: the two agree bit for bit.                          */
+     * launches.  (fp32 from S * (Hq + Hkv) = 2^27 on: pair by pair all the same, as one
+     * launch has fewer than 2^32 lanes.)  The offload pipeline always runs pair by pair,
+     * with the same kernels in the same order as this mode: the two agree bit for bit.   */
     FPDT_PAIRWISE = 1u << 4,
     /* Backward only (bf16; the forward ignores it): the stored-dS backward.  The paper's
      * backward, like any FlashAttention backward, recomputes the probabilities per chunk

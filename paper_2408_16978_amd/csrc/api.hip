@@ -58,7 +58,7 @@ struct Problem {
     bool act_host() const { return flags & FPDT_ACT_ON_HOST; }
     bool store_ds() const { return flags & FPDT_BWD_STORE_DS; }
     bool fused() const { return bf16() && !(flags & (FPDT_KV_ON_HOST | FPDT_ACT_ON_HOST | FPDT_PAIRWISE | FPDT_BWD_STORE_DS)); }
-    bool f32_pairs() const { return flags & FPDT_PAIRWISE; }
+    bool f32_pairs() const { return (flags & FPDT_PAIRWISE) || !f32_one_launch(S, Hq, Hkv); }
     bool q_outer() const
     {
         if (flags & FPDT_BWD_Q_OUTER) return true;

@@ -31,6 +31,13 @@ static inline int sweep_key_groups(int64_t n_q, int64_t n_keys, int Hq, bool cau
     return best;
 }
 
+// Does an fp32 call over the whole sequence fit into one launch?  (Workgroups of 512 lanes, one per 16 rows and
+// head, for the queries and for the keys; a launch has fewer than 2^32 lanes.)
+static inline bool f32_one_launch(int64_t S, int Hq, int Hkv)
+{
+    return ((S + 15) / 16 * ((int64_t)Hq + Hkv)) < (int64_t)1 << 23;
+}
+
 // Into how many splits a dK/dV launch divides the query walk of its key tiles.  Unsplit it has n_k / 256
 // * Hkv workgroups of four waves, one per compute unit: 64 at 8K tokens and two KV heads, so that three
 // quarters of the chip idle, and below the diagonal's last rows the longest workgroup decides.  Each

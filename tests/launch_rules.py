@@ -11,6 +11,7 @@ SHIM = """
 #include "launch_rules.h"
 #include "tw_plan.h"
 extern "C" int key_groups(int64_t n_q, int64_t n_k, int Hq, int causal) { return fpdt::sweep_key_groups(n_q, n_k, Hq, causal); }
+extern "C" int f32_one_launch(int64_t S, int Hq, int Hkv) { return fpdt::f32_one_launch(S, Hq, Hkv); }
 extern "C" int dkdv_splits(int64_t n_q, int64_t n_k, int Hq, int Hkv, int D, int causal) { return fpdt::bwd_dkdv_splits(n_q, n_k, Hq, Hkv, D, causal); }
 extern "C" void product(int64_t M, int64_t N, int64_t K, int* out)
 {
@@ -32,6 +33,7 @@ def _lib():
     i64, ci = ctypes.c_int64, ctypes.c_int
     L.key_groups.argtypes = [i64, i64, ci, ci]
     L.dkdv_splits.argtypes = [i64, i64, ci, ci, ci, ci]
+    L.f32_one_launch.argtypes = [i64, ci, ci]
     L.product.argtypes = [i64, i64, i64, ctypes.POINTER(ci)]
     L.product.restype = None
     return L
@@ -43,6 +45,10 @@ def forward_key_groups(S, Hq):
 
 def dq_key_groups(rows, Hq, diagonal):
     return _lib().key_groups(rows, rows, Hq, int(diagonal))
+
+
+def f32_one_launch(S, Hq, Hkv):
+    return bool(_lib().f32_one_launch(S, Hq, Hkv))
 
 
 def dkdv_splits(rows, Hq, Hkv, D, one_launch):

@@ -6,6 +6,7 @@ import re
 
 import pytest
 
+import launch_rules
 from paper_2408_16978_amd import binding as B
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -189,6 +190,13 @@ def test_pick_chunk_host_logic(lib):
     assert B.fpdt_attn_pick_chunk(0, 2, 2, 64, BF) == 0 and B.fpdt_last_error() != ""
     assert B.fpdt_attn_pick_chunk(4096, 3, 2, 64, BF) == 0 and "Hq" in B.fpdt_last_error()
     assert B.fpdt_attn_pick_chunk(4096, 2, 2, 64, BF, 0, 16) == 0 and "workspace" in B.fpdt_last_error()
+
+
+@pytest.mark.parametrize("S,Hq,Hkv", [(1024, 2, 2), (1 << 22, 16, 15), (1 << 22, 16, 16), ((1 << 22) - 16, 16, 16), (1 << 26, 1, 1),
+                                      (1 << 30, 1, 1), ((1 << 26) - 17, 1, 1)])
+def test_fp32_runs_as_one_launch_while_that_has_fewer_than_2_to_32_lanes(S, Hq, Hkv):
+    lanes = -(-S // 16) * (Hq + Hkv) * 512
+    assert launch_rules.f32_one_launch(S, Hq, Hkv) == (lanes < 1 << 32)
 
 
 def test_calibration_arguments_are_checked_without_a_gpu(lib):
