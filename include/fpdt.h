@@ -127,12 +127,12 @@ size_t fpdt_attn_workspace_bytes(int64_t S, int64_t chunk, int Hq, int Hkv, int 
  * 64K tokens).  Returns the largest chunk c <= FPDT_PREFERRED_CHUNK with S % c == 0, c a
  * multiple of FPDT_CHUNK_MULTIPLE (bf16 only), for which both workspaces
  * (fpdt_attn_workspace_bytes with is_bwd = 0 and 1) fit in max_workspace_bytes (0 = no
- * limit).  Why that cap: one launch of the dK/dV kernel has chunk / 256 * Hkv workgroups,
- * which fills the 256 compute units only from 32K tokens on at two KV heads, and every
- * chunk pair costs a fixed launch, state load and state store; measured on the Llama-8B head
- * share with K/V offloaded the throughput rises steeply up to 32K tokens, by 3% (S = 256K)
- * or 1% (S = 2M) from 32K to 64K, and by 0.3% at most from 64K to 128K, while every chunk-sized
- * buffer doubles.  64K is the knee of that curve on this machine as well.
+ * limit).  Why that cap: every chunk pair costs its launches, a state load and a state store, and
+ * K/V chunks that live on the host cross the link once per pair, while every chunk-sized buffer
+ * doubles with the chunk.  Measured on the Llama-8B head share with K/V offloaded (recomputing
+ * backward), TFLOP/s: S = 256K 611, 851, 948, 969, 950, 956 at chunks of 4K, 8K, .. 128K; S = 2M 968,
+ * 985, 990, 992 from 16K to 128K.  The curve is flat within 2% from 32K tokens on; 64K, the paper's
+ * choice, lies on its flat part and keeps the link traffic low.
  * Returns 0 when the arguments are invalid or no chunk fits (fpdt_last_error says which).
  * Host logic only: no device is touched.
  */

@@ -25,9 +25,10 @@
  * failure; text from fpdt_tw_last_error).  Besides the caller's workspace the library keeps one
  * device scratch pool per GPU for the running call: logit gradients of up to 2 hidden rows, fp32
  * sums of output tiles that several workgroups share, copies of operands whose rows are not
- * 16-byte aligned.  It grows
- * on demand with hipMalloc -- so the first call of a
- * given size must not run under stream capture -- and is kept until the process ends.  Calls
+ * 16-byte aligned.  It grows on demand with hipMalloc -- so the first call of a given size must not
+ * run under stream capture -- by doubling from 256 MiB, and is kept until the process ends, as are
+ * the buffers it has outgrown (work in flight may read them): up to four times what the largest
+ * call needs.  Calls
  * that overlap in time on one GPU (different streams or threads) would share that pool: keep
  * the library's calls on one stream.
  */

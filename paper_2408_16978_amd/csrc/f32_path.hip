@@ -6,8 +6,8 @@
 // product's operand.  Their tensors are small (the accuracy configuration has 1K tokens), so what bounds
 // them is the chain of one row tile and the number of launches: tiles have 16 rows (of 32 rows there are
 // 64 at 1K tokens and two heads, a quarter of the compute units), the eight waves of a workgroup share a
-// tile, each walking every eighth 32-row block of the other side, and their results meet in LDS; a dense
-// call is one forward and one backward launch.  At 1024 tokens, 2 heads, D = 64, chunks of 256, forward
+// tile, each walking every eighth 32-row block of the other side, and their results meet in LDS; a call
+// without FPDT_PAIRWISE is one forward and one backward launch.  At 1024 tokens, 2 heads, D = 64, chunks of 256, forward
 // and backward: one wave per row with scalar dot products, pair by pair, 1799 us; 32-row tiles 110 us;
 // this 64 us, with errors against fp64 below those of the scalar kernels in O, dQ, dK and dV (2.5e-7 .. 7.0e-7
 // against 3.3e-7 .. 9.7e-7 over four shapes).

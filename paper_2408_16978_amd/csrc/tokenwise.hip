@@ -37,7 +37,7 @@ int fail(int code, const char* fmt, ...)
 std::mutex g_mu;
 
 // The dense products are this library's own MFMA kernels (tw_gemm.hip).  A "handle" is just the
-// stream of the current call; taking it starts a call (packed weights of the previous call are
+// stream of the current call; taking it starts a call (copies of the previous call's weights are
 // forgotten, its scratch is reused).
 struct GemmCtx { hipStream_t st; };
 typedef GemmCtx* gemm_handle;

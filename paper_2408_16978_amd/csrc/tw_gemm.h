@@ -20,6 +20,7 @@ bool reads_in_place(const void* A, int64_t rows, int64_t k, const void* C, int64
 //   C row-major [M,N], leading dimension ldc, bf16 or fp32 (c_f32); accumulate: C += instead of C =
 //   lda wider than A's rows: they are followed by zeros up to a multiple of 8
 //   cache_b: B is a weight that further products of this library call will use again
+//   A or B may be what C overwrites
 // Only enqueues on `st`.  Returns 0, 1 (HIP failure) or 2 (sizes beyond the launch limits).
 int gemm(int a_transposed, int b_transposed, int M, int N, int K, const void* A, int64_t lda, const void* B,
          int64_t ldb, void* C, int64_t ldc, bool c_f32, bool accumulate, bool cache_b, hipStream_t st);

@@ -1,6 +1,6 @@
 // Dense bf16 products of the token-wise chunked operations (Sec. 4.1, 5.4: the per-chunk QKV
 // projection, the feed-forward block and the output projection of the loss are plain GEMMs over
-// one chunk of tokens at a time) on v_mfma_f32_32x32x16_bf16: a four-slot LDS ring filled by direct
+// one chunk of tokens at a time) on v_mfma_f32_16x16x32_bf16: a four-slot LDS ring filled by direct
 // global -> LDS copies three stages ahead, four waves (one per SIMD) per output tile of up to
 // 256 x 256.
 //
@@ -32,7 +32,8 @@ namespace {
 // ---- realign ----------------------------------------------------------------------------
 // The product kernel copies 16-byte pieces of its operands' rows and needs at least one whole stage of
 // k.  An operand that does not offer that (a width that is not a multiple of 8, a base that is not
-// 16-byte aligned, k < 32) is copied once into out [R2, C2], zero behind X [R, C].
+// 16-byte aligned, k < 32), or that the product overwrites, is copied once into out [R2, C2], zero behind
+// X [R, C].
 __global__ __launch_bounds__(256) void tw_realign_kernel(const uint16_t* __restrict__ X, int64_t R, int64_t C, int64_t ld,
                                                          u32x4* __restrict__ out, int64_t R2, int64_t C2)
 {
@@ -188,7 +189,7 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand 
     constexpr unsigned STAGE = (WMT + WNT) * PANEL;      // bytes of a slot: A's panels, then B's
     constexpr int MI = 2 * WMT, NI = 2 * WNT, NH = NI / 2;  // accumulator tiles of a wave; NH: columns of a phase
     constexpr int NC = WMT + WNT;                        // copies of a wave per stage
-    constexpr int NC0 = (NC + 1) / 2;                    // .. of which in the first of the two k-steps that issue them
+    constexpr int NC0 = (NC + 1) / 2;                    // .. of which in the second phase of a stage, the rest in the first phase of the next
     static_assert(NWAVE == 4, "a wave copies a quarter of every panel");
     __shared__ __attribute__((aligned(256))) u32x4 ring[(RING + 1) * STAGE / 16];
     // Consecutive workgroup ids land on different XCDs (each with its own L2): give every XCD a
