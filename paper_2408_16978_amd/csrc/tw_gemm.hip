@@ -384,22 +384,40 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand 
         store_tile(tile, ldc, std::integral_constant<bool, ACCUM>{});
         return;
     }
-    const int m0 = mw + (lane & 15), n0 = nw + 4 * (lane >> 4);
+    // A tile that reaches behind C, or rows of C that are not aligned for four elements: sixteen rows at a time
+    // through LDS as above, one element per lane and access, consecutive lanes on consecutive columns.  (Straight
+    // from the accumulators an access touched 16 rows at 16 bytes each: odd widths then took up to twice the
+    // time of the tiles' MFMAs.)  The old values of eight accesses are requested together.
+    constexpr int PITCH = 32 * WNT + 4, CPR = 32 * WNT / 64, BATCH = 8;  // accesses per row, and between two waits
+    float* rows = reinterpret_cast<float*>(ring) + wu * (16 * PITCH);
+    float* put = rows + (lane & 15) * PITCH + 4 * (lane >> 4);
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
+    for (int i = 0; i < MI; ++i) {
+        if (mt + mw + 16 * i >= M) break;  // (wave-uniform)
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             asm volatile("" : "+a"(acc[i][j]));
-            if (mt + m0 + 16 * i >= M) continue;
-            out_t* c = tile + (size_t)(m0 + 16 * i) * ldc + n0 + 16 * j;
-            out_t old[4] = {};
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (ACCUM && nt + n0 + 16 * j + r < N) old[r] = c[r];
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (nt + n0 + 16 * j + r < N) c[r] = combine<ACCUM>(acc[i][j][r], old[r]);
+            *reinterpret_cast<floatx4*>(put + 16 * j) = acc[i][j];
         }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+        for (int k0 = 0; k0 < 16 * CPR; k0 += BATCH) {
+            out_t* c[BATCH];
+            out_t old[BATCH];
+            bool on[BATCH];
+#pragma unroll
+            for (int k = 0; k < BATCH; ++k) {
+                const int row = (k0 + k) / CPR, col = 64 * ((k0 + k) % CPR) + lane, m = mw + 16 * i + row, n = nw + col;
+                on[k] = mt + m < M && nt + n < N;
+                c[k] = tile + (size_t)m * ldc + n;
+                old[k] = ACCUM && on[k] ? *c[k] : out_t(0);
+            }
+#pragma unroll
+            for (int k = 0; k < BATCH; ++k)
+                if (on[k]) *c[k] = combine<ACCUM>(rows[((k0 + k) / CPR) * PITCH + 64 * ((k0 + k) % CPR) + lane], old[k]);
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
 }
 
 // The divided tiles of a product: C (+)= the sums of their splits, part [split][tile][TM x TN] fp32.
