@@ -387,35 +387,34 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand 
     // A tile that reaches behind C, or rows of C that are not aligned for four elements: sixteen rows at a time
     // through LDS as above, one element per lane and access, consecutive lanes on consecutive columns.  (Straight
     // from the accumulators an access touched 16 rows at 16 bytes each: odd widths then took up to twice the
-    // time of the tiles' MFMAs.)  The old values of eight accesses are requested together.
-    constexpr int PITCH = 32 * WNT + 4, CPR = 32 * WNT / 64, BATCH = 8;  // accesses per row, and between two waits
+    // time of the tiles' MFMAs.)  The old values of the sixteen rows are requested together.
+    constexpr int PITCH = 32 * WNT + 4, CPR = 32 * WNT / 64;  // floats between rows, accesses per row
     float* rows = reinterpret_cast<float*>(ring) + wu * (16 * PITCH);
     float* put = rows + (lane & 15) * PITCH + 4 * (lane >> 4);
+    bool in[CPR];
+#pragma unroll
+    for (int p = 0; p < CPR; ++p) in[p] = nt + nw + 64 * p + lane < N;
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-        if (mt + mw + 16 * i >= M) break;  // (wave-uniform)
+        const int left = M - (mt + mw + 16 * i);  // rows of C from here on
+        if (left <= 0) break;
+        out_t* c = tile + (size_t)(mw + 16 * i) * ldc + nw + lane;
+        out_t old[16][CPR];
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+#pragma unroll
+            for (int p = 0; p < CPR; ++p) old[r][p] = ACCUM && r < left && in[p] ? c[(size_t)r * ldc + 64 * p] : out_t(0);
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             asm volatile("" : "+a"(acc[i][j]));
             *reinterpret_cast<floatx4*>(put + 16 * j) = acc[i][j];
         }
         __builtin_amdgcn_wave_barrier();
-#pragma unroll 1
-        for (int k0 = 0; k0 < 16 * CPR; k0 += BATCH) {
-            out_t* c[BATCH];
-            out_t old[BATCH];
-            bool on[BATCH];
 #pragma unroll
-            for (int k = 0; k < BATCH; ++k) {
-                const int row = (k0 + k) / CPR, col = 64 * ((k0 + k) % CPR) + lane, m = mw + 16 * i + row, n = nw + col;
-                on[k] = mt + m < M && nt + n < N;
-                c[k] = tile + (size_t)m * ldc + n;
-                old[k] = ACCUM && on[k] ? *c[k] : out_t(0);
-            }
+        for (int r = 0; r < 16; ++r)
 #pragma unroll
-            for (int k = 0; k < BATCH; ++k)
-                if (on[k]) *c[k] = combine<ACCUM>(rows[((k0 + k) / CPR) * PITCH + 64 * ((k0 + k) % CPR) + lane], old[k]);
-        }
+            for (int p = 0; p < CPR; ++p)
+                if (r < left && in[p]) c[(size_t)r * ldc + 64 * p] = combine<ACCUM>(rows[r * PITCH + 64 * p + lane], old[r][p]);
         __builtin_amdgcn_wave_barrier();
     }
 }
