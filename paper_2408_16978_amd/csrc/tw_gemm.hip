@@ -39,11 +39,17 @@ __global__ __launch_bounds__(256) void tw_realign_kernel(const uint16_t* __restr
 {
     const int64_t pieces = C2 / 8, n = R2 * pieces;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-        const int64_t r = i / pieces, c = i % pieces * 8;
-        unsigned e[8];
+        const int64_t r = n >> 32 ? i / pieces : (unsigned)i / (unsigned)pieces, c = (i - r * pieces) * 8;
+        u32x4 v;
+        if (r < R && c + 8 <= C) {  // (16 bytes at any even address in one access)
+            __builtin_memcpy(&v, X + r * ld + c, 16);
+        } else {
+            unsigned e[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) e[j] = r < R && c + j < C ? X[r * ld + c + j] : 0u;
-        out[r * (pitch / 8) + c / 8] = u32x4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+            for (int j = 0; j < 8; ++j) e[j] = r < R && c + j < C ? X[r * ld + c + j] : 0u;
+            v = u32x4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+        }
+        out[r * (pitch / 8) + c / 8] = v;
     }
 }
 
