@@ -498,6 +498,7 @@ int pool_take(Pool& p, size_t bytes, char** out)
 // A lane's offset within its tile (255 rows of form N, 7 of form T) is kept in 32 bits
 constexpr int64_t MAX_PITCH = (int64_t)1 << 23;    // elements between rows along k
 constexpr int64_t MAX_PITCH_T = (int64_t)1 << 28;  // and between the rows of k, form T
+constexpr int64_t COPY_PAD = 64;                   // a copy's rows are this many elements further apart at most
 
 // The bytes that a product writes
 struct Written {
@@ -661,7 +662,7 @@ static int any_product(Pool& pool, int a_transposed, int b_transposed, int M, in
     // Rows of k too far apart (form T, an operand of more than 2^28 columns): the columns, which are rows or
     // columns of C, in segments, whose copies have a shorter pitch.
     constexpr int SEG_T = 1 << 24;
-    if (b_transposed && ldb >= MAX_PITCH_T && N > SEG_T) {
+    if (b_transposed && ldb > MAX_PITCH_T - COPY_PAD && N > SEG_T) {
         for (int64_t n0 = 0; n0 < N; n0 += SEG_T) {
             const int rc = any_product(pool, a_transposed, b_transposed, M, (int)(N - n0 < SEG_T ? N - n0 : SEG_T), K, A, lda, static_cast<const uint16_t*>(B) + n0, ldb,
                                        static_cast<char*>(C) + n0 * (c_f32 ? 4 : 2), ldc, c_f32, accumulate, false, st);
@@ -669,7 +670,7 @@ static int any_product(Pool& pool, int a_transposed, int b_transposed, int M, in
         }
         return 0;
     }
-    if (a_transposed && lda >= MAX_PITCH_T && M > SEG_T) {
+    if (a_transposed && lda > MAX_PITCH_T - COPY_PAD && M > SEG_T) {
         for (int64_t m0 = 0; m0 < M; m0 += SEG_T) {
             const int rc = any_product(pool, a_transposed, b_transposed, (int)(M - m0 < SEG_T ? M - m0 : SEG_T), N, K, static_cast<const uint16_t*>(A) + m0, lda, B, ldb,
                                        static_cast<char*>(C) + (size_t)m0 * ldc * (c_f32 ? 4 : 2), ldc, c_f32, accumulate, cache_b, st);
@@ -677,7 +678,7 @@ static int any_product(Pool& pool, int a_transposed, int b_transposed, int M, in
         }
         return 0;
     }
-    const bool long_a = !a_transposed && lda >= MAX_PITCH, long_b = !b_transposed && ldb >= MAX_PITCH;
+    const bool long_a = !a_transposed && lda > MAX_PITCH - COPY_PAD, long_b = !b_transposed && ldb > MAX_PITCH - COPY_PAD;
     if (!long_a && !long_b)
         return product(pool, a_transposed, b_transposed, M, N, K, A, lda, B, ldb, C, ldc, c_f32, accumulate, cache_b, st);
     // Rows too long for the kernel's offsets: k in segments, which are the splits of every tile, one launch

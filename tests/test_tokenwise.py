@@ -502,7 +502,7 @@ def test_gpu_linear_copies_one_chunk_at_a_time(n_in, in_place):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("rows,n_in,n_out", [(2, (1 << 28) + 8, 3), (3, 8, (1 << 28) + 24), (33, (1 << 28) + 1, 1)])
+@pytest.mark.parametrize("rows,n_in,n_out", [(2, (1 << 28) + 8, 3), (3, 8, (1 << 28) + 24), (33, (1 << 28) + 1, 1), (2, (1 << 28) - 3, 2)])
 def test_gpu_linear_rows_of_two_hundred_million(rows, n_in, n_out):
     """Gradients where consecutive rows of k lie further apart than the product kernel's 32-bit offsets reach:
     the columns run in segments.  Every element against sums of exact products in fp32 (up to 33 terms; where
@@ -629,3 +629,18 @@ def test_gpu_every_layout_of_a_product(size, plan):
     sg = torch.sigmoid(a)
     first = bf64(bf64(dh * b * sg * (1 + a * (1 - sg))) @ W1.double())
     rowwise("SwiGLU dX", dX, first + bf64(dh * a * sg) @ W3.double(), 2e-2)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_in", [(1 << 23) - 3, (1 << 23) - 63, (1 << 23) - 64])
+def test_gpu_linear_rows_just_short_of_eight_million(n_in):
+    """Widths that are within the product kernel's offsets, but whose copies' rounded rows would not be."""
+    n_out, rows = 8, 9
+    print("[case] linear rows just short of the limit", n_in, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    X = torch.randn(rows, n_in, device="cuda", generator=g).to(torch.bfloat16)
+    W = (torch.randn(n_out, n_in, device="cuda", generator=g) * n_in ** -0.5).to(torch.bfloat16)
+    Y = torch.empty(rows, n_out, dtype=torch.bfloat16, device="cuda")
+    TW.fpdt_tw_linear_fwd(X, W, Y, 1)
+    torch.cuda.synchronize()
+    _rowwise_ok("Y", Y.double().cpu().numpy(), (X.double() @ W.double().t()).cpu().numpy(), rel=4e-4)
