@@ -660,11 +660,14 @@ static int any_product(Pool& pool, int a_transposed, int b_transposed, int M, in
                        int64_t ldb, void* C, int64_t ldc, bool c_f32, bool accumulate, bool cache_b, hipStream_t st)
 {
     // Rows of k too far apart (form T, an operand of more than 2^28 columns): the columns, which are rows or
-    // columns of C, in segments, whose copies have a shorter pitch.
-    constexpr int SEG_T = 1 << 24;
-    if (b_transposed && ldb > MAX_PITCH_T - COPY_PAD && N > SEG_T) {
-        for (int64_t n0 = 0; n0 < N; n0 += SEG_T) {
-            const int rc = any_product(pool, a_transposed, b_transposed, M, (int)(N - n0 < SEG_T ? N - n0 : SEG_T), K, A, lda, static_cast<const uint16_t*>(B) + n0, ldb,
+    // columns of C, in segments, whose copies have a shorter pitch.  More than 2^30 columns of C in segments
+    // too: the last tile would reach behind 2^31.
+    constexpr int SEG_T = 1 << 24, SEG_N = 1 << 30;
+    const int seg_n = b_transposed && ldb > MAX_PITCH_T - COPY_PAD ? SEG_T : SEG_N;
+    if (N > seg_n) {
+        for (int64_t n0 = 0; n0 < N; n0 += seg_n) {
+            const int rc = any_product(pool, a_transposed, b_transposed, M, (int)(N - n0 < seg_n ? N - n0 : seg_n), K, A, lda,
+                                       static_cast<const uint16_t*>(B) + (b_transposed ? n0 : n0 * ldb), ldb,
                                        static_cast<char*>(C) + n0 * (c_f32 ? 4 : 2), ldc, c_f32, accumulate, false, st);
             if (rc) return rc;
         }

@@ -644,3 +644,27 @@ def test_gpu_linear_rows_just_short_of_eight_million(n_in):
     TW.fpdt_tw_linear_fwd(X, W, Y, 1)
     torch.cuda.synchronize()
     _rowwise_ok("Y", Y.double().cpu().numpy(), (X.double() @ W.double().t()).cpu().numpy(), rel=4e-4)
+
+
+@pytest.mark.gpu
+def test_gpu_linear_two_billion_columns():
+    """n_out = 2^31 - 1, the largest that the argument holds: the last tile of C would reach behind 2^31.  Rows of
+    W are zero but for some at its ends and around 2^30, where the segments meet."""
+    n_in, n_out = 32, (1 << 31) - 1
+    print("[case] linear two billion columns", flush=True)
+    if torch.cuda.mem_get_info()[0] < 160 << 30:
+        torch.cuda.empty_cache()
+    X = torch.randn(1, n_in, device="cuda").to(torch.bfloat16)
+    W = torch.zeros(n_out, n_in, dtype=torch.bfloat16, device="cuda")
+    parts = [slice(0, 300), slice((1 << 30) - 300, (1 << 30) + 300), slice(n_out - 300, n_out)]
+    for p in parts:
+        W[p] = torch.randn(W[p].shape, device="cuda").to(torch.bfloat16)
+    Y = torch.ones(1, n_out, dtype=torch.bfloat16, device="cuda")
+    TW.fpdt_tw_linear_fwd(X, W, Y, 1)
+    torch.cuda.synchronize()
+    for p in parts:
+        _rowwise_ok("Y", Y[:, p].double().cpu().numpy(), (X.double() @ W[p].double().t()).cpu().numpy(), rel=1e-4)
+        Y[:, p] = 0
+    assert int(torch.count_nonzero(Y)) == 0
+    del W, Y
+    torch.cuda.empty_cache()
