@@ -48,6 +48,18 @@ def test_fp32_blocksparse():
         print(parity.check_all(out, ref, False))
 
 
+@pytest.mark.parametrize("S,chunk,Hq,Hkv,D", [(300, 100, 4, 2, 80), (99, 11, 4, 1, 128), (85, 17, 2, 1, 64), (231, 33, 6, 2, 128)])
+def test_fp32_blocksparse_ragged_chunks(S, chunk, Hq, Hkv, D):
+    """Carried state and accumulation over pairs whose chunks are no multiples of a tile (16 rows) or a block (32)."""
+    print("[case] fp32 block-sparse, ragged", S, chunk, Hq, Hkv, D, flush=True)
+    Q, K, V, dO = inputs.make_qkvdo(S, Hq, Hkv, D, "f32", seed=32)
+    mask = chunk_mask(S // chunk, 33)
+    ref = oracle(Q, K, V, dO, D ** -0.5, chunk, mask)
+    for flags in (0, B.FPDT_BWD_Q_OUTER):
+        out = run(Q, K, V, dO, chunk, D ** -0.5, mask, flags)
+        print(parity.check_all(out, ref, False))
+
+
 @pytest.mark.parametrize("Hq,Hkv,D", [(4, 4, 80), (8, 2, 128)])
 @pytest.mark.parametrize("order", [B.FPDT_BWD_KV_OUTER, B.FPDT_BWD_Q_OUTER])
 def test_bf16_blocksparse(Hq, Hkv, D, order):
