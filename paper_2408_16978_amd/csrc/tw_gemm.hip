@@ -1,7 +1,7 @@
 // Dense bf16 products of the token-wise chunked operations (Sec. 4.1, 5.4: the per-chunk QKV
 // projection, the feed-forward block and the output projection of the loss are plain GEMMs over
-// one chunk of tokens at a time) on v_mfma_f32_16x16x32_bf16: a four-slot LDS ring filled by direct
-// global -> LDS copies three stages ahead, four waves (one per SIMD) per output tile of up to
+// one chunk of tokens at a time) on v_mfma_f32_16x16x32_bf16: stages of 64 k in LDS, filled by direct
+// global -> LDS copies two stages ahead, four waves (one per SIMD) per output tile of up to
 // 256 x 256.
 //
 //   C[M,N] (+)= sum_k Aop[m,k] * Bop[n,k]          fp32 accumulation, C bf16 or fp32
@@ -15,6 +15,7 @@
 #include <cstdint>
 #include <mutex>
 #include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "mfma_tiles.h"
@@ -30,23 +31,22 @@ using fpdt::u32x4;
 namespace {
 
 // ---- realign ----------------------------------------------------------------------------
-// The product kernel copies 16-byte pieces of its operands' rows and needs at least one whole stage of
-// k.  An operand that does not offer that (a width that is not a multiple of 8, a base that is not
-// 16-byte aligned, k < 32), or that the product overwrites, is copied once into out [R2, C2], zero behind
-// X [R, C], rows `pitch` elements apart.
+// The product kernel copies 16-byte pieces of its operands' rows.  An operand that does not offer that (a
+// width that is not a multiple of 8, a base that is not 16-byte aligned), or that the product overwrites, is
+// copied once: X [R, C] with its columns rounded up to 8, zero behind C, rows `pitch` elements apart.
 __global__ __launch_bounds__(256) void tw_realign_kernel(const uint16_t* __restrict__ X, int64_t R, int64_t C, int64_t ld,
-                                                         u32x4* __restrict__ out, int64_t R2, int64_t C2, int64_t pitch)
+                                                         u32x4* __restrict__ out, int64_t pitch)
 {
-    const int64_t pieces = C2 / 8, n = R2 * pieces;
+    const int64_t pieces = (C + 7) / 8, n = R * pieces;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
         const int64_t r = n >> 32 ? i / pieces : (unsigned)i / (unsigned)pieces, c = (i - r * pieces) * 8;
         u32x4 v;
-        if (r < R && c + 8 <= C) {  // (16 bytes at any even address in one access)
+        if (c + 8 <= C) {  // (16 bytes at any even address in one access)
             __builtin_memcpy(&v, X + r * ld + c, 16);
         } else {
             unsigned e[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) e[j] = r < R && c + j < C ? X[r * ld + c + j] : 0u;
+            for (int j = 0; j < 8; ++j) e[j] = c + j < C ? X[r * ld + c + j] : 0u;
             v = u32x4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
         }
         out[r * (pitch / 8) + c / 8] = v;
@@ -55,14 +55,19 @@ __global__ __launch_bounds__(256) void tw_realign_kernel(const uint16_t* __restr
 
 // ---- product ----------------------------------------------------------------------------
 constexpr int NWAVE = 4, NTHREAD = NWAVE * 64;
-constexpr int RING = 4;       // LDS slots of one stage each; one more holds a last stage of less than SK
-constexpr unsigned PANEL = 4096;  // bytes of a panel: 64 rows of one operand x SK
+constexpr unsigned PANEL = 8192;  // bytes of a panel: 64 rows of one operand x STAGE_K
 
 __device__ __forceinline__ uint16_t to_bf16(float f)
 {
     const unsigned u = __float_as_uint(f);
     if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40);
     return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
+}
+// eight values rounded to nearest even, two per instruction
+__device__ __forceinline__ u32x4 pack_bf16(floatx4 lo, floatx4 hi)
+{
+    const fpdt::floatx8 x = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(u32x4, __builtin_convertvector(x, bf16x8));
 }
 __device__ __forceinline__ float from_bf16(uint16_t b) { return __uint_as_float((unsigned)b << 16); }
 
@@ -82,32 +87,37 @@ struct Operand {
 };
 
 // Per-lane source of one operand's copies and fragment reads.  A stage of an operand is PANEL bytes per 64
-// rows; wave w copies quarter w of every panel.
-//   Form N: panel row r (64 bytes) holds its four 16-byte pieces q at position q ^ f(r),
-//           f(r) = (r / 2) % 4 ^ (r / 8) % 2: any 8 rows aligned to 8, read at one piece, lie in different
-//           16-byte columns of 128 bytes, and any 16 rows in different columns of 256 bytes.
-//   Form T: panel row k (128 bytes, 64 columns) holds its 32-byte quarter u at u ^ (2 ((k / 2) % 2) + (k / 8) % 2):
-//           the eight k x 16 columns that half a wave's transposing read covers lie in different 32-byte
-//           columns of 256 bytes.
+// rows, in eight copies of 1 KiB; wave w makes copies w and w + 4 of every panel.  Both forms read whole
+// 128-byte lines: stages of half as many k, with 64 bytes of a row of form N, moved every line from L2
+// twice (copies alone: 70 bytes per ns and compute unit against 140).
+//   Form N: panel row r (128 bytes) holds its eight 16-byte pieces q at position q ^ (r / 2) % 8: the sixteen
+//           lanes that a 16-byte read serves at a time (0-3, 12-15, 20-23 and 24-27 of 32, then the others)
+//           lie in different 16-byte columns of 256 bytes.
+//   Form T: two halves of 32 k; panel row k (128 bytes, 64 columns) holds its 32-byte quarter u at
+//           u ^ (2 ((k / 2) % 2) + (k / 8) % 2): the eight k x 16 columns that half a wave's transposing read
+//           covers lie in different 32-byte columns of 256 bytes.
+__device__ __forceinline__ int piece_swizzle(int row) { return (row >> 1) & 7; }
 template <bool T, int NP>
 struct Side {
-    uint64_t pos;        // scalar: the current stage
-    uint64_t step;       // bytes from a stage to the next
-    unsigned off[NP];    // this lane's piece of panel j
-    unsigned rd[4];      // LDS bytes within a stage: of fragments 0, 4, .., of 1, 5, .., (form N: rd[0] only)
+    uint64_t pos;           // scalar: the stage that is copied next
+    uint64_t step;          // bytes from a stage to the next
+    uint64_t half;          // form T: bytes from the rows of copy w to those of copy w + 4
+    unsigned off[2][NP];    // this lane's piece of panel j, copies w and w + 4
+    unsigned rd[T ? 4 : 2];  // LDS bytes within a stage.  T: of fragments 0, 4, .., of 1, 5, ..; N: of the two k-steps
 
     __device__ __forceinline__ void init(const Operand& x, int row0, int stage0, int w, int wave_frag0, int lane, unsigned lds0)
     {
         const uint64_t pitch = (uint64_t)x.ld * 2;
         const int limit = x.rows - row0;  // >= 1
-        if (T) {
-            step = SK * pitch;
+        if constexpr (T) {
+            step = STAGE_K * pitch;
+            half = 32 * pitch;
             pos = (uint64_t)(uintptr_t)(x.p + row0) + (uint64_t)stage0 * step + (uint64_t)(8 * w) * pitch;
             const int k = lane >> 3, u = ((lane >> 1) & 3) ^ (2 * ((k >> 1) & 1) + (w & 1));
 #pragma unroll
             for (int j = 0; j < NP; ++j) {
                 const int c = 64 * j + 16 * u + 8 * (lane & 1);
-                off[j] = (unsigned)k * (unsigned)pitch + 2u * (unsigned)(c < limit - 8 ? c : limit - 8);
+                off[0][j] = off[1][j] = (unsigned)k * (unsigned)pitch + 2u * (unsigned)(c < limit - 8 ? c : limit - 8);
             }
             // 16-lane group g supplies k rows 8 g + 0..3 (and + 4..7 with the second read), lane i of it row
             // i / 4, columns 4 (i % 4) .. + 3
@@ -119,70 +129,132 @@ struct Side {
                 rd[q] = lds0 + PANEL * (unsigned)(f >> 2) + 32u * (unsigned)((f & 3) ^ (2 * (e >> 1) + (g & 1))) + lane_part;
             }
         } else {
-            step = SK * 2;
+            step = STAGE_K * 2;
+            half = 0;
             pos = (uint64_t)(uintptr_t)x.p + (uint64_t)row0 * pitch + (uint64_t)stage0 * step;
-            const int r = lane >> 2, q = (lane & 3) ^ ((r >> 1) & 3) ^ ((r >> 3) & 1);
+            const int r = lane >> 3, q = (lane & 7) ^ piece_swizzle(8 * w + r);
 #pragma unroll
-            for (int j = 0; j < NP; ++j) {
-                // rows behind the operand are read as its last row: their products are not stored
-                const int mine = 64 * j + 16 * w + r < limit ? 64 * j + 16 * w + r : limit - 1;
-                off[j] = (unsigned)mine * (unsigned)pitch + 16u * (unsigned)q;
-            }
-            const int fr = lane & 15, swz = ((fr >> 1) & 3) ^ ((fr >> 3) & 1);
-            rd[0] = lds0 + 64u * (unsigned)(16 * wave_frag0 + fr) + 16u * (unsigned)((lane >> 4) ^ swz);
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int j = 0; j < NP; ++j) {
+                    // rows behind the operand are read as its last row: their products are not stored
+                    const int mine = 64 * j + 32 * h + 8 * w + r < limit ? 64 * j + 32 * h + 8 * w + r : limit - 1;
+                    off[h][j] = (unsigned)mine * (unsigned)pitch + 16u * (unsigned)q;
+                }
+            const int fr = lane & 15;
+            rd[0] = lds0 + 128u * (unsigned)(16 * wave_frag0 + fr) + 16u * (unsigned)((lane >> 4) ^ piece_swizzle(fr));
+            rd[1] = rd[0] ^ 64u;
         }
         pos = fpdt::uniform(pos);
     }
-    // does this lane's piece of stage `s` hold k < K (form N: K rounded up to 8)?
-    __device__ __forceinline__ bool has(int s, int K, int w, int lane) const
+    // The copies of the last `k_left` < STAGE_K of k, with pos at their stage: what lies behind them is fetched
+    // from where k is in range instead (and cleared by clear_tail).
+    __device__ __forceinline__ void turn_to_tail(const Operand& x, int k_left, int w, int lane)
     {
-        if (T) return s * SK + 8 * w + (lane >> 3) < K;
-        const int r = lane >> 2, q = (lane & 3) ^ ((r >> 1) & 3) ^ ((r >> 3) & 1);
-        return s * SK + 8 * q < K;
+        if constexpr (T) {
+            const uint64_t pitch = (uint64_t)x.ld * 2;
+            const int first0 = 8 * w < k_left ? 8 * w : k_left - 1, first1 = 8 * w + 32 < k_left ? 8 * w + 32 : k_left - 1;
+            pos = fpdt::uniform(pos - (uint64_t)(8 * w - first0) * pitch);
+            half = (uint64_t)(first1 - first0) * pitch;
+            const int k = lane >> 3;
+            const int back0 = k > k_left - 1 - first0 ? k - (k_left - 1 - first0) : 0, back1 = k > k_left - 1 - first1 ? k - (k_left - 1 - first1) : 0;
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                off[0][j] -= (unsigned)back0 * (unsigned)pitch;
+                off[1][j] -= (unsigned)back1 * (unsigned)pitch;
+            }
+        } else {
+            const int q = (lane & 7) ^ piece_swizzle(8 * w + (lane >> 3));
+            const unsigned back = 8 * q < k_left ? 0u : 16u * (unsigned)q;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int j = 0; j < NP; ++j) off[h][j] -= back;
+        }
+        step = 0;
     }
-    // fragment i of the wave (16 rows x 32 k: lane l holds row l % 16, k = 8 (l / 16) .. + 7) of the stage at
-    // LDS byte `slot`
-    __device__ __forceinline__ bf16x8 frag(int i, unsigned slot) const
+    // Zeros into this lane's pieces of a stage of which `k_left` < STAGE_K of k are in range (form N: rounded up to
+    // 8); lds0: this wave's first piece of the operand in the slot
+    __device__ __forceinline__ void clear_tail(int k_left, int w, int lane, unsigned lds0) const
     {
-        if (T) {
+        typedef __attribute__((address_space(3))) u32x4* lds_u32x4_ptr;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int k = T ? 32 * h + 8 * w + (lane >> 3) : 8 * ((lane & 7) ^ piece_swizzle(8 * w + (lane >> 3)));
+            if (k >= k_left)
+#pragma unroll
+                for (int j = 0; j < NP; ++j) *(lds_u32x4_ptr)(uintptr_t)(lds0 + PANEL * (unsigned)j + 4096u * (unsigned)h + 16u * (unsigned)lane) = u32x4{0, 0, 0, 0};
+        }
+    }
+    // LDS byte of the fragments 0, 4, .. (q = 0), .. of k-step ks of the stage at LDS byte `slot` (form N: of all
+    // of them, q = 0); opaque, so that the fragments are reached by the reads' constant offsets from here
+    __device__ __forceinline__ unsigned base(int q, int ks, unsigned slot) const
+    {
+        unsigned at = T ? rd[q % (T ? 4 : 2)] + slot : rd[ks] + slot;
+        asm volatile("" : "+v"(at));
+        return at;
+    }
+    // fragment i of the wave (16 rows x 32 k: lane l holds row l % 16, k = 8 (l / 16) .. + 7) of k-step ks; at:
+    // base(i % 4 (form N: 0), ks, the stage's slot)
+    __device__ __forceinline__ bf16x8 frag(int i, int ks, unsigned at) const
+    {
+        if constexpr (T) {
             typedef short short4v __attribute__((ext_vector_type(4)));
             typedef short short8v __attribute__((ext_vector_type(8)));
             typedef __attribute__((address_space(3))) short4v* lds_short4_ptr;
-            const unsigned at = rd[i & 3] + slot + PANEL * (unsigned)(i >> 2);
+            at += PANEL * (unsigned)(i >> 2) + 4096u * (unsigned)ks;
             const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(uintptr_t)at);
             const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(uintptr_t)(at + 512u));
             const short8v both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
             return __builtin_bit_cast(bf16x8, both);
+        } else {
+            typedef __attribute__((address_space(3))) u32x4* lds_u32x4_ptr;
+            return fpdt::as_bf16x8(*(lds_u32x4_ptr)(uintptr_t)(at + 2048u * (unsigned)i));
         }
-        typedef __attribute__((address_space(3))) u32x4* lds_u32x4_ptr;
-        return fpdt::as_bf16x8(*(lds_u32x4_ptr)(uintptr_t)(rd[0] + slot + 1024u * (unsigned)i));
     }
 };
+
+// A finished accumulator tile in ordinary registers.  The compiler does not know that the MFMAs are MFMAs, so it must
+// not move an accumulator by itself (it would not wait for the result): behind the last MFMA they are read here and
+// nowhere else, by statements that stay behind the wait.  (The last instruction: VALU results need two wait
+// states before a lane exchange reads them, which the compiler does not see either.)
+__device__ __forceinline__ floatx4 read_accumulator(const floatx4& acc)
+{
+    float x, y, z, w;
+    asm volatile("v_accvgpr_read_b32 %0, %4\n\tv_accvgpr_read_b32 %1, %5\n\tv_accvgpr_read_b32 %2, %6\n\tv_accvgpr_read_b32 %3, %7\n\ts_nop 1"
+                 : "=&v"(x), "=&v"(y), "=&v"(z), "=&v"(w)
+                 : "a"(acc[0]), "a"(acc[1]), "a"(acc[2]), "a"(acc[3]));
+    return floatx4{x, y, z, w};
+}
+
+// f(0), f(1), .. with the index as a constant of its type
+template <int... I, typename F>
+__device__ __forceinline__ void for_each_index(std::integer_sequence<int, I...>, F f)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
 
 // C [M, N] row-major, leading dimension ldc elements.  A workgroup of four waves, one per SIMD, computes a
 // (64 WMT) x (64 WNT) tile over the stages of its split; wave (w / 2, w % 2) owns 2 WMT x 2 WNT accumulator
 // tiles of 16 x 16.
 //
-// What bounds it: LDS traffic next to the MFMAs.  The 128 x 128 elements of a wave at WMT = WNT = 4 need
-// 16 KiB of fragments per 32 k; eight waves of 128 x 64 need 24 KiB each pair, and with the copies' writes
-// LDS was then as busy as the MFMA pipes.  The 256 accumulator registers leave room for one wave per SIMD,
-// so nothing but this wave's own instruction order hides a latency.  A stage runs in two phases, the left
-// and the right half of the wave's columns.  Each fragment register is read again as soon as its last MFMA
-// of the stage is issued, at least 28 MFMAs (of 64) ahead of its next use: B's right half in the first
-// phase, A and B's left half (of the next stage) in the second.  The copies go out one at a time between
-// the MFMAs.  Stages of 32 k keep four slots in LDS, so a copy has two to three stages to land.  One barrier
-// per stage, between the phases: there stage s + 1 has landed and every wave has read all of stage s,
-// whose slot is free for stage s + RING.
+// What bounds it: the matrix cores are busy in 0.8 of the cycles (8192^3; nine tenths of the main loop's) at a clock that
+// the power budget holds at 1.7 GHz, where the same loop without its copies runs at 1.9 and on registers alone at 2.0.
+// The 128 x 128 elements of a wave at WMT = WNT = 4 need 16 KiB of fragments per 32 k (eight waves of 128 x 64: 24 KiB
+// each pair).  The 256 accumulator registers leave room for one wave per SIMD, so nothing but this wave's own
+// instruction order hides a latency.  A stage is two k-steps; the fragments of a k-step are read into a set of registers
+// of their own under the MFMAs of the one before it.  The copies of stage s + 2 go out one at a time between the MFMAs
+// of stage s: A's part, for which LDS has a third slot, in the first half, B's part in the second, into the slot that
+// stage s has left.  One barrier per stage, between the halves: there stage s + 1 has landed and every wave has read all
+// of stage s.
 //
-// The 16 x 16 x 32 MFMA moves half as many accumulator registers per product as the 32 x 32 x 16 one and
-// leaves the fragments in the registers they were read into for a whole stage (64 instead of 128
-// registers): 8192^3, X W^T 889 -> 832 us, dY W 872 -> 818, dY^T X 961 -> 867.
-//
-// Measured: 1030-1340 TFLOP/s.  With the 32 x 32 x 16 MFMA 8192^3 ran at 1237 TFLOP/s, the same loop without
-// its copies at 1497, with every copy a hit in L2 at 1217, with three or five slots as with four: the
-// copies' throughput into LDS next to the fragment reads is what is left, not their latency.  Operands
-// packed into MFMA fragments first (contiguous KiB per copy) gave the loop 5-10% and cost 8-15% of an
-// operation in packing.
+// Measured (8192^3 on cards where a library product takes 705-720 us; X W^T, dY W, dY^T X +=, us): stages of 32 k in
+// four slots, whose copies read 64 bytes of a row of form N, 846, 857, 886; this 734, 712, 760: whole lines 765, 750,
+// 808, the copies spread over the stage 751, 736, 765 (in half of its second half: 790, 775, 835), the bf16 epilogue
+// straight from the accumulators (below) the rest.  16384 x 8192 x 8192: 1672, 1688, 1714 -> 1396, 1428, 1471.  Conflicts
+// of form N's reads (half of their cycles with q ^ r % 8 ^ (r / 8) % 2 for a swizzle) cost nothing here.  With the
+// 32 x 32 x 16 MFMA, which moves twice the accumulator registers per product, the loop took 6% more.  Operands packed
+// into MFMA fragments first gave the loop 5-10% and cost 8-15% of an operation in packing.
 //
 // The MFMAs are issued through inline assembly so that the accumulators stay in accumulation registers
 // for the whole loop (with the builtin the allocator moved tiles between the two register files).
@@ -192,12 +264,14 @@ template <bool TA, bool TB, bool OUT_F32, bool ACCUM, int WMT, int WNT>
 __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand B, int K, void* __restrict__ Cout, int64_t ldc,
                                                               int M, int N, Units u, float* __restrict__ part)
 {
-    constexpr unsigned STAGE = (WMT + WNT) * PANEL;      // bytes of a slot: A's panels, then B's
-    constexpr int MI = 2 * WMT, NI = 2 * WNT, NH = NI / 2;  // accumulator tiles of a wave; NH: columns of a phase
-    constexpr int NC = WMT + WNT;                        // copies of a wave per stage
-    constexpr int NC0 = (NC + 1) / 2;                    // .. of which in the second phase of a stage, the rest in the first phase of the next
+    // LDS: slots of a stage each, three of A and two of B.  64 x 256 tiles: two of each, so that two workgroups fit a
+    // compute unit as with 128 x 128 (one runs its MFMAs under the other's first copies and its epilogue).
+    constexpr bool SPREAD = WMT > 1;  // A's copies go out in the first half of a stage, into the third slot
+    constexpr unsigned SLOT_A = WMT * PANEL, SLOT_B = WNT * PANEL, B0 = (SPREAD ? 3 : 2) * SLOT_A, LDS_BYTES = B0 + 2 * SLOT_B;
+    constexpr int MI = 2 * WMT, NI = 2 * WNT;                   // accumulator tiles of a wave
+    constexpr int NCA = 2 * WMT, NCB = 2 * WNT;                 // copies of a wave per stage
     static_assert(NWAVE == 4, "a wave copies a quarter of every panel");
-    __shared__ __attribute__((aligned(256))) u32x4 ring[(RING + 1) * STAGE / 16];
+    __shared__ __attribute__((aligned(256))) u32x4 ring[LDS_BYTES / 16];
     // Consecutive workgroup ids land on different XCDs (each with its own L2): give every XCD a
     // contiguous run of tiles, so that the tiles that share an operand row share an L2.  The units of the
     // divided tiles go half in front of the whole tiles and half behind them: the compute units that
@@ -228,43 +302,37 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand 
     const int lane = threadIdx.x & 63;
     const int wu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wu >> 1, wn = wu & 1;
-    const int stages = K / SK;  // whole ones, >= 1 in every split (host)
+    const int stages = K / STAGE_K;  // whole ones
     const int unit_stages = is_part ? u.split_stages : stages, stage0 = (int)split * unit_stages;
     const int n_full = stages - stage0 < unit_stages ? stages - stage0 : unit_stages;
-    const bool tail = K % SK != 0 && stage0 + n_full == stages;  // the last split's stage of less than SK
+    const int k_left = stage0 + n_full == stages ? K % STAGE_K : 0;  // the last split's stage of less than STAGE_K
+    const int total = n_full + (k_left > 0 ? 1 : 0);            // >= 1 (host)
 
     const unsigned ring0 = fpdt::lds_address(ring);
     Side<TA, WMT> a_side;
     Side<TB, WNT> b_side;
     a_side.init(A, tile_m * (64 * WMT), stage0, wu, wm * MI, lane, ring0);
-    b_side.init(B, tile_n * (64 * WNT), stage0, wu, wn * NI, lane, ring0 + WMT * PANEL);
+    b_side.init(B, tile_n * (64 * WNT), stage0, wu, wn * NI, lane, ring0);
     const unsigned copy_lds = ring0 + 1024u * (unsigned)wu;
-    // Copy j of the stage at a_at / b_at into the slot at LDS byte `slot_lds`: two scalar instructions besides
-    // the copy, the second one for copy_address_rule (mfma_tiles.h) and as m0's wait state.
-    auto copy = [&](int j, uint64_t a_at, uint64_t b_at, unsigned slot_lds) {
+    // Copy j of a side's stage into the slot at LDS byte `slot_lds`: two scalar instructions besides the copy, the
+    // second one for copy_address_rule (mfma_tiles.h) and as m0's wait state.
+    auto copy = [](int j, unsigned off, uint64_t at, unsigned slot_lds) {
         uint64_t addr;
         asm volatile("s_add_u32 m0, %1, %2\n\ts_mov_b64 %0, %4\n\tglobal_load_lds_dwordx4 %3, %0"
                      : "=&s"(addr)
-                     : "s"(slot_lds), "i"(PANEL * j), "v"(j < WMT ? a_side.off[j % WMT] : b_side.off[(j - WMT) % WNT]), "s"(j < WMT ? a_at : b_at)
+                     : "s"(slot_lds), "i"(PANEL * (j / 2) + 4096 * (j % 2)), "v"(off), "s"(at)
                      : "memory", "scc");
     };
-    auto stage_at = [&](uint64_t pos, int t, uint64_t step) { return pos + (uint64_t)((int64_t)t * (int64_t)step); };  // t stages behind pos
-    if (tail) {  // its pieces pass through registers, zero behind K, into the slot behind the ring
-        u32x4 v[NC];
-#pragma unroll
-        for (int j = 0; j < NC; ++j) {
-            v[j] = u32x4{0, 0, 0, 0};
-            if (j < WMT) {
-                const uint64_t src = a_side.pos + (uint64_t)n_full * a_side.step + a_side.off[j % WMT];
-                if (a_side.has(stages, K, wu, lane)) v[j] = *reinterpret_cast<const u32x4*>((uintptr_t)src);
-            } else {
-                const uint64_t src = b_side.pos + (uint64_t)n_full * b_side.step + b_side.off[(j - WMT) % WNT];
-                if (b_side.has(stages, K, wu, lane)) v[j] = *reinterpret_cast<const u32x4*>((uintptr_t)src);
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < NC; ++j) ring[(RING * STAGE + PANEL * j + 1024u * wu) / 16 + lane] = v[j];
-    }
+    auto copy_a = [&](int j, unsigned slot_lds) { copy(j, a_side.off[j % 2][j / 2 % WMT], a_side.pos + (j % 2 ? a_side.half : 0), slot_lds); };
+    auto copy_b = [&](int j, unsigned slot_lds) { copy(j, b_side.off[j % 2][j / 2 % WNT], b_side.pos + (j % 2 ? b_side.half : 0), slot_lds); };
+    auto turn_to_tail = [&] {
+        a_side.turn_to_tail(A, k_left, wu, lane);
+        b_side.turn_to_tail(B, k_left, wu, lane);
+    };
+    auto clear_tail = [&](unsigned a_slot, unsigned b_slot) {  // (this wave's own copies have landed)
+        a_side.clear_tail(k_left, wu, lane, copy_lds + a_slot);
+        b_side.clear_tail(k_left, wu, lane, copy_lds + b_slot);
+    };
 
     floatx4 acc[MI][NI];
 #pragma unroll
@@ -275,86 +343,143 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand 
             asm volatile("" : "+a"(acc[i][j]));
         }
 
-    // Stages 0 .. RING - 2 whole and the first copies of stage RING - 1.  A copy behind the last whole
-    // stage fetches that stage again, into a slot that nobody reads any more: the loop then needs no
-    // branch (with one, the allocator spilled the accumulators) and its wait counts are constants.
-    auto ahead = [&](int t, int full) { return t < full ? t : full - 1; };
+    // the first two stages
+    auto first_copies = [&](unsigned stage) {
 #pragma unroll
-    for (int t = 0; t < RING; ++t)
+        for (int j = 0; j < NCA; ++j) copy_a(j, copy_lds + stage * SLOT_A);
 #pragma unroll
-        for (int j = 0; j < (t < RING - 1 ? NC : NC0); ++j)
-            fpdt::frag_to_lds_at(j < WMT ? stage_at(a_side.pos, ahead(t, n_full), a_side.step) : stage_at(b_side.pos, ahead(t, n_full), b_side.step),
-                                 copy_lds + (unsigned)t * STAGE + PANEL * (unsigned)j,
-                                 (int)(j < WMT ? a_side.off[j % WMT] : b_side.off[(j - WMT) % WNT]));
-    fpdt::wait_vmem_at_most<(RING - 2) * NC + NC0>();
-    fpdt::barrier_no_fence();
-
-    bf16x8 a[MI], b[NI];
-#pragma unroll
-    for (int j = 0; j < NH; ++j) b[j] = b_side.frag(j, 0u);
-#pragma unroll
-    for (int i = 0; i < MI; ++i) a[i] = a_side.frag(i, 0u);
-
-    // the sides' pos is at the current stage, which is in slot `cur`
-    unsigned cur = 0;
-    int left = n_full + (tail ? 1 : 0);
-    do {
-        const int full = tail ? left - 1 : left;  // (0 in the tail stage: its copies fetch the stage before it)
-        const unsigned nxt = tail && left == 2 ? RING : (cur + 1) % RING, prv = (cur + RING - 1) % RING;
-        const int t_prv = ahead(RING - 1, full), t_cur = ahead(RING, full);
-        const uint64_t a_prv = stage_at(a_side.pos, t_prv, a_side.step), b_prv = stage_at(b_side.pos, t_prv, b_side.step);
-        const uint64_t a_cur = stage_at(a_side.pos, t_cur, a_side.step), b_cur = stage_at(b_side.pos, t_cur, b_side.step);
-        const unsigned lds_prv = copy_lds + prv * STAGE, lds_cur = copy_lds + cur * STAGE;
-        constexpr int NM = MI * NH;  // MFMAs of a phase
-#pragma unroll
-        for (int m = 0; m < NM; ++m) {
-            TW_MFMA(acc[m / NH][m % NH], a[m / NH], b[m % NH]);
-            if (m < NH) b[NH + m] = b_side.frag(NH + m, cur * STAGE);
-#pragma unroll
-            for (int q = m * (NC - NC0) / NM; q < (m + 1) * (NC - NC0) / NM; ++q) copy(NC0 + q, a_prv, b_prv, lds_prv);  // the rest of stage s + RING - 1
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        fpdt::wait_vmem_at_most<(RING - 2) * NC>();
-        fpdt::barrier_no_fence();
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int m = 0; m < NM; ++m) {
-            TW_MFMA(acc[m / NH][NH + m % NH], a[m / NH], b[NH + m % NH]);
-            if (m < NH) b[m] = b_side.frag(m, nxt * STAGE);
-            if (m % NH == NH - 1) a[m / NH] = a_side.frag(m / NH, nxt * STAGE);
-#pragma unroll
-            for (int q = m * NC0 / NM; q < (m + 1) * NC0 / NM; ++q) copy(q, a_cur, b_cur, lds_cur);  // stage s + RING
-            __builtin_amdgcn_sched_barrier(0);
-        }
+        for (int j = 0; j < NCB; ++j) copy_b(j, copy_lds + B0 + stage * SLOT_B);
+    };
+    if (n_full == 0) turn_to_tail();
+    first_copies(0);
+    if (total > 1) {
         a_side.pos += a_side.step;
         b_side.pos += b_side.step;
-        cur = nxt;
-    } while (--left > 0);
-    fpdt::wait_vmem_at_most<0>();  // nothing may still be on its way into LDS when the ring is used again or the workgroup ends
+        if (n_full == 1) turn_to_tail();
+        first_copies(1);
+        fpdt::wait_vmem_at_most<NCA + NCB>();
+    } else {
+        fpdt::wait_vmem_at_most<0>();
+        if (n_full == 0) clear_tail(0, B0);
+    }
     fpdt::barrier_no_fence();
+
+    bf16x8 a[2][MI], b[2][NI];  // by k-step
+#pragma unroll
+    for (int j = 0; j < NI; ++j) b[0][j] = b_side.frag(j, 0, b_side.base(TB ? j % 4 : 0, 0, B0));
+#pragma unroll
+    for (int i = 0; i < MI; ++i) a[0][i] = a_side.frag(i, 0, a_side.base(TA ? i % 4 : 0, 0, 0u));
+
+    // Half of a stage: the MFMAs of k-step ks and, evenly between them, the fragments of the k-step behind it (of
+    // the slots at LDS bytes a_slot and b_slot) and, with COPY, the copies of a stage: of A into the slot at `a_lds` in
+    // the first half (SPREAD), of B into that at `b_lds` in the second.  (All of a stage's copies in its second half: 2%
+    // slower; in half of that: 5%.)
+    auto half_stage = [&](auto ks_tag, auto copy_tag, unsigned a_slot, unsigned b_slot, unsigned a_lds, unsigned b_lds) {
+        constexpr int ks = decltype(ks_tag)::value, nx = 1 - ks;
+        constexpr bool COPY = decltype(copy_tag)::value;
+        constexpr int NM = MI * NI, NR = MI + NI;  // MFMAs, fragments
+        constexpr int A_HERE = SPREAD == (ks == 0) ? NCA : 0, NC = A_HERE + (ks == 1 ? NCB : 0);  // copies
+        constexpr int READ_SPAN = NM * 3 / 4;  // MFMAs over which the reads are spread: the last ones are not waited for
+        unsigned a_at[4], b_at[4];
+        for_each_index(std::make_integer_sequence<int, NM>{}, [&](auto m_tag) __attribute__((always_inline)) {
+            constexpr int m = decltype(m_tag)::value;
+            TW_MFMA(acc[m / NI][m % NI], a[ks][m / NI], b[ks][m % NI]);
+            constexpr int r = (m * NR + READ_SPAN - 1) / READ_SPAN;
+            if constexpr (m < READ_SPAN && r * READ_SPAN < (m + 1) * NR) {  // fragments in the order of their use
+                if constexpr (r < NI) {
+                    if (r < (TB ? 4 : 1)) b_at[r % 4] = b_side.base(r, nx, b_slot);
+                    b[nx][r] = b_side.frag(r, nx, b_at[TB ? r % 4 : 0]);
+                } else {
+                    if (r - NI < (TA ? 4 : 1)) a_at[(r - NI) % 4] = a_side.base(r - NI, nx, a_slot);
+                    a[nx][r - NI] = a_side.frag(r - NI, nx, a_at[TA ? (r - NI) % 4 : 0]);
+                }
+            }
+            constexpr int c = (m * NC + NM - 1) / NM;
+            if constexpr (COPY && c * NM < (m + 1) * NC) {
+                if constexpr (c < A_HERE) copy_a(c, a_lds);
+                else copy_b(c - A_HERE, b_lds);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        static_assert(NR <= READ_SPAN && NC <= NM, "at most one of each behind an MFMA");
+    };
+    typedef std::integral_constant<int, 0> Ks0;
+    typedef std::integral_constant<int, 1> Ks1;
+    // slots (LDS bytes) of the current stage s, of stage s + 1, and of A's part of stage s + 2 (its part of B takes the
+    // slot of stage s)
+    unsigned cur_a = 0, cur_b = B0, nxt_a = SLOT_A, nxt_b = B0 + SLOT_B, free_a = SPREAD ? 2 * SLOT_A : 0;
+    auto next_stage = [&] {
+        const unsigned was_a = cur_a, was_b = cur_b;
+        cur_a = nxt_a;
+        cur_b = nxt_b;
+        nxt_a = free_a;
+        nxt_b = was_b;
+        free_a = SPREAD ? was_a : cur_a;
+    };
+    // the stages behind the first two: the whole ones, then the last one of less than STAGE_K
+    int copied = n_full > 2 ? n_full - 2 : 0;
+#pragma unroll 1
+    for (int pass = 0; pass < 2; ++pass) {
+#pragma unroll 1
+        for (; copied > 0; --copied) {
+            a_side.pos += a_side.step;
+            b_side.pos += b_side.step;
+            half_stage(Ks0{}, std::true_type{}, cur_a, cur_b, copy_lds + free_a, 0u);
+            fpdt::wait_vmem_at_most<SPREAD ? NCA : 0>();  // the next stage: all but the copies just issued
+            fpdt::barrier_no_fence();  // everyone's part of it; everyone has read all of this one
+            __builtin_amdgcn_sched_barrier(0);
+            half_stage(Ks1{}, std::true_type{}, nxt_a, nxt_b, copy_lds + free_a, copy_lds + cur_b);
+            next_stage();
+        }
+        if (pass == 0 && k_left > 0 && n_full >= 2) {
+            a_side.pos += a_side.step;
+            b_side.pos += b_side.step;
+            turn_to_tail();
+            copied = 1;
+        }
+    }
+    // the last two
+    int left = total < 2 ? total : 2;
+    do {
+        half_stage(Ks0{}, std::false_type{}, cur_a, cur_b, 0u, 0u);
+        fpdt::wait_vmem_at_most<0>();
+        if (left == 2 && k_left > 0) clear_tail(nxt_a, nxt_b);
+        fpdt::barrier_no_fence();
+        __builtin_amdgcn_sched_barrier(0);
+        half_stage(Ks1{}, std::false_type{}, nxt_a, nxt_b, 0u, 0u);  // (behind the last stage: fragments of idle slots, not used)
+        next_stage();
+    } while (--left > 0);
+    fpdt::barrier_no_fence();  // nobody reads the ring any more
 
     // the accumulators are read by ordinary instructions from here on
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
     // accumulator tile (i, j): lane l holds row l % 16, columns 4 (l / 16) .. + 3
     const int mw = wm * (32 * WMT), nw = wn * (32 * WNT);  // the wave's first row and column within the tile
-    // Sixteen rows at a time pass through LDS (each wave its own part of the idle ring), so that a store
-    // covers 128 WNT bytes of a row in fp32.  With ACC the old values of sixteen rows are all requested, and
-    // those of the next sixteen in front of their stores: one load at a time, each waited for behind the
-    // store before it, left the read-modify-write of a weight gradient at a sixth of the memory rate.
-    auto store_tile = [&](auto* out, int64_t pitch, auto acc_tag) {
-        constexpr bool ACC = decltype(acc_tag)::value;
-        typedef std::remove_pointer_t<decltype(out)> out_t;
-        typedef out_t out4 __attribute__((ext_vector_type(4)));
+    // `m_left`, `n_left` below: rows and columns of C from `out` on; where they end within the tile, they end with
+    // 16 bytes (WHOLE: they do not, and no access is conditional: conditional loads of old values wait for each
+    // other, 8192^3, dY^T X, 800 -> 890 us).  With ACC the old values of sixteen rows are all requested, and those of the next sixteen in front of
+    // their stores: one load at a time, each waited for behind the store before it, left the read-modify-write of a
+    // weight gradient at a sixth of the memory rate.
+    //
+    // fp32: sixteen rows at a time pass through LDS (each wave its own part of the idle ring), so that an access
+    // covers 128 WNT bytes of a row.  This is bound by the memory: 14 us per tile of 256 x 256 added to, of all
+    // compute units.  (Straight from the accumulators, 64 bytes of sixteen rows or 128 of eight per access: 8192^3,
+    // dY^T X, 779 -> 830 and 860 us.)
+    auto store_f32 = [&](float* out, int64_t pitch, int m_left, int n_left, auto acc_tag, auto whole_tag) {
+        constexpr bool ACC = decltype(acc_tag)::value, WHOLE = decltype(whole_tag)::value;
         constexpr int LPR = 8 * WNT, RPI = 64 / LPR, PITCH = 32 * WNT + 4;  // lanes per row, rows per access, floats (4 apart: no bank conflicts)
-        static_assert(4 * 16 * PITCH * 4 <= (RING + 1) * (int)STAGE, "the ring holds sixteen rows of every wave");
+        static_assert(4 * 16 * PITCH * 4 <= (int)LDS_BYTES, "the ring holds sixteen rows of every wave");
         float* rows = reinterpret_cast<float*>(ring) + wu * (16 * PITCH);
         float* put = rows + (lane & 15) * PITCH + 4 * (lane >> 4);
         const float* get = rows + (lane / LPR) * PITCH + 4 * (lane % LPR);
-        out_t* c0 = out + (size_t)(mw + lane / LPR) * pitch + nw + 4 * (lane % LPR);
-        out4 old[2][NI];
+        const int row = mw + lane / LPR, col = nw + 4 * (lane % LPR);
+        float* c0 = out + (int64_t)row * pitch + col;
+        auto in = [&](int i, int k) { return WHOLE || (row + 16 * i + RPI * k < m_left && col < n_left); };
+        floatx4 old[2][NI];
         auto request = [&](int i) {
 #pragma unroll
-            for (int k = 0; k < NI; ++k) old[i & 1][k] = *reinterpret_cast<const out4*>(c0 + (size_t)(16 * i + RPI * k) * pitch);
+            for (int k = 0; k < NI; ++k)
+                if (in(i, k)) old[i & 1][k] = *reinterpret_cast<const floatx4*>(c0 + (int64_t)(16 * i + RPI * k) * pitch);
         };
         if (ACC) request(0);
 #pragma unroll
@@ -363,38 +488,87 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand 
             __builtin_amdgcn_sched_barrier(0);  // no further ahead: the registers are spoken for
 #pragma unroll
             for (int j = 0; j < NI; ++j) {
-                asm volatile("" : "+a"(acc[i][j]));  // stays in its accumulation registers until here
-                *reinterpret_cast<floatx4*>(put + 16 * j) = acc[i][j];
+                *reinterpret_cast<floatx4*>(put + 16 * j) = read_accumulator(acc[i][j]);
             }
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
             for (int k = 0; k < NI; ++k) {
-                const floatx4 x = *reinterpret_cast<const floatx4*>(get + RPI * k * PITCH);
-                out4 v;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = combine<ACC>(x[r], ACC ? old[i & 1][k][r] : out_t(0));
-                *reinterpret_cast<out4*>(c0 + (size_t)(16 * i + RPI * k) * pitch) = v;
+                floatx4 v = *reinterpret_cast<const floatx4*>(get + RPI * k * PITCH);
+                if (ACC) v = old[i & 1][k] + v;
+                if (in(i, k)) *reinterpret_cast<floatx4*>(c0 + (int64_t)(16 * i + RPI * k) * pitch) = v;
             }
             __builtin_amdgcn_wave_barrier();
         }
     };
+    // bf16: straight from the accumulators, 16 bytes per lane and access.  Two neighbouring tiles exchange lane groups,
+    // so that group g holds columns 8 (g / 2) .. + 7 of tile j + g % 2: an access covers 64 bytes of sixteen rows.
+    // (Through LDS, and rounded in integer arithmetic, a tile of 256 x 256 took 17 us, during which the matrix
+    // cores idle: 8192^3, X W^T, 755 -> 738 us.  128 bytes of eight rows per access: the same.)
+    auto store_bf16 = [&](uint16_t* out, int64_t pitch, int m_left, int n_left, auto acc_tag, auto whole_tag) {
+        constexpr bool ACC = decltype(acc_tag)::value, WHOLE = decltype(whole_tag)::value;
+        constexpr int NA = NI / 2;
+        const int g = lane >> 4, row = mw + (lane & 15), col = nw + 16 * (g & 1) + 8 * (g >> 1);
+        uint16_t* c0 = out + (int64_t)row * pitch + col;
+        auto in = [&](int i, int k) { return WHOLE || (row + 16 * i < m_left && col + 32 * k < n_left); };
+        u32x4 old[2][NA];
+        auto request = [&](int i) {
+#pragma unroll
+            for (int k = 0; k < NA; ++k)
+                if (in(i, k)) old[i & 1][k] = *reinterpret_cast<const u32x4*>(c0 + (int64_t)(16 * i) * pitch + 32 * k);
+        };
+        if (ACC) request(0);
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            if (ACC && i + 1 < MI) request(i + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < NA; ++k) {
+                const floatx4 a0 = read_accumulator(acc[i][2 * k]), a1 = read_accumulator(acc[i][2 * k + 1]);
+                u32x4 v;
+                if constexpr (!ACC) {
+                    const u32x4 x = pack_bf16(a0, a1);
+                    const auto lo = __builtin_amdgcn_permlane16_swap(x[0], x[2], false, false);
+                    const auto hi = __builtin_amdgcn_permlane16_swap(x[1], x[3], false, false);
+                    v = u32x4{lo[0], hi[0], lo[1], hi[1]};
+                } else {  // exchanged in fp32, as they are added to before they are rounded
+                    const u32x4 o = old[i & 1][k];
+                    floatx4 x, y;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const auto xy = __builtin_amdgcn_permlane16_swap(__float_as_uint(a0[r]), __float_as_uint(a1[r]), false, false);
+                        x[r] = __uint_as_float((o[r / 2] << (r % 2 ? 0 : 16)) & 0xffff0000u) + __uint_as_float(xy[0]);
+                        y[r] = __uint_as_float((o[2 + r / 2] << (r % 2 ? 0 : 16)) & 0xffff0000u) + __uint_as_float(xy[1]);
+                    }
+                    v = pack_bf16(x, y);
+                }
+                if (in(i, k)) *reinterpret_cast<u32x4*>(c0 + (int64_t)(16 * i) * pitch + 32 * k) = v;
+            }
+        }
+    };
     if (is_part) {  // this split's sums of the whole tile; tw_split_sum_kernel adds them
         constexpr size_t TILE_ELEMS = (size_t)(64 * WMT) * (64 * WNT);
-        store_tile(part + ((size_t)split * divided + (id - (unsigned)u.whole)) * TILE_ELEMS, 64 * WNT, std::false_type{});
+        store_f32(part + ((size_t)split * divided + (id - (unsigned)u.whole)) * TILE_ELEMS, 64 * WNT, 64 * WMT, 64 * WNT, std::false_type{}, std::true_type{});
         return;
     }
     typedef typename std::conditional<OUT_F32, float, uint16_t>::type out_t;
     const int mt = tile_m * (64 * WMT), nt = tile_n * (64 * WNT);
     out_t* tile = static_cast<out_t*>(Cout) + (size_t)mt * ldc + nt;
-    if (mt + 64 * WMT <= M && nt + 64 * WNT <= N && ldc % 4 == 0 && reinterpret_cast<uintptr_t>(Cout) % (4 * sizeof(out_t)) == 0) {
-        store_tile(tile, ldc, std::integral_constant<bool, ACCUM>{});
+    constexpr int PER16 = 16 / sizeof(out_t);
+    if (N % PER16 == 0 && ldc % PER16 == 0 && reinterpret_cast<uintptr_t>(Cout) % 16 == 0) {
+        auto store = [&](auto whole_tag) {
+            if constexpr (OUT_F32) store_f32(tile, ldc, M - mt, N - nt, std::integral_constant<bool, ACCUM>{}, whole_tag);
+            else store_bf16(tile, ldc, M - mt, N - nt, std::integral_constant<bool, ACCUM>{}, whole_tag);
+        };
+        if (mt + 64 * WMT <= M && nt + 64 * WNT <= N) store(std::true_type{});
+        else store(std::false_type{});
         return;
     }
-    // A tile that reaches behind C, or rows of C that are not aligned for four elements: sixteen rows at a time
-    // through LDS as above, one element per lane and access, consecutive lanes on consecutive columns.  (Straight
+    // Rows of C that do not come in pieces of 16 bytes: sixteen rows at a time through LDS (each wave its own part
+    // of the idle ring), one element per lane and access, consecutive lanes on consecutive columns.  (Straight
     // from the accumulators an access touched 16 rows at 16 bytes each: odd widths then took up to twice the
     // time of the tiles' MFMAs.)  The old values of the sixteen rows are requested together.
-    constexpr int PITCH = 32 * WNT + 4, CPR = 32 * WNT / 64;  // floats between rows, accesses per row
+    constexpr int PITCH = 32 * WNT + 4, CPR = 32 * WNT / 64;  // floats between rows (4 apart: no bank conflicts), accesses per row
+    static_assert(4 * 16 * PITCH * 4 <= (int)LDS_BYTES, "the ring holds sixteen rows of every wave");
     float* rows = reinterpret_cast<float*>(ring) + wu * (16 * PITCH);
     float* put = rows + (lane & 15) * PITCH + 4 * (lane >> 4);
     bool in[CPR];
@@ -412,8 +586,7 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand 
             for (int p = 0; p < CPR; ++p) old[r][p] = ACCUM && r < left && in[p] ? c[(size_t)r * ldc + 64 * p] : out_t(0);
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
-            asm volatile("" : "+a"(acc[i][j]));
-            *reinterpret_cast<floatx4*>(put + 16 * j) = acc[i][j];
+            *reinterpret_cast<floatx4*>(put + 16 * j) = read_accumulator(acc[i][j]);
         }
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -465,7 +638,7 @@ struct Pool {
 };
 struct Realigned {
     const void* src;
-    int64_t R, C, ld, R2, C2;
+    int64_t R, C, ld;
     const uint16_t* copy;
 };
 Pool g_pool[64];
@@ -515,7 +688,7 @@ struct Written {
 // Can the product kernel read X [R, C] where it is?
 bool readable(const void* X, int64_t R, int64_t C, int64_t ld, bool k_rows, bool padded, const Written& out)
 {
-    return (k_rows ? R : C) >= SK && (C % 8 == 0 || padded) && ld % 8 == 0 && ld < (k_rows ? MAX_PITCH_T : MAX_PITCH) &&
+    return (C % 8 == 0 || padded) && ld % 8 == 0 && ld < (k_rows ? MAX_PITCH_T : MAX_PITCH) &&
            reinterpret_cast<uintptr_t>(X) % 16 == 0 && !out.overlaps(X, R, C, ld);
 }
 
@@ -531,7 +704,7 @@ int take_operand(Pool& pool, const void* X, int64_t R, int64_t C, int64_t ld, bo
         res->p = static_cast<const uint16_t*>(X);
         res->ld = ld;
     } else {
-        const int64_t R2 = k_rows && R < SK ? SK : R, C2 = !k_rows && C < SK ? SK : (C + 7) / 8 * 8;
+        const int64_t C2 = (C + 7) / 8 * 8;
         // whole cache lines from row to row: a stage's pieces of a row are half a line (form N), of four
         // rows' columns a whole one (form T), and with 8208 bytes in place of 8320 straddled two
         // (16384 x 4097 x 4096 in 8 chunks: 864 -> 743 us)
@@ -539,15 +712,15 @@ int take_operand(Pool& pool, const void* X, int64_t R, int64_t C, int64_t ld, bo
         res->p = nullptr;
         if (cache)
             for (const Realigned& c : g_cache)
-                if (c.src == X && c.R == R && c.C == C && c.ld == ld && c.R2 == R2 && c.C2 == C2) res->p = c.copy;
+                if (c.src == X && c.R == R && c.C == C && c.ld == ld) res->p = c.copy;
         if (!res->p) {
             char* mem = nullptr;
-            if (pool_take(pool, (size_t)R2 * res->ld * 2, &mem)) return 1;
-            const int64_t blocks = (R2 * (C2 / 8) + 255) / 256;
+            if (pool_take(pool, (size_t)R * res->ld * 2, &mem)) return 1;
+            const int64_t blocks = (R * (C2 / 8) + 255) / 256;
             tw_realign_kernel<<<dim3((unsigned)(blocks < 65536 ? blocks : 65536)), 256, 0, st>>>(
-                static_cast<const uint16_t*>(X), R, C, ld, reinterpret_cast<u32x4*>(mem), R2, C2, res->ld);
+                static_cast<const uint16_t*>(X), R, C, ld, reinterpret_cast<u32x4*>(mem), res->ld);
             res->p = reinterpret_cast<const uint16_t*>(mem);
-            if (cache) g_cache.push_back({X, R, C, ld, R2, C2, res->p});
+            if (cache) g_cache.push_back({X, R, C, ld, res->p});
         }
     }
     return res->ld >= (k_rows ? MAX_PITCH_T : MAX_PITCH) ? 2 : 0;
@@ -630,8 +803,7 @@ static int product(Pool& pool, int a_transposed, int b_transposed, int M, int N,
                    int64_t ldb, void* C, int64_t ldc, bool c_f32, bool accumulate, bool cache_b, hipStream_t st)
 {
     const size_t off0 = pool.off;
-    const int Kp = K < SK ? SK : K;  // (realigned operands of less are padded to one stage)
-    const Plan plan = plan_product(M, N, Kp / SK);
+    const Plan plan = plan_launch(M, N, (K < SK ? SK : K) / SK);
     if (plan.u.tiles == 0) return 2;
     // Aop[m,k]: A stored [M,K] (as is) or [K,M] (transposed); Bop[n,k]: B stored [N,K] or [K,N]
     const Written out = {C, M, N, ldc, c_f32 ? 4 : 2};
@@ -647,7 +819,7 @@ static int product(Pool& pool, int a_transposed, int b_transposed, int M, int N,
         if (pool_take(pool, part_bytes(plan), &mem)) return 1;
         part = reinterpret_cast<float*>(mem);
     }
-    rc = launch_product(plan, a_transposed, b_transposed, pa, pb, M, N, Kp, C, ldc, c_f32, accumulate, part, st);
+    rc = launch_product(plan, a_transposed, b_transposed, pa, pb, M, N, K, C, ldc, c_f32, accumulate, part, st);
     if (rc) return rc;
     if (plan.u.splits > 1) launch_split_sum(plan, part, M, N, C, ldc, c_f32, accumulate, st);
     // The next product's copies run after this launch on the same stream, so this product's scratch
@@ -706,9 +878,8 @@ static int any_product(Pool& pool, int a_transposed, int b_transposed, int M, in
         if (rc) return rc;
         Plan one = plan;
         one.u.splits = 1;
-        const int Kp = k < SK ? SK : (int)k;
-        one.u.split_stages = Kp / SK;
-        rc = launch_product(one, a_transposed, b_transposed, a, b, M, N, Kp, C, ldc, c_f32, accumulate, part + (size_t)i * (part_bytes(one) / 4), st);
+        one.u.split_stages = (int)(k / STAGE_K);
+        rc = launch_product(one, a_transposed, b_transposed, a, b, M, N, (int)k, C, ldc, c_f32, accumulate, part + (size_t)i * (part_bytes(one) / 4), st);
         if (rc) return rc;
         pool.off = off1;
     }
