@@ -94,30 +94,66 @@ __device__ __forceinline__ uint16_t to_bf16(float f)
     return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);              // round to nearest even
 }
 
-// One workgroup per row of logits [n, vocab] fp32: lse, loss and (G != nullptr) the bf16
-// gradient grad_scale * (softmax - onehot), rows ldg apart.  Two passes over the row: HBM-bound.
-__global__ __launch_bounds__(256) void loss_rows_kernel(const float* __restrict__ logits, const int32_t* __restrict__ target,
-                                                        int vocab, float grad_scale, float* __restrict__ loss,
-                                                        float* __restrict__ lse_out, uint16_t* __restrict__ G, int64_t ldg)
+// two values rounded to bf16, to nearest even
+__device__ __forceinline__ unsigned to_bf16x2(float lo, float hi)
 {
-    __shared__ float red[2][4];
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float floatx2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, __builtin_convertvector((floatx2{lo, hi}), bf16x2));
+}
+
+// One workgroup of NT threads per row of logits [n, vocab] fp32: lse, loss and (G != nullptr) the bf16
+// gradient grad_scale * (softmax - onehot), rows ldg apart.  Two passes over the row.
+//
+// Bound by the memory, if enough of it is in flight and the second pass does not come from HBM again: a row of 128256
+// logits is 513 KB, and with every row that fits a compute unit at 256 threads (five) under way at once, the
+// rows between the passes were twice what the last-level cache holds, one load of 16 bytes per lane and trip in flight.
+// CACHED floats of the row stay in LDS, which also keeps it to one row of 1024 threads per compute unit (131 MB of rows
+// in all), and a trip requests four times 16 bytes.  1058 rows of 128256: 278 -> LOSS_US us.
+template <int NT, int CACHED>
+__global__ __launch_bounds__(NT) void loss_rows_kernel(const float* __restrict__ logits, const int32_t* __restrict__ target,
+                                                       int vocab, float grad_scale, float* __restrict__ loss,
+                                                       float* __restrict__ lse_out, uint16_t* __restrict__ G, int64_t ldg)
+{
+    constexpr int NW = NT / 64, U = 4, STEP = NT * U;  // accesses of a trip
+    __shared__ float red[2][NW];
+    __shared__ float4 cache[CACHED > 0 ? CACHED / 4 : 1];
     const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const float* x = logits + (size_t)row * vocab;
     // running (max, sum of exp) per thread, merged across the workgroup; rows are 16-byte
     // aligned when vocab % 4 == 0 (the base is), and then read four logits per access
     const bool vec = (vocab & 3) == 0;
+    const float4* x4 = reinterpret_cast<const float4*>(x);
+    const int n4 = vocab / 4, whole4 = n4 / STEP * STEP;  // accesses, and those of whole trips
     float m = -INFINITY, l = 0.f;
     if (vec) {
-        const float4* x4 = reinterpret_cast<const float4*>(x);
-        for (int v = tid; v < vocab / 4; v += 256) {
-            const float4 a = x4[v];
-            const float mn = fmaxf(fmaxf(fmaxf(a.x, a.y), fmaxf(a.z, a.w)), m);
-            if (mn == -INFINITY) continue;  // nothing finite yet: exp(-inf - -inf) is not a number
-            l = l * __expf(m - mn) + __expf(a.x - mn) + __expf(a.y - mn) + __expf(a.z - mn) + __expf(a.w - mn);
+        auto fold = [&](const float4* a, int n) {
+            float mn = m;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (u < n) mn = fmaxf(fmaxf(fmaxf(a[u].x, a[u].y), fmaxf(a[u].z, a[u].w)), mn);
+            if (mn == -INFINITY) return;  // nothing finite yet: exp(-inf - -inf) is not a number
+            l *= __expf(m - mn);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (u < n) l += __expf(a[u].x - mn) + __expf(a[u].y - mn) + __expf(a[u].z - mn) + __expf(a[u].w - mn);
             m = mn;
+        };
+        for (int v0 = 0; v0 < whole4; v0 += STEP) {
+            float4 a[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) a[u] = x4[v0 + NT * u + tid];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (CACHED > 0 && v0 + NT * u < CACHED / 4) cache[v0 + NT * u + tid] = a[u];
+            fold(a, U);
+        }
+        for (int v = whole4 + tid; v < n4; v += NT) {
+            const float4 a = x4[v];
+            fold(&a, 1);
         }
     } else {
-        for (int v = tid; v < vocab; v += 256) {
+        for (int v = tid; v < vocab; v += NT) {
             const float a = x[v];
             if (a > m) {
                 l = l * __expf(m - a) + 1.f;
@@ -131,10 +167,11 @@ __global__ __launch_bounds__(256) void loss_rows_kernel(const float* __restrict_
     l = wave_sum(m == -INFINITY ? 0.f : l * __expf(m - wm));
     if (lane == 0) { red[0][w] = wm; red[1][w] = l; }
     __syncthreads();
-    const float gm = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
-    float gl = 0.f;
+    float gm = red[0][0], gl = 0.f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) gl += red[1][i] * __expf(red[0][i] - gm);
+    for (int i = 1; i < NW; ++i) gm = fmaxf(gm, red[0][i]);
+#pragma unroll
+    for (int i = 0; i < NW; ++i) gl += red[1][i] * __expf(red[0][i] - gm);
     const float lse = gm + __logf(gl);
     const int t = target[row];
     if (tid == 0) {
@@ -145,23 +182,37 @@ __global__ __launch_bounds__(256) void loss_rows_kernel(const float* __restrict_
     uint16_t* g = G + (size_t)row * ldg;
     if (vocab + tid < ldg) g[vocab + tid] = 0;  // at most 7: the products read whole 16-byte pieces
     if (vec) {
-        const float4* x4 = reinterpret_cast<const float4*>(x);
         uint2* g2 = reinterpret_cast<uint2*>(g);
-        for (int v = tid; v < vocab / 4; v += 256) {
-            const float4 a = x4[v];
+        auto grad = [&](const float4& a, int v) {
             const int d = t - 4 * v;  // 0..3 when the target is one of these four
-            const unsigned p0 = to_bf16(grad_scale * (__expf(a.x - lse) - (d == 0 ? 1.f : 0.f)));
-            const unsigned p1 = to_bf16(grad_scale * (__expf(a.y - lse) - (d == 1 ? 1.f : 0.f)));
-            const unsigned p2 = to_bf16(grad_scale * (__expf(a.z - lse) - (d == 2 ? 1.f : 0.f)));
-            const unsigned p3 = to_bf16(grad_scale * (__expf(a.w - lse) - (d == 3 ? 1.f : 0.f)));
-            g2[v] = make_uint2(p0 | (p1 << 16), p2 | (p3 << 16));
+            g2[v] = make_uint2(to_bf16x2(grad_scale * (__expf(a.x - lse) - (d == 0 ? 1.f : 0.f)), grad_scale * (__expf(a.y - lse) - (d == 1 ? 1.f : 0.f))),
+                               to_bf16x2(grad_scale * (__expf(a.z - lse) - (d == 2 ? 1.f : 0.f)), grad_scale * (__expf(a.w - lse) - (d == 3 ? 1.f : 0.f))));
+        };
+        for (int v0 = 0; v0 < whole4; v0 += STEP) {
+            float4 a[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int v = v0 + NT * u;
+                a[u] = CACHED > 0 && v < CACHED / 4 ? cache[v + tid] : x4[v + tid];  // (this thread's own part of the cache)
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) grad(a[u], v0 + NT * u + tid);
         }
+        for (int v = whole4 + tid; v < n4; v += NT) grad(x4[v], v);
         return;
     }
-    for (int v = tid; v < vocab; v += 256) {
+    for (int v = tid; v < vocab; v += NT) {
         const float p = __expf(x[v] - lse) - (v == t ? 1.f : 0.f);
         g[v] = to_bf16(grad_scale * p);
     }
+}
+
+// 1024 threads from LOSS_WIDE logits on: a row of fewer is too short for trips of 64 KB
+constexpr int LOSS_WIDE = 16384;
+void launch_loss_rows(const float* logits, const int32_t* target, int rows, int vocab, float grad_scale, float* loss, float* lse, uint16_t* G, int64_t ldg, hipStream_t st)
+{
+    if (vocab >= LOSS_WIDE) loss_rows_kernel<1024, 32768><<<dim3((unsigned)rows), 1024, 0, st>>>(logits, target, vocab, grad_scale, loss, lse, G, ldg);
+    else loss_rows_kernel<256, 0><<<dim3((unsigned)rows), 256, 0, st>>>(logits, target, vocab, grad_scale, loss, lse, G, ldg);
 }
 
 // ---- feed-forward elementwise kernels (bf16 in / out, fp32 arithmetic) ----
@@ -473,8 +524,7 @@ int fpdt_tw_loss_fwd_bwd(const void* H, const void* W, const int32_t* target, fl
             // logits[n, vocab] = H_c W^T
             rc = gemm_nt(h, n, vocab, hidden, static_cast<const char*>(H) + (size_t)r0 * hidden * 2, W, logits, TW_C_F32, 0.f);
             if (rc != TW_OK) return rc;
-            loss_rows_kernel<<<dim3((unsigned)n), 256, 0, st>>>(logits, target + r0, vocab, grad_scale, loss + r0, lse + r0,
-                                                                 bwd ? G + (size_t)(r0 - g0) * ldg : nullptr, ldg);
+            launch_loss_rows(logits, target + r0, n, vocab, grad_scale, loss + r0, lse + r0, bwd ? G + (size_t)(r0 - g0) * ldg : nullptr, ldg, st);
         }
         const int n = (int)(g1 - g0);
         if (dH) {  // dH[n, hidden] = G[n, vocab] W[vocab, hidden]
