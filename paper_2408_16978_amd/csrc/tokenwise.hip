@@ -111,7 +111,7 @@ __device__ __forceinline__ unsigned to_bf16x2(float lo, float hi)
 // CACHED floats of the row stay in LDS, which also keeps it to one row of 1024 threads per compute unit (131 MB of rows
 // in all), and a trip requests four times 16 bytes.  1058 rows of 128256: 278 -> 208 us.
 template <int NT, int CACHED>
-__global__ __launch_bounds__(NT) void loss_rows_kernel(const float* __restrict__ logits, const int32_t* __restrict__ target,
+__global__ __launch_bounds__(NT) void loss_rows_kernel(const float* __restrict__ logits, int64_t ldl, const int32_t* __restrict__ target,
                                                        int vocab, float grad_scale, float* __restrict__ loss,
                                                        float* __restrict__ lse_out, uint16_t* __restrict__ G, int64_t ldg)
 {
@@ -119,10 +119,10 @@ __global__ __launch_bounds__(NT) void loss_rows_kernel(const float* __restrict__
     __shared__ float red[2][NW];
     __shared__ float4 cache[CACHED > 0 ? CACHED / 4 : 1];
     const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const float* x = logits + (size_t)row * vocab;
+    const float* x = logits + (size_t)row * ldl;
     // running (max, sum of exp) per thread, merged across the workgroup; rows are 16-byte
-    // aligned when vocab % 4 == 0 (the base is), and then read four logits per access
-    const bool vec = (vocab & 3) == 0;
+    // aligned when ldl % 4 == 0 (the base is), and then read four logits per access
+    const bool vec = (ldl & 3) == 0;
     const float4* x4 = reinterpret_cast<const float4*>(x);
     const int n4 = vocab / 4, whole4 = n4 / STEP * STEP;  // accesses, and those of whole trips
     float m = -INFINITY, l = 0.f;
@@ -152,15 +152,14 @@ __global__ __launch_bounds__(NT) void loss_rows_kernel(const float* __restrict__
             const float4 a = x4[v];
             fold(&a, 1);
         }
-    } else {
-        for (int v = tid; v < vocab; v += NT) {
-            const float a = x[v];
-            if (a > m) {
-                l = l * __expf(m - a) + 1.f;
-                m = a;
-            } else {
-                l += __expf(a - m);
-            }
+    }
+    for (int v = (vec ? 4 * n4 : 0) + tid; v < vocab; v += NT) {
+        const float a = x[v];
+        if (a > m) {
+            l = l * __expf(m - a) + 1.f;
+            m = a;
+        } else {
+            l += __expf(a - m);
         }
     }
     const float wm = wave_max(m);
@@ -199,9 +198,8 @@ __global__ __launch_bounds__(NT) void loss_rows_kernel(const float* __restrict__
             for (int u = 0; u < U; ++u) grad(a[u], v0 + NT * u + tid);
         }
         for (int v = whole4 + tid; v < n4; v += NT) grad(x4[v], v);
-        return;
     }
-    for (int v = tid; v < vocab; v += NT) {
+    for (int v = (vec ? 4 * n4 : 0) + tid; v < vocab; v += NT) {
         const float p = __expf(x[v] - lse) - (v == t ? 1.f : 0.f);
         g[v] = to_bf16(grad_scale * p);
     }
@@ -209,10 +207,10 @@ __global__ __launch_bounds__(NT) void loss_rows_kernel(const float* __restrict__
 
 // 1024 threads from LOSS_WIDE logits on: a row of fewer is too short for trips of 64 KB
 constexpr int LOSS_WIDE = 16384;
-void launch_loss_rows(const float* logits, const int32_t* target, int rows, int vocab, float grad_scale, float* loss, float* lse, uint16_t* G, int64_t ldg, hipStream_t st)
+void launch_loss_rows(const float* logits, int64_t ldl, const int32_t* target, int rows, int vocab, float grad_scale, float* loss, float* lse, uint16_t* G, int64_t ldg, hipStream_t st)
 {
-    if (vocab >= LOSS_WIDE) loss_rows_kernel<1024, 32768><<<dim3((unsigned)rows), 1024, 0, st>>>(logits, target, vocab, grad_scale, loss, lse, G, ldg);
-    else loss_rows_kernel<256, 0><<<dim3((unsigned)rows), 256, 0, st>>>(logits, target, vocab, grad_scale, loss, lse, G, ldg);
+    if (vocab >= LOSS_WIDE) loss_rows_kernel<1024, 32768><<<dim3((unsigned)rows), 1024, 0, st>>>(logits, ldl, target, vocab, grad_scale, loss, lse, G, ldg);
+    else loss_rows_kernel<256, 0><<<dim3((unsigned)rows), 256, 0, st>>>(logits, ldl, target, vocab, grad_scale, loss, lse, G, ldg);
 }
 
 // ---- feed-forward elementwise kernels (bf16 in / out, fp32 arithmetic) ----
@@ -505,26 +503,40 @@ int fpdt_tw_loss_fwd_bwd(const void* H, const void* W, const int32_t* target, fl
     if (rc != TW_OK) return rc;
     // The logit gradients of several chunks are gathered before they are multiplied: dW += G^T H reads and
     // writes the whole fp32 dW (2.1 GB at 128256 x 4096), which at 1058 rows per chunk took as long as its
-    // MFMAs, and dH = G W has too few tiles at that height.  As many chunks as make 2 `hidden` rows: their
+    // MFMAs, and dH = G W has too few tiles at that height.  About 2 `hidden` rows at a time: their
     // G then takes the memory of two bf16 copies of W, in the library's scratch.  Rows of G are padded to 16
     // bytes there, so an odd vocabulary takes this way with a single chunk too.
     // Measured (65536 tokens, hidden 4096, 62 chunks): 310 -> 235 ms with `hidden` rows, 210 -> 204 ms from there to twice as many.
-    const int64_t per_group = 2 * (int64_t)hidden / c > 1 ? 2 * (int64_t)hidden / c : 1;
-    int64_t ldg = vocab;
-    if (bwd && (per_group > 1 || vocab % 8)) {
-        const int64_t group_rows = per_group * c < rows ? per_group * c : rows, ld = ((int64_t)vocab + 7) / 8 * 8;
-        G = static_cast<uint16_t*>(fpdt_tw::scratch((size_t)group_rows * ld * 2));
+    // The logits then have the room of the chunk's gradients in the workspace too, half as many rows again: they are
+    // computed for a multiple of 256 rows at a time, whole tiles of the product (1058-row chunks fill four and an
+    // eighth), and their rows start with a cache line.
+    const bool gathered = bwd && (2 * (int64_t)hidden >= 2 * c || vocab % 8);
+    int64_t ldg = vocab, ldl = vocab, group = c, step = c;
+    if (gathered) {
+        if (group < 2 * (int64_t)hidden) {
+            const int64_t groups = (rows + 2 * hidden - 1) / (2 * (int64_t)hidden);  // of about the same size
+            group = ((rows + groups - 1) / groups + 255) / 256 * 256;
+        }
+        ldg = ((int64_t)vocab + 7) / 8 * 8;
+        G = static_cast<uint16_t*>(fpdt_tw::scratch((size_t)(group < rows ? group : rows) * ldg * 2));
         if (!G) return gemm_status(1);  // (no smaller groups instead: how dW is summed depends on the arguments alone)
-        ldg = ld;
     }
-    for (int64_t g0 = 0; g0 < rows; g0 += per_group * c) {
-        const int64_t g1 = rows - g0 < per_group * c ? rows : g0 + per_group * c;
-        for (int64_t r0 = g0; r0 < g1; r0 += c) {
-            const int n = (int)(g1 - r0 < c ? g1 - r0 : c);
+    if (gathered || !bwd) {
+        const int64_t room = (int64_t)(need / 4), ld = ((int64_t)vocab + 31) / 32 * 32;
+        if (c * ld <= room) ldl = ld;
+        step = room / ldl >= 256 ? room / ldl / 256 * 256 : room / ldl;
+        if (step > MAX_ROWS) step = MAX_ROWS;
+    }
+    if (!bwd) group = rows;
+    for (int64_t g0 = 0; g0 < rows; g0 += group) {
+        const int64_t g1 = rows - g0 < group ? rows : g0 + group;
+        for (int64_t r0 = g0; r0 < g1; r0 += step) {
+            const int n = (int)(g1 - r0 < step ? g1 - r0 : step);
             // logits[n, vocab] = H_c W^T
-            rc = gemm_nt(h, n, vocab, hidden, static_cast<const char*>(H) + (size_t)r0 * hidden * 2, W, logits, TW_C_F32, 0.f);
+            rc = gemm_status(fpdt_tw::gemm(0, 0, n, vocab, hidden, static_cast<const char*>(H) + (size_t)r0 * hidden * 2, hidden, W, hidden, logits,
+                                           ldl, true, false, true, h->st));
             if (rc != TW_OK) return rc;
-            launch_loss_rows(logits, target + r0, n, vocab, grad_scale, loss + r0, lse + r0, bwd ? G + (size_t)(r0 - g0) * ldg : nullptr, ldg, st);
+            launch_loss_rows(logits, ldl, target + r0, n, vocab, grad_scale, loss + r0, lse + r0, bwd ? G + (size_t)(r0 - g0) * ldg : nullptr, ldg, st);
         }
         const int n = (int)(g1 - g0);
         if (dH) {  // dH[n, hidden] = G[n, vocab] W[vocab, hidden]

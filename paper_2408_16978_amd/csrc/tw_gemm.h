@@ -18,6 +18,7 @@ bool reads_in_place(const void* A, int64_t rows, int64_t k, const void* C, int64
 //   a_transposed = 0: A is stored [M,K] (leading dimension lda); 1: A is stored [K,M]
 //   b_transposed = 0: B is stored [N,K] (ldb);                   1: B is stored [K,N]
 //   C row-major [M,N], leading dimension ldc, bf16 or fp32 (c_f32); accumulate: C += instead of C =
+//   ldc wider than N, fp32, not accumulating: what follows a row up to a multiple of 4 may be overwritten
 //   lda wider than A's rows: they are followed by zeros up to a multiple of 8
 //   cache_b: B is a weight that further products of this library call will use again
 //   A or B may be what C overwrites

@@ -554,7 +554,8 @@ __global__ __launch_bounds__(NTHREAD, 1) void tw_gemm_kernel(Operand A, Operand 
     const int mt = tile_m * (64 * WMT), nt = tile_n * (64 * WNT);
     out_t* tile = static_cast<out_t*>(Cout) + (size_t)mt * ldc + nt;
     constexpr int PER16 = 16 / sizeof(out_t);
-    if (N % PER16 == 0 && ldc % PER16 == 0 && reinterpret_cast<uintptr_t>(Cout) % 16 == 0) {
+    // (fp32, not added to: rows that are not a multiple of four long but that far apart end with room for one, tw_gemm.h)
+    if ((N % PER16 == 0 || (OUT_F32 && !ACCUM)) && ldc % PER16 == 0 && reinterpret_cast<uintptr_t>(Cout) % 16 == 0) {
         auto store = [&](auto whole_tag) {
             if constexpr (OUT_F32) store_f32(tile, ldc, M - mt, N - nt, std::integral_constant<bool, ACCUM>{}, whole_tag);
             else store_bf16(tile, ldc, M - mt, N - nt, std::integral_constant<bool, ACCUM>{}, whole_tag);
