@@ -6,11 +6,12 @@
 // product's operand.  Their tensors are small (the accuracy configuration has 1K tokens), so what bounds
 // them is the chain of one row tile and the number of launches: tiles have 16 rows (of 32 rows there are
 // 64 at 1K tokens and two heads, a quarter of the compute units), the eight waves of a workgroup share a
-// tile, each walking every eighth 32-row block of the other side, and their results meet in LDS; a call
+// tile, each walking every eighth 16-row block of the other side, and their results meet in LDS; a call
 // without FPDT_PAIRWISE is one forward and one backward launch.  At 1024 tokens, 2 heads, D = 64, chunks of 256, forward
-// and backward: one wave per row with scalar dot products, pair by pair, 1799 us; 32-row tiles 110 us;
-// this 64 us, with errors against fp64 below those of the scalar kernels in O, dQ, dK and dV (2.5e-7 .. 7.0e-7
-// against 3.3e-7 .. 9.7e-7 over four shapes).
+// and backward: one wave per row with scalar dot products, pair by pair, 1799 us; 32-row tiles 110 us; 16-row tiles
+// whose operands are fetched where they are used, rows and again columns, and whose addresses are vector arithmetic
+// (64-bit divisions among it), 64 us; this 48 us (twelve or sixteen waves: no faster).  Errors against fp64 are below those
+// of the scalar kernels in O, dQ, dK and dV (2.5e-7 .. 7.0e-7 against 3.3e-7 .. 9.7e-7 over four shapes).
 #include "fpdt_internal.h"
 #include "mfma_tiles.h"
 
@@ -29,7 +30,7 @@ __device__ __forceinline__ floatx4 mfma_f32(float a, float b, floatx4 c)
 
 constexpr int NW = 8;    // waves of a workgroup
 constexpr int TR = 16;   // rows of a tile
-constexpr int BR = 32;   // rows of a block of the other side: two of the tiles' height
+constexpr int BR = 16;   // rows of a block of the other side
 
 // Row operand of a product contracted over the channels: lane (row = lane % 16, g = lane / 16) holds
 // channels 16 j + 4 g + 0..3, j = 0 .. D/16 - 1, of its row.  (Any order of the channels does, as both
@@ -54,37 +55,64 @@ __device__ __forceinline__ floatx4 dot_rows(const Rows<D>& a, const Rows<D>& b)
     return s;
 }
 
-// acc^T [D x 16] += X^T [D x 16 rows] T [16 rows x 16 columns]: `t` is a score tile in accumulator layout
-// (this lane: column lane % 16, rows 4 (lane / 16) + r), rows of X behind n_rows are not read.  `keep` has
-// bit r set where t[r] counts; where it does not, t[r] is 0, but the row of X may hold infinities or NaN (a
-// later key of this query), which 0 times it must not let through: those elements stay out of the product
-// and are added one by one where they count.
+// A wave's own part of LDS: the rows of two blocks, for the products contracted over them, and a score tile.  (Rows 4 floats
+// apart from a multiple of the banks: what a read takes, sixteen elements of every fourth row, lies in different ones.)
 template <int D>
-__device__ __forceinline__ void add_rows(floatx4 (&acc)[D / 16], const floatx4& t, unsigned keep, const float* X, size_t pitch, int n_rows,
-                                         int lane, float* park)
+struct Shelf {
+    static constexpr int PITCH = D + 4, ROWS = TR * PITCH, FLOATS = 2 * ROWS + TR * TR;
+    float* p;
+    int lane;
+    // Rows x into place `at` (0 or 1), zeros for elements that are not finite; are there any?
+    __device__ __forceinline__ bool put(int at, const Rows<D>& x) const
+    {
+        float z = 0.f;
+#pragma unroll
+        for (int j = 0; j < D / 16; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) z = fmaf(x.v[j][c], 0.f, z);  // not a number if one is not finite
+        const bool odd = __any(!(z == 0.f));
+        f32x4* to = reinterpret_cast<f32x4*>(p + at * ROWS + (lane & 15) * PITCH + 4 * (lane >> 4));
+#pragma unroll
+        for (int j = 0; j < D / 16; ++j) to[4 * j] = x.v[j];
+        if (__builtin_expect(odd, 0)) {
+#pragma unroll
+            for (int j = 0; j < D / 16; ++j) {
+                f32x4 v = x.v[j];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[c] = fabsf(v[c]) < INFINITY ? v[c] : 0.f;
+                to[4 * j] = v;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        return odd;
+    }
+    // Column operand: element 16 db + lane % 16 of row 4 (lane / 16) + r
+    __device__ __forceinline__ float get(int at, int db, int r) const { return p[at * ROWS + (4 * (lane >> 4) + r) * PITCH + 16 * db + (lane & 15)]; }
+    __device__ __forceinline__ float* tile() const { return p + 2 * ROWS; }
+};
+
+// acc^T [D x 16] += X^T [D x 16 rows] T [16 rows x 16 columns]: `t` is a score tile in accumulator layout
+// (this lane: column lane % 16, rows 4 (lane / 16) + r), the rows of X are in place `at` of the shelf.  `keep` has
+// bit r set where t[r] counts; where it does not, t[r] is 0, but the row of X may hold infinities or NaN (a
+// later key of this query), which 0 times it must not let through: those elements (`odd`: there are some) stay
+// out of the product and are added one by one where they count.
+template <int D>
+__device__ __forceinline__ void add_rows(floatx4 (&acc)[D / 16], const floatx4& t, unsigned keep, const Shelf<D>& shelf, int at, bool odd,
+                                         const float* X, size_t pitch, int n_rows, int lane)
 {
     const int g = lane >> 4, col = lane & 15;
-    bool odd = false;
-    if (n_rows <= 0) return;  // (wave-uniform)
 #pragma unroll
-    for (int db = 0; db < D / 16; ++db) {
-        float x[4];
+    for (int db = 0; db < D / 16; ++db)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) x[r] = X[(size_t)(4 * g + r < n_rows ? 4 * g + r : 0) * pitch + 16 * db + col];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const bool fine = fabsf(x[r]) < INFINITY;
-            odd |= !fine;
-            acc[db] = mfma_f32(fine ? x[r] : 0.f, t[r], acc[db]);
-        }
-    }
-    if (__builtin_expect(__any(odd), 0)) {
+        for (int r = 0; r < 4; ++r) acc[db] = mfma_f32(shelf.get(at, db, r), t[r], acc[db]);
+    if (__builtin_expect(odd, 0)) {
         // t by row through LDS; a NaN pattern that no arithmetic produces marks what does not count
+        float* park = shelf.tile();
 #pragma unroll
         for (int r = 0; r < 4; ++r) park[(4 * g + r) * 16 + col] = (keep >> r) & 1 ? t[r] : __uint_as_float(0xffffdeadu);
         __builtin_amdgcn_wave_barrier();
 #pragma unroll 1
-        for (int row = 0; row < (n_rows < TR ? n_rows : TR); ++row) {
+        for (int row = 0; row < n_rows; ++row) {
             const float p = park[row * 16 + col];
             const bool on = __float_as_uint(p) != 0xffffdeadu;
 #pragma unroll
@@ -138,10 +166,11 @@ __device__ __forceinline__ float sum_over_rows(float v)
 template <int D>
 __global__ __launch_bounds__(64 * NW) void f32_fwd_kernel(F32FwdArgs a)
 {
-    constexpr int DB = D / 16, ALL = D * 17;
-    __shared__ float lds[NW * ALL];
+    constexpr int DB = D / 16;
+    static_assert(Shelf<D>::FLOATS >= D * 17, "sum_waves uses the same memory");
+    __shared__ __attribute__((aligned(16))) float lds[NW * Shelf<D>::FLOATS];
     __shared__ float ml[NW][2][TR];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, col = lane & 15;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, col = lane & 15;
     const int n_tiles = (int)((a.n_q + TR - 1) / TR);
     const int head = blockIdx.x % (unsigned)a.Hq, tile = n_tiles - 1 - (int)(blockIdx.x / (unsigned)a.Hq);  // longest first
     const int kvh = head / (a.Hq / a.Hkv);
@@ -165,47 +194,57 @@ __global__ __launch_bounds__(64 * NW) void f32_fwd_kernel(F32FwdArgs a)
     }
     int64_t need = a.q_pos0 + row0 + rows - a.k_pos0;  // keys at positions <= the last query's
     if (need > a.n_k) need = a.n_k;
+    // Rows are fetched once, 16 bytes per lane, the next block's as soon as this one's have been consumed, so that they
+    // arrive under its products; the products contracted over rows take their operand from the wave's shelf in LDS.
+    // (Fetched again as columns, 4 bytes per lane and access, where they are used: forward 22.6 us, backward 40.)
+    auto keys_at = [&](int64_t j) { return (int)(a.n_k - j < BR ? a.n_k - j : BR); };
+    auto row_at = [&](int64_t j) { return (j + (col < keys_at(j) ? col : keys_at(j) - 1)) * k_pitch + (size_t)kvh * D; };
+    const Shelf<D> shelf = {lds + w * Shelf<D>::FLOATS, lane};
+    Rows<D> k, v;
+    if (BR * w < need) {
+        k.load(a.K + row_at(BR * w), g);
+        v.load(a.V + row_at(BR * w), g);
+    }
+#pragma unroll 1
     for (int64_t j0 = BR * w; j0 < need; j0 += BR * NW) {
-        const int keys = (int)(a.n_k - j0 < BR ? a.n_k - j0 : BR);
-        const float* k0 = a.K + j0 * k_pitch + (size_t)kvh * D;
-        const float* v0 = a.V + j0 * k_pitch + (size_t)kvh * D;
-        floatx4 s[2];
-        unsigned keep[2] = {0, 0};
+        const int keys = keys_at(j0);
+        floatx4 s = dot_rows<D>(k, q);
+        const bool odd = shelf.put(0, v);
+        if (j0 + BR * NW < need) {
+            k.load(a.K + row_at(j0 + BR * NW), g);
+            v.load(a.V + row_at(j0 + BR * NW), g);
+        }
+        unsigned keep = 0;
         float mx = -INFINITY;
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            Rows<D> k;
-            k.load(k0 + (size_t)(16 * b + col < keys ? 16 * b + col : keys - 1) * k_pitch, g);
-            s[b] = dot_rows<D>(k, q);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int key = 16 * b + 4 * g + r;
-                const bool on = key < keys && a.k_pos0 + j0 + key <= qpos;
-                keep[b] |= (unsigned)on << r;
-                s[b][r] = on ? a.scale * s[b][r] : -INFINITY;
-                mx = fmaxf(mx, s[b][r]);
-            }
+        for (int r = 0; r < 4; ++r) {
+            const int key = 4 * g + r;
+            const bool on = key < keys && a.k_pos0 + j0 + key <= qpos;
+            keep |= (unsigned)on << r;
+            s[r] = on ? a.scale * s[r] : -INFINITY;
+            mx = fmaxf(mx, s[r]);
         }
-        const float m_new = fmaxf(m, max_over_rows(mx));
+        // Where no row of the tile has a new maximum nothing is exchanged or rescaled.  (A reference that moves only when a
+        // score exceeds it by 2 or 8 is no faster and adds 4% to the error of the LSE.)
         // (every score of this wave so far may be -infinity, masked or overflowed: then 0 takes the maximum's
         // place, whatever was added is 0, and so stays what the next finite score rescales)
-        const float m_ref = m_new > -INFINITY ? m_new : 0.f;
-        const float alpha = expf(m - m_ref);
-        l *= alpha;
+        if (__any(mx > m)) {
+            const float m_new = fmaxf(m, max_over_rows(mx));
+            const float alpha = expf(m - (m_new > -INFINITY ? m_new : 0.f));
+            l *= alpha;
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+            for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                s[b][r] = (keep[b] >> r) & 1 ? expf(s[b][r] - m_ref) : 0.f;
-                l += s[b][r];
-            }
+                for (int r = 0; r < 4; ++r) acc[db][r] *= alpha;
+            m = m_new;
+        }
+        const float m_ref = m > -INFINITY ? m : 0.f;
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[db][r] *= alpha;
-#pragma unroll
-        for (int b = 0; b < 2; ++b) add_rows<D>(acc, s[b], keep[b], v0 + 16 * b * k_pitch, k_pitch, keys - 16 * b, lane, lds + w * ALL);
-        m = m_new;
+        for (int r = 0; r < 4; ++r) {
+            s[r] = (keep >> r) & 1 ? expf(s[r] - m_ref) : 0.f;
+            l += s[r];
+        }
+        add_rows<D>(acc, s, keep, shelf, 0, odd, a.V + j0 * k_pitch + (size_t)kvh * D, k_pitch, keys, lane);
     }
     l = sum_over_rows(l);
     if (g == 0) {
@@ -248,12 +287,12 @@ __global__ __launch_bounds__(64 * NW) void f32_fwd_kernel(F32FwdArgs a)
 template <int D>
 __global__ __launch_bounds__(64 * NW) void f32_bwd_kernel(F32BwdArgs a, unsigned dq_blocks)
 {
-    constexpr int DB = D / 16, ALL = D * 17;
-    __shared__ float lds[NW * ALL];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, col = lane & 15;
+    constexpr int DB = D / 16;
+    __shared__ __attribute__((aligned(16))) float lds[NW * Shelf<D>::FLOATS];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, col = lane & 15;
     const int group = a.Hq / a.Hkv;
     const size_t q_pitch = (size_t)a.Hq * D, k_pitch = (size_t)a.Hkv * D;
-    float* park = lds + w * ALL;
+    const Shelf<D> shelf = {lds + w * Shelf<D>::FLOATS, lane};
     if (blockIdx.x < dq_blocks) {
         const int n_tiles = (int)((a.n_q + TR - 1) / TR);
         const int head = blockIdx.x % (unsigned)a.Hq, tile = n_tiles - 1 - (int)(blockIdx.x / (unsigned)a.Hq);
@@ -269,27 +308,33 @@ __global__ __launch_bounds__(64 * NW) void f32_bwd_kernel(F32BwdArgs a, unsigned
         floatx4 acc[DB] = {};
         int64_t need = a.q_pos0 + row0 + rows - a.k_pos0;
         if (need > a.n_k) need = a.n_k;
+        auto keys_at = [&](int64_t j) { return (int)(a.n_k - j < BR ? a.n_k - j : BR); };
+        auto row_at = [&](int64_t j) { return (j + (col < keys_at(j) ? col : keys_at(j) - 1)) * k_pitch + (size_t)kvh * D; };
+        Rows<D> k, v;  // (as in the forward)
+        if (BR * w < need) {
+            k.load(a.K + row_at(BR * w), g);
+            v.load(a.V + row_at(BR * w), g);
+        }
+#pragma unroll 1
         for (int64_t j0 = BR * w; j0 < need; j0 += BR * NW) {
-            const int keys = (int)(a.n_k - j0 < BR ? a.n_k - j0 : BR);
+            const int keys = keys_at(j0);
             const size_t k0 = j0 * k_pitch + (size_t)kvh * D;
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                const size_t kr = k0 + (size_t)(16 * b + col < keys ? 16 * b + col : keys - 1) * k_pitch;
-                Rows<D> k;
-                k.load(a.K + kr, g);
-                floatx4 s = dot_rows<D>(k, q);
-                k.load(a.V + kr, g);
-                const floatx4 dp = dot_rows<D>(k, go);
-                unsigned keep = 0;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int key = 16 * b + 4 * g + r;
-                    const bool on = key < keys && a.k_pos0 + j0 + key <= qpos;
-                    keep |= (unsigned)on << r;
-                    s[r] = on ? expf(a.scale * s[r] - lse) * (dp[r] - delta) : 0.f;
-                }
-                add_rows<D>(acc, s, keep, a.K + k0 + 16 * b * k_pitch, k_pitch, keys - 16 * b, lane, park);
+            floatx4 s = dot_rows<D>(k, q);
+            const bool odd = shelf.put(0, k);
+            const floatx4 dp = dot_rows<D>(v, go);
+            if (j0 + BR * NW < need) {
+                k.load(a.K + row_at(j0 + BR * NW), g);
+                v.load(a.V + row_at(j0 + BR * NW), g);
             }
+            unsigned keep = 0;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int key = 4 * g + r;
+                const bool on = key < keys && a.k_pos0 + j0 + key <= qpos;
+                keep |= (unsigned)on << r;
+                s[r] = on ? expf(a.scale * s[r] - lse) * (dp[r] - delta) : 0.f;
+            }
+            add_rows<D>(acc, s, keep, shelf, 0, odd, a.K + k0, k_pitch, keys, lane);
         }
         sum_waves<D>(acc, lds, [&](int d, int c, float v) {
             if (c < rows) {
@@ -311,33 +356,64 @@ __global__ __launch_bounds__(64 * NW) void f32_bwd_kernel(F32BwdArgs a, unsigned
     int64_t i_first = a.k_pos0 + key0 - a.q_pos0;  // first query row that attends the tile's first key
     if (i_first < 0) i_first = 0;
     const int64_t blocks = i_first < a.n_q ? (a.n_q - i_first + BR - 1) / BR : 0;
-    for (int64_t t = w; t < blocks * group; t += NW) {
-        const int head = kvh * group + (int)(t / blocks);
-        const int64_t i0 = i_first + t % blocks * BR;
-        const int rows = (int)(a.n_q - i0 < BR ? a.n_q - i0 : BR);
+    // the tile's walk: sixteen query rows of a head after the other, every NW-th of them by this wave
+    struct Step {
+        int64_t block;
+        int head;
+        __device__ __forceinline__ void forward(int64_t n, int64_t blocks)  // (no division: a walk has few heads)
+        {
+            block += n;
+            while (block >= blocks) {
+                block -= blocks;
+                ++head;
+            }
+        }
+    };
+    auto rows_at = [&](int64_t i) { return (int)(a.n_q - i < BR ? a.n_q - i : BR); };
+    auto row_at = [&](const Step& t) {
+        const int64_t i = i_first + t.block * BR;
+        return (i + (col < rows_at(i) ? col : rows_at(i) - 1)) * q_pitch + (size_t)(kvh * group + t.head) * D;
+    };
+    Rows<D> xq, xo;  // (as in the forward)
+    auto load_rows = [&](const Step& t) {
+        xq.load(a.Q + row_at(t), g);
+        xo.load(a.dO + row_at(t), g);
+    };
+    Step t = {0, 0};
+    if (blocks > 0) t.forward(w, blocks);
+    else t.head = group;
+    if (t.head < group) load_rows(t);
+#pragma unroll 1
+    while (t.head < group) {
+        const int head = kvh * group + t.head;
+        const int64_t i0 = i_first + t.block * BR;
+        const int rows = rows_at(i0);
         const size_t q0 = i0 * q_pitch + (size_t)head * D;
         const float* lse = a.LSE + (size_t)head * a.row_stat_stride + i0;
         const float* delta = a.Delta + (size_t)head * a.row_stat_stride + i0;
+        float ls[4], de[4];
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const size_t qr = q0 + (size_t)(16 * b + col < rows ? 16 * b + col : rows - 1) * q_pitch;
-            Rows<D> x;
-            x.load(a.Q + qr, g);
-            floatx4 s = dot_rows<D>(x, k);
-            x.load(a.dO + qr, g);
-            floatx4 ds = dot_rows<D>(x, v);
-            unsigned keep = 0;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = 16 * b + 4 * g + r;
-                const bool on = row < rows && kpos <= a.q_pos0 + i0 + row;
-                keep |= (unsigned)on << r;
-                s[r] = on ? expf(a.scale * s[r] - lse[row < rows ? row : 0]) : 0.f;
-                ds[r] = on ? s[r] * (ds[r] - delta[row < rows ? row : 0]) : 0.f;
-            }
-            add_rows<D>(dv, s, keep, a.dO + q0 + 16 * b * q_pitch, q_pitch, rows - 16 * b, lane, park);
-            add_rows<D>(dk, ds, keep, a.Q + q0 + 16 * b * q_pitch, q_pitch, rows - 16 * b, lane, park);
+        for (int r = 0; r < 4; ++r) {
+            ls[r] = lse[4 * g + r < rows ? 4 * g + r : 0];
+            de[r] = delta[4 * g + r < rows ? 4 * g + r : 0];
         }
+        floatx4 s = dot_rows<D>(xq, k);
+        const bool odd_q = shelf.put(0, xq);
+        floatx4 ds = dot_rows<D>(xo, v);
+        const bool odd_o = shelf.put(1, xo);
+        t.forward(NW, blocks);
+        if (t.head < group) load_rows(t);
+        unsigned keep = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = 4 * g + r;
+            const bool on = row < rows && kpos <= a.q_pos0 + i0 + row;
+            keep |= (unsigned)on << r;
+            s[r] = on ? expf(a.scale * s[r] - ls[r]) : 0.f;
+            ds[r] = on ? s[r] * (ds[r] - de[r]) : 0.f;
+        }
+        add_rows<D>(dv, s, keep, shelf, 1, odd_o, a.dO + q0, q_pitch, rows, lane);
+        add_rows<D>(dk, ds, keep, shelf, 0, odd_q, a.Q + q0, q_pitch, rows, lane);
     }
     auto put = [&](float* out, float mul) {
         return [=](int d, int c, float x) {
