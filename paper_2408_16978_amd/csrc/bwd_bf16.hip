@@ -814,8 +814,8 @@ __global__ __launch_bounds__(NTHREAD) void bwd_dq_kernel(BwdKernelArgs p)
 // group and load).  The 16-byte piece of writer lane (key c, h') of fragment s2 is placed at
 // position 32 h' + (c ^ 4 h' ^ 8 s2) by the copy's per-lane source address, so that the 32 lanes
 // one load serves per cycle touch 32 different 8-byte bank pairs.
-template <int D>
-__global__ __launch_bounds__(NTHREAD) void bwd_dq_ds_kernel(BwdKernelArgs p)
+template <int D, int NWAVE>
+__global__ __launch_bounds__(NWAVE * 64, 2) void bwd_dq_ds_kernel(BwdKernelArgs p)
 {
     constexpr int DT = D / 16, DP = (D + 31) / 32 * 32, DB = DP / 32;
     constexpr int BK = 64, KB = BK / 32;
@@ -1133,10 +1133,18 @@ void launch_bwd_dkdv(const BwdArgs& a, hipStream_t st)
 void launch_bwd_dq_from_ds(const BwdArgs& a, hipStream_t st)
 {
     const BwdKernelArgs k = to_kernel_args(a);
-    dim3 grid((unsigned)((a.n_q / bwd_q_tile(a.D)) * a.Hq));
-    if (a.D == 128) bwd_dq_ds_kernel<128><<<grid, NTHREAD, 0, st>>>(k);
-    else if (a.D == 80) bwd_dq_ds_kernel<80><<<grid, NTHREAD, 0, st>>>(k);
-    else bwd_dq_ds_kernel<64><<<grid, NTHREAD, 0, st>>>(k);
+    const int waves = sweep_waves(a.n_q, a.Hq);  // (the accumulators' layout follows it: the same in every launch of a call)
+    const dim3 grid((unsigned)((a.n_q / (32 * waves)) * a.Hq));
+#define DQ_DS_LAUNCH(D_)                                                     \
+    do {                                                                     \
+        if (waves == 8) bwd_dq_ds_kernel<D_, 8><<<grid, 512, 0, st>>>(k);    \
+        else if (waves == 4) bwd_dq_ds_kernel<D_, 4><<<grid, 256, 0, st>>>(k); \
+        else bwd_dq_ds_kernel<D_, 2><<<grid, 128, 0, st>>>(k);               \
+    } while (0)
+    if (a.D == 128) DQ_DS_LAUNCH(128);
+    else if (a.D == 80) DQ_DS_LAUNCH(80);
+    else DQ_DS_LAUNCH(64);
+#undef DQ_DS_LAUNCH
 }
 
 void launch_bwd_dq(const BwdArgs& a, hipStream_t st)

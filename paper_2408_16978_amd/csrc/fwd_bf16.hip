@@ -10,7 +10,7 @@
 // stays in registers.
 //
 // Workgroup = 8 waves (two per SIMD, so one wave's softmax arithmetic runs under the other's
-// MFMAs), each wave owns 32 query rows of one head and at most 256 registers.  The K/V tiles travel
+// MFMAs; 4 or 2 where a launch of one key group would otherwise leave half of the chip idle, sweep_waves), each wave owns 32 query rows of one head and at most 256 registers.  The K/V tiles travel
 // global -> LDS directly (no register staging) through a ring filled ahead.  KG = 1: the waves own 256
 // query rows and share 64-key tiles.  KG = 2, 4: 128 or 64 query rows, the waves of one row block take
 // every KG-th 32-key block and merge their (max, sum, output) through LDS at the end, for launches whose
@@ -22,8 +22,6 @@ namespace fpdt {
 
 namespace {
 
-constexpr int NWAVE = 8;
-constexpr int NTHREAD = NWAVE * 64;
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
@@ -43,14 +41,14 @@ struct FwdKernelArgs {
     float c;  // scale * log2(e)
 };
 
-template <int D, int KG>
-__global__ __launch_bounds__(NTHREAD) void fwd_sweep_kernel(FwdKernelArgs p)
+template <int D, int KG, int NWAVE>
+__global__ __launch_bounds__(NWAVE * 64, 2) void fwd_sweep_kernel(FwdKernelArgs p)
 {
     constexpr int DT = D / 16, DP = (D + 31) / 32 * 32, DB = DP / 32;
     constexpr int KB = KG == 1 ? 2 : 1;     // 32-key blocks of a wave per tile
     constexpr int NB = KG * KB, BK = NB * 32;  // blocks and keys per LDS tile
     constexpr int NQ = NWAVE / KG, BQ = NQ * 32;  // row blocks and query rows per workgroup
-    constexpr int RING = KG == 4 ? 2 : 3;   // (a tile of 128 keys: 64 KiB at D = 128)
+    constexpr int RING = KG == 4 || NWAVE < 8 ? 2 : 3;  // (a tile of 128 keys: 64 KiB at D = 128; four waves: room for two workgroups)
     constexpr int PF = RING - 1;            // tiles in flight ahead of the one being computed
     constexpr int K_U4 = NB * DT * 64;      // u32x4 per K tile
     constexpr int V_U4 = NB * 2 * DB * 64;  // u32x4 per V tile
@@ -355,13 +353,14 @@ void launch_fwd_sweep(const FwdArgs& a, hipStream_t st)
     k.g = a.Hq / a.Hkv;
     k.flags = a.flags;
     k.c = a.scale * LOG2E;
-    const int kg = a.key_groups;
+    const int kg = a.key_groups, waves = kg > 1 || sweep_waves(a.n_q, a.Hq) == 8 ? 8 : 4;
 #define FWD_LAUNCH(D_)                                                                              \
     do {                                                                                            \
-        const dim3 grid((unsigned)((a.n_q / (NWAVE * 32 / kg)) * a.Hq));                            \
-        if (kg == 4) fwd_sweep_kernel<D_, 4><<<grid, NTHREAD, 0, st>>>(k);                          \
-        else if (kg == 2) fwd_sweep_kernel<D_, 2><<<grid, NTHREAD, 0, st>>>(k);                     \
-        else fwd_sweep_kernel<D_, 1><<<grid, NTHREAD, 0, st>>>(k);                                  \
+        const dim3 grid((unsigned)((a.n_q / (waves * 32 / kg)) * a.Hq));                            \
+        if (kg == 4) fwd_sweep_kernel<D_, 4, 8><<<grid, 512, 0, st>>>(k);                           \
+        else if (kg == 2) fwd_sweep_kernel<D_, 2, 8><<<grid, 512, 0, st>>>(k);                      \
+        else if (waves == 8) fwd_sweep_kernel<D_, 1, 8><<<grid, 512, 0, st>>>(k);                   \
+        else fwd_sweep_kernel<D_, 1, 4><<<grid, 256, 0, st>>>(k);                                   \
     } while (0)
     if (a.D == 128) FWD_LAUNCH(128);
     else if (a.D == 80) FWD_LAUNCH(80);

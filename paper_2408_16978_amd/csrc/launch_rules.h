@@ -31,6 +31,19 @@ static inline int sweep_key_groups(int64_t n_q, int64_t n_keys, int Hq, bool cau
     return best;
 }
 
+// Waves (of 32 query rows each) of a workgroup of the forward with one key group and of dQ from stored dS: eight, or four or
+// two where a chunk pair has so few row tiles that half of the 256 compute units, or more, would have none.  A wave computes
+// the same whatever the count (the bits do not depend on it); with four or two on a compute unit no second wave of a
+// SIMD works under its MFMAs, but twice or four times the compute units work.  The forward stops at four: two would each move half of every key tile.
+// Measured, us per launch with eight waves -> with fewer (pairs of equal chunks): forward 8 heads, D = 128, chunks of 4K 101.7 ->
+// 92.1 (4), of 2K 51.3 -> 43.4 (4; 2: 64.9); 4 heads, D = 80, 8K 163.9 -> 135.1 (4); D = 64, 4K 66.1 -> 48.8 (4; 2: 59.1); dQ of
+// the same 68.9 -> 52.8 (4), 36.0 -> 31.4 (2), 114.1 -> 86.8 (4), 50.8 -> 31.0 (2).
+static inline int sweep_waves(int64_t n_q, int Hq)
+{
+    const int64_t wgs = n_q / 256 * Hq;
+    return wgs <= 64 ? 2 : wgs <= 128 ? 4 : 8;
+}
+
 // Does an fp32 call over the whole sequence fit into one launch?  (Workgroups of 512 lanes, one per 16 rows and
 // head, for the queries and for the keys; a launch has fewer than 2^32 lanes.)
 static inline bool f32_one_launch(int64_t S, int Hq, int Hkv)
