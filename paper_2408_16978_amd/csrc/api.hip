@@ -505,8 +505,20 @@ int fwd_f32(const Problem& p, const float* Q, const float* K, const float* V, fl
 int fwd_bf16_fused(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* LSE,
                    const FwdPlan& f, hipStream_t st)
 {
-    launch_pack({{K, p.Hkv, f.Knat, nullptr}, {V, p.Hkv, nullptr, f.Vtr}}, p.S, p.D, p.S / 32, st);
     FwdArgs a;
+    // K and V are read where they are (sweep_reads_tensors) unless the sweep overwrites them: a row tile's O is stored while
+    // others still read.
+    auto apart = [&](const void* x, const void* out, size_t bytes_out) {
+        const uintptr_t x0 = reinterpret_cast<uintptr_t>(x), o0 = reinterpret_cast<uintptr_t>(out);
+        return x0 + (size_t)p.S * p.Hkv * p.D * 2 <= o0 || o0 + bytes_out <= x0;
+    };
+    const size_t o_bytes = (size_t)p.S * p.Hq * p.D * 2, lse_bytes = (size_t)p.S * p.Hq * 4;
+    if (sweep_reads_tensors(p.S, p.D, p.fwd_kg) && apart(K, O, o_bytes) && apart(V, O, o_bytes) && apart(K, LSE, lse_bytes) && apart(V, LSE, lse_bytes)) {
+        a.K = K;
+        a.V = V;
+    } else {
+        launch_pack({{K, p.Hkv, f.Knat, nullptr}, {V, p.Hkv, nullptr, f.Vtr}}, p.S, p.D, p.S / 32, st);
+    }
     a.Q = Q; a.Knat = f.Knat; a.Vtr = f.Vtr; a.kv_head_stride_blocks = p.S / 32;
     a.O = O; a.LSE = LSE; a.lse_stride = p.S; a.st_acc = nullptr; a.st_ml = nullptr;
     a.q_pos0 = 0; a.k_pos0 = 0; a.n_q = p.S; a.n_keys = p.S;

@@ -53,6 +53,8 @@ struct FwdArgs {
     const void* Q;      // first query row of the launch, [n_q, Hq, D] bf16
     const void* Knat;   // packed NAT, block 0 = keys k_pos0..k_pos0+31
     const void* Vtr;    // packed TR
+    const void* K = nullptr;  // several key groups: both tensors themselves, [n_keys, Hkv, D], in place of the packed forms
+    const void* V = nullptr;
     int64_t kv_head_stride_blocks;
     void* O;            // [n_q, Hq, D] bf16 (written when SWEEP_FINAL)
     float* LSE;         // &LSE[0][q_pos0]; head stride lse_stride

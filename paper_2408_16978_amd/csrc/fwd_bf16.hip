@@ -6,8 +6,8 @@
 // (column lane%32) and 16 keys per 32-key block, so the running max of a query needs a single
 // exchange between lanes l and l+32, the running sum none until the epilogue, and the
 // exponentiated tile -- still in registers -- is directly the B operand of O^T += V^T P^T.
-// K arrives as NAT fragments, V as TR fragments (fpdt_internal.h); Q is loaded once and
-// stays in registers.
+// K arrives as NAT fragments, V as TR fragments (fpdt_internal.h), or both from their tensors (RAW below); Q is loaded
+// once and stays in registers.
 //
 // Workgroup = 8 waves (two per SIMD, so one wave's softmax arithmetic runs under the other's
 // MFMAs; 4 or 2 where a launch of one key group would otherwise leave half of the chip idle, sweep_waves), each wave owns 32 query rows of one head and at most 256 registers.  The K/V tiles travel
@@ -29,6 +29,9 @@ struct FwdKernelArgs {
     const uint16_t* Q;
     const u32x4* Knat;
     const u32x4* Vtr;
+    const uint16_t* K;  // RAW: the tensors themselves, [n_keys, Hkv, D]
+    const uint16_t* V;
+    int64_t kv_pitch;   // elements between their rows
     int64_t kv_head_stride_blocks;
     uint16_t* O;
     float* LSE;
@@ -41,7 +44,12 @@ struct FwdKernelArgs {
     float c;  // scale * log2(e)
 };
 
-template <int D, int KG, int NWAVE>
+// RAW: K and V come from their row-major tensors instead of packed fragments.  A 32-key block is copied row by row, 16-byte
+// piece q of row r at position q ^ swz(r) of its row, swz(r) = 4 (r % 4) + (r / 4) % 4 (D = 64: 4 (r / 2 % 2) + (r / 4) %
+// 4; D = 80: rows of ten pieces as they are): the lanes that a fragment read serves at a time, and the four rows of a
+// transposing read, lie in different banks.  V's operand is then read with transposing loads, two for one plain
+// read.  For short sequences, where the packing launch costs more than these reads (sweep_reads_tensors, launch_rules.h).
+template <int D, int KG, int NWAVE, bool RAW>
 __global__ __launch_bounds__(NWAVE * 64, 2) void fwd_sweep_kernel(FwdKernelArgs p)
 {
     constexpr int DT = D / 16, DP = (D + 31) / 32 * 32, DB = DP / 32;
@@ -51,11 +59,13 @@ __global__ __launch_bounds__(NWAVE * 64, 2) void fwd_sweep_kernel(FwdKernelArgs 
     constexpr int RING = KG == 4 || NWAVE < 8 ? 2 : 3;  // (a tile of 128 keys: 64 KiB at D = 128; four waves: room for two workgroups)
     constexpr int PF = RING - 1;            // tiles in flight ahead of the one being computed
     constexpr int K_U4 = NB * DT * 64;      // u32x4 per K tile
-    constexpr int V_U4 = NB * 2 * DB * 64;  // u32x4 per V tile
+    constexpr int VF = RAW ? DT : 2 * DB;   // 1 KiB copies of V per 32-key block
+    constexpr int V_U4 = NB * VF * 64;      // u32x4 per V tile
     constexpr int T_U4 = K_U4 + V_U4;
-    constexpr int KFRAG = NB * DT, NFRAG = KFRAG + NB * 2 * DB;  // 1 KiB fragments per tile
+    constexpr int KFRAG = NB * DT, NFRAG = KFRAG + NB * VF;  // 1 KiB copies per tile
+    constexpr int PAD = RAW && DP > D ? 4 : 0;  // the last row's padded channels are read from behind it
     // KG = 1: one LDS array per ring slot; otherwise one for all, which the final merge uses again
-    __shared__ u32x4 ring_a[KG == 1 ? T_U4 : RING * T_U4], ring_b[KG == 1 ? T_U4 : 1], ring_c[KG == 1 ? T_U4 : 1];
+    __shared__ u32x4 ring_a[KG == 1 ? T_U4 : RING * T_U4 + PAD], ring_b[KG == 1 ? T_U4 : 1], ring_c[KG == 1 ? T_U4 : 1];
     u32x4* const ring0 = ring_a;
     u32x4* const ring1 = KG == 1 ? ring_b : ring_a + T_U4;
     u32x4* const ring2 = KG == 1 ? ring_c : ring_a + (RING - 1) * T_U4;
@@ -80,8 +90,48 @@ __global__ __launch_bounds__(NWAVE * 64, 2) void fwd_sweep_kernel(FwdKernelArgs 
     const u32x4* kbase = p.Knat + (size_t)kvh * p.kv_head_stride_blocks * (DT * 64);
     const u32x4* vbase = p.Vtr + (size_t)kvh * p.kv_head_stride_blocks * (2 * DB * 64);
 
+    // RAW: this lane's byte offset within copy c of a 32-key block, and its reads within a block
+    typedef short short4v __attribute__((ext_vector_type(4)));
+    typedef short short8v __attribute__((ext_vector_type(8)));
+    typedef __attribute__((address_space(3))) short4v* lds_short4_ptr;
+    typedef __attribute__((address_space(3))) u32x4* lds_u32x4_ptr;
+    constexpr int PPR = D / 8, ROW = 2 * D;  // pieces and bytes of a row
+    const unsigned pitch = RAW ? (unsigned)p.kv_pitch * 2u : 0u;
+    auto swz = [](int r) { return D == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : D == 64 ? (((r >> 1) & 1) << 2) | ((r >> 2) & 3) : 0; };
+    auto raw_offset = [&](int c) {
+        const int piece = 64 * c + lane, r = D == 80 ? (piece * 6554) >> 16 : piece / PPR;
+        return (unsigned)r * pitch + 16u * (unsigned)((piece - r * PPR) ^ swz(r));
+    };
+    const unsigned raw_off = RAW && D != 80 ? raw_offset(wu % DT) : 0u;  // (every copy of a wave is the same one of its block)
+    const unsigned k_rd = (unsigned)(col * ROW + 16 * (half ^ swz(col)));
+    unsigned v_rd[2];
+    {
+        const int grp = lane >> 4, h = grp >> 1, dblk = grp & 1, e = (lane & 15) >> 2, x = lane & 3;
+#pragma unroll
+        for (int I = 0; I < 2; ++I) {
+            const int r = 8 * I + 4 * h + e;
+            v_rd[I] = (unsigned)(r * ROW + 16 * ((2 * dblk + (x >> 1)) ^ swz(r)) + 8 * (x & 1));
+        }
+    }
+
     // Copy tile `it` into ring slot `slot`: wave w moves fragments w, w+8, ...
     auto issue = [&](int it, u32x4* slot) {
+        if constexpr (RAW) {
+            static_assert(D == 80 || (KFRAG % NWAVE == 0 && NWAVE % DT == 0), "a wave's copies are the same one of every block");
+            const unsigned lds = lds_address(slot);
+            const uint64_t row0 = (uint64_t)it * BK * pitch + (uint64_t)kvh * ROW;
+#pragma unroll
+            for (int f0 = 0; f0 < NFRAG; f0 += NWAVE) {
+                const int f = f0 + wu;
+                if (f0 + NWAVE <= NFRAG || f < NFRAG) {
+                    const bool of_k = f < KFRAG;
+                    const int fb = of_k ? f : f - KFRAG, blk = fb / DT, c = fb - blk * DT;
+                    const uint64_t src = (uint64_t)(uintptr_t)(of_k ? p.K : p.V) + row0 + (uint64_t)(32 * blk) * pitch;
+                    frag_to_lds_at(uniform(src), lds + 1024u * (unsigned)f, (int)(D == 80 ? raw_offset(c) : raw_off));
+                }
+            }
+            return;
+        }
         const u32x4* ksrc = kbase + (size_t)it * K_U4;
         const u32x4* vsrc = vbase + (size_t)it * V_U4;
 #pragma unroll
@@ -147,7 +197,14 @@ __global__ __launch_bounds__(NWAVE * 64, 2) void fwd_sweep_kernel(FwdKernelArgs 
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-                for (int t = 0; t < DT; ++t) kfr[kb][t] = as_bf16x8(ks[((kb0 + kb) * DT + t) * 64 + lane]);
+                for (int t = 0; t < DT; ++t) {
+                    if constexpr (RAW) {
+                        const unsigned at = D == 80 ? k_rd + 32u * (unsigned)t : k_rd ^ (32u * (unsigned)t);
+                        kfr[kb][t] = as_bf16x8(*(lds_u32x4_ptr)(uintptr_t)(lds_address(ks) + 1024u * (unsigned)((kb0 + kb) * DT) + at));
+                    } else {
+                        kfr[kb][t] = as_bf16x8(ks[((kb0 + kb) * DT + t) * 64 + lane]);
+                    }
+                }
             floatx16 s[KB];
 #pragma unroll
             for (int t = 0; t < DT; ++t)
@@ -162,8 +219,19 @@ __global__ __launch_bounds__(NWAVE * 64, 2) void fwd_sweep_kernel(FwdKernelArgs 
 #pragma unroll
                 for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
-                    for (int db = 0; db < DB; ++db) vfr[kb][s2][db] = as_bf16x8(vs[(((kb0 + kb) * 2 + s2) * DB + db) * 64 + lane]);
-            __builtin_amdgcn_sched_group_barrier(0x100, KB * 2 * DB, 0);
+                    for (int db = 0; db < DB; ++db) {
+                        if constexpr (RAW) {
+                            const unsigned blk = lds_address(vs) + 1024u * (unsigned)((kb0 + kb) * DT) + (unsigned)(16 * s2 * ROW);
+                            auto at = [&](int I) { return blk + (D == 80 ? v_rd[I] + 64u * (unsigned)db : v_rd[I] ^ (64u * (unsigned)db)); };
+                            const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(uintptr_t)at(0));
+                            const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(uintptr_t)at(1));
+                            const short8v both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+                            vfr[kb][s2][db] = __builtin_bit_cast(bf16x8, both);
+                        } else {
+                            vfr[kb][s2][db] = as_bf16x8(vs[(((kb0 + kb) * 2 + s2) * DB + db) * 64 + lane]);
+                        }
+                    }
+            __builtin_amdgcn_sched_group_barrier(0x100, KB * 2 * DB * (RAW ? 2 : 1), 0);
             // ---- online softmax, one query per lane ----
             if (key0 + 32 * KB - 1 > qpos_first) {  // wave-uniform: the tile straddles the diagonal
                 // key index within the tile vs this lane's query, in 32 bits: a key is masked
@@ -339,6 +407,9 @@ void launch_fwd_sweep(const FwdArgs& a, hipStream_t st)
     k.Q = static_cast<const uint16_t*>(a.Q);
     k.Knat = static_cast<const u32x4*>(a.Knat);
     k.Vtr = static_cast<const u32x4*>(a.Vtr);
+    k.K = static_cast<const uint16_t*>(a.K);
+    k.V = static_cast<const uint16_t*>(a.V);
+    k.kv_pitch = (int64_t)a.Hkv * a.D;
     k.kv_head_stride_blocks = a.kv_head_stride_blocks;
     k.O = static_cast<uint16_t*>(a.O);
     k.LSE = a.LSE;
@@ -357,10 +428,12 @@ void launch_fwd_sweep(const FwdArgs& a, hipStream_t st)
 #define FWD_LAUNCH(D_)                                                                              \
     do {                                                                                            \
         const dim3 grid((unsigned)((a.n_q / (waves * 32 / kg)) * a.Hq));                            \
-        if (kg == 4) fwd_sweep_kernel<D_, 4, 8><<<grid, 512, 0, st>>>(k);                           \
-        else if (kg == 2) fwd_sweep_kernel<D_, 2, 8><<<grid, 512, 0, st>>>(k);                      \
-        else if (waves == 8) fwd_sweep_kernel<D_, 1, 8><<<grid, 512, 0, st>>>(k);                   \
-        else fwd_sweep_kernel<D_, 1, 4><<<grid, 256, 0, st>>>(k);                                   \
+        if (kg == 4 && a.K) fwd_sweep_kernel<D_, 4, 8, true><<<grid, 512, 0, st>>>(k);              \
+        else if (kg == 4) fwd_sweep_kernel<D_, 4, 8, false><<<grid, 512, 0, st>>>(k);               \
+        else if (kg == 2 && a.K) fwd_sweep_kernel<D_, 2, 8, true><<<grid, 512, 0, st>>>(k);         \
+        else if (kg == 2) fwd_sweep_kernel<D_, 2, 8, false><<<grid, 512, 0, st>>>(k);               \
+        else if (waves == 8) fwd_sweep_kernel<D_, 1, 8, false><<<grid, 512, 0, st>>>(k);            \
+        else fwd_sweep_kernel<D_, 1, 4, false><<<grid, 256, 0, st>>>(k);                            \
     } while (0)
     if (a.D == 128) FWD_LAUNCH(128);
     else if (a.D == 80) FWD_LAUNCH(80);

@@ -44,6 +44,19 @@ static inline int sweep_waves(int64_t n_q, int Hq)
     return wgs <= 64 ? 2 : wgs <= 128 ? 4 : 8;
 }
 
+// Does the one-launch forward read K and V from their tensors, without the launch that packs them?  With several key groups
+// (short sequences) that launch costs more than the transposing reads that take its place.  Longer ones gain from the packed
+// copies (fewer LDS reads per tile; and inputs that are not in a cache yet are fetched once, not under every workgroup's
+// chain), at D = 80 soonest, whose rows of ten pieces are not spread over the banks.
+// Measured, new inputs in every call (us, packed -> not; query / KV heads): D = 64, 8 / 8, 2K 19.3 -> 15.4; 4 / 4, 6K 45.4 -> 36.0; 4
+// / 2, 7936 55.7 -> 50.4; 8 / 1, 11K 160 -> 181; D = 80, 8 / 2, 3K 29.0 -> 27.7; 8 / 1, 4K 41.3 -> 39.1, 6K 79.0 -> 81.1; 2 / 2,
+// 15616 116 -> 120 and, in a forward and backward on new inputs, 450 -> 510; D = 128, 8 / 2, 512 14.2 -> 12.3, 2K 27.4 -> 26.3,
+// 4K 55.3 -> 53.4; 2 / 2, 6K 65.3 -> 60.3; 8 / 1, 7936 136.5 -> 138.0.
+static inline bool sweep_reads_tensors(int64_t S, int D, int key_groups)
+{
+    return key_groups > 1 && S <= (D == 64 ? 8192 : D == 80 ? 4096 : 6144);
+}
+
 // Does an fp32 call over the whole sequence fit into one launch?  (Workgroups of 512 lanes, one per 16 rows and
 // head, for the queries and for the keys; a launch has fewer than 2^32 lanes.)
 static inline bool f32_one_launch(int64_t S, int Hq, int Hkv)
