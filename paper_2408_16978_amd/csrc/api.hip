@@ -513,7 +513,7 @@ int fwd_bf16_fused(const Problem& p, const void* Q, const void* K, const void* V
         return x0 + (size_t)p.S * p.Hkv * p.D * 2 <= o0 || o0 + bytes_out <= x0;
     };
     const size_t o_bytes = (size_t)p.S * p.Hq * p.D * 2, lse_bytes = (size_t)p.S * p.Hq * 4;
-    if (sweep_reads_tensors(p.S, p.D, p.fwd_kg) && apart(K, O, o_bytes) && apart(V, O, o_bytes) && apart(K, LSE, lse_bytes) && apart(V, LSE, lse_bytes)) {
+    if (sweep_reads_tensors(p.S, p.Hq, p.Hkv, p.D, p.fwd_kg) && apart(K, O, o_bytes) && apart(V, O, o_bytes) && apart(K, LSE, lse_bytes) && apart(V, LSE, lse_bytes)) {
         a.K = K;
         a.V = V;
     } else {

@@ -10,7 +10,8 @@
 // once and stays in registers.
 //
 // Workgroup = 8 waves (two per SIMD, so one wave's softmax arithmetic runs under the other's
-// MFMAs; 4 or 2 where a launch of one key group would otherwise leave half of the chip idle, sweep_waves), each wave owns 32 query rows of one head and at most 256 registers.  The K/V tiles travel
+// MFMAs; 4 where a launch of one key group would otherwise leave half of the chip idle, sweep_waves), each wave owns 32 query
+// rows of one head and at most 256 registers.  The K/V tiles travel
 // global -> LDS directly (no register staging) through a ring filled ahead.  KG = 1: the waves own 256
 // query rows and share 64-key tiles.  KG = 2, 4: 128 or 64 query rows, the waves of one row block take
 // every KG-th 32-key block and merge their (max, sum, output) through LDS at the end, for launches whose
@@ -175,6 +176,26 @@ __global__ __launch_bounds__(NWAVE * 64, 2) void fwd_sweep_kernel(FwdKernelArgs 
 
     if (n_tiles > 0) issue(0, ring0);
     if (PF > 1 && n_tiles > 1) issue(1, ring1);
+    if constexpr (RAW && KG == 4) {
+        // The packing launch also brought K and V into the caches, all of them at once.  With one tile in flight a workgroup
+        // would fetch them tile after tile, each at the latency of HBM (inputs that no cache holds: 8 / 2 heads, D = 128, 2K
+        // 31.4 us, 8 / 8, D = 64, 4K 46.0; packed 28.5, 35.0; this 27.1, 32.6).  So the workgroups of a head that start
+        // first read a word of every line of its K and V between them, in the shadow of the first tile.  (Up to 768 keys
+        // there are too few tiles for it; two key groups have two in flight and 16 heads and more: it gained nothing and cost up to 8%.)
+        const int starting = 256 / p.Hq > 0 ? 256 / p.Hq : 1, readers = n_qt < starting ? n_qt : starting, turn = (int)(blockIdx.x / p.Hq);
+        if (turn < readers && p.n_keys > 768) {
+            constexpr int LINES = D == 64 ? 1 : 2;  // of 128 bytes, of a row of the head: those of its first and its last word
+            const int rows = (p.n_keys + readers - 1) / readers, row0 = turn * rows;
+            const int words = (p.n_keys - row0 < rows ? p.n_keys - row0 : rows) * LINES;
+            unsigned seen = 0;
+#pragma unroll 2
+            for (int i = tid; i < words; i += NWAVE * 64) {
+                const size_t at = (size_t)(row0 + i / LINES) * p.kv_pitch + (size_t)kvh * D + (i % LINES ? D - 2 : 0);
+                seen |= *reinterpret_cast<const unsigned*>(p.K + at) | *reinterpret_cast<const unsigned*>(p.V + at);
+            }
+            asm volatile("" ::"v"(seen));
+        }
+    }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 

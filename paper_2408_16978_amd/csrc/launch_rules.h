@@ -45,16 +45,22 @@ static inline int sweep_waves(int64_t n_q, int Hq)
 }
 
 // Does the one-launch forward read K and V from their tensors, without the launch that packs them?  With several key groups
-// (short sequences) that launch costs more than the transposing reads that take its place.  Longer ones gain from the packed
-// copies (fewer LDS reads per tile; and inputs that are not in a cache yet are fetched once, not under every workgroup's
-// chain), at D = 80 soonest, whose rows of ten pieces are not spread over the banks.
-// Measured, new inputs in every call (us, packed -> not; query / KV heads): D = 64, 8 / 8, 2K 19.3 -> 15.4; 4 / 4, 6K 45.4 -> 36.0; 4
-// / 2, 7936 55.7 -> 50.4; 8 / 1, 11K 160 -> 181; D = 80, 8 / 2, 3K 29.0 -> 27.7; 8 / 1, 4K 41.3 -> 39.1, 6K 79.0 -> 81.1; 2 / 2,
-// 15616 116 -> 120 and, in a forward and backward on new inputs, 450 -> 510; D = 128, 8 / 2, 512 14.2 -> 12.3, 2K 27.4 -> 26.3,
-// 4K 55.3 -> 53.4; 2 / 2, 6K 65.3 -> 60.3; 8 / 1, 7936 136.5 -> 138.0.
-static inline bool sweep_reads_tensors(int64_t S, int D, int key_groups)
+// (short sequences) that launch costs more than the transposing reads that take its place, up to a length: longer ones gain
+// from the packed copies (fewer LDS reads per tile), at D = 80, whose rows of ten pieces are not spread over the banks,
+// and D = 128 sooner than at D = 64, and with two key groups, whose workgroups hide less of them, soonest; where every query head
+// has K and V of its own there is most to pack.  More than 512 workgroups have to share the compute units: at D = 64 two of
+// the packed kernel fit one, of this one, with 134 registers, one.
+// Measured over 15 head counts and 20 lengths, with the inputs in the caches and without (us, packed -> not, the two in turn;
+// query / KV heads): D = 64, 8 / 2, 2K 18.8 -> 16.4, 4K 34.5 -> 32.9, 5K (640 workgroups) 44 -> 51, 4 / 4, 8K 59 -> 56, 16 / 4,
+// 5K (two key groups, 640) 76 -> 87; D = 80, 8 / 2, 2K 23.2 -> 22.0, 4K 42.6 -> 43.4; 16 / 4, 3K (two key groups) 46.1 -> 46.3;
+// D = 128, 8 / 2, 1K 19.6 -> 17.8, 2K 28.4 -> 27.2, 4K 55.5 -> 57.2, 8 / 8, 4K 60.2 -> 58.1, 16 / 4, 4K (two key groups) 82.8 -> 83.6.
+static inline bool sweep_reads_tensors(int64_t S, int Hq, int Hkv, int D, int key_groups)
 {
-    return key_groups > 1 && S <= (D == 64 ? 8192 : D == 80 ? 4096 : 6144);
+    if (key_groups == 1) return false;
+    const int64_t workgroups = S / 256 * key_groups * Hq;
+    if (D == 64) return S <= 8192 && workgroups <= 512;
+    if (Hq == Hkv && Hkv >= 8) return S <= (D == 80 ? 4096 : 6144);
+    return key_groups == 4 ? S <= (D == 80 ? 3584 : 3072) && workgroups <= 512 : S <= 2048;
 }
 
 // Does an fp32 call over the whole sequence fit into one launch?  (Workgroups of 512 lanes, one per 16 rows and
