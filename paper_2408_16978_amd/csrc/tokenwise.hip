@@ -11,6 +11,7 @@
 
 #include "../../include/fpdt_tokenwise.h"
 #include "tw_gemm.h"
+#include "tw_plan.h"
 
 namespace {
 
@@ -503,20 +504,17 @@ int fpdt_tw_loss_fwd_bwd(const void* H, const void* W, const int32_t* target, fl
     if (rc != TW_OK) return rc;
     // The logit gradients of several chunks are gathered before they are multiplied: dW += G^T H reads and
     // writes the whole fp32 dW (2.1 GB at 128256 x 4096), which at 1058 rows per chunk took as long as its
-    // MFMAs, and dH = G W has too few tiles at that height.  About 2 `hidden` rows at a time: their
-    // G then takes the memory of two bf16 copies of W, in the library's scratch.  Rows of G are padded to 16
+    // MFMAs, and dH = G W has too few tiles at that height.  Up to 2 `hidden` rows at a time (loss_group): their
+    // G then takes the memory of two bf16 copies of W at most, in the library's scratch.  Rows of G are padded to 16
     // bytes there, so an odd vocabulary takes this way with a single chunk too.
     // Measured (65536 tokens, hidden 4096, 62 chunks): 310 -> 235 ms with `hidden` rows, 210 -> 204 ms from there to twice as many.
     // The logits then have the room of the chunk's gradients in the workspace too, half as many rows again: they are
     // computed for a multiple of 256 rows at a time, whole tiles of the product (1058-row chunks fill four and an
     // eighth), and their rows start with a cache line.
-    const bool gathered = bwd && (2 * (int64_t)hidden >= 2 * c || vocab % 8);
+    const bool gathered = bwd && (hidden >= c || vocab % 8);
     int64_t ldg = vocab, ldl = vocab, group = c, step = c;
     if (gathered) {
-        if (group < 2 * (int64_t)hidden) {
-            const int64_t groups = (rows + 2 * hidden - 1) / (2 * (int64_t)hidden);  // of about the same size
-            group = ((rows + groups - 1) / groups + 255) / 256 * 256;
-        }
+        group = fpdt_tw::loss_group(rows, c, hidden);
         ldg = ((int64_t)vocab + 7) / 8 * 8;
         G = static_cast<uint16_t*>(fpdt_tw::scratch((size_t)(group < rows ? group : rows) * ldg * 2));
         if (!G) return gemm_status(1);  // (no smaller groups instead: how dW is summed depends on the arguments alone)

@@ -113,4 +113,14 @@ static inline Plan plan_launch(int64_t M, int64_t N, int steps)
     return best_cost < 0.95 * cost(first.wmt, first.wnt, (double)(first.u.tiles - rest), (double)rest, first.u.splits) ? best : first;
 }
 
+// Rows whose logit gradients the loss gathers before it multiplies them: a chunk's `c`, or where at least two chunks make 2
+// `hidden` rows, as many groups as it takes at 2 `hidden` rows each, of about the same size, in whole tiles of 256 rows
+// unless that would be more than 2 `hidden`, which bounds the scratch.
+static inline int64_t loss_group(int64_t rows, int64_t c, int64_t hidden)
+{
+    if (hidden < c) return c;
+    const int64_t groups = (rows + 2 * hidden - 1) / (2 * hidden), even = (rows + groups - 1) / groups, tiles = (even + 255) / 256 * 256;
+    return tiles <= 2 * hidden ? tiles : even;
+}
+
 }  // namespace fpdt_tw
