@@ -509,25 +509,24 @@ int fpdt_tw_loss_fwd_bwd(const void* H, const void* W, const int32_t* target, fl
     // bytes there, so an odd vocabulary takes this way with a single chunk too.
     // Measured (65536 tokens, hidden 4096, 62 chunks): 310 -> 235 ms with `hidden` rows, 210 -> 204 ms from there to twice as many.
     // The logits then have the room of the chunk's gradients in the workspace too, half as many rows again: they are
-    // computed for a multiple of 256 rows at a time, whole tiles of the product (1058-row chunks fill four and an
+    // computed for a multiple of 256 rows at a time (loss_step), whole tiles of the product (1058-row chunks fill four and an
     // eighth), and their rows start with a cache line.
     const bool gathered = bwd && (hidden >= c || vocab % 8);
-    int64_t ldg = vocab, ldl = vocab, group = c, step = c;
+    int64_t ldg = vocab, ldl = vocab, group = c, full = c;  // full: rows of logits that have room
+    if (gathered || !bwd) {
+        const int64_t room = (int64_t)(need / 4), ld = ((int64_t)vocab + 31) / 32 * 32;
+        if (c * ld <= room) ldl = ld;
+        full = room / ldl < MAX_ROWS ? room / ldl : MAX_ROWS;
+    }
     if (gathered) {
         group = fpdt_tw::loss_group(rows, c, hidden);
         ldg = ((int64_t)vocab + 7) / 8 * 8;
         G = static_cast<uint16_t*>(fpdt_tw::scratch((size_t)(group < rows ? group : rows) * ldg * 2));
         if (!G) return gemm_status(1);  // (no smaller groups instead: how dW is summed depends on the arguments alone)
     }
-    if (gathered || !bwd) {
-        const int64_t room = (int64_t)(need / 4), ld = ((int64_t)vocab + 31) / 32 * 32;
-        if (c * ld <= room) ldl = ld;
-        step = room / ldl >= 256 ? room / ldl / 256 * 256 : room / ldl;
-        if (step > MAX_ROWS) step = MAX_ROWS;
-    }
     if (!bwd) group = rows;
     for (int64_t g0 = 0; g0 < rows; g0 += group) {
-        const int64_t g1 = rows - g0 < group ? rows : g0 + group;
+        const int64_t g1 = rows - g0 < group ? rows : g0 + group, step = fpdt_tw::loss_step(g1 - g0, full, vocab, hidden);
         for (int64_t r0 = g0; r0 < g1; r0 += step) {
             const int n = (int)(g1 - r0 < step ? g1 - r0 : step);
             // logits[n, vocab] = H_c W^T

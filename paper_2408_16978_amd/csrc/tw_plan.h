@@ -66,6 +66,20 @@ static inline Plan plan_product(int64_t M, int64_t N, int steps)
     return best;
 }
 
+// Clocks of a launch: `whole` tiles over all of k and `rest` tiles in `sp` splits each (plan_launch says from what)
+static inline double launch_cost(int wm, int wn, double whole, double rest, int sp, int steps)
+{
+    const bool two = wm * wn <= 4;
+    const double slots = two ? 512.0 : 256.0, per = sp == 1 ? steps : (double)(((steps + sp - 1) / sp + 1) / 2 * 2);
+    const double mfma = two ? 161.0 * wm * wn + 158.0 : 64.0 * wm * wn + 116.0, copies = (two ? 175.0 : 85.0) * (wm + wn);
+    const double step = mfma > copies ? mfma : copies, fixed = two ? 8100.0 + 1385.0 * wm * wn : 6900.0 + 1630.0 * wm * wn;
+    const double units = rest * sp, full = std::floor(units / slots), last = units - full * slots;
+    double c = whole / slots * (steps * step + fixed) + full * (per * step + fixed) + 7600.0;
+    if (last > 0.0) c += (per * step + fixed) * (two && last <= 256.0 ? 0.56 : 1.0);
+    if (sp > 1) c += 3800.0 + (sp + 1) * 4.0 * rest * (64 * wm) * (64 * wn) / 8300.0;
+    return c;
+}
+
 // What a launch runs: plan_product's answer, or another tile and division that the measured times of 68 products
 // (M and N of 300 .. 16384, k of 65 .. 15776, every tile and division; 2.8% above the best of them on average,
 // plan_product alone 8.2%) put at least 5% below it.  The terms are plan_product's, but with two workgroups on
@@ -80,17 +94,7 @@ static inline Plan plan_launch(int64_t M, int64_t N, int steps)
     static const int shapes[][2] = {{4, 4}, {3, 4}, {2, 4}, {1, 4}, {2, 2}};
     const Plan first = plan_product(M, N, steps);
     if (first.u.tiles == 0 || M < 512 || N < 512 || (first.u.splits > 2 && first.u.whole > 0)) return first;
-    auto cost = [&](int wm, int wn, double whole, double rest, int sp) {
-        const bool two = wm * wn <= 4;
-        const double slots = two ? 512.0 : 256.0, per = sp == 1 ? steps : (double)(((steps + sp - 1) / sp + 1) / 2 * 2);
-        const double mfma = two ? 161.0 * wm * wn + 158.0 : 64.0 * wm * wn + 116.0, copies = (two ? 175.0 : 85.0) * (wm + wn);
-        const double step = mfma > copies ? mfma : copies, fixed = two ? 8100.0 + 1385.0 * wm * wn : 6900.0 + 1630.0 * wm * wn;
-        const double units = rest * sp, full = std::floor(units / slots), last = units - full * slots;
-        double c = whole / slots * (steps * step + fixed) + full * (per * step + fixed) + 7600.0;
-        if (last > 0.0) c += (per * step + fixed) * (two && last <= 256.0 ? 0.56 : 1.0);
-        if (sp > 1) c += 3800.0 + (sp + 1) * 4.0 * rest * (64 * wm) * (64 * wn) / 8300.0;
-        return c;
-    };
+    auto cost = [&](int wm, int wn, double whole, double rest, int sp) { return launch_cost(wm, wn, whole, rest, sp, steps); };
     Plan best = first;
     double best_cost = 0.0;
     for (const auto& sh : shapes) {
@@ -111,6 +115,30 @@ static inline Plan plan_launch(int64_t M, int64_t N, int steps)
     const int slots = first.wmt * first.wnt <= 4 ? 512 : 256;
     const int64_t rest = first.u.tiles % slots;
     return best_cost < 0.95 * cost(first.wmt, first.wnt, (double)(first.u.tiles - rest), (double)rest, first.u.splits) ? best : first;
+}
+
+// Clocks of the products of `n` rows of logits, `step` rows at a time
+static inline double loss_cost(int64_t n, int64_t step, int64_t vocab, int64_t hidden)
+{
+    const int steps = (int)((hidden < SK ? SK : hidden) / SK);
+    auto one = [&](int64_t rows) {
+        const Plan p = plan_launch(rows, vocab, steps);
+        const int rest = p.u.tiles % (p.wmt * p.wnt <= 4 ? 512 : 256);
+        return launch_cost(p.wmt, p.wnt, p.u.tiles - rest, rest, p.u.splits, steps);
+    };
+    return (n >= step ? (double)(n / step) * one(step) : 0.0) + (n % step ? one(n % step) : 0.0);
+}
+
+// Rows of logits that the loss computes at a time, of `n` rows of which `full` have room: whole tile rows (256), or as many as
+// there is room for, where that is one product or costs at least a sixteenth less.  Measured (us, as whole tile rows | as many
+// as have room): forward, 300 rows, hidden 2048, vocabulary 8000: 52.5 | 38.6; hidden 1024, 32000: 61.5 | 43.0; 3396 rows, room
+// for 1273, 4096, 16384: 428 | 470; with gradients, 2075 rows, room for 390, 2048, 50304: 1426 | 1495; 1602 rows, room for 400,
+// 1024, 8000: 261 | 245.
+static inline int64_t loss_step(int64_t n, int64_t full, int64_t vocab, int64_t hidden)
+{
+    const int64_t tiles = full / 256 * 256;
+    if (tiles == 0 || n <= full) return full;
+    return 15 * loss_cost(n, tiles, vocab, hidden) <= 16 * loss_cost(n, full, vocab, hidden) ? tiles : full;
 }
 
 // Rows whose logit gradients the loss gathers before it multiplies them: a chunk's `c`, or where at least two chunks make 2
