@@ -55,14 +55,14 @@ __device__ __forceinline__ floatx4 dot_rows(const Rows<D>& a, const Rows<D>& b)
     return s;
 }
 
-// A wave's own part of LDS: the rows of two blocks, for the products contracted over them, and a score tile.  (Rows 4 floats
+// A wave's own part of LDS: the rows of `PLACES` blocks, for the products contracted over them, and a score tile.  (Rows 4 floats
 // apart from a multiple of the banks: what a read takes, sixteen elements of every fourth row, lies in different ones.)
-template <int D>
+template <int D, int PLACES>
 struct Shelf {
-    static constexpr int PITCH = D + 4, ROWS = TR * PITCH, FLOATS = 2 * ROWS + TR * TR;
+    static constexpr int PITCH = D + 4, ROWS = TR * PITCH, FLOATS = PLACES * ROWS + TR * TR;
     float* p;
     int lane;
-    // Rows x into place `at` (0 or 1), zeros for elements that are not finite; are there any?
+    // Rows x into place `at`, zeros for elements that are not finite; are there any?
     __device__ __forceinline__ bool put(int at, const Rows<D>& x) const
     {
         float z = 0.f;
@@ -88,7 +88,7 @@ struct Shelf {
     }
     // Column operand: element 16 db + lane % 16 of row 4 (lane / 16) + r
     __device__ __forceinline__ float get(int at, int db, int r) const { return p[at * ROWS + (4 * (lane >> 4) + r) * PITCH + 16 * db + (lane & 15)]; }
-    __device__ __forceinline__ float* tile() const { return p + 2 * ROWS; }
+    __device__ __forceinline__ float* tile() const { return p + PLACES * ROWS; }
 };
 
 // acc^T [D x 16] += X^T [D x 16 rows] T [16 rows x 16 columns]: `t` is a score tile in accumulator layout
@@ -96,8 +96,8 @@ struct Shelf {
 // bit r set where t[r] counts; where it does not, t[r] is 0, but the row of X may hold infinities or NaN (a
 // later key of this query), which 0 times it must not let through: those elements (`odd`: there are some) stay
 // out of the product and are added one by one where they count.
-template <int D>
-__device__ __forceinline__ void add_rows(floatx4 (&acc)[D / 16], const floatx4& t, unsigned keep, const Shelf<D>& shelf, int at, bool odd,
+template <int D, int PLACES>
+__device__ __forceinline__ void add_rows(floatx4 (&acc)[D / 16], const floatx4& t, unsigned keep, const Shelf<D, PLACES>& shelf, int at, bool odd,
                                          const float* X, size_t pitch, int n_rows, int lane)
 {
     const int g = lane >> 4, col = lane & 15;
@@ -163,16 +163,23 @@ __device__ __forceinline__ float sum_over_rows(float v)
 
 // Workgroup = one 16-query tile of one head; wave w folds key blocks w, w + 8, .. into its own (max, sum,
 // un-normalised output), wave 0 starting from the carried state; they are merged at the end.
+//
+// At D = 64 and 80 two workgroups fit a compute unit, where one runs its products under the other's exponentials (D = 80, 32 / 8
+// heads, 1K tokens: one 117 us, two 90).  Tiles start with the longest walks; between 257 and 512 of them, which then all start at
+// once, the shortest follow on the 256 longest, so that what shares a compute unit is about the same everywhere (D = 80, 4 heads, 2K
+// tokens: one at a time 51 us, two in order 63, this 47; D = 64: in order 52, this 39).
 template <int D>
-__global__ __launch_bounds__(64 * NW) void f32_fwd_kernel(F32FwdArgs a)
+__global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 4) void f32_fwd_kernel(F32FwdArgs a)
 {
     constexpr int DB = D / 16;
-    static_assert(Shelf<D>::FLOATS >= D * 17, "sum_waves uses the same memory");
-    __shared__ __attribute__((aligned(16))) float lds[NW * Shelf<D>::FLOATS];
+    typedef Shelf<D, 1> MyShelf;
+    static_assert(MyShelf::FLOATS >= D * 17, "sum_waves uses the same memory");
+    __shared__ __attribute__((aligned(16))) float lds[NW * MyShelf::FLOATS];
     __shared__ float ml[NW][2][TR];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, col = lane & 15;
     const int n_tiles = (int)((a.n_q + TR - 1) / TR);
-    const int head = blockIdx.x % (unsigned)a.Hq, tile = n_tiles - 1 - (int)(blockIdx.x / (unsigned)a.Hq);  // longest first
+    const unsigned turn = D < 128 && gridDim.x <= 512 && blockIdx.x >= 256 ? gridDim.x - 1 - (blockIdx.x - 256) : blockIdx.x;
+    const int head = turn % (unsigned)a.Hq, tile = n_tiles - 1 - (int)(turn / (unsigned)a.Hq);  // longest first
     const int kvh = head / (a.Hq / a.Hkv);
     const int64_t row0 = (int64_t)tile * TR;
     const int rows = (int)(a.n_q - row0 < TR ? a.n_q - row0 : TR), my_row = col < rows ? col : rows - 1;
@@ -199,7 +206,7 @@ __global__ __launch_bounds__(64 * NW) void f32_fwd_kernel(F32FwdArgs a)
     // (Fetched again as columns, 4 bytes per lane and access, where they are used: forward 22.6 us, backward 40.)
     auto keys_at = [&](int64_t j) { return (int)(a.n_k - j < BR ? a.n_k - j : BR); };
     auto row_at = [&](int64_t j) { return (j + (col < keys_at(j) ? col : keys_at(j) - 1)) * k_pitch + (size_t)kvh * D; };
-    const Shelf<D> shelf = {lds + w * Shelf<D>::FLOATS, lane};
+    const MyShelf shelf = {lds + w * MyShelf::FLOATS, lane};
     Rows<D> k, v;
     if (BR * w < need) {
         k.load(a.K + row_at(BR * w), g);
@@ -244,7 +251,7 @@ __global__ __launch_bounds__(64 * NW) void f32_fwd_kernel(F32FwdArgs a)
             s[r] = (keep >> r) & 1 ? expf(s[r] - m_ref) : 0.f;
             l += s[r];
         }
-        add_rows<D>(acc, s, keep, shelf, 0, odd, a.V + j0 * k_pitch + (size_t)kvh * D, k_pitch, keys, lane);
+        add_rows(acc, s, keep, shelf, 0, odd, a.V + j0 * k_pitch + (size_t)kvh * D, k_pitch, keys, lane);
     }
     l = sum_over_rows(l);
     if (g == 0) {
@@ -288,11 +295,11 @@ template <int D>
 __global__ __launch_bounds__(64 * NW) void f32_bwd_kernel(F32BwdArgs a, unsigned dq_blocks)
 {
     constexpr int DB = D / 16;
-    __shared__ __attribute__((aligned(16))) float lds[NW * Shelf<D>::FLOATS];
+    __shared__ __attribute__((aligned(16))) float lds[NW * Shelf<D, 2>::FLOATS];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, col = lane & 15;
     const int group = a.Hq / a.Hkv;
     const size_t q_pitch = (size_t)a.Hq * D, k_pitch = (size_t)a.Hkv * D;
-    const Shelf<D> shelf = {lds + w * Shelf<D>::FLOATS, lane};
+    const Shelf<D, 2> shelf = {lds + w * Shelf<D, 2>::FLOATS, lane};
     if (blockIdx.x < dq_blocks) {
         const int n_tiles = (int)((a.n_q + TR - 1) / TR);
         const int head = blockIdx.x % (unsigned)a.Hq, tile = n_tiles - 1 - (int)(blockIdx.x / (unsigned)a.Hq);
@@ -334,7 +341,7 @@ __global__ __launch_bounds__(64 * NW) void f32_bwd_kernel(F32BwdArgs a, unsigned
                 keep |= (unsigned)on << r;
                 s[r] = on ? expf(a.scale * s[r] - lse) * (dp[r] - delta) : 0.f;
             }
-            add_rows<D>(acc, s, keep, shelf, 0, odd, a.K + k0, k_pitch, keys, lane);
+            add_rows(acc, s, keep, shelf, 0, odd, a.K + k0, k_pitch, keys, lane);
         }
         sum_waves<D>(acc, lds, [&](int d, int c, float v) {
             if (c < rows) {
@@ -412,8 +419,8 @@ __global__ __launch_bounds__(64 * NW) void f32_bwd_kernel(F32BwdArgs a, unsigned
             s[r] = on ? expf(a.scale * s[r] - ls[r]) : 0.f;
             ds[r] = on ? s[r] * (ds[r] - de[r]) : 0.f;
         }
-        add_rows<D>(dv, s, keep, shelf, 1, odd_o, a.dO + q0, q_pitch, rows, lane);
-        add_rows<D>(dk, ds, keep, shelf, 0, odd_q, a.Q + q0, q_pitch, rows, lane);
+        add_rows(dv, s, keep, shelf, 1, odd_o, a.dO + q0, q_pitch, rows, lane);
+        add_rows(dk, ds, keep, shelf, 0, odd_q, a.Q + q0, q_pitch, rows, lane);
     }
     auto put = [&](float* out, float mul) {
         return [=](int d, int c, float x) {
