@@ -13,12 +13,14 @@ SHIM = """
 extern "C" int key_groups(int64_t n_q, int64_t n_k, int Hq, int causal) { return fpdt::sweep_key_groups(n_q, n_k, Hq, causal); }
 extern "C" int f32_one_launch(int64_t S, int Hq, int Hkv) { return fpdt::f32_one_launch(S, Hq, Hkv); }
 extern "C" int dkdv_splits(int64_t n_q, int64_t n_k, int Hq, int Hkv, int D, int causal) { return fpdt::bwd_dkdv_splits(n_q, n_k, Hq, Hkv, D, causal); }
-extern "C" void product(int64_t M, int64_t N, int64_t K, int* out)
+static void put(const fpdt_tw::Plan& p, int* out)
 {
-    const fpdt_tw::Plan p = fpdt_tw::plan_product(M, N, (int)((K < fpdt_tw::SK ? fpdt_tw::SK : K) / fpdt_tw::SK));
-    const int v[] = {p.wmt, p.wnt, p.u.tiles, p.u.whole, p.u.splits, p.u.split_stages};
-    for (int i = 0; i < 6; ++i) out[i] = v[i];
+    const int v[] = {p.wmt, p.wnt, p.u.tiles, p.u.tiles_n, p.u.whole, p.u.splits, p.u.split_stages};
+    for (int i = 0; i < 7; ++i) out[i] = v[i];
 }
+static int steps(int64_t K) { return (int)((K < fpdt_tw::SK ? fpdt_tw::SK : K) / fpdt_tw::SK); }
+extern "C" void launched(int64_t M, int64_t N, int64_t K, int* out) { put(fpdt_tw::plan_launch(M, N, steps(K)), out); }
+extern "C" void first_answer(int64_t M, int64_t N, int64_t K, int* out) { put(fpdt_tw::plan_product(M, N, steps(K)), out); }
 """
 
 
@@ -34,8 +36,8 @@ def _lib():
     L.key_groups.argtypes = [i64, i64, ci, ci]
     L.dkdv_splits.argtypes = [i64, i64, ci, ci, ci, ci]
     L.f32_one_launch.argtypes = [i64, ci, ci]
-    L.product.argtypes = [i64, i64, i64, ctypes.POINTER(ci)]
-    L.product.restype = None
+    for f in (L.launched, L.first_answer):
+        f.argtypes, f.restype = [i64, i64, i64, ctypes.POINTER(ci)], None
     return L
 
 
@@ -55,9 +57,26 @@ def dkdv_splits(rows, Hq, Hkv, D, one_launch):
     return _lib().dkdv_splits(rows, rows, Hq, Hkv, D, int(one_launch))
 
 
-def product(M, N, K):
+def _plan(f, M, N, K):
+    v = (ctypes.c_int * 7)()
+    f(M, N, K, v)
+    return dict(zip(("wmt", "wnt", "tiles", "tiles_n", "whole", "splits", "split_stages"), v))
+
+
+def launched(M, N, K):
+    """The layout that a product runs (plan_launch)"""
+    return _plan(_lib().launched, M, N, K)
+
+
+def first_answer(M, N, K):
+    """plan_product's answer, which plan_launch starts from"""
+    return _plan(_lib().first_answer, M, N, K)
+
+
+def kind(p):
     """(64-row units of a tile, 64-column units, "whole" / "divided" / "mixed")"""
-    v = (ctypes.c_int * 6)()
-    _lib().product(M, N, K, v)
-    wmt, wnt, tiles, whole, splits, _ = v
-    return wmt, wnt, "whole" if splits == 1 else "divided" if whole == 0 else "mixed"
+    return p["wmt"], p["wnt"], "whole" if p["splits"] == 1 else "divided" if p["whole"] == 0 else "mixed"
+
+
+def product(M, N, K):
+    return kind(launched(M, N, K))

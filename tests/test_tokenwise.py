@@ -561,15 +561,15 @@ print("replayed")
 
 
 # ------------------------------------------------------------------ every layout of a product
-# (M, N, K) and what the planning rule makes of them: the output tile in units of 64, and whether its tiles
-# run whole, divided along k, or some each.  Ragged in all three; widths that are read in place, but for the
-# last two.  (The rule does not choose 2 x 2 tiles whole, nor 1 x 4 ones of both kinds for more than 64 rows.)
+# (M, N, K) and what is launched for them: the output tile in units of 64, and whether its tiles run whole,
+# divided along k, or some each.  Ragged in all three; widths that are read in place, but for the last three.
+# (1 x 4 tiles of both kinds are not chosen for more than 64 rows.)
 PRODUCTS = [((72, 72, 72), (1, 4, "whole")), ((72, 72, 648), (1, 4, "divided")), ((40, 67248, 792), (1, 4, "mixed")),
             ((4304, 72, 1288), (2, 2, "divided")), ((67872, 72, 752), (2, 2, "mixed")),
             ((17104, 72, 72), (2, 4, "whole")), ((1488, 72, 5496), (2, 4, "divided")), ((5448, 1384, 4632), (2, 4, "mixed")),
             ((33368, 72, 72), (3, 4, "whole")), ((136, 7392, 1304), (3, 4, "divided")), ((3544, 6824, 2328), (3, 4, "mixed")),
             ((49552, 72, 72), (4, 4, "whole")), ((6248, 264, 2448), (4, 4, "divided")), ((6536, 2312, 712), (4, 4, "mixed")),
-            ((6541, 2317, 711), (4, 4, "mixed")), ((1501, 251, 5003), (1, 4, "divided"))]
+            ((6541, 2317, 711), (4, 4, "mixed")), ((1501, 251, 5003), (1, 4, "divided")), ((1630, 2695, 33), (2, 2, "whole"))]
 
 
 def test_products_cover_the_rule():
