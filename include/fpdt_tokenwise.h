@@ -6,10 +6,11 @@
  * time.
  *
  *   fpdt_tw_loss_fwd_bwd   softmax cross-entropy over the vocabulary with its last linear
- *                          projection, forward and backward fused per chunk: the fp32 logits
- *                          [rows, vocab] never exist for more than one chunk (Sec. 5.4 names
- *                          the loss over a large vocabulary as the place where memory peaks
- *                          and suggests vocab / hidden * 2 chunks).
+ *                          projection, forward and backward fused: the fp32 logits
+ *                          [rows, vocab] exist for as many rows at a time as the workspace has
+ *                          room for, one chunk and a half (Sec. 5.4 names the loss over a large
+ *                          vocabulary as the place where memory peaks and suggests
+ *                          vocab / hidden * 2 chunks).
  *   fpdt_tw_linear_*       the per-chunk QKV projection in front of the attention.
  *   fpdt_tw_ffn_*          the feed-forward block, chunked with twice the attention's chunk
  *                          count, forward and (recomputing) backward.
@@ -23,14 +24,14 @@
  * buffers, `stream` is a hipStream_t passed as void*, calls only enqueue, every function returns
  * an fpdt status code (0 = OK, 1 = invalid argument, 2 = unsupported, 3 = workspace, 4 = HIP
  * failure; text from fpdt_tw_last_error).  Besides the caller's workspace the library keeps one
- * device scratch pool per GPU for the running call: logit gradients of up to 2 hidden rows, fp32
- * sums of output tiles that several workgroups share, copies of operands whose rows are not
- * 16-byte aligned.  It grows on demand with hipMalloc -- so the first call of a given size must not
- * run under stream capture -- by doubling from 256 MiB, and is kept until the process ends, as are
- * the buffers it has outgrown (work in flight may read them): up to four times what the largest
- * call needs.  Calls
- * that overlap in time on one GPU (different streams or threads) would share that pool: keep
- * the library's calls on one stream.
+ * device scratch pool per GPU for the running call: logit gradients of up to 2 hidden rows (of a
+ * chunk, where that is more and the vocabulary is not a multiple of 8), fp32 sums of output tiles
+ * that several workgroups share, copies of operands whose rows are not 16-byte aligned.  It grows on
+ * demand with hipMalloc -- so the first call of a given size must not run under stream capture -- by
+ * doubling from 256 MiB, and is kept until the process ends, as are the buffers it has outgrown (work
+ * in flight may read them): up to four times what the largest call needs.  Calls that overlap in time
+ * on one GPU (different streams or threads) would share that pool: keep the library's calls on one
+ * stream.
  */
 #ifndef FPDT_TOKENWISE_H
 #define FPDT_TOKENWISE_H
@@ -43,7 +44,8 @@ extern "C" {
 #endif
 
 /* Bytes of device workspace fpdt_tw_loss_fwd_bwd needs: one chunk of fp32 logits and one chunk
- * of bf16 logit gradients, chunk = ceil(rows / n_chunks) rows.  0 if the arguments are invalid. */
+ * of bf16 logit gradients, chunk = ceil(rows / n_chunks) rows; where the gradients are in the
+ * library's scratch, or not asked for, all of it holds logits.  0 if the arguments are invalid. */
 size_t fpdt_tw_loss_workspace_bytes(int64_t rows, int hidden, int vocab, int n_chunks);
 
 /*
@@ -59,10 +61,11 @@ size_t fpdt_tw_loss_workspace_bytes(int64_t rows, int hidden, int vocab, int n_c
  *   loss, lse [rows] fp32                                                             out
  *   dH [rows, hidden] bf16 or NULL, dW [vocab, hidden] fp32 or NULL                   out / in-out
  *   workspace: device memory, 256-byte aligned, >= fpdt_tw_loss_workspace_bytes(...)
- * dW is summed in fp32 over as many chunks at a time as make 2 hidden rows (one chunk at least); the
- * logit gradients of these rows are gathered in the library's scratch, [rows, vocab rounded up to 8],
- * and the workspace's are then not used (they are where a chunk has more than hidden rows and vocab is
- * a multiple of 8).  Status 4 if there is no memory for them.
+ * dW is summed in fp32 over groups of up to 2 hidden rows, of about the same size and in general not
+ * whole chunks; the logit gradients of a group are gathered in the library's scratch, [rows, vocab rounded
+ * up to 8], and the workspace holds logits only, of one and a half chunks.  Where a chunk has more than
+ * hidden rows, dW is summed chunk by chunk, and if vocab is a multiple of 8 both the chunk's logits and its
+ * gradients are in the workspace.  Status 4 if there is no memory for the scratch.
  * A target outside [0, vocab) is not detected (its row's loss is lse_r and its gradient the
  * plain softmax).
  */

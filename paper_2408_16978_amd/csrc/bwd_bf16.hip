@@ -806,8 +806,8 @@ __global__ __launch_bounds__(NTHREAD) void bwd_dq_kernel(BwdKernelArgs p)
 // no exp).  Per chunk pair the tiles are n_q * n_k * Hq * 2 bytes, read once from HBM, which is
 // what bounds this kernel; its MFMA work is a third of bwd_dq_kernel's.
 //
-// Workgroup = 8 waves x 32 query rows of one head, as in bwd_dq_kernel.  Per 64-key tile the
-// K-NAT block is staged once for all waves (same layout, swizzle and transposing loads as above)
+// Workgroup = 8 waves x 32 query rows of one head, as in bwd_dq_kernel (4 or 2 waves where a launch
+// has few row tiles, sweep_waves).  Per 64-key tile the K-NAT block is staged once for all waves (same layout, swizzle and transposing loads as above)
 // and every wave stages the four dS fragments (2 key blocks x 2 query halves) of ITS query block.
 // A stored fragment holds, per key, eight queries; the B operand of dQ^T += K^T dS^T wants, per
 // query, eight keys: the same transposing LDS load delivers that (4 keys x 16 queries per 16-lane

@@ -706,9 +706,9 @@ int take_operand(Pool& pool, const void* X, int64_t R, int64_t C, int64_t ld, bo
         res->ld = ld;
     } else {
         const int64_t C2 = (C + 7) / 8 * 8;
-        // whole cache lines from row to row: a stage's pieces of a row are half a line (form N), of four
-        // rows' columns a whole one (form T), and with 8208 bytes in place of 8320 straddled two
-        // (16384 x 4097 x 4096 in 8 chunks: 864 -> 743 us)
+        // whole cache lines from row to row: a stage's part of a row is a line (form N: 64 k, form T: 64 columns), and with
+        // 8208 bytes from row to row in place of 8320 it lay in two (Y of 16384 x 4097 x 4096: 493 -> 451 us, in 8 chunks
+        // 626 -> 542)
         res->ld = C2 <= 64 ? C2 : (C2 + 63) / 64 * 64;
         res->p = nullptr;
         if (cache)
