@@ -33,6 +33,7 @@ struct FwdKernelArgs {
     const uint16_t* K;  // RAW: the tensors themselves, [n_keys, Hkv, D]
     const uint16_t* V;
     int64_t kv_pitch;   // elements between their rows
+    int ahead_rows;     // of K and V that each of the first workgroups of a head reads ahead (0: none)
     int64_t kv_head_stride_blocks;
     uint16_t* O;
     float* LSE;
@@ -180,15 +181,12 @@ __global__ __launch_bounds__(NWAVE * 64, 2) void fwd_sweep_kernel(FwdKernelArgs 
         // The packing launch also brought K and V into the caches, all of them at once.  With one tile in flight a workgroup
         // would fetch them tile after tile, each at the latency of HBM (inputs that no cache holds: 8 / 2 heads, D = 128, 2K
         // 31.4 us, 8 / 8, D = 64, 4K 46.0; packed 28.5, 35.0; this 27.1, 32.6).  So the workgroups of a head that start
-        // first read a word of every line of its K and V between them, in the shadow of the first tile.  (Up to 768 keys
-        // there are too few tiles for it; two key groups have two in flight and 16 heads and more: it gained nothing and cost up to 8%.)
-        const int starting = 256 / p.Hq > 0 ? 256 / p.Hq : 1, readers = n_qt < starting ? n_qt : starting, turn = (int)(blockIdx.x / p.Hq);
-        if (turn < readers && p.n_keys > 768) {
-            constexpr int LINES = D == 64 ? 1 : 2;  // of 128 bytes, of a row of the head: those of its first and its last word
-            const int rows = (p.n_keys + readers - 1) / readers, row0 = turn * rows;
-            const int words = (p.n_keys - row0 < rows ? p.n_keys - row0 : rows) * LINES;
+        // first read a word of every line of its K and V between them, in the shadow of the first tile.
+        constexpr int LINES = D == 64 ? 1 : 2;  // of 128 bytes, of a row of the head: those of its first and its last word
+        const int row0 = (n_qt - 1 - qt) * p.ahead_rows, words = (p.n_keys - row0 < p.ahead_rows ? p.n_keys - row0 : p.ahead_rows) * LINES;
+        if (words > 0) {
             unsigned seen = 0;
-#pragma unroll 2
+#pragma unroll 1
             for (int i = tid; i < words; i += NWAVE * 64) {
                 const size_t at = (size_t)(row0 + i / LINES) * p.kv_pitch + (size_t)kvh * D + (i % LINES ? D - 2 : 0);
                 seen |= *reinterpret_cast<const unsigned*>(p.K + at) | *reinterpret_cast<const unsigned*>(p.V + at);
@@ -445,6 +443,10 @@ void launch_fwd_sweep(const FwdArgs& a, hipStream_t st)
     k.g = a.Hq / a.Hkv;
     k.flags = a.flags;
     k.c = a.scale * LOG2E;
+    // 256 workgroups start at once.  (Up to 768 keys there are too few tiles for it; two key groups have two tiles in flight and 16
+    // heads and more: reading ahead gained nothing there and cost up to 8%.)
+    const int tiles = a.n_q / 64, first = 256 / a.Hq > 0 ? 256 / a.Hq : 1, readers = tiles < first ? tiles : first;
+    k.ahead_rows = a.K && a.key_groups == 4 && a.n_keys > 768 ? (a.n_keys + readers - 1) / readers : 0;
     const int kg = a.key_groups, waves = kg > 1 || sweep_waves(a.n_q, a.Hq) == 8 ? 8 : 4;
 #define FWD_LAUNCH(D_)                                                                              \
     do {                                                                                            \

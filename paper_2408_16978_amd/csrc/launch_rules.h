@@ -60,7 +60,8 @@ static inline bool sweep_reads_tensors(int64_t S, int Hq, int Hkv, int D, int ke
     const int64_t workgroups = S / 256 * key_groups * Hq;
     if (D == 64) return S <= 8192 && workgroups <= 512;
     if (Hq == Hkv && Hkv >= 8) return S <= (D == 80 ? 4096 : 6144);
-    return key_groups == 4 ? S <= (D == 80 ? 3584 : 3072) && workgroups <= 512 : S <= 2048;
+    if (key_groups == 2) return S <= 2048;
+    return workgroups <= 512 && S <= (D == 128 ? 3072 : workgroups <= 256 ? 4096 : 3584);
 }
 
 // Does an fp32 call over the whole sequence fit into one launch?  (Workgroups of 512 lanes, one per 16 rows and
