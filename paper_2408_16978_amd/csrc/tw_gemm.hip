@@ -238,8 +238,8 @@ __device__ __forceinline__ void for_each_index(std::integer_sequence<int, I...>,
 // (64 WMT) x (64 WNT) tile over the stages of its split; wave (w / 2, w % 2) owns 2 WMT x 2 WNT accumulator
 // tiles of 16 x 16.
 //
-// What bounds it: the matrix cores are busy in 0.8 of the cycles (8192^3; nine tenths of the main loop's) at a clock that
-// the power budget holds at 1.7 GHz, where the same loop without its copies runs at 1.9 and on registers alone at 2.0.
+// What bounds it: the matrix cores are busy in 0.82, 0.79 and 0.73 of the cycles (8192^3, X W^T, dY W, dY^T X +=; nine tenths of
+// the main loop's) at a clock that the power budget holds at 1.6-1.7 GHz, where the same loop without its copies runs at 1.9 and on registers alone at 2.0.
 // The 128 x 128 elements of a wave at WMT = WNT = 4 need 16 KiB of fragments per 32 k (eight waves of 128 x 64: 24 KiB
 // each pair).  The 256 accumulator registers leave room for one wave per SIMD, so nothing but this wave's own
 // instruction order hides a latency.  A stage is two k-steps; the fragments of a k-step are read into a set of registers
