@@ -52,7 +52,8 @@ static inline int sweep_waves(int64_t n_q, int Hq)
 // the packed kernel fit one, of this one, with 134 registers, one.
 // Measured over 15 head counts and 20 lengths, with the inputs in the caches and without (us, packed -> not, the two in turn;
 // query / KV heads): D = 64, 8 / 2, 2K 18.8 -> 16.4, 4K 34.5 -> 32.9, 5K (640 workgroups) 44 -> 51, 4 / 4, 8K 59 -> 56, 16 / 4,
-// 5K (two key groups, 640) 76 -> 87; D = 80, 8 / 2, 2K 23.2 -> 22.0, 4K 42.6 -> 43.4; 16 / 4, 3K (two key groups) 46.1 -> 46.3;
+// 5K (two key groups, 640) 76 -> 87; D = 80, 8 / 2, 2K 23.2 -> 22.0, 4K (512) 42.6 -> 43.4, 4 / 1, 4K
+// (256) 35.0 -> 33.0; 16 / 4, 3K (two key groups) 46.1 -> 46.3;
 // D = 128, 8 / 2, 1K 19.6 -> 17.8, 2K 28.4 -> 27.2, 4K 55.5 -> 57.2, 8 / 8, 4K 60.2 -> 58.1, 16 / 4, 4K (two key groups) 82.8 -> 83.6.
 static inline bool sweep_reads_tensors(int64_t S, int Hq, int Hkv, int D, int key_groups)
 {
