@@ -12,21 +12,22 @@ namespace fpdt {
 // waves that share the keys): the cheapest of 1, 2, 4 in units of a 64-key tile of eight row blocks.  A
 // launch on the diagonal lasts as long as its longest row tile or as the average load of the 256 compute
 // units; KG > 1 divides the first, and costs a little more per tile (copies and barriers per MFMA).
-// Measured (us for KG = 1, 2, 4; forward | dQ): 2K tokens, 8 heads, D = 128: 57, 38, 29 | 77, 50, 35;
-// 8K: 216, 169, 207 | 303, 230, 270; 16K: 535, 592, 684 | 753, 812, 903; 32K, 2 heads, D = 64: 517, 388,
-// 354 | 670, 461, 477.
+// Measured (us for KG = 1, 2, 4; forward | dQ): 2K tokens, 8 heads, D = 128: 40, 30, 21 | 77, 50, 35;
+// 8K: 184, 138, 154 | 303, 230, 270; 16K: 463, 487, 551 | 753, 812, 903; forward, 8 heads, D = 64: 4K 45, 35, 30;
+// 5K 80, 44, 48; 16K 288, 299, 307; 2 heads, D = 128: 16K 257, 191, 143; 32K 697, 491, 526.  (The constants choose
+// the fastest count at all of 32 sizes so measured.)
 static inline int sweep_key_groups(int64_t n_q, int64_t n_keys, int Hq, bool causal)
 {
     const double tiles = (double)n_keys / 64.0, cus = 256.0;
     int best = 1;
     double best_cost = 0.0;
     for (int kg = 1; kg <= 4; kg *= 2) {
-        const double work = kg == 1 ? 1.0 : kg == 2 ? 1.08 : 1.15, wgs = (double)n_q / 256.0 * kg * Hq;
-        const double longest = tiles / kg * work + 2.0;
+        const double work = kg == 1 ? 1.0 : kg == 2 ? 1.03 : 1.22, wgs = (double)n_q / 256.0 * kg * Hq;
+        const double longest = tiles / kg * work + 1.5;
         const double load = (double)(int64_t)((wgs + cus - 1.0) / cus) * longest;       // below the diagonal
-        const double mean = wgs / cus * (tiles / kg / 2 * work + 2.0) + longest / 4.0;  // on it
+        const double mean = wgs / cus * (tiles / kg / 2 * work + 1.5) + longest / 4.0;  // on it
         const double cost = causal ? (mean > longest ? mean : longest) : load;
-        if (kg == 1 || cost < 0.97 * best_cost) { best = kg; best_cost = cost; }
+        if (kg == 1 || cost < 0.93 * best_cost) { best = kg; best_cost = cost; }
     }
     return best;
 }
@@ -35,9 +36,9 @@ static inline int sweep_key_groups(int64_t n_q, int64_t n_keys, int Hq, bool cau
 // two where a chunk pair has so few row tiles that half of the 256 compute units, or more, would have none.  A wave computes
 // the same whatever the count (the bits do not depend on it); with four or two on a compute unit no second wave of a
 // SIMD works under its MFMAs, but twice or four times the compute units work.  The forward stops at four: two would each move half of every key tile.
-// Measured, us per launch with eight waves -> with fewer (pairs of equal chunks): forward 8 heads, D = 128, chunks of 4K 101.7 ->
-// 92.1 (4), of 2K 51.3 -> 43.4 (4; 2: 64.9); 4 heads, D = 80, 8K 163.9 -> 135.1 (4); D = 64, 4K 66.1 -> 48.8 (4; 2: 59.1); dQ of
-// the same 68.9 -> 52.8 (4), 36.0 -> 31.4 (2), 114.1 -> 86.8 (4), 50.8 -> 31.0 (2).
+// Measured, us per launch with eight waves -> with fewer (pairs of equal chunks): forward 8 heads, D = 128, chunks of 4K 99.1 ->
+// 77.8 (4); dQ of pairs of 4K, 2K with 8 heads, D = 128, of 8K with 4 heads, D = 80, and of 4K, D = 64: 68.9 -> 52.8 (4), 36.0 -> 31.4 (2),
+// 114.1 -> 86.8 (4), 50.8 -> 31.0 (2).
 static inline int sweep_waves(int64_t n_q, int Hq)
 {
     const int64_t wgs = n_q / 256 * Hq;
@@ -47,19 +48,18 @@ static inline int sweep_waves(int64_t n_q, int Hq)
 // Does the one-launch forward read K and V from their tensors, without the launch that packs them?  With several key groups
 // (short sequences) that launch costs more than the transposing reads that take its place, up to a length: longer ones gain
 // from the packed copies (fewer LDS reads per tile), at D = 80, whose rows of ten pieces are not spread over the banks,
-// and D = 128 sooner than at D = 64, and with two key groups, whose workgroups hide less of them, soonest; where every query head
-// has K and V of its own there is most to pack.  More than 512 workgroups have to share the compute units: at D = 64 two of
-// the packed kernel fit one, of this one, with 134 registers, one.
-// Measured over 15 head counts and 20 lengths, with the inputs in the caches and without (us, packed -> not, the two in turn;
-// query / KV heads): D = 64, 8 / 2, 2K 18.8 -> 16.4, 4K 34.5 -> 32.9, 5K (640 workgroups) 44 -> 51, 4 / 4, 8K 59 -> 56, 16 / 4,
-// 5K (two key groups, 640) 76 -> 87; D = 80, 8 / 2, 2K 23.2 -> 22.0, 4K (512) 42.6 -> 43.4, 4 / 1, 4K
-// (256) 35.0 -> 33.0; 16 / 4, 3K (two key groups) 46.1 -> 46.3;
-// D = 128, 8 / 2, 1K 19.6 -> 17.8, 2K 28.4 -> 27.2, 4K 55.5 -> 57.2, 8 / 8, 4K 60.2 -> 58.1, 16 / 4, 4K (two key groups) 82.8 -> 83.6.
+// and D = 128 sooner than at D = 64, and with two key groups, whose workgroups hide less of them, soonest (at D = 64 the two differ by
+// 3% and less there, either way); where every query head has K and V of its own there is most to pack.
+// Measured with the inputs in no cache and in the caches (us, packed -> not; query / KV heads): four key groups, D = 64, 8 / 2, 2K 16.8, 16.7 ->
+// 14.8, 14.3, 4K 32.2, 31.5 -> 30.0, 28.7, 4 / 4, 8K 52.7, 57.6 -> 49.8, 47.9; D = 80, 8 / 2, 2K 19.1, 18.9 -> 17.5, 16.6, 4K 39.8, 37.6 -> 39.3,
+// 35.8, 4 / 4, 8K 65.0, 67.7 -> 68.2, 64.9; D = 128, 8 / 2, 1K 16.6, 16.3 -> 14.2, 13.5, 2K 22.8, 22.1 -> 20.8, 19.4, 4K 47.5, 46.8 -> 46.9, 43.4, 8 / 8,
+// 4K 51.5, 52.6 -> 48.2, 44.4; two key groups, D = 64, 8 / 2, 6K 55.0, 54.7 -> 53.5, 52.5, 8K 83.7, 82.9 -> 84.8, 81.7; D = 80, 8 / 2, 8K 101.7, 102.0 -> 109.0,
+// 106.1; D = 128, 8 / 2, 8K 137.7, 133.5 -> 140.5, 133.5.
 static inline bool sweep_reads_tensors(int64_t S, int Hq, int Hkv, int D, int key_groups)
 {
     if (key_groups == 1) return false;
     const int64_t workgroups = S / 256 * key_groups * Hq;
-    if (D == 64) return S <= 8192 && workgroups <= 512;
+    if (D == 64) return S <= 8192 && workgroups <= 512 && (key_groups == 4 || S >= 6144);
     if (Hq == Hkv && Hkv >= 8) return S <= (D == 80 ? 4096 : 6144);
     if (key_groups == 2) return S <= 2048;
     return workgroups <= 512 && S <= (D == 128 ? 3072 : workgroups <= 256 ? 4096 : 3584);
