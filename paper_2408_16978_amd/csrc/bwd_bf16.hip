@@ -573,6 +573,11 @@ __global__ __launch_bounds__(256) void dkdv_sum_kernel(BwdKernelArgs p, unsigned
 // stationary in registers).  Every step stages a 64-key tile (K-NAT, V-NAT, K-TR) in a 3-slot
 // LDS ring, loaded two tiles ahead.
 //
+// What bounds it is how well the vector work of a block hides under MFMAs, and the instructions of a wave, of which two on a SIMD issue
+// one in about five clocks each: exponentials stand between the MFMAs of dP, the second half of dS between those of dQ, positions are
+// 32-bit, a copy takes five instructions.  us, vector work behind the MFMAs it follows -> this (8 / 2 heads, D = 128; 64 last): 2K
+// 32.2 -> 30.1, 8K 195 -> 189, 64K 10504 -> 10159 (1300 TFLOP/s executed); 64K 6020 -> 5761.
+//
 // KG = 2, 4 (as in the forward): 128 or 64 query rows per workgroup, the waves of one row block take every
 // KG-th 32-key block and add their results through LDS at the end (sweep_key_groups).
 template <int D, int KG>
@@ -606,16 +611,11 @@ __global__ __launch_bounds__(NTHREAD) void bwd_dq_kernel(BwdKernelArgs p)
     const int kvh = head / p.g;
     const int q0 = qt * BQ, qw0 = q0 + qb * 32;
 
-    const int64_t last_q_pos = p.q_pos0 + q0 + BQ - 1;
-    int64_t need = last_q_pos - p.k_pos0 + 1;
-    if (need > p.n_k) need = p.n_k;
+    const int ahead_pos = (int)(p.q_pos0 - p.k_pos0) + q0;  // position of the workgroup's first row behind the launch's first key (below 2^30)
+    int need = ahead_pos + BQ < p.n_k ? ahead_pos + BQ : p.n_k;
     if (need < 0) need = 0;
-    const int n_tiles = (int)((need + BK - 1) / BK);
+    const int n_tiles = (need + BK - 1) / BK;
 
-    const u32x4* knb = p.Knat + (size_t)kvh * p.kv_head_stride_blocks * (DT * 64);
-    const u32x4* vnb = p.Vnat + (size_t)kvh * p.kv_head_stride_blocks * (DT * 64);
-
-    const int cp_lane0 = 32 * half + (col ^ (4 * half));  // even fragment; odd: ^ 8
     const int natpos[2] = {32 * half + (col ^ (4 * half)), 32 * half + (col ^ (4 * half) ^ 8)};
     int trb[2];  // byte offsets of this lane's two transposing loads within a 32-key block
     {
@@ -628,18 +628,27 @@ __global__ __launch_bounds__(NTHREAD) void bwd_dq_kernel(BwdKernelArgs p)
     typedef short short4v __attribute__((ext_vector_type(4)));
     typedef short short8v __attribute__((ext_vector_type(8)));
     typedef __attribute__((address_space(3))) short4v* lds_short4_ptr;
-    auto issue = [&](int it, u32x4* slot) {
+    // This wave's copies of a tile: fragments w, w + 8, .. of K and of V.  (A wave without one in the last round copies another's once more.)
+    constexpr int COPIES = (NATF + NWAVE - 1) / NWAVE;
+    static_assert(COPIES * NWAVE <= 2 * NATF, "every wave has something to copy");
+    unsigned cp_at[COPIES], k_off[COPIES];
 #pragma unroll
-        for (int f0 = 0; f0 < NFRAG; f0 += NWAVE) {
-            const int f = f0 + wu;
-            if (f0 + NWAVE <= NFRAG || f < NFRAG) {
-                const u32x4* src = f < NATF ? knb + (size_t)it * NAT_U4 + f * 64 : vnb + (size_t)it * NAT_U4 + (f - NATF) * 64;
-                // a K fragment's 16-byte pieces land swizzled by the parity of its index within
-                // the key block (DT even: that is the wave's parity)
-                const int par = DT % 2 == 0 ? (wu & 1) : ((f % DT) & 1);
-                frag_to_lds(src, slot + f * 64, f < NATF ? (cp_lane0 ^ (8 * par)) : lane);
-            }
-        }
+    for (int i = 0; i < COPIES; ++i) {
+        const int f = NWAVE * i + wu < NATF ? NWAVE * i + wu : NWAVE * i + wu - NATF;
+        cp_at[i] = 1024u * (unsigned)f;
+        // a K fragment's 16-byte pieces land swizzled by the parity of its index within the key block (DT even: that is the wave's parity)
+        k_off[i] = 16u * (unsigned)((32 * half + (col ^ (4 * half))) ^ (8 * ((DT % 2 == 0 ? wu : f % DT) & 1)));
+    }
+    uint64_t k_src = uniform((uint64_t)(uintptr_t)(p.Knat + (size_t)kvh * p.kv_head_stride_blocks * (DT * 64)));
+    uint64_t v_src = uniform((uint64_t)(uintptr_t)(p.Vnat + (size_t)kvh * p.kv_head_stride_blocks * (DT * 64)));
+    auto issue = [&](const u32x4* slot) {  // the tile that comes next
+        const unsigned lds = lds_address(slot);
+#pragma unroll
+        for (int i = 0; i < COPIES; ++i) copy_1k(k_src + cp_at[i], lds, cp_at[i], k_off[i]);
+#pragma unroll
+        for (int i = 0; i < COPIES; ++i) copy_1k(v_src + cp_at[i], lds + 16u * NAT_U4, cp_at[i], 16u * (unsigned)lane);
+        k_src += NAT_U4 * 16;
+        v_src += NAT_U4 * 16;
     };
 
     bf16x8 qf[DT], of[DT];
@@ -681,27 +690,25 @@ __global__ __launch_bounds__(NTHREAD) void bwd_dq_kernel(BwdKernelArgs p)
             for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
     }
 
-    if (n_tiles > 0) issue(0, ring0);
-    if (PF > 1 && n_tiles > 1) issue(1, ring1);
+    if (n_tiles > 0) issue(ring0);
+    if (PF > 1 && n_tiles > 1) issue(ring1);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
-    const int64_t qpos_first = p.q_pos0 + qw0, qpos_last = qpos_first + 31, qpos = qpos_first + col;
+    const int reach = ahead_pos + 32 * qb;         // of the wave's first row behind the launch's first key
+    const int row_key = reach + col - 4 * half;    // the last key this lane's query sees, less the lane's offset
     const floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    // One tile: compute on slot `kn`, prefetch tile it+PF into slot `pf_slot`.
+    // One tile: compute on slot `kn`, prefetch tile it+PF into slot `pf_slot`.  A block is straight code in three steps, whose vector work stands
+    // between MFMAs that do not depend on it: S, with the reads of V | dP with exp(S) and the reads of K^T | dQ with the second half of dS.
     auto tile = [&](int it, const u32x4* kn, u32x4* pf_slot) {
-        if (it + PF < n_tiles) issue(it + PF, pf_slot);
+        if (it + PF < n_tiles) issue(pf_slot);
         const u32x4* vn = kn + NAT_U4;
         const unsigned kn_addr = lds_address(kn);
 #pragma unroll
         for (int kb_i = 0; kb_i < KB; ++kb_i) {
             const int kb = kg * KB + kb_i;
-            const int64_t key0 = p.k_pos0 + (int64_t)it * BK + 32 * kb;
-            if (key0 <= qpos_last) {  // wave-uniform
-                // K fragments first; the V fragments are requested one per score MFMA (each has
-                // the rest of the chain in front of its first use), the K-TR fragments after the
-                // dP chain: they arrive under the exp2 / multiply arithmetic.  No more than two
-                // fragment sets are live at a time.
+            const int key0 = it * BK + 32 * kb;
+            if (key0 <= reach + 31) {  // wave-uniform
                 bf16x8 kfr[DT], vfr[DT], tfr[2][DB];
 #pragma unroll
                 for (int t = 0; t < DT; ++t) kfr[t] = as_bf16x8(kn[(kb * DT + t) * 64 + natpos[t & 1]]);
@@ -711,45 +718,50 @@ __global__ __launch_bounds__(NTHREAD) void bwd_dq_kernel(BwdKernelArgs p)
                     s = mfma32(kfr[t], qf[t], t == 0 ? zero : s);
                     vfr[t] = as_bf16x8(vn[(kb * DT + t) * 64 + lane]);
                 }
-#pragma unroll
-                for (int t = 0; t < DT; ++t) dp = mfma32(vfr[t], of[t], t == 0 ? neg_delta : dp);
                 __builtin_amdgcn_sched_group_barrier(0x100, DT, 0);
 #pragma unroll
                 for (int t = 0; t < DT; ++t) {
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                     __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
                 }
-                __builtin_amdgcn_sched_group_barrier(0x008, DT, 0);
+                asm volatile("" ::: "memory");  // (the reads of V stay in front of the branch)
+                if (key0 + 31 > reach) {  // wave-uniform: the block straddles the diagonal
+                    const int last = row_key - key0;
 #pragma unroll
-                for (int s2 = 0; s2 < 2; ++s2)
+                    for (int r = 0; r < 16; ++r)
+                        if (8 * (r >> 2) + (r & 3) > last) s[r] = -INFINITY;
+                }
+                for_each<DT>([&](auto step) {
+                    constexpr int t = decltype(step)::value;
+                    dp = mfma32(vfr[t], of[t], t == 0 ? neg_delta : dp);
 #pragma unroll
-                    for (int db = 0; db < DB; ++db) {
-                        const unsigned o = kn_addr + 16u * 64u * (unsigned)(kb * DT) + 2048u * (unsigned)db + 256u * (unsigned)s2;
+                    for (int i = reads_before(t, DT, 2 * DB); i < reads_before(t + 1, DT, 2 * DB); ++i) {
+                        const unsigned o = kn_addr + 1024u * (unsigned)(kb * DT) + 2048u * (unsigned)(i % DB) + 256u * (unsigned)(i / DB);
                         const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(uintptr_t)(o + (unsigned)trb[0]));
                         const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(uintptr_t)(o + (unsigned)trb[1]));
                         const short8v both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-                        tfr[s2][db] = __builtin_bit_cast(bf16x8, both);
+                        tfr[i / DB][i % DB] = __builtin_bit_cast(bf16x8, both);
                     }
-                __builtin_amdgcn_sched_group_barrier(0x100, 2 * DB, 0);
 #pragma unroll
-                for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], p.c, -lse2));
-                if (key0 + 31 > qpos_first) {  // wave-uniform: the block straddles the diagonal
+                    for (int r = 16 * t / DT; r < 16 * (t + 1) / DT; ++r) s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], p.c, -lse2));
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                bf16x8 df[2];
 #pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        if (key0 + 8 * (r >> 2) + 4 * half + (r & 3) > qpos) s[r] = 0.f;
-                }
+                for (int r = 0; r < 8; ++r) dp[r] = s[r] * dp[r];
+                df[0] = pack_half<0>(dp);
+                for_each<2 * DB>([&](auto step) {
+                    constexpr int i = decltype(step)::value;
+                    acc[i % DB] = mfma32(tfr[i / DB][i % DB], df[i / DB], acc[i % DB]);
 #pragma unroll
-                for (int r = 0; r < 16; ++r) dp[r] = s[r] * dp[r];
-                const bf16x8 df0 = pack_half<0>(dp), df1 = pack_half<1>(dp);
-#pragma unroll
-                for (int db = 0; db < DB; ++db) {
-                    acc[db] = mfma32(tfr[0][db], df0, acc[db]);
-                    acc[db] = mfma32(tfr[1][db], df1, acc[db]);
-                }
+                    for (int r = 8 + 8 * i / DB; i < DB && r < 8 + 8 * (i + 1) / DB; ++r) dp[r] = s[r] * dp[r];
+                    if (i == DB - 1) df[1] = pack_half<1>(dp);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
             }
         }
         // tile it+1 must have landed; the loads of tile it+PF issued above may stay in flight (PF = 2)
-        if (it + PF < n_tiles) wait_vmem_at_most<(PF - 1) * (NFRAG / NWAVE)>();
+        if (it + PF < n_tiles) wait_vmem_at_most<(PF - 1) * 2 * COPIES>();
         else wait_vmem_at_most<0>();
         barrier_no_fence();
     };

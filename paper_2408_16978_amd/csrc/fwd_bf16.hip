@@ -21,7 +21,6 @@
 // pairs of chunks): D = 128, 1K 17.2 -> 14.2, 2K 26.2 -> 20.8, 8K 146 -> 137, 64K 7445 -> 7210 (1220 TFLOP/s), 4K chunks 90.5 -> 77.8; D = 80, 2K 20.1 ->
 // 17.5, 64K (4 heads) 2774 -> 2639, 8K chunks (4 heads) 126 -> 105; D = 64, 8K 94 -> 84, 64K 4464 -> 4262, 4K chunks 53.8 -> 47.1.
 #include <type_traits>
-#include <utility>
 
 #include "fpdt_internal.h"
 #include "mfma_tiles.h"
@@ -52,29 +51,6 @@ struct FwdKernelArgs {
     int Hq, g, flags;
     float c;  // scale * log2(e)
 };
-
-template <int N, typename F, int... I>
-__device__ __forceinline__ void for_each_of(F&& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
-template <int N, typename F>
-__device__ __forceinline__ void for_each(F&& f) { for_each_of<N>(f, std::make_integer_sequence<int, N>{}); }
-
-// Of the `reads` LDS reads of a phase of `steps` MFMAs, how many stand before MFMA `step`: all of them in its first half, so that none
-// is waited for at its end.
-__host__ __device__ constexpr int reads_before(int step, int steps, int reads)
-{
-    const int half = (steps + 1) / 2;
-    return step >= half ? reads : reads * step / half;
-}
-
-// frag_to_lds_at with the destination in two parts
-__device__ __forceinline__ void copy_1k(uint64_t src_uniform, unsigned lds_slot, unsigned lds_at, unsigned lane_off)
-{
-    uint64_t addr;
-    asm volatile("s_add_u32 m0, %1, %4\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
-                 : "=&s"(addr)
-                 : "s"(lds_slot), "v"(lane_off), "s"(src_uniform), "s"(lds_at)
-                 : "memory", "scc");
-}
 
 // KG key groups: 256 / KG query rows per workgroup of eight waves; the waves of a row block take every KG-th 32-key block and merge
 // their (max, sum, output) through LDS at the end.

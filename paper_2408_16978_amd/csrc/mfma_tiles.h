@@ -3,6 +3,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+#include <utility>
+
 namespace fpdt {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -130,6 +133,16 @@ __device__ __forceinline__ void frag_to_lds_at(uint64_t src_uniform, unsigned ld
                  : "memory");
 }
 
+// frag_to_lds_at with the destination in two parts
+__device__ __forceinline__ void copy_1k(uint64_t src_uniform, unsigned lds_slot, unsigned lds_at, unsigned lane_off)
+{
+    uint64_t addr;
+    asm volatile("s_add_u32 m0, %1, %4\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
+                 : "=&s"(addr)
+                 : "s"(lds_slot), "v"(lane_off), "s"(src_uniform), "s"(lds_at)
+                 : "memory", "scc");
+}
+
 // 256 bytes (one dword per lane) global -> LDS the same way: lane l's dword, read from
 // src + lane4, lands at lds_addr + 4 l.  lane4 = 4 * lane.
 __device__ __forceinline__ void dwords_to_lds_at(uint64_t src_uniform, unsigned lds_addr_uniform, int lane4)
@@ -139,6 +152,20 @@ __device__ __forceinline__ void dwords_to_lds_at(uint64_t src_uniform, unsigned 
                  : "=&s"(addr)
                  : "s"(lds_addr_uniform), "v"(lane4), "s"(src_uniform)
                  : "memory");
+}
+
+// f(integral_constant<int, 0>), f(integral_constant<int, 1>), .. N times
+template <int N, typename F, int... I>
+__device__ __forceinline__ void for_each_of(F&& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, typename F>
+__device__ __forceinline__ void for_each(F&& f) { for_each_of<N>(f, std::make_integer_sequence<int, N>{}); }
+
+// Of the `reads` LDS reads of a phase of `steps` MFMAs, how many stand before MFMA `step`: all of them in its first half, so that none
+// is waited for at its end.
+__host__ __device__ constexpr int reads_before(int step, int steps, int reads)
+{
+    const int half = (steps + 1) / 2;
+    return step >= half ? reads : reads * step / half;
 }
 
 __device__ __forceinline__ float xor32(float v) { return __shfl_xor(v, 32, 64); }
