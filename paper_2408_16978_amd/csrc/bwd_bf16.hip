@@ -329,11 +329,20 @@ __global__ __launch_bounds__(256) void bwd_dkdv_kernel_w4(BwdKernelArgs p)
                 return __builtin_bit_cast(bf16x8, both);
             };
 #define FPDT_AFRAG(u_) afrag(u_)
+            // Nothing hides an LDS read that is waited for: the single wave of a SIMD stops.  At D = 64 and 80, whose pairs of MFMAs are the
+            // fewest per vector instruction, V is read two pairs ahead, the statistics one chunk (both were read where they are used,
+            // V one pair ahead: 32K tokens, 8 / 2 heads, D = 64 2319 -> 2102 us, 64K, 4 heads, D = 80 5433 -> 5180; at D = 128 V
+            // two pairs ahead takes 0.7% longer).  Not kept: the dK MFMAs behind the next step's S, with half of the exponentials
+            // between them (three slots): D = 64 another 2%, D = 80 the same, D = 128 1% longer.
+            constexpr int VAHEAD = D == 128 ? 1 : 2;
             bf16x8 fr[6], vb0[3], vb1[3];
 #pragma unroll
             for (int u = 0; u < 4; ++u) fr[u] = FPDT_AFRAG(u);
-            vb0[0] = as_bf16x8(vmine[(0 * DT + 0) * 64 + lane]);
-            vb1[0] = as_bf16x8(vmine[(1 * DT + 0) * 64 + lane]);
+#pragma unroll
+            for (int t = 0; t < VAHEAD; ++t) {
+                vb0[t] = as_bf16x8(vmine[(0 * DT + t) * 64 + lane]);
+                vb1[t] = as_bf16x8(vmine[(1 * DT + t) * 64 + lane]);
+            }
             floatx16 s0, s1, dp0, dp1;
             bf16x8 pf[NK][2], df[NK][2];
             // per-row statistics are read one chunk ahead of their use and BEFORE the fragment
@@ -352,7 +361,8 @@ __global__ __launch_bounds__(256) void bwd_dkdv_kernel_w4(BwdKernelArgs p)
 #pragma unroll
                 for (int b = 0; b < 4; ++b) nd[4 * a4 + b] = q4[b];
             }
-            float2 stat_nx = stat2(0, 0);
+            float2 lse[8];  // of rows 2 k, 2 k + 1 (two or three of them live at a time)
+            lse[0] = stat2(0, 0);
             // ---- A: S = Q K^T, two chains ----
 #pragma unroll
             for (int t = 0; t < DT; ++t) {
@@ -372,8 +382,9 @@ __global__ __launch_bounds__(256) void bwd_dkdv_kernel_w4(BwdKernelArgs p)
 #pragma unroll
             for (int t = 0; t < DT; ++t) {
                 const int u = DT + t;
-                float2 lse = stat_nx;
-                if (DT == 8 && t + 1 < DT) stat_nx = stat2(0, 2 * t + 2);
+#pragma unroll
+                for (int r = 16 * t / DT; r < 16 * (t + 1) / DT; ++r)  // what the rows behind this chunk's need
+                    if (r % 2 == 0 && r < 14) lse[r / 2 + 1] = stat2(0, r + 2);
                 if (t == 0) {
                     FPDT_MFMA_VC(dp0, fr[u % 6], vb0[t % 3], nd);
                     FPDT_MFMA_VC(dp1, fr[u % 6], vb1[t % 3], nd);
@@ -383,15 +394,14 @@ __global__ __launch_bounds__(256) void bwd_dkdv_kernel_w4(BwdKernelArgs p)
                     FPDT_MFMA_V(dp1, fr[u % 6], vb1[t % 3]);
                 }
                 fr[(u + 4) % 6] = FPDT_AFRAG(u + 4);
-                if (t + 1 < DT) {
-                    vb0[(t + 1) % 3] = as_bf16x8(vmine[(0 * DT + t + 1) * 64 + lane]);
-                    vb1[(t + 1) % 3] = as_bf16x8(vmine[(1 * DT + t + 1) * 64 + lane]);
+                if (t + VAHEAD < DT) {
+                    vb0[(t + VAHEAD) % 3] = as_bf16x8(vmine[(0 * DT + t + VAHEAD) * 64 + lane]);
+                    vb1[(t + VAHEAD) % 3] = as_bf16x8(vmine[(1 * DT + t + VAHEAD) * 64 + lane]);
                 }
                 FPDT_SCHED_FENCE();
 #pragma unroll
                 for (int r = 16 * t / DT; r < 16 * (t + 1) / DT; ++r) {
-                    if (DT != 8 && (r % 2 == 0 || r == 16 * t / DT)) lse = stat2(0, r & ~1);  // read at use
-                    const float lse2 = (r & 1) ? lse.y : lse.x;
+                    const float lse2 = (r & 1) ? lse[r / 2].y : lse[r / 2].x;
                     float e0 = __builtin_amdgcn_exp2f(fmaf(s0[r], p.c, -lse2));
                     float e1 = __builtin_amdgcn_exp2f(fmaf(s1[r], p.c, -lse2));
                     if (MASKED) {
