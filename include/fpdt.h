@@ -113,7 +113,9 @@ enum {
  * Both hold, where a launch would leave most of the GPU idle, what lets several workgroups share a
  * tile: the forward 2 or 4 carried states per row of a chunk (short sequences, pair by pair), the
  * backward partial dK and dV of the s - 1 (s = 2 .. 16) further workgroups of a key tile, rows * Hkv *
- * dpad(D) * 8 bytes each (rows = chunk; S in one launch, which then also holds the first's).  The
+ * dpad(D) * 8 bytes each (rows = chunk; S in one launch, which then also holds the first's); the fp32
+ * backward of short sequences, where two workgroups share a tile of 16 rows, their sums (256 * D bytes per
+ * tile and query or key/value head).  The
  * entry points take a workspace without them too: the forward then runs in smaller chunks (which
  * offloaded K/V cross the link more often for) with the same bits, or with one state per row where
  * these do not fit either, the backward with fewer workgroups per key tile and sums in another order.

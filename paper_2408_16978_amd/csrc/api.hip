@@ -205,7 +205,8 @@ struct BwdPlan {
     char* dq_out[2] = {nullptr, nullptr};
     void* ds_frag = nullptr;  // stored-dS backward: the dS tiles of one chunk pair
     int dkdv_splits = 1;      // workgroups that share a key tile's query walk
-    float* dkdv_part = nullptr;  // their partial dK, dV
+    float* dkdv_part = nullptr;  // their partial dK, dV (fp32: of both workgroups of a tile, dQ too)
+    unsigned* arrived = nullptr;  // fp32: per tile, how many of its two workgroups are done
     float* stat2 = nullptr;   // row statistics of the packed query rows, as the dK/dV kernel reads them
     size_t total = 0;
 };
@@ -217,6 +218,11 @@ BwdPlan plan_bwd(const Problem& p, void* ws, size_t have = SIZE_MAX, int most_sp
     Bump b(ws);
     if (!p.bf16()) {
         f.Delta = b.take<float>((size_t)p.Hq * p.S * 4);
+        f.dkdv_splits = most_splits > 1 && !p.f32_pairs() && f32_bwd_split(p.S, p.Hq, p.Hkv) ? 2 : 1;
+        if (f.dkdv_splits > 1) {
+            f.dkdv_part = b.take<float>(f32_bwd_part_bytes(p.S, p.Hq, p.Hkv, p.D));
+            f.arrived = b.take<unsigned>((size_t)f32_bwd_tiles(p.S, p.Hq, p.Hkv) * 4);
+        }
     } else {
         const int64_t rows = p.fused() ? p.S : p.C;  // rows covered by the packed buffers
         // NAT fragments only: the backward kernels read the row-contracted operands (Q^T, dO^T,
@@ -643,7 +649,7 @@ int bwd_f32(const Problem& p, const float* Q, const float* K, const float* V, co
         launch_zero(dK, (size_t)p.S * p.Hkv * p.D * 4, st);
         launch_zero(dV, (size_t)p.S * p.Hkv * p.D * 4, st);
     }
-    launch_delta(O, dO, p.S, p.Hq, p.D, 0, f.Delta, p.S, st);
+    launch_delta(O, dO, p.S, p.Hq, p.D, 0, f.Delta, p.S, st, f.arrived, f.arrived ? (int)f32_bwd_tiles(p.S, p.Hq, p.Hkv) : 0);
     const int64_t C = pairs ? p.C : p.S;
     auto pair = [&](int64_t i, int64_t j) {
         F32BwdArgs a;
@@ -656,6 +662,7 @@ int bwd_f32(const Problem& p, const float* Q, const float* K, const float* V, co
         a.dK = dK + (size_t)j * C * p.Hkv * p.D;
         a.dV = dV + (size_t)j * C * p.Hkv * p.D;
         a.accumulate = pairs;
+        a.part = f.dkdv_part; a.arrived = f.arrived;
         a.q_pos0 = i * C; a.k_pos0 = j * C; a.n_q = C; a.n_k = C;
         a.Hq = p.Hq; a.Hkv = p.Hkv; a.D = p.D; a.scale = p.scale;
         launch_f32_bwd(a, st);

@@ -1024,9 +1024,11 @@ __device__ __forceinline__ float dot16(const uint16_t* a, const uint16_t* b)
 template <typename T>
 __global__ __launch_bounds__(256) void delta_kernel(const T* __restrict__ O, const T* __restrict__ dO,
                                                     int64_t rows, int Hq, int D, float* __restrict__ Delta,
-                                                    int64_t stride)
+                                                    int64_t stride, unsigned* __restrict__ clear, int n_clear)
 {
     constexpr int V = 16 / (int)sizeof(T);
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < n_clear; i += 256) clear[i] = 0;
     // 16 lanes per (row, head): 4 pairs per wave, 16 pairs per workgroup
     const int tid = threadIdx.x;
     const int64_t pair = (int64_t)blockIdx.x * 16 + (tid >> 4);
@@ -1196,14 +1198,14 @@ void launch_stat_pack(const float* LSE, const float* Delta, int64_t stride, int6
 }
 
 void launch_delta(const void* O, const void* dO, int64_t rows, int Hq, int D, int is_bf16,
-                  float* Delta, int64_t delta_stride, hipStream_t st)
+                  float* Delta, int64_t delta_stride, hipStream_t st, unsigned* clear, int n_clear)
 {
     const int64_t pairs = rows * Hq;
     dim3 grid((unsigned)((pairs + 15) / 16));
     if (is_bf16)
-        delta_kernel<uint16_t><<<grid, 256, 0, st>>>((const uint16_t*)O, (const uint16_t*)dO, rows, Hq, D, Delta, delta_stride);
+        delta_kernel<uint16_t><<<grid, 256, 0, st>>>((const uint16_t*)O, (const uint16_t*)dO, rows, Hq, D, Delta, delta_stride, clear, n_clear);
     else
-        delta_kernel<float><<<grid, 256, 0, st>>>((const float*)O, (const float*)dO, rows, Hq, D, Delta, delta_stride);
+        delta_kernel<float><<<grid, 256, 0, st>>>((const float*)O, (const float*)dO, rows, Hq, D, Delta, delta_stride, clear, n_clear);
 }
 
 void launch_delta_head(const void* Q, const void* dO, const void* K, const void* V, const float* LSE,

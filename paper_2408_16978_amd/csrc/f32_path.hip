@@ -127,26 +127,33 @@ __device__ __forceinline__ void add_rows(floatx4 (&acc)[D / 16], const floatx4& 
     }
 }
 
-// Sum over the waves of a workgroup of acc^T [D x 16], and the result to out(d, column) for every element
-// (17 floats per channel: the final reads, channel fastest, then fall into different banks)
-template <int D, typename F>
-__device__ __forceinline__ void sum_waves(const floatx4 (&acc)[D / 16], float* lds, F out)
+// Sum over the waves of a workgroup of acc^T [D x 16] (and of more_acc^T), and the result to out(0, d, column) (out(1, d, column)) for
+// every element (17 floats per channel: the final reads, channel fastest, then fall into different banks)
+template <int D, bool MORE, typename F>
+__device__ __forceinline__ void sum_waves(const floatx4 (&acc)[D / 16], const floatx4 (&more_acc)[D / 16], float* lds, F out)
 {
-    constexpr int ALL = D * 17;
+    constexpr int ALL = D * 17, WAVES = NW * ALL;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, col = lane & 15;
     __syncthreads();
 #pragma unroll
     for (int db = 0; db < D / 16; ++db)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) lds[w * ALL + (16 * db + 4 * g + r) * 17 + col] = acc[db][r];
+        for (int r = 0; r < 4; ++r) {
+            lds[w * ALL + (16 * db + 4 * g + r) * 17 + col] = acc[db][r];
+            if (MORE) lds[WAVES + w * ALL + (16 * db + 4 * g + r) * 17 + col] = more_acc[db][r];
+        }
     __syncthreads();
     // channel fastest over the threads: rows of the result are written in whole lines
     for (int e = threadIdx.x; e < D * TR; e += NW * 64) {
         const int d = e % D, c = e / D;
-        float v = lds[d * 17 + c];
+        float v = lds[d * 17 + c], x = MORE ? lds[WAVES + d * 17 + c] : 0.f;
 #pragma unroll
-        for (int i = 1; i < NW; ++i) v += lds[i * ALL + d * 17 + c];
-        out(d, c, v);
+        for (int i = 1; i < NW; ++i) {
+            v += lds[i * ALL + d * 17 + c];
+            if (MORE) x += lds[WAVES + i * ALL + d * 17 + c];
+        }
+        out(0, d, c, v);
+        if (MORE) out(1, d, c, x);
     }
 }
 
@@ -284,25 +291,46 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 4) void f32_fwd_kernel(F32F
         }
         ml[0][1][col] = final ? 1.f / l_all : 1.f;
     }
-    sum_waves<D>(acc, lds, [&](int d, int c, float v) {
+    sum_waves<D, false>(acc, acc, lds, [&](int, int d, int c, float v) {
         if (c < rows) (final ? a.O : a.st_acc)[((size_t)(row0 + c) * a.Hq + head) * D + d] = v * ml[0][1][c];
     });
 }
 
-// One launch for both sides: the first workgroups own 16-query tiles (dQ), the others 16-key tiles (dK, dV:
+// One launch for both sides: the first tiles are of 16 queries (dQ), the others of 16 keys (dK, dV:
 // all query heads of the group).  Waves share the walk of a tile as in the forward.
-template <int D>
-__global__ __launch_bounds__(64 * NW) void f32_bwd_kernel(F32BwdArgs a, unsigned dq_blocks)
+//
+// SPLIT (f32_bwd_split): two workgroups share a tile, each wave taking every 16th block.  Both store their sums; the one that arrives second
+// adds the two (always in the same order) and writes the result.  Nobody waits.  Tiles start with the longest walks, of both
+// kinds, so the second halves go in reverse: a compute unit then has a long and a short tile.  (Two workgroups on a compute unit at
+// D = 64 take 25 registers of a loop to scratch memory: 28.9 us instead of 31.6 at 1K tokens, 2 / 2 heads, where one a tile takes 29.3, and
+// 18.7 instead of 15.6 at 512.)
+template <int D, bool SPLIT>
+__global__ __launch_bounds__(64 * NW) void f32_bwd_kernel(F32BwdArgs a, unsigned dq_blocks, unsigned tiles)
 {
-    constexpr int DB = D / 16;
+    constexpr int DB = D / 16, STRIDE = SPLIT ? 2 * NW : NW;  // of the blocks of a walk that a wave takes
     __shared__ __attribute__((aligned(16))) float lds[NW * Shelf<D, 2>::FLOATS];
+    const unsigned half = SPLIT && blockIdx.x >= tiles ? 1 : 0, tile_id = half ? 2 * tiles - 1 - blockIdx.x : blockIdx.x;
+    float* const part = a.part + (size_t)(2 * tile_id) * (2 * TR * D);  // two halves of up to two results
+    // The halves travel in accesses of the device's scope, past the caches of the XCDs, so that a wait for the own ones is all that the
+    // arrival needs.  (With plain stores it needs a fence, which writes back an XCD's whole L2: 179 us instead of 29 at 1K tokens.)
+    auto keep = [&](int at, float v) { __hip_atomic_store(part + at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    auto kept = [&](int at) { return __hip_atomic_load(part + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    // My half is stored; is the other one?
+    auto last = [&] {
+        __shared__ unsigned before;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (threadIdx.x == 0) before = __hip_atomic_fetch_add(a.arrived + tile_id, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        return before != 0;
+    };
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, col = lane & 15;
-    const int group = a.Hq / a.Hkv;
+    const int group = a.Hq / a.Hkv, first = w + NW * (int)half;
     const size_t q_pitch = (size_t)a.Hq * D, k_pitch = (size_t)a.Hkv * D;
     const Shelf<D, 2> shelf = {lds + w * Shelf<D, 2>::FLOATS, lane};
-    if (blockIdx.x < dq_blocks) {
+    if (tile_id < dq_blocks) {
         const int n_tiles = (int)((a.n_q + TR - 1) / TR);
-        const int head = blockIdx.x % (unsigned)a.Hq, tile = n_tiles - 1 - (int)(blockIdx.x / (unsigned)a.Hq);
+        const int head = tile_id % (unsigned)a.Hq, tile = n_tiles - 1 - (int)(tile_id / (unsigned)a.Hq);
         const int kvh = head / group;
         const int64_t row0 = (int64_t)tile * TR;
         const int rows = (int)(a.n_q - row0 < TR ? a.n_q - row0 : TR), mine = col < rows ? col : rows - 1;
@@ -318,20 +346,20 @@ __global__ __launch_bounds__(64 * NW) void f32_bwd_kernel(F32BwdArgs a, unsigned
         auto keys_at = [&](int64_t j) { return (int)(a.n_k - j < BR ? a.n_k - j : BR); };
         auto row_at = [&](int64_t j) { return (j + (col < keys_at(j) ? col : keys_at(j) - 1)) * k_pitch + (size_t)kvh * D; };
         Rows<D> k, v;  // (as in the forward)
-        if (BR * w < need) {
-            k.load(a.K + row_at(BR * w), g);
-            v.load(a.V + row_at(BR * w), g);
+        if (BR * first < need) {
+            k.load(a.K + row_at(BR * first), g);
+            v.load(a.V + row_at(BR * first), g);
         }
 #pragma unroll 1
-        for (int64_t j0 = BR * w; j0 < need; j0 += BR * NW) {
+        for (int64_t j0 = BR * first; j0 < need; j0 += BR * STRIDE) {
             const int keys = keys_at(j0);
             const size_t k0 = j0 * k_pitch + (size_t)kvh * D;
             floatx4 s = dot_rows<D>(k, q);
             const bool odd = shelf.put(0, k);
             const floatx4 dp = dot_rows<D>(v, go);
-            if (j0 + BR * NW < need) {
-                k.load(a.K + row_at(j0 + BR * NW), g);
-                v.load(a.V + row_at(j0 + BR * NW), g);
+            if (j0 + BR * STRIDE < need) {
+                k.load(a.K + row_at(j0 + BR * STRIDE), g);
+                v.load(a.V + row_at(j0 + BR * STRIDE), g);
             }
             unsigned keep = 0;
 #pragma unroll
@@ -343,15 +371,22 @@ __global__ __launch_bounds__(64 * NW) void f32_bwd_kernel(F32BwdArgs a, unsigned
             }
             add_rows(acc, s, keep, shelf, 0, odd, a.K + k0, k_pitch, keys, lane);
         }
-        sum_waves<D>(acc, lds, [&](int d, int c, float v) {
+        auto put = [&](int d, int c, float v) {
             if (c < rows) {
                 float* o = a.dQ + (row0 + c) * q_pitch + (size_t)head * D + d;
                 *o = (a.accumulate ? *o : 0.f) + a.scale * v;
             }
-        });
+        };
+        if constexpr (SPLIT) {
+            sum_waves<D, false>(acc, acc, lds, [&](int, int d, int c, float v) { keep((int)half * TR * D + c * D + d, v); });
+            if (!last()) return;
+            for (int e = threadIdx.x; e < TR * D; e += NW * 64) put(e % D, e / D, kept(e) + kept(TR * D + e));
+        } else {
+            sum_waves<D, false>(acc, acc, lds, [&](int, int d, int c, float v) { put(d, c, v); });
+        }
         return;
     }
-    const unsigned blk = blockIdx.x - dq_blocks;
+    const unsigned blk = tile_id - dq_blocks;
     const int kvh = blk % (unsigned)a.Hkv;
     const int64_t key0 = (int64_t)(blk / (unsigned)a.Hkv) * TR;  // first keys first: theirs is the longest walk
     const int keys = (int)(a.n_k - key0 < TR ? a.n_k - key0 : TR), mine = col < keys ? col : keys - 1;
@@ -387,7 +422,7 @@ __global__ __launch_bounds__(64 * NW) void f32_bwd_kernel(F32BwdArgs a, unsigned
         xo.load(a.dO + row_at(t), g);
     };
     Step t = {0, 0};
-    if (blocks > 0) t.forward(w, blocks);
+    if (blocks > 0) t.forward(first, blocks);
     else t.head = group;
     if (t.head < group) load_rows(t);
 #pragma unroll 1
@@ -408,7 +443,7 @@ __global__ __launch_bounds__(64 * NW) void f32_bwd_kernel(F32BwdArgs a, unsigned
         const bool odd_q = shelf.put(0, xq);
         floatx4 ds = dot_rows<D>(xo, v);
         const bool odd_o = shelf.put(1, xo);
-        t.forward(NW, blocks);
+        t.forward(STRIDE, blocks);
         if (t.head < group) load_rows(t);
         unsigned keep = 0;
 #pragma unroll
@@ -422,16 +457,21 @@ __global__ __launch_bounds__(64 * NW) void f32_bwd_kernel(F32BwdArgs a, unsigned
         add_rows(dv, s, keep, shelf, 1, odd_o, a.dO + q0, q_pitch, rows, lane);
         add_rows(dk, ds, keep, shelf, 0, odd_q, a.Q + q0, q_pitch, rows, lane);
     }
-    auto put = [&](float* out, float mul) {
-        return [=](int d, int c, float x) {
-            if (c < keys) {
-                float* o = out + (key0 + c) * k_pitch + (size_t)kvh * D + d;
-                *o = (a.accumulate ? *o : 0.f) + mul * x;
-            }
-        };
+    auto put = [&](int n, int d, int c, float x) {
+        if (c < keys) {
+            float* o = (n ? a.dV : a.dK) + (key0 + c) * k_pitch + (size_t)kvh * D + d;
+            *o = (a.accumulate ? *o : 0.f) + (n ? 1.f : a.scale) * x;
+        }
     };
-    sum_waves<D>(dk, lds, put(a.dK, a.scale));
-    sum_waves<D>(dv, lds, put(a.dV, 1.f));
+    static_assert(NW * Shelf<D, 2>::FLOATS >= 2 * NW * D * 17, "both sums at a time");
+    if constexpr (SPLIT) {
+        sum_waves<D, true>(dk, dv, lds, [&](int n, int d, int c, float v) { keep((2 * n + (int)half) * TR * D + c * D + d, v); });
+        if (!last()) return;
+        for (int e = threadIdx.x; e < TR * D; e += NW * 64)
+            for (int n = 0; n < 2; ++n) put(n, e % D, e / D, kept(2 * n * TR * D + e) + kept((2 * n + 1) * TR * D + e));
+    } else {
+        sum_waves<D, true>(dk, dv, lds, put);
+    }
 }
 
 __device__ __forceinline__ float load_elem(const float* p) { return *p; }
@@ -492,11 +532,19 @@ void launch_f32_fwd(const F32FwdArgs& a, hipStream_t st)
 void launch_f32_bwd(const F32BwdArgs& a, hipStream_t st)
 {
     const unsigned dq = (unsigned)((a.n_q + TR - 1) / TR * a.Hq);
-    const dim3 grid(dq + (unsigned)((a.n_k + TR - 1) / TR * a.Hkv));
-    if (a.D == 128) f32_bwd_kernel<128><<<grid, 64 * NW, 0, st>>>(a, dq);
-    else if (a.D == 80) f32_bwd_kernel<80><<<grid, 64 * NW, 0, st>>>(a, dq);
-    else f32_bwd_kernel<64><<<grid, 64 * NW, 0, st>>>(a, dq);
+    const unsigned tiles = dq + (unsigned)((a.n_k + TR - 1) / TR * a.Hkv);
+#define F32_BWD(D_)                                                                             \
+    do {                                                                                        \
+        if (a.part) f32_bwd_kernel<D_, true><<<2 * tiles, 64 * NW, 0, st>>>(a, dq, tiles);      \
+        else f32_bwd_kernel<D_, false><<<tiles, 64 * NW, 0, st>>>(a, dq, tiles);                \
+    } while (0)
+    if (a.D == 128) F32_BWD(128);
+    else if (a.D == 80) F32_BWD(80);
+    else F32_BWD(64);
+#undef F32_BWD
 }
+
+size_t f32_bwd_part_bytes(int64_t S, int Hq, int Hkv, int D) { return (size_t)f32_bwd_tiles(S, Hq, Hkv) * (4 * TR * (size_t)D) * sizeof(float); }
 
 void launch_merge(const void* Oa, const float* La, const void* Ob, const float* Lb, void* Oo,
                   float* Lo, int64_t rows, int Hq, int D, int is_bf16, hipStream_t st)

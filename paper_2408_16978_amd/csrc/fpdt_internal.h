@@ -75,9 +75,9 @@ void launch_fwd_sweep(const FwdArgs& a, hipStream_t st);
 // ---------------------------------------------------------------------------
 // bf16 backward
 // ---------------------------------------------------------------------------
-// Delta[h][row] = sum_d dO[row,h,d] * O[row,h,d].
+// Delta[h][row] = sum_d dO[row,h,d] * O[row,h,d].  The launch also clears `n_clear` words at `clear`.
 void launch_delta(const void* O, const void* dO, int64_t rows, int Hq, int D, int is_bf16,
-                  float* Delta, int64_t delta_stride, hipStream_t st);
+                  float* Delta, int64_t delta_stride, hipStream_t st, unsigned* clear = nullptr, int n_clear = 0);
 
 // Overwrite Delta for rows [0, rows) of the sequence with sum_j p_ij (dO_i . v_j), which does
 // not depend on the rounded O, rows = DELTA_HEAD_ROWS.  All pointers are at row 0.
@@ -159,8 +159,12 @@ struct F32BwdArgs {
     int64_t q_pos0, k_pos0, n_q, n_k;
     int Hq, Hkv, D;
     float scale;
+    // two workgroups per tile (f32_bwd_splits): their sums, and per tile how many have arrived (0 before the launch); null: one
+    float* part = nullptr;
+    unsigned* arrived = nullptr;
 };
 void launch_f32_bwd(const F32BwdArgs& a, hipStream_t st);
+size_t f32_bwd_part_bytes(int64_t S, int Hq, int Hkv, int D);
 
 // merge of two partial results (both dtypes)
 void launch_merge(const void* Oa, const float* La, const void* Ob, const float* Lb, void* Oo,

@@ -72,6 +72,19 @@ static inline bool f32_one_launch(int64_t S, int Hq, int Hkv)
     return ((S + 15) / 16 * ((int64_t)Hq + Hkv)) < (int64_t)1 << 23;
 }
 
+static inline int64_t f32_bwd_tiles(int64_t S, int Hq, int Hkv) { return (S + 15) / 16 * ((int64_t)Hq + Hkv); }
+
+// Do two workgroups share each 16-row tile of the fp32 backward over the whole sequence?  Unshared, the launch lasts as long as the walk of
+// the first key tile, through all query heads of its group; sharing halves that and costs every tile its operands and
+// its sums once more, and an exchange through memory (about 4 us).  It pays where the compute units that it fills had nothing to do, and longer
+// where a group has several heads.  Measured, us of the backward alone -> shared (query / KV heads): one head a group, D = 64, 2 / 2,
+// 128 tokens 11.3 -> 11.5, 256 13.3 -> 12.7, 512 19.0 -> 15.6, 640 21.6 -> 19.4, 1K 29.3 -> 31.6, 4 / 4, 512 19.2 -> 23.5; groups of two, 4 / 2, 512
+// 29.2 -> 21.1, 1K 55.5 -> 45.7, 2K (D = 80) 158.8 -> 153.9, 3K 209.7 -> 236.4; 2 / 1, D = 128, 3K 307.9 -> 231.6; 8 / 2, 2K 251 -> 215; 8 / 1, 4K 947 -> 737.
+static inline bool f32_bwd_split(int64_t S, int Hq, int Hkv)
+{
+    return S > 128 && (S + 15) / 16 * Hkv <= (Hq > Hkv ? 256 : 80);
+}
+
 // Into how many splits a dK/dV launch divides the query walk of its key tiles.  Unsplit it has n_k / 256
 // * Hkv workgroups of four waves, one per compute unit: 64 at 8K tokens and two KV heads, so that three
 // quarters of the chip idle, and below the diagonal's last rows the longest workgroup decides.  Each
