@@ -14,15 +14,15 @@ namespace fpdt {
 // units; KG > 1 divides the first, and costs a little more per tile (copies and barriers per MFMA).
 // Measured (us for KG = 1, 2, 4; forward | dQ): 2K tokens, 8 heads, D = 128: 40, 30, 21 | 77, 50, 35;
 // 8K: 184, 138, 154 | 303, 230, 270; 16K: 463, 487, 551 | 753, 812, 903; forward, 8 heads, D = 64: 4K 45, 35, 30;
-// 5K 80, 44, 48; 16K 288, 299, 307; 2 heads, D = 128: 16K 257, 191, 143; 32K 697, 491, 526.  (The constants choose
-// the fastest count at all of 32 sizes so measured.)
+// 5K 80, 44, 48; 14.5K 241, 251, 292; 2 heads, D = 128: 16K 257, 191, 143; 32K 697, 491, 526.  (At 52 sizes so measured the constants
+// choose the fastest count, or one within 0.5% of it.)
 static inline int sweep_key_groups(int64_t n_q, int64_t n_keys, int Hq, bool causal)
 {
     const double tiles = (double)n_keys / 64.0, cus = 256.0;
     int best = 1;
     double best_cost = 0.0;
     for (int kg = 1; kg <= 4; kg *= 2) {
-        const double work = kg == 1 ? 1.0 : kg == 2 ? 1.03 : 1.22, wgs = (double)n_q / 256.0 * kg * Hq;
+        const double work = kg == 1 ? 1.0 : kg == 2 ? 1.04 : 1.22, wgs = (double)n_q / 256.0 * kg * Hq;
         const double longest = tiles / kg * work + 1.5;
         const double load = (double)(int64_t)((wgs + cus - 1.0) / cus) * longest;       // below the diagonal
         const double mean = wgs / cus * (tiles / kg / 2 * work + 1.5) + longest / 4.0;  // on it
