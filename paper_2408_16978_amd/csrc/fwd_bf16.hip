@@ -393,6 +393,13 @@ __global__ __launch_bounds__(NWAVE * 64, 2) void fwd_sweep_kernel(FwdKernelArgs 
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) s[kb] = ahead[kb];
         end_phase(more_a);
+        // Where the second block lies behind all of the wave's rows (only ever in its last tile, which is no steady one) its probabilities are 0:
+        // its V counts as 0 too, so that an infinity or NaN there does not reach rows of the block before.
+        if constexpr (KB == 2 && !STEADY)
+            if (it * BK + 32 > reach + 31) {  // wave-uniform
+#pragma unroll
+                for (int i = 2 * DB; i < VR; ++i) vfr[i] = as_bf16x8(u32x4{0, 0, 0, 0});
+            }
         // ---- B ----
         if (!STEADY && more_b) request(cp[1]);
         for_each<VR>([&](auto step) {
@@ -409,7 +416,7 @@ __global__ __launch_bounds__(NWAVE * 64, 2) void fwd_sweep_kernel(FwdKernelArgs 
     };
     int it = 0;
 #pragma unroll 1
-    for (; it + 1 < n_w && it + 4 < n_tiles; it += 2) {
+    for (; it + KB < n_w && it + 4 < n_tiles; it += 2) {
         tile(std::true_type{}, it, ZERO);
         tile(std::true_type{}, it + 1, ONE);
     }
