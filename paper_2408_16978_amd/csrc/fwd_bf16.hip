@@ -459,12 +459,13 @@ __global__ __launch_bounds__(NWAVE * 64, 2) void fwd_sweep_kernel(FwdKernelArgs 
                 for (int i = 0; i < SHARE / 4; ++i) part[at(owner, kg - (kg > owner), i)] = quad(owner * (SHARE / 4) + i);
             }
         if (KG > 1) __syncthreads();
-        float m_all = -INFINITY, l_all = 0.f, wt[KG];  // finite maximum: the wave of group 0 saw the first key of every row
+        float m_all = -INFINITY, l_all = 0.f, wt[KG];
 #pragma unroll
         for (int i = 0; i < KG; ++i) m_all = fmaxf(m_all, KG > 1 ? ml[i * NQ + qb][0][lane] : m_run);
 #pragma unroll
         for (int i = 0; i < KG; ++i) {
-            wt[i] = KG > 1 ? __builtin_amdgcn_exp2f(ml[i * NQ + qb][0][lane] - m_all) : 1.f;
+            // (0 in the place of a maximum of -infinity: a row that scores nothing else has a sum of 0 then, with every key group count)
+            wt[i] = KG > 1 ? __builtin_amdgcn_exp2f(ml[i * NQ + qb][0][lane] - (m_all > -INFINITY ? m_all : 0.f)) : 1.f;
             l_all += KG > 1 ? ml[i * NQ + qb][1][lane] * wt[i] : l_run;
         }
         const float l_tot = l_all + xor32(l_all), inv = 1.f / l_tot;
