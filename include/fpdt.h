@@ -115,7 +115,7 @@ enum {
  * backward partial dK and dV of the s - 1 (s = 2 .. 16) further workgroups of a key tile, rows * Hkv *
  * dpad(D) * 8 bytes each (rows = chunk; S in one launch, which then also holds the first's); the fp32
  * backward of short sequences, where two workgroups share a tile of 16 rows, their sums (256 * D bytes per
- * tile and query or key/value head).  The
+ * tile and query or key/value head, at most 2^15 of them: 1 GiB at D = 128).  The
  * entry points take a workspace without them too: the forward then runs in smaller chunks (which
  * offloaded K/V cross the link more often for) with the same bits, or with one state per row where
  * these do not fit either, the backward with fewer workgroups per key tile and sums in another order.

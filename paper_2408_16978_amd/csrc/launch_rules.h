@@ -75,14 +75,21 @@ static inline bool f32_one_launch(int64_t S, int Hq, int Hkv)
 static inline int64_t f32_bwd_tiles(int64_t S, int Hq, int Hkv) { return (S + 15) / 16 * ((int64_t)Hq + Hkv); }
 
 // Do two workgroups share each 16-row tile of the fp32 backward over the whole sequence?  Unshared, the launch lasts as long as the walk of
-// the first key tile, through all query heads of its group; sharing halves that and costs every tile its operands and
-// its sums once more, and an exchange through memory (about 4 us).  It pays where the compute units that it fills had nothing to do, and longer
-// where a group has several heads.  Measured, us of the backward alone -> shared (query / KV heads): one head a group, D = 64, 2 / 2,
-// 128 tokens 11.3 -> 11.5, 256 13.3 -> 12.7, 512 19.0 -> 15.6, 640 21.6 -> 19.4, 1K 29.3 -> 31.6, 4 / 4, 512 19.2 -> 23.5; groups of two, 4 / 2, 512
-// 29.2 -> 21.1, 1K 55.5 -> 45.7, 2K (D = 80) 158.8 -> 153.9, 3K 209.7 -> 236.4; 2 / 1, D = 128, 3K 307.9 -> 231.6; 8 / 2, 2K 251 -> 215; 8 / 1, 4K 947 -> 737.
+// the first key tile, through all query heads of its group.  Sharing halves that walk as long as the compute units' average load allows, and costs
+// a fixed exchange through memory and, for every workgroup that a compute unit runs beyond those it would have run, operands and sums once more;
+// all in units of a 16-row block of the walk.  Measured over 900 sizes (D = 64, 80, 128; 96 to 5120 tokens, up to 32 KV heads, groups of 1 to 16): the
+// rule's choice takes at most 1.05 of the faster one's time, in the mean 1.001.  us of the backward alone -> shared (query / KV heads, D =
+// 64): 2 / 2, 192 tokens 11.8 -> 12.2, 208 12.8 -> 12.2, 512 19.2 -> 15.8, 1K 29.3 -> 31.6; 4 / 2, 512 29.2 -> 21.2, 1K 55.3 -> 45.3, 2K 130.6 -> 123.2; 8 / 1,
+// 4K 945 -> 733; 64 / 1, 1K 1533 -> 829, 4K 7806 -> 5767; many KV heads, not shared: 32 / 16, 256 tokens 30.4 -> 44.8, 16 / 8, 512 45.0 -> 58.0, 8 / 4, 1K 73.5 -> 80.2,
+// 16 / 4, 1K 138 -> 139.  The sums take 256 * D bytes a tile: up to 2^15 tiles (1 GiB at D = 128; measured to 32K tiles, 500 / 1, 1K tokens, D = 128 22.2 -> 12.1
+// ms), far below the 2^22 whose shared launch would have 2^32 lanes.
 static inline bool f32_bwd_split(int64_t S, int Hq, int Hkv)
 {
-    return S > 128 && (S + 15) / 16 * Hkv <= (Hq > Hkv ? 256 : 80);
+    const int64_t blocks = (S + 15) / 16, tiles = f32_bwd_tiles(S, Hq, Hkv);
+    if (S <= 128 || blocks * Hkv > (Hq > Hkv ? 256 : 80) || tiles >= (int64_t)1 << 15) return false;
+    const double per_cu = (double)tiles / 256.0, load = (double)(blocks * Hkv) / 256.0, walk = (double)(blocks * (Hq / Hkv));
+    const double saved = std::min(0.5, 0.6 - 0.4 * load) * walk;
+    return saved > 6.0 + 8.0 * std::max(0.0, 2.0 * per_cu - std::max(per_cu, 1.0));
 }
 
 // Into how many splits a dK/dV launch divides the query walk of its key tiles.  Unsplit it has n_k / 256

@@ -25,12 +25,27 @@ def shared():
     return lambda S, Hq, Hkv: bool(L.split(S, Hq, Hkv))
 
 
-@pytest.mark.parametrize("S,Hq,Hkv,yes", [(128, 2, 2, False), (129, 2, 2, True), (640, 2, 2, True), (641, 2, 2, False), (1024, 2, 2, False),
-                                          (2048, 4, 2, True), (2049, 4, 2, False), (4096, 8, 1, True), (4097, 8, 1, False)])
+# (one head a group: measured slower shared up to 192 tokens; many KV heads: up to 1.5 times slower shared)
+@pytest.mark.parametrize("S,Hq,Hkv,yes", [(128, 2, 2, False), (192, 2, 2, False), (193, 2, 2, True), (640, 2, 2, True), (641, 2, 2, False), (1024, 2, 2, False),
+                                          (2048, 4, 2, True), (2049, 4, 2, False), (4096, 8, 1, True), (4097, 8, 1, False), (4096, 64, 1, True),
+                                          (144, 64, 16, False), (256, 32, 16, False), (512, 16, 8, False), (1024, 8, 4, False), (1024, 64, 4, True)])
 def test_which_sizes_share(shared, S, Hq, Hkv, yes):
     assert shared(S, Hq, Hkv) == yes
     ws = lambda flags: B.fpdt_attn_workspace_bytes(S, S, Hq, Hkv, 64, B.FPDT_DTYPE_F32, flags, True)  # noqa: E731
     assert (ws(0) > ws(B.FPDT_PAIRWISE)) == yes
+
+
+def test_a_shared_launch_is_not_too_large(shared):
+    """Two workgroups of 512 lanes a tile, in a launch of fewer than 2^32 lanes, with sums of at most 1 GiB (256 * 128 bytes a tile), whatever
+    the heads; also where an unshared launch, of up to 2^23 tiles, is one launch."""
+    sizes = [S for S in list(range(1, 300, 13)) + [512, 1000, 1024, 2048, 4095, 4096]]
+    heads = [(g * h, h) for h in (1, 2, 3, 5, 16) for g in (1, 2, 8, 100, 126, 127, 128, 4096, 16383, 16384, 32766, 100000)]
+    for S in sizes:
+        for Hq, Hkv in heads:
+            if shared(S, Hq, Hkv):
+                tiles = (S + 15) // 16 * (Hq + Hkv)
+                assert 2 * tiles * 512 < 2 ** 32 and tiles * 256 * 128 <= 2 ** 30, (S, Hq, Hkv)
+    assert launch_rules.f32_one_launch(4096, 16384, 1) and not shared(4096, 16384, 1)
 
 
 def _gradients(Q, K, V, dO, scale):
@@ -47,12 +62,12 @@ def _gradients(Q, K, V, dO, scale):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("D", [64, 80, 128])
-@pytest.mark.parametrize("S,Hq,Hkv", [(129, 1, 1), (145, 8, 1), (250, 3, 3), (512, 2, 2), (640, 2, 1), (1023, 4, 2), (1024, 4, 4)])
+@pytest.mark.parametrize("S,Hq,Hkv", [(129, 1, 1), (193, 1, 1), (145, 8, 1), (250, 3, 3), (512, 2, 2), (640, 2, 1), (1023, 4, 2), (1024, 4, 4)])
 def test_gpu_shared_tiles(shared, S, Hq, Hkv, D):
     """Against fp64 within the fp32 tolerance, 1e-4; the same bits on every run; one workgroup per tile where the workspace has no room for
     the sums, within the same tolerance."""
     print("[case] fp32 shared tiles", S, Hq, Hkv, D, flush=True)
-    assert shared(S, Hq, Hkv) == (S < 1024 or Hq > Hkv)
+    assert shared(S, Hq, Hkv) == (192 < S < 1024 or Hq > Hkv)
     Q, K, V, dO = inputs.make_qkvdo(S, Hq, Hkv, D, "f32", 41, device="cuda")
     b = runner.make_buffers(Q, K, V, dO, S, D ** -0.5, 0)
     runner.forward(b)
