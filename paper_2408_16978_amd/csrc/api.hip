@@ -107,7 +107,7 @@ int validate_scalars(Problem& p, int64_t S, int64_t chunk, int Hq, int Hkv, int 
     if (S > (int64_t)1 << 30 || (int64_t)Hq * (S / 32 + 1) > (int64_t)1 << 30) return fail(FPDT_ERR_UNSUPPORTED, "S=%lld beyond launch limits", (long long)S);
     p.S = S; p.C = chunk; p.u = S / chunk; p.Hq = Hq; p.Hkv = Hkv; p.D = D; p.dtype = dtype;
     p.flags = flags; p.scale = scale;
-    p.fwd_kg = sweep_key_groups(S, S, Hq, true);
+    p.fwd_kg = sweep_key_groups(S, Hq);
     return FPDT_OK;
 }
 

@@ -590,7 +590,7 @@ __global__ __launch_bounds__(256) void dkdv_sum_kernel(BwdKernelArgs p, unsigned
 // 32.2 -> 30.1, 8K 195 -> 189, 64K 10504 -> 10159 (1300 TFLOP/s executed); 64K 6020 -> 5761.
 //
 // KG = 2, 4 (as in the forward): 128 or 64 query rows per workgroup, the waves of one row block take every
-// KG-th 32-key block and add their results through LDS at the end (sweep_key_groups).
+// KG-th 32-key block and add their results through LDS at the end (dq_key_groups).
 template <int D, int KG>
 __global__ __launch_bounds__(NTHREAD) void bwd_dq_kernel(BwdKernelArgs p)
 {
@@ -1236,7 +1236,7 @@ void launch_bwd_dq_from_ds(const BwdArgs& a, hipStream_t st)
 void launch_bwd_dq(const BwdArgs& a, hipStream_t st)
 {
     const BwdKernelArgs k = to_kernel_args(a);
-    const int kg = sweep_key_groups(a.n_q, a.n_k, a.Hq, a.q_pos0 == a.k_pos0);
+    const int kg = dq_key_groups(a.n_q, a.n_k, a.Hq, a.D, a.q_pos0 == a.k_pos0);
     const dim3 grid((unsigned)((a.n_q / (bwd_q_tile(a.D) / kg)) * a.Hq));
 #define DQ_LAUNCH(D_)                                                        \
     do {                                                                     \

@@ -11,25 +11,47 @@ namespace fpdt {
 // Key groups of a forward or dQ launch (a workgroup of eight waves = 8 / KG row blocks of 32 queries x KG
 // waves that share the keys): the cheapest of 1, 2, 4 in units of a 64-key tile of eight row blocks.  A
 // launch on the diagonal lasts as long as its longest row tile or as the average load of the 256 compute
-// units; KG > 1 divides the first, and costs a little more per tile (copies and barriers per MFMA).
-// Measured (us for KG = 1, 2, 4; forward | dQ): 2K tokens, 8 heads, D = 128: 40, 30, 21 | 77, 50, 35;
-// 8K: 184, 138, 154 | 303, 230, 270; 16K: 463, 487, 551 | 753, 812, 903; forward, 8 heads, D = 64: 4K 45, 35, 30;
-// 5K 80, 44, 48; 14.5K 241, 251, 292; 2 heads, D = 128: 16K 257, 191, 143; 32K 697, 491, 526.  (At 52 sizes so measured the constants
-// choose the fastest count, or one within 0.5% of it.)
-static inline int sweep_key_groups(int64_t n_q, int64_t n_keys, int Hq, bool causal)
+// units, one below it as its rounds of workgroups; KG > 1 divides a workgroup's walk, and costs a little more per tile (copies
+// and barriers per MFMA).
+struct KeyGroupCosts {
+    double two, four;  // a tile with two, four key groups
+    double fixed;      // of a workgroup
+    double gain;       // more groups are taken where they cost less than this share
+};
+static inline int cheapest_key_groups(int64_t n_q, int64_t n_keys, int Hq, bool diagonal, const KeyGroupCosts& c)
 {
     const double tiles = (double)n_keys / 64.0, cus = 256.0;
     int best = 1;
     double best_cost = 0.0;
     for (int kg = 1; kg <= 4; kg *= 2) {
-        const double work = kg == 1 ? 1.0 : kg == 2 ? 1.04 : 1.22, wgs = (double)n_q / 256.0 * kg * Hq;
-        const double longest = tiles / kg * work + 1.5;
-        const double load = (double)(int64_t)((wgs + cus - 1.0) / cus) * longest;       // below the diagonal
-        const double mean = wgs / cus * (tiles / kg / 2 * work + 1.5) + longest / 4.0;  // on it
-        const double cost = causal ? (mean > longest ? mean : longest) : load;
-        if (kg == 1 || cost < 0.93 * best_cost) { best = kg; best_cost = cost; }
+        const double work = kg == 1 ? 1.0 : kg == 2 ? c.two : c.four, wgs = (double)n_q / 256.0 * kg * Hq;
+        const double longest = tiles / kg * work + c.fixed;
+        const double load = (double)(int64_t)((wgs + cus - 1.0) / cus) * longest;           // below the diagonal
+        const double mean = wgs / cus * (tiles / kg / 2 * work + c.fixed) + longest / 4.0;  // on it
+        const double cost = diagonal ? (mean > longest ? mean : longest) : load;
+        if (kg == 1 || cost < c.gain * best_cost) { best = kg; best_cost = cost; }
     }
     return best;
+}
+
+// The forward's, by the whole sequence.  Measured (us for KG = 1, 2, 4): 8 heads, D = 128, 2K tokens 40, 30, 21; 8K 184, 138, 154; 16K 463, 487, 551;
+// D = 64, 4K 45, 35, 30; 5K 80, 44, 48; 14.5K 241, 251, 292; 2 heads, D = 128: 16K 257, 191, 143; 32K 697, 491, 526.  (At 52 sizes so
+// measured the constants choose the fastest count, or one within 0.5% of it.)
+static inline int sweep_key_groups(int64_t S, int Hq)
+{
+    return cheapest_key_groups(S, S, Hq, true, {1.04, 1.22, 1.5, 0.93});
+}
+
+// The recomputing dQ's, by the launch.  With D = 64 and 80, whose tiles are shorter, four groups pay up to longer launches on the diagonal; below
+// it, where every workgroup walks all keys, sooner ones cost a round more.  Measured at 464 sizes (chunks of 256 to 32K rows, 1 to 32 heads; us for
+// KG = 1, 2, 4).  Diagonal: 8 heads, D = 128, 2K rows 67, 43, 30, 8K 257, 194, 215, 12K 448, 442, 464; D = 64, 5K 96, 61, 57, 8K 155, 111,
+// 118; 4 heads, D = 80, 11K 244, 168, 154.  Below: 8 heads, D = 128, 4.25K 138, 178, 161, 5K 158, 205, 185, 10K 712, 622, 623; 2 heads, 18K 534, 699,
+// 607; D = 64, 9K 376, 325, 297; 4 heads, 18K 740, 636, 578.  The choice takes at most 1.03 of the fastest one's time, but for 768 rows of 32 heads
+// on the diagonal at D = 128 (1.05); the forward's constants took up to 1.14.
+static inline int dq_key_groups(int64_t n_q, int64_t n_k, int Hq, int D, bool diagonal)
+{
+    if (diagonal) return cheapest_key_groups(n_q, n_k, Hq, true, D == 128 ? KeyGroupCosts{1.04, 1.22, 1.5, 0.93} : KeyGroupCosts{1.12, 1.25, 1.5, 1.0});
+    return cheapest_key_groups(n_q, n_k, Hq, false, {1.16, 1.35, D == 128 ? 1.5 : 0.5, 0.99});
 }
 
 // Waves (of 32 query rows each) of a workgroup of the forward with one key group and of dQ from stored dS: eight, or four or

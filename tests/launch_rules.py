@@ -10,7 +10,8 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 SHIM = """
 #include "launch_rules.h"
 #include "tw_plan.h"
-extern "C" int key_groups(int64_t n_q, int64_t n_k, int Hq, int causal) { return fpdt::sweep_key_groups(n_q, n_k, Hq, causal); }
+extern "C" int key_groups(int64_t S, int Hq) { return fpdt::sweep_key_groups(S, Hq); }
+extern "C" int dq_key_groups(int64_t rows, int Hq, int D, int diagonal) { return fpdt::dq_key_groups(rows, rows, Hq, D, diagonal); }
 extern "C" int f32_one_launch(int64_t S, int Hq, int Hkv) { return fpdt::f32_one_launch(S, Hq, Hkv); }
 extern "C" int dkdv_splits(int64_t n_q, int64_t n_k, int Hq, int Hkv, int D, int causal) { return fpdt::bwd_dkdv_splits(n_q, n_k, Hq, Hkv, D, causal); }
 static void put(const fpdt_tw::Plan& p, int* out)
@@ -33,7 +34,8 @@ def _lib():
         subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, src, "-o", so], check=True)
         L = ctypes.CDLL(so)
     i64, ci = ctypes.c_int64, ctypes.c_int
-    L.key_groups.argtypes = [i64, i64, ci, ci]
+    L.key_groups.argtypes = [i64, ci]
+    L.dq_key_groups.argtypes = [i64, ci, ci, ci]
     L.dkdv_splits.argtypes = [i64, i64, ci, ci, ci, ci]
     L.f32_one_launch.argtypes = [i64, ci, ci]
     for f in (L.launched, L.first_answer):
@@ -42,11 +44,11 @@ def _lib():
 
 
 def forward_key_groups(S, Hq):
-    return _lib().key_groups(S, S, Hq, 1)
+    return _lib().key_groups(S, Hq)
 
 
-def dq_key_groups(rows, Hq, diagonal):
-    return _lib().key_groups(rows, rows, Hq, int(diagonal))
+def dq_key_groups(rows, Hq, diagonal, D=128):
+    return _lib().dq_key_groups(rows, Hq, D, int(diagonal))
 
 
 def f32_one_launch(S, Hq, Hkv):

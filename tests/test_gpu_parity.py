@@ -408,8 +408,8 @@ def test_bf16_every_key_group_count(sizes, groups, D):
     schedules' O and LSE have the same bits."""
     S, chunk, Hq, Hkv = sizes
     announce("bf16 key group count", S, chunk, Hq, Hkv, D, groups)
-    assert (launch_rules.forward_key_groups(S, Hq), launch_rules.dq_key_groups(chunk, Hq, True),
-            launch_rules.dq_key_groups(chunk, Hq, False)) == groups
+    assert (launch_rules.forward_key_groups(S, Hq), launch_rules.dq_key_groups(chunk, Hq, True, D),
+            launch_rules.dq_key_groups(chunk, Hq, False, D)) == groups
     Q, K, V, dO = inputs.make_qkvdo(S, Hq, Hkv, D, "bf16", seed=23)
     scale = D ** -0.5
     ref = parity.oracle_full(Q, K, V, dO, scale)
