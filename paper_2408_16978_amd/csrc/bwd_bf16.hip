@@ -789,13 +789,16 @@ __global__ __launch_bounds__(NTHREAD) void bwd_dq_kernel(BwdKernelArgs p)
         }
     }
 
+    // The lane's number once more, and what follows from it: kept through the loop, at D = 128 with several key groups, three registers of
+    // it would go to scratch memory.
+    const int end_lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), end_row = qw0 + (end_lane & 31);
     if constexpr (KG > 1) {  // (the loop ended with a barrier behind the last reads of the ring)
         constexpr int PART = DB * 16 * 64;
         static_assert((NWAVE - NQ) * PART * 4 <= RING * SLOT_U4 * 16, "the ring holds the parts");
         __syncthreads();
         float* part = reinterpret_cast<float*>(ring_a);
         if (kg > 0) {
-            float* mine = part + (size_t)((kg - 1) * NQ + qb) * PART + lane;
+            float* mine = part + (size_t)((kg - 1) * NQ + qb) * PART + end_lane;
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -805,7 +808,7 @@ __global__ __launch_bounds__(NTHREAD) void bwd_dq_kernel(BwdKernelArgs p)
         if (kg > 0) return;
 #pragma unroll
         for (int i = 1; i < KG; ++i) {
-            const float* other = part + (size_t)((i - 1) * NQ + qb) * PART + lane;
+            const float* other = part + (size_t)((i - 1) * NQ + qb) * PART + end_lane;
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -814,12 +817,12 @@ __global__ __launch_bounds__(NTHREAD) void bwd_dq_kernel(BwdKernelArgs p)
     }
 
     if (p.flags & ACC_FINAL) {
-        store_rows_bf16<D, DB>(acc, p.scale, p.dQ + ((size_t)row * p.Hq + head) * D, half);
+        store_rows_bf16<D, DB>(acc, p.scale, p.dQ + ((size_t)end_row * p.Hq + head) * D, end_lane >> 5);
     } else {
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) aq[(db * 16 + r) * 64 + lane] = acc[db][r];
+            for (int r = 0; r < 16; ++r) aq[(db * 16 + r) * 64 + end_lane] = acc[db][r];
     }
 }
 

@@ -20,9 +20,10 @@ def kernels(source):
     found = {}
     for m in re.finditer(r"\.group_segment_fixed_size: (\d+)(.*?)\.vgpr_count:\s+(\d+)", text, re.S):
         name = re.search(r"\.name:\s+(\S+)", m.group(2)).group(1)
-        name = subprocess.run(["c++filt", name], capture_output=True, text=True, check=True).stdout.split("(")
+        name = subprocess.run(["c++filt", name], capture_output=True, text=True, check=True).stdout
         scratch = re.search(r"\.private_segment_fixed_size: (\d+)", m.group(2)).group(1)
-        key = "(".join(name).split("(anonymous namespace)::")[-1].split("(")[0]
+        # "void fpdt::(anonymous namespace)::kernel<..>(fpdt::(anonymous namespace)::Args)": up to the parameters
+        key = re.split(r"[ :](?=\w+(?:<[^()]*>)?\()", name.replace("(anonymous namespace)::", ""), maxsplit=1)[-1].split("(")[0]
         found[key] = int(m.group(3)), int(m.group(1)), int(scratch)
     return found
 
