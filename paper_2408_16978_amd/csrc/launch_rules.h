@@ -68,23 +68,21 @@ static inline int sweep_waves(int64_t n_q, int Hq)
 }
 
 // Does the one-launch forward read K and V from their tensors, without the launch that packs them?  With several key groups
-// (short sequences) that launch costs more than the transposing reads that take its place, up to a length: longer ones gain
-// from the packed copies (fewer LDS reads per tile), at D = 80, whose rows of ten pieces are not spread over the banks,
-// and D = 128 sooner than at D = 64, and with two key groups, whose workgroups hide less of them, soonest (at D = 64 the two differ by
-// 3% and less there, either way); where every query head has K and V of its own there is most to pack.
-// Measured with the inputs in no cache and in the caches (us, packed -> not; query / KV heads): four key groups, D = 64, 8 / 2, 2K 16.8, 16.7 ->
-// 14.8, 14.3, 4K 32.2, 31.5 -> 30.0, 28.7, 4 / 4, 8K 52.7, 57.6 -> 49.8, 47.9; D = 80, 8 / 2, 2K 19.1, 18.9 -> 17.5, 16.6, 4K 39.8, 37.6 -> 39.3,
-// 35.8, 4 / 4, 8K 65.0, 67.7 -> 68.2, 64.9; D = 128, 8 / 2, 1K 16.6, 16.3 -> 14.2, 13.5, 2K 22.8, 22.1 -> 20.8, 19.4, 4K 47.5, 46.8 -> 46.9, 43.4, 8 / 8,
-// 4K 51.5, 52.6 -> 48.2, 44.4; two key groups, D = 64, 8 / 2, 6K 55.0, 54.7 -> 53.5, 52.5, 8K 83.7, 82.9 -> 84.8, 81.7; D = 80, 8 / 2, 8K 101.7, 102.0 -> 109.0,
-// 106.1; D = 128, 8 / 2, 8K 137.7, 133.5 -> 140.5, 133.5.
+// (short sequences) that launch costs more than the transposing reads that take its place.  Packed copies need fewer LDS reads per tile, and at D =
+// 80, whose rows of ten pieces are not spread over the banks, gain from it with two key groups, whose workgroups hide less: there longer sequences are
+// packed, later where every query head has K and V of its own and there is most to pack.  Up to 16K tokens, behind which the two
+// are within 2% of each other at D = 64 and 128.
+// Measured over 13 head counts and 24 lengths, with the inputs in no cache and in the caches: the choice takes at most 1.02 of the other's time (us,
+// packed -> not; query / KV heads).  D = 64, four key groups, 8 / 2, 2K 17.9, 17.2 -> 15.2, 14.8, 4K 33.6, 32.1 -> 31.5, 29.4; two, 64 / 8, 512 15.1, 13.9 ->
+// 12.0, 10.9, 32 / 8, 1.5K 27.4, 25.3 -> 23.1, 21.9, 8 / 2, 8K 85.0, 84.1 -> 81.7, 80.5.  D = 80, four, 8 / 2, 4K 39.9, 38.1 -> 38.5, 36.0, 4 / 4, 8K 69.9, 68.2 -> 65.4,
+// 62.5; two, 16 / 4, 4K 62.1, 60.2 -> 61.5, 59.7, 8 / 2, 5K 57.8, 55.9 -> 57.5, 56.6, 8K 103.2, 101.7 -> 105.8, 104.9, 8 / 8, 8K 107.9, 105.7 -> 106.3, 105.3.  D = 128,
+// four, 8 / 2, 2K 24.6, 23.5 -> 22.0, 20.4, 4K 49.6, 47.7 -> 46.3, 43.7, 8 / 8, 4K 53.8, 51.8 -> 47.0, 43.7; two, 16 / 4, 4K 79.8, 78.3 -> 76.5, 73.1, 8 / 2, 8K
+// 137.6, 136.7 -> 133.9, 133.1, 4 / 1, 12K 170.2, 169.8 -> 168.8, 164.6.
 static inline bool sweep_reads_tensors(int64_t S, int Hq, int Hkv, int D, int key_groups)
 {
     if (key_groups == 1) return false;
-    const int64_t workgroups = S / 256 * key_groups * Hq;
-    if (D == 64) return S <= 8192 && workgroups <= 512 && (key_groups == 4 || S >= 6144);
-    if (Hq == Hkv && Hkv >= 8) return S <= (D == 80 ? 4096 : 6144);
-    if (key_groups == 2) return S <= 2048;
-    return workgroups <= 512 && S <= (D == 128 ? 3072 : workgroups <= 256 ? 4096 : 3584);
+    if (D == 80 && key_groups == 2) return S <= (Hq == Hkv ? 8192 : 4608);
+    return S <= 16384;
 }
 
 // Does an fp32 call over the whole sequence fit into one launch?  (Workgroups of 512 lanes, one per 16 rows and
