@@ -356,7 +356,8 @@ __global__ __launch_bounds__(NWAVE * 64, 2) void fwd_sweep_kernel(FwdKernelArgs 
                 // The next block's scores are here too, and count: the largest probability of a reference is exact in bf16, and of the
                 // first 64 keys, which make up the short rows, it is so in more rows than of the first 32 (8 heads, 16K tokens: error of
                 // O against 64 bits 2.168e-3 with 32, 2.154e-3 with 64; sums of 64 keys: of the LSE 5.4e-8, 5.3e-8).
-                const int last = row_key - (it + 1) * BK;
+                int last = row_key - (it + 1) * BK;
+                asm volatile("" : "+v"(last));  // (the comparisons stay in the branch)
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
                     if (8 * (r >> 2) + (r & 3) <= last) mx = fmaxf(mx, ahead[0][r]);
