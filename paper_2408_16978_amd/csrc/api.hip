@@ -697,13 +697,7 @@ int bwd_bf16_fused(const Problem& p, const void* Q, const void* K, const void* V
     a.dkdv_splits = f.dkdv_splits; a.dkdv_part = f.dkdv_part;
     a.dQ = dQ; a.dK = dK; a.dV = dV;
     a.flags = ACC_FINAL;
-    if (!launch_bwd_prepare(a, O, f.Delta, f.stat2, f.Qnat, f.dOnat, f.Knat, f.Vnat, st)) {
-        launch_delta(O, dO, p.S, p.Hq, p.D, 1, f.Delta, p.S, st);
-        launch_delta_head(Q, dO, K, V, LSE, p.S, p.Hq, p.Hkv, p.D, p.scale, f.Delta, st);
-        launch_stat_pack(LSE, f.Delta, p.S, p.S, p.Hq, p.S / 32, f.stat2, st);
-        launch_pack({{Q, p.Hq, f.Qnat, nullptr}, {dO, p.Hq, f.dOnat, nullptr}, {K, p.Hkv, f.Knat, nullptr}, {V, p.Hkv, f.Vnat, nullptr}},
-                    p.S, p.D, p.S / 32, st);
-    }
+    launch_bwd_prepare(a, O, f.Delta, f.stat2, f.Qnat, f.dOnat, f.Knat, f.Vnat, st);
     { PROF(FPDT_PROF_DKDV, st); launch_bwd_dkdv(a, st); }
     { PROF(FPDT_PROF_DQ, st); launch_bwd_dq(a, st); }
     return launch_status("bf16 backward");

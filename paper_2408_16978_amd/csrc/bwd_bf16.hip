@@ -1134,12 +1134,12 @@ struct PrepareArgs {
     int Hq, Hkv;
     float c;
     PackJobs jobs;
-    unsigned head_blocks, delta_blocks;
+    unsigned head_blocks, delta_blocks, first;  // first: block of the launch's first workgroup
 };
 template <int D>
 __global__ __launch_bounds__(512) void bwd_prepare_kernel(PrepareArgs p)
 {
-    unsigned block = blockIdx.x;
+    unsigned block = p.first + blockIdx.x;
     if (block < p.head_blocks) {
         delta_head_block<D>(p.Q, p.dO, p.K, p.V, p.LSE, p.S, p.Hq, p.Hkv, p.c, p.Delta, p.stat2, p.S / 32, block);
         return;
@@ -1273,7 +1273,7 @@ void launch_delta(const void* O, const void* dO, int64_t rows, int Hq, int D, in
         delta_kernel<float><<<grid, 256, 0, st>>>((const float*)O, (const float*)dO, rows, Hq, D, Delta, delta_stride, clear, n_clear);
 }
 
-bool launch_bwd_prepare(const BwdArgs& a, const void* O, float* Delta, float* stat2, void* Qnat, void* dOnat, void* Knat, void* Vnat, hipStream_t st)
+void launch_bwd_prepare(const BwdArgs& a, const void* O, float* Delta, float* stat2, void* Qnat, void* dOnat, void* Knat, void* Vnat, hipStream_t st)
 {
     PrepareArgs p;
     p.Q = (const uint16_t*)a.Q; p.dO = (const uint16_t*)a.dO; p.K = (const uint16_t*)a.K; p.V = (const uint16_t*)a.V; p.O = (const uint16_t*)O;
@@ -1281,13 +1281,15 @@ bool launch_bwd_prepare(const BwdArgs& a, const void* O, float* Delta, float* st
     p.S = a.n_q; p.Hq = a.Hq; p.Hkv = a.Hkv; p.c = a.scale * LOG2E;
     p.jobs = {{{a.Q, a.Hq, Qnat, nullptr}, {a.dO, a.Hq, dOnat, nullptr}, {a.K, a.Hkv, Knat, nullptr}, {a.V, a.Hkv, Vnat, nullptr}}};
     p.head_blocks = DELTA_HEAD_ROWS / 32 * (unsigned)a.Hq;
-    const int64_t delta = (a.n_q - DELTA_HEAD_ROWS) / 32 * a.Hq, all = p.head_blocks + delta + a.n_q / 32 * 2 * ((int64_t)a.Hq + a.Hkv);
-    if (all >= (int64_t)1 << 23) return false;  // a launch has fewer than 2^32 lanes
-    p.delta_blocks = (unsigned)delta;
-    if (a.D == 128) bwd_prepare_kernel<128><<<(unsigned)all, 512, 0, st>>>(p);
-    else if (a.D == 80) bwd_prepare_kernel<80><<<(unsigned)all, 512, 0, st>>>(p);
-    else bwd_prepare_kernel<64><<<(unsigned)all, 512, 0, st>>>(p);
-    return true;
+    p.delta_blocks = (unsigned)((a.n_q - DELTA_HEAD_ROWS) / 32 * a.Hq);
+    const int64_t blocks = bwd_prepare_blocks(a.n_q, a.Hq, a.Hkv);
+    for (int64_t first = 0, n; first < blocks; first += n) {
+        n = bwd_prepare_next(first, blocks);
+        p.first = (unsigned)first;
+        if (a.D == 128) bwd_prepare_kernel<128><<<(unsigned)n, 512, 0, st>>>(p);
+        else if (a.D == 80) bwd_prepare_kernel<80><<<(unsigned)n, 512, 0, st>>>(p);
+        else bwd_prepare_kernel<64><<<(unsigned)n, 512, 0, st>>>(p);
+    }
 }
 
 void launch_delta_head(const void* Q, const void* dO, const void* K, const void* V, const float* LSE,

@@ -128,8 +128,8 @@ struct BwdArgs {
     float* dkdv_part = nullptr;
 };
 // launch_delta, launch_delta_head, launch_stat_pack and launch_pack of a backward over the whole sequence (a.Q, dO, K, V, LSE and sizes) in one
-// launch; false, and nothing launched, where it would have too many lanes
-bool launch_bwd_prepare(const BwdArgs& a, const void* O, float* Delta, float* stat2, void* Qnat, void* dOnat, void* Knat, void* Vnat, hipStream_t st);
+// launch (bwd_prepare_blocks)
+void launch_bwd_prepare(const BwdArgs& a, const void* O, float* Delta, float* stat2, void* Qnat, void* dOnat, void* Knat, void* Vnat, hipStream_t st);
 size_t bwd_acc_dq_bytes(int64_t n_q, int Hq, int D);
 size_t bwd_acc_dkv_bytes(int64_t n_k, int Hkv, int D);  // each of dK, dV
 size_t bwd_part_dkdv_bytes(int64_t n_k, int Hkv, int D, int splits);

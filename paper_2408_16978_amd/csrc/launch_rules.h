@@ -112,6 +112,13 @@ static inline bool f32_bwd_split(int64_t S, int Hq, int Hkv)
     return saved > 6.0 + 8.0 * std::max(0.0, 2.0 * per_cu - std::max(per_cu, 1.0));
 }
 
+// Workgroups of 512 lanes that prepare a backward over the whole sequence: one per 32-row block of every query head for Delta and one per
+// block and head of Q, dO, K and V for the packed operands.  (Fewer than 2^32 of any tensors that fit a GPU.)  A launch has fewer than 2^32 lanes, so
+// that from 2^23 workgroups on (64 / 8 heads: 1.26M tokens) it takes several.
+static inline int64_t bwd_prepare_blocks(int64_t S, int Hq, int Hkv) { return S / 32 * (3 * (int64_t)Hq + 2 * (int64_t)Hkv); }
+static const int64_t BWD_PREPARE_MOST = ((int64_t)1 << 23) - 1;
+static inline int64_t bwd_prepare_next(int64_t first, int64_t blocks) { return std::min(blocks - first, BWD_PREPARE_MOST); }
+
 // Into how many splits a dK/dV launch divides the query walk of its key tiles.  Unsplit it has n_k / 256
 // * Hkv workgroups of four waves, one per compute unit: 64 at 8K tokens and two KV heads, so that three
 // quarters of the chip idle, and below the diagonal's last rows the longest workgroup decides.  Each

@@ -12,6 +12,8 @@ SHIM = """
 #include "tw_plan.h"
 extern "C" int key_groups(int64_t S, int Hq) { return fpdt::sweep_key_groups(S, Hq); }
 extern "C" int dq_key_groups(int64_t rows, int Hq, int D, int diagonal) { return fpdt::dq_key_groups(rows, rows, Hq, D, diagonal); }
+extern "C" int64_t prepare_blocks(int64_t S, int Hq, int Hkv) { return fpdt::bwd_prepare_blocks(S, Hq, Hkv); }
+extern "C" int64_t prepare_next(int64_t first, int64_t blocks) { return fpdt::bwd_prepare_next(first, blocks); }
 extern "C" int f32_one_launch(int64_t S, int Hq, int Hkv) { return fpdt::f32_one_launch(S, Hq, Hkv); }
 extern "C" int dkdv_splits(int64_t n_q, int64_t n_k, int Hq, int Hkv, int D, int causal) { return fpdt::bwd_dkdv_splits(n_q, n_k, Hq, Hkv, D, causal); }
 static void put(const fpdt_tw::Plan& p, int* out)
@@ -38,6 +40,8 @@ def _lib():
     L.dq_key_groups.argtypes = [i64, ci, ci, ci]
     L.dkdv_splits.argtypes = [i64, i64, ci, ci, ci, ci]
     L.f32_one_launch.argtypes = [i64, ci, ci]
+    L.prepare_blocks.argtypes, L.prepare_blocks.restype = [i64, ci, ci], i64
+    L.prepare_next.argtypes, L.prepare_next.restype = [i64, i64], i64
     for f in (L.launched, L.first_answer):
         f.argtypes, f.restype = [i64, i64, i64, ctypes.POINTER(ci)], None
     return L
@@ -49,6 +53,15 @@ def forward_key_groups(S, Hq):
 
 def dq_key_groups(rows, Hq, diagonal, D=128):
     return _lib().dq_key_groups(rows, Hq, D, int(diagonal))
+
+
+def prepare_launches(S, Hq, Hkv):
+    """(first block, workgroups) of each launch that prepares a backward over the whole sequence"""
+    blocks, first, out = _lib().prepare_blocks(S, Hq, Hkv), 0, []
+    while first < blocks:
+        out.append((first, _lib().prepare_next(first, blocks)))
+        first += out[-1][1]
+    return out
 
 
 def f32_one_launch(S, Hq, Hkv):
