@@ -296,6 +296,33 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 4) void f32_fwd_kernel(F32F
     });
 }
 
+// What the two workgroups of a tile hand over to each other.  They may run on different XCDs, whose L2 caches are not coherent: every access to
+// these floats has the device's scope, which takes it past those caches to the memory that all of them see, and there are no others
+// (the memory is private to this class; a plain load or store of it could be stale, or be seen late).  What orders them is
+// not the language's (all are relaxed) but the chip's: a store of that scope has reached that memory when vmcnt counts it down, each
+// wave waits for its own in front of the barrier, and only behind the barrier is the arrival counted, in the same memory; who
+// finds the other's arrival there loads behind a second barrier.  (Ordered by the language, with a fence, each workgroup writes back an XCD's whole L2:
+// 179 us instead of 29 at 1K tokens.)
+class SharedSums {
+    float* const part_;
+    unsigned* const arrived_;
+
+public:
+    __device__ SharedSums(const F32BwdArgs& a, unsigned tile, int floats) : part_(a.part + (size_t)tile * floats), arrived_(a.arrived + tile) {}
+    __device__ void store(int at, float v) const { __hip_atomic_store(part_ + at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ float load(int at) const { return __hip_atomic_load(part_ + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    // All stores of this workgroup are done; are the other's too?  (By the whole workgroup.)
+    __device__ bool both_stored() const
+    {
+        __shared__ unsigned before;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (threadIdx.x == 0) before = __hip_atomic_fetch_add(arrived_, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        return before != 0;
+    }
+};
+
 // One launch for both sides: the first tiles are of 16 queries (dQ), the others of 16 keys (dK, dV:
 // all query heads of the group).  Waves share the walk of a tile as in the forward.
 //
@@ -310,20 +337,7 @@ __global__ __launch_bounds__(64 * NW) void f32_bwd_kernel(F32BwdArgs a, unsigned
     constexpr int DB = D / 16, STRIDE = SPLIT ? 2 * NW : NW;  // of the blocks of a walk that a wave takes
     __shared__ __attribute__((aligned(16))) float lds[NW * Shelf<D, 2>::FLOATS];
     const unsigned half = SPLIT && blockIdx.x >= tiles ? 1 : 0, tile_id = half ? 2 * tiles - 1 - blockIdx.x : blockIdx.x;
-    float* const part = a.part + (size_t)(2 * tile_id) * (2 * TR * D);  // two halves of up to two results
-    // The halves travel in accesses of the device's scope, past the caches of the XCDs, so that a wait for the own ones is all that the
-    // arrival needs.  (With plain stores it needs a fence, which writes back an XCD's whole L2: 179 us instead of 29 at 1K tokens.)
-    auto keep = [&](int at, float v) { __hip_atomic_store(part + at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-    auto kept = [&](int at) { return __hip_atomic_load(part + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-    // My half is stored; is the other one?
-    auto last = [&] {
-        __shared__ unsigned before;
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (threadIdx.x == 0) before = __hip_atomic_fetch_add(a.arrived + tile_id, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        return before != 0;
-    };
+    const SharedSums sums(a, tile_id, 2 * (2 * TR * D));  // two halves of up to two results
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, col = lane & 15;
     const int group = a.Hq / a.Hkv, first = w + NW * (int)half;
     const size_t q_pitch = (size_t)a.Hq * D, k_pitch = (size_t)a.Hkv * D;
@@ -378,9 +392,9 @@ __global__ __launch_bounds__(64 * NW) void f32_bwd_kernel(F32BwdArgs a, unsigned
             }
         };
         if constexpr (SPLIT) {
-            sum_waves<D, false>(acc, acc, lds, [&](int, int d, int c, float v) { keep((int)half * TR * D + c * D + d, v); });
-            if (!last()) return;
-            for (int e = threadIdx.x; e < TR * D; e += NW * 64) put(e % D, e / D, kept(e) + kept(TR * D + e));
+            sum_waves<D, false>(acc, acc, lds, [&](int, int d, int c, float v) { sums.store((int)half * TR * D + c * D + d, v); });
+            if (!sums.both_stored()) return;
+            for (int e = threadIdx.x; e < TR * D; e += NW * 64) put(e % D, e / D, sums.load(e) + sums.load(TR * D + e));
         } else {
             sum_waves<D, false>(acc, acc, lds, [&](int, int d, int c, float v) { put(d, c, v); });
         }
@@ -465,10 +479,10 @@ __global__ __launch_bounds__(64 * NW) void f32_bwd_kernel(F32BwdArgs a, unsigned
     };
     static_assert(NW * Shelf<D, 2>::FLOATS >= 2 * NW * D * 17, "both sums at a time");
     if constexpr (SPLIT) {
-        sum_waves<D, true>(dk, dv, lds, [&](int n, int d, int c, float v) { keep((2 * n + (int)half) * TR * D + c * D + d, v); });
-        if (!last()) return;
+        sum_waves<D, true>(dk, dv, lds, [&](int n, int d, int c, float v) { sums.store((2 * n + (int)half) * TR * D + c * D + d, v); });
+        if (!sums.both_stored()) return;
         for (int e = threadIdx.x; e < TR * D; e += NW * 64)
-            for (int n = 0; n < 2; ++n) put(n, e % D, e / D, kept(2 * n * TR * D + e) + kept((2 * n + 1) * TR * D + e));
+            for (int n = 0; n < 2; ++n) put(n, e % D, e / D, sums.load(2 * n * TR * D + e) + sums.load((2 * n + 1) * TR * D + e));
     } else {
         sum_waves<D, true>(dk, dv, lds, put);
     }
