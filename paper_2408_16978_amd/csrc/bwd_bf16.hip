@@ -639,7 +639,8 @@ __global__ __launch_bounds__(NTHREAD) void bwd_dq_kernel(BwdKernelArgs p)
     typedef short short4v __attribute__((ext_vector_type(4)));
     typedef short short8v __attribute__((ext_vector_type(8)));
     typedef __attribute__((address_space(3))) short4v* lds_short4_ptr;
-    // This wave's copies of a tile: fragments w, w + 8, .. of K and of V.  (A wave without one in the last round copies another's once more.)
+    // This wave's copies of a tile: fragments w, w + 8, .. of K and of V.  (A wave without one in the last round copies another's once more: at D
+    // = 80 32 copies for 20 fragments with one key group.)
     constexpr int COPIES = (NATF + NWAVE - 1) / NWAVE;
     static_assert(COPIES * NWAVE <= 2 * NATF, "every wave has something to copy");
     unsigned cp_at[COPIES], k_off[COPIES];

@@ -81,6 +81,8 @@ __global__ __launch_bounds__(NWAVE * 64, 2) void fwd_sweep_kernel(FwdKernelArgs 
     constexpr int KFRAG = NB * DT, VFRAG = NB * VF;  // copies of K, V per tile
     constexpr bool PAIR = KG == 1 && KB == 1;        // two tiles share a reference and a partial sum, as one of two blocks does
     constexpr int CPP = ((VFRAG > KFRAG ? VFRAG : KFRAG) + NWAVE - 1) / NWAVE;  // copies of a wave per phase
+    // (The count of copies is every wave's, so that a phase's wait is one constant: at D = 80 more than there are fragments.  With one key group and
+    // eight waves a tile of 22 KiB requests 32, K 16 for 10 fragments, V 16 for 12.  What that costs has not been timed by itself.)
     static_assert(CPP * NWAVE <= 2 * KFRAG && CPP * NWAVE >= VFRAG, "a wave without a fragment of its own copies another's once more");
     constexpr int K_U4 = KFRAG * 64, V_U4 = VFRAG * 64;  // u32x4 per K, V tile
     constexpr int PAD = RAW && DP > D ? 4 : 0;  // the last row's padded channels are read from behind it

@@ -35,8 +35,9 @@ static inline int cheapest_key_groups(int64_t n_q, int64_t n_keys, int Hq, bool 
 }
 
 // The forward's, by the whole sequence.  Measured (us for KG = 1, 2, 4): 8 heads, D = 128, 2K tokens 40, 30, 21; 8K 184, 138, 154; 16K 463, 487, 551;
-// D = 64, 4K 45, 35, 30; 5K 80, 44, 48; 14.5K 241, 251, 292; 2 heads, D = 128: 16K 257, 191, 143; 32K 697, 491, 526.  (At 52 sizes so
-// measured the constants choose the fastest count, or one within 0.5% of it.)
+// D = 64, 4K 45, 35, 30; 5K 80, 44, 48; 14.5K 241, 251, 292; 2 heads, D = 128: 16K 257, 191, 143; 32K 697, 491, 526.  (At 802 sizes so
+// measured, D = 64, 80 and 128 alike, 1 to 64 heads, the count that the constants choose takes 1.001 of the fastest one's time in the mean, more than 1.02
+// at 12 of them and at most 1.14: 64 heads, 1.25K, D = 80 37, 43, 51.  No constants that were tried do better everywhere.)
 static inline int sweep_key_groups(int64_t S, int Hq)
 {
     return cheapest_key_groups(S, S, Hq, true, {1.04, 1.22, 1.5, 0.93});
