@@ -162,7 +162,7 @@ struct F32BwdArgs {
     int64_t q_pos0, k_pos0, n_q, n_k;
     int Hq, Hkv, D;
     float scale;
-    // two workgroups per tile (f32_bwd_splits): their sums, and per tile how many have arrived (0 before the launch); null: one
+    // two workgroups per tile (f32_bwd_split): their sums, and per tile how many have arrived (0 before the launch); null: one
     float* part = nullptr;
     unsigned* arrived = nullptr;
 };
